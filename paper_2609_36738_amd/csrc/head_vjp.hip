@@ -12,8 +12,9 @@
 // SIMD) each owning 128 x 64, k tiles of 64 in two LDS stages (lds256w_kernel). Small products: one fused launch of
 // 64 x 64 tiles of both products (vjp_fused_small_kernel), or 128 x 128 split-K tiles with a
 // fixed-order reduction. dW = H^T G has both operands k-outer in memory (transposing LDS reads or a
-// transpose while staging); dH = G W^T has both operands k-contiguous. fp32 path (and unaligned
-// bf16): a SIMT tiled GEMM.
+// transpose while staging); dH = G W^T has both operands k-contiguous. The fused and the 256-tile
+// kernels also take R and W with rows at any alignment and of any length (UA). fp32 path (and bf16 with H unaligned):
+// a SIMT tiled GEMM, at 30-40 TFLOP/s; a 4088 x 1024 x 50,257 head VJP takes 0.93 ms with UA and took 22.5 ms there.
 #include <algorithm>
 #include <array>
 #include <map>
@@ -896,7 +897,14 @@ constexpr int kWideDH = 0, kWideDW = 1, kWideFWD = 2;
 // so that one wave's copies and LDS reads overlap the other's MFMAs) each own 128 x 64.
 // ZR: the operand that is R (dH's A, dW's B) holds the logits Z, and each copy is turned into R in
 // registers before its LDS write (z_chunk_to_r).
-template <int MODE, typename TO, int NW, bool ZR = false, bool FS = false>
+// UA: operands with the vocabulary along their rows (R, W) need not be aligned to 16 bytes nor have a multiple
+// of eight columns. Every chunk is then read with one 16-byte load at a 2-byte aligned address that lies
+// inside the row: the unaligned loads of a row pair run at half the rate of aligned ones (60 against 115 B/ns per
+// CU from L2; rows at an odd offset alone at 37), which still is above the 36 B/ns that the tiles ask for. A chunk
+// that would cross the end of the row is moved back to the row's last eight columns: along n (dW, forward) the
+// epilogue maps its tile columns to where they came from, along k (dH) the main loop stops at the last whole
+// chunk and the K % 8 columns left go through one MFMA step of their own before it.
+template <int MODE, typename TO, int NW, bool ZR = false, bool FS = false, bool UA = false>
 __device__ __forceinline__ void wide_tile(const WideArgs& args, int id, uint16_t (&lds)[2][2][WSE], float (&rv_s)[LB],
                                           float2* zs = nullptr) {
     static_assert(NW == 4 || NW == 8, "four or eight waves");
@@ -909,11 +917,18 @@ __device__ __forceinline__ void wide_tile(const WideArgs& args, int id, uint16_t
     constexpr bool RANK1 = MODE != kWideFWD;   // rank-1 epilogue (the head VJP products)
     constexpr bool KA = MODE != kWideDW;       // operand A k-contiguous
     constexpr bool KB = MODE == kWideDH;       // operand B k-contiguous
+    static_assert(!UA || (NW == 8 && !ZR && !FS), "unaligned rows: eight waves, R as stored");
     const uint16_t* __restrict__ Xa = args.Xa;
     const int64_t lda = args.lda;
     const uint16_t* __restrict__ Xb = args.Xb;
     const int64_t ldb = args.ldb;
+    // UA: descriptors start at the 16-byte boundary at or before the operand, offsets carry the difference
+    const int da = UA ? (int)(reinterpret_cast<uintptr_t>(Xa) & 15) : 0;
+    const int db = UA ? (int)(reinterpret_cast<uintptr_t>(Xb) & 15) : 0;
+    Xa -= da / 2;
+    Xb -= db / 2;
     const int M = args.M, Nn = args.Nn, K = args.K, kps = args.kps;
+    const int Km = UA && MODE == kWideDH ? K & ~7 : K;   // k of the main loop
     const TileRange& tr = args.tr;
     const float* alpha_p = args.alpha_p;
     const float* __restrict__ rv = args.rv;
@@ -929,9 +944,18 @@ __device__ __forceinline__ void wide_tile(const WideArgs& args, int id, uint16_t
     tn = __builtin_amdgcn_readfirstlane(tn);
     kz = __builtin_amdgcn_readfirstlane(kz);
     const int m0 = tm * LB, n0 = tn * LB;
-    const int kb = kz * kps, ke = min(K, kb + kps);
+    const int kb = kz * kps, ke = min(Km, kb + kps);
     const int nk = (ke - kb + KT - 1) / KT;
     const int l = threadIdx.x % kWave;
+    // output column of tile column c, or one past every column where it has none
+    auto out_col = [&](int c) {
+        const int n = n0 + c;
+        if constexpr (UA && !KB) {
+            const int cs = Nn & ~7;               // columns from cs on came from Nn - 8, Nn - 7, ...
+            if (n >= cs) return n < cs + 8 && n - 8 + (Nn - cs) >= cs ? n - 8 + (Nn - cs) : 0x7fffffff;
+        }
+        return n;
+    };
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int wm = wave / (NW / 2), wn = wave % (NW / 2);
 
@@ -941,7 +965,7 @@ __device__ __forceinline__ void wide_tile(const WideArgs& args, int id, uint16_t
     float cvv[NJ];
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
-        const int n = n0 + wn * WCOLS + j * 32 + l % 32;
+        const int n = out_col(wn * WCOLS + j * 32 + l % 32);
         cvv[j] = (r1 && n < Nn) ? cv[n] : 0.f;
     }
 
@@ -966,6 +990,17 @@ __device__ __forceinline__ void wide_tile(const WideArgs& args, int id, uint16_t
     for (int q = 0; q < CPO; ++q) {
         geo(KA, lda, M - m0, q, &voff_a[q], &kc_a[q], &ok_a[q]);
         geo(KB, ldb, Nn - n0, q, &voff_b[q], &kc_b[q], &ok_b[q]);
+        if constexpr (UA) {
+            voff_a[q] += da;
+            if constexpr (KB) {
+                voff_b[q] += db;
+            } else {   // offsets from column 0, the chunk across the last column moved back, none past it
+                const int chunk = (wave * CPO + q) * 64 + l;
+                const int krow = chunk / 32, c0 = n0 + (((chunk % 32) ^ ((krow & 3) << 2)) << 3);
+                const int c = c0 + 8 <= Nn ? c0 : Nn - 8;
+                voff_b[q] = c0 < Nn ? (int)((int64_t)krow * ldb * 2) + c * 2 + db : kOob;
+            }
+        }
     }
     // logits input: c of each row of the R operand and its label. dH: the tile's 256 rows are fixed, so
     // (c, label) sit in LDS (zs) and each copy looks its row up at write time, the label as an offset
@@ -983,8 +1018,8 @@ __device__ __forceinline__ void wide_tile(const WideArgs& args, int id, uint16_t
         if constexpr (ZB) zcol[q] = n0 + (((chunk % 32) ^ (((chunk / 32) & 3) << 2)) << 3);
     }
     // k-contiguous operands: one descriptor per workgroup over the tile's rows (exact extent)
-    const int bytes_ta = KA ? (int)(((int64_t)(min(LB, M - m0) - 1) * lda + K) * 2) : 0;
-    const int bytes_tb = KB ? (int)(((int64_t)(min(LB, Nn - n0) - 1) * ldb + K) * 2) : 0;
+    const int bytes_ta = KA ? (int)(((int64_t)(min(LB, M - m0) - 1) * lda + K) * 2) + da : 0;
+    const int bytes_tb = KB ? (int)(((int64_t)(min(LB, Nn - n0) - 1) * ldb + K) * 2) + db : 0;
     struct TileLoad {
         const uint16_t* ba;
         const uint16_t* bb;
@@ -1002,11 +1037,14 @@ __device__ __forceinline__ void wide_tile(const WideArgs& args, int id, uint16_t
             tl.bytes_a = bytes_ta;
         } else {
             tl.ba = Xa + (int64_t)kr * lda + m0;
-            tl.bytes_a = nv > 0 ? (int)(((int64_t)(nv1 - 1) * lda + (M - m0)) * 2) : 0;
+            tl.bytes_a = nv > 0 ? (int)(((int64_t)(nv1 - 1) * lda + (M - m0)) * 2) + da : 0;
         }
         if constexpr (KB) {
             tl.bb = Xb + (int64_t)n0 * ldb;
             tl.bytes_b = bytes_tb;
+        } else if constexpr (UA) {
+            tl.bb = Xb + (int64_t)kr * ldb;
+            tl.bytes_b = nv > 0 ? (int)(((int64_t)(nv1 - 1) * ldb + Nn) * 2) + db : 0;
         } else {
             tl.bb = Xb + (int64_t)kr * ldb + n0;
             tl.bytes_b = nv > 0 ? (int)(((int64_t)(nv1 - 1) * ldb + (Nn - n0)) * 2) : 0;
@@ -1126,6 +1164,28 @@ __device__ __forceinline__ void wide_tile(const WideArgs& args, int id, uint16_t
         }
         __syncthreads();
     }
+    if constexpr (UA && MODE == kWideDH) {
+        if (Km < K && kz == 0) {   // the K % 8 columns past the last whole chunk: one MFMA step of their own
+            static_assert(NW * kWave == 2 * LB, "one thread per operand row");
+            const int op = threadIdx.x / LB, row = threadIdx.x % LB;
+            const bool ok = op ? n0 + row < Nn : m0 + row < M;
+            const uint16_t* src = op ? args.Xb + (int64_t)(n0 + row) * ldb + Km : args.Xa + (int64_t)(m0 + row) * lda + Km;
+            uint32_t e[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) e[i] = ok && Km + i < K ? src[i] : 0u;
+            char* dst = reinterpret_cast<char*>(&lds[0][op][0]) + row * 128;
+            *reinterpret_cast<u32x4_t*>(dst + swz(row, 0) * 16) =
+                u32x4_t{e[0] | e[1] << 16, e[2] | e[3] << 16, e[4] | e[5] << 16, e[6] | e[7] << 16};
+            *reinterpret_cast<u32x4_t*>(dst + swz(row, 1) * 16) = u32x4_t{0u, 0u, 0u, 0u};
+            __syncthreads();
+            read_frags(0, 0, a0, b0);
+#pragma unroll
+            for (int m = 0; m < 4 * NJ; ++m)
+                acc[m / NJ][m % NJ] =
+                    __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0[m / NJ], b0[m % NJ], acc[m / NJ][m % NJ], 0, 0, 0);
+            __syncthreads();
+        }
+    }
     {
         const TileLoad t0 = tile_load(0), t1 = tile_load(1);
 #pragma unroll
@@ -1173,7 +1233,7 @@ __device__ __forceinline__ void wide_tile(const WideArgs& args, int id, uint16_t
         const uint16_t* __restrict__ bias = args.bias;
         if constexpr (!FS) {
             for_each_acc([&](int r, int c, int, float v) {
-                const int m = m0 + r, n = n0 + c;
+                const int m = m0 + r, n = out_col(c);
                 if (m < M && n < Nn) stf<TO>(out, (int64_t)m * ldo + n, bias ? v + bf16_to_f32(bias[n]) : v);
             });
             return;
@@ -1257,7 +1317,7 @@ __device__ __forceinline__ void wide_tile(const WideArgs& args, int id, uint16_t
         if ((int)threadIdx.x < LB) rv_s[threadIdx.x] = rv_reg;
         __syncthreads();
         for_each_acc([&](int r, int c, int j, float v) {
-            const int m = m0 + r, n = n0 + c;
+            const int m = m0 + r, n = out_col(c);
             if (m < M && n < Nn) {
                 const float x = fmaf(alpha, v, rv_s[r] * cvv[j]);
                 if constexpr (IS_DW) {
@@ -1271,41 +1331,41 @@ __device__ __forceinline__ void wide_tile(const WideArgs& args, int id, uint16_t
     } else {
         float* pz = part + (int64_t)kz * tr.pstride;
         for_each_acc([&](int r, int c, int, float v) {
-            const int m = m0 + r, n = n0 + c;
+            const int m = m0 + r, n = out_col(c);
             if (m < M && n < Nn) pz[(int64_t)(m - tr.pm0) * tr.ldp + (n - tr.pn0)] = alpha * v;
         });
     }
 }
 
-template <bool IS_DW, typename TO, int NW, bool ZR = false>
+template <bool IS_DW, typename TO, int NW, bool ZR = false, bool UA = false>
 __global__ __launch_bounds__(NW * 64, 1) void lds256w_kernel(WideArgs a) {
     __shared__ __attribute__((aligned(1024))) uint16_t lds[2][2][WSE];
     __shared__ float rv_s[LB];
     __shared__ float2 zs[ZR && !IS_DW ? LB : 1];
-    wide_tile<IS_DW ? kWideDW : kWideDH, TO, NW, ZR>(a, blockIdx.x, lds, rv_s, zs);
+    wide_tile<IS_DW ? kWideDW : kWideDH, TO, NW, ZR, false, UA>(a, blockIdx.x, lds, rv_s, zs);
 }
 
 // The head forward Z = H W (+ b) in bf16 on the same tiles (fp32 accumulation, one rounding of Z); FS:
 // with the per-tile row statistics in the epilogue (a kernel of its own: the statistics epilogue's
 // registers would otherwise constrain the plain forward's k loop).
-template <typename TO, int NW, bool FS = false>
+template <typename TO, int NW, bool FS = false, bool UA = false>
 __global__ __launch_bounds__(NW * 64, 1) void lds256w_fwd_kernel(WideArgs a) {
     __shared__ __attribute__((aligned(1024))) uint16_t lds[2][2][WSE];
     __shared__ float rv_s[LB];
-    wide_tile<kWideFWD, TO, NW, false, FS>(a, blockIdx.x, lds, rv_s);
+    wide_tile<kWideFWD, TO, NW, false, FS, UA>(a, blockIdx.x, lds, rv_s);
 }
 
 // Both products in one grid: blocks [0, nh) run dH's units (the long k ranges first), the rest dW's
 // tiles, so that the shorter dW tiles fill the compute units that dH's last round leaves idle instead of
 // a second launch starting after a partly empty round. nh is a multiple of 8, so each part keeps its
 // own XCD order.
-template <typename TO, int NW, bool ZR = false>
+template <typename TO, int NW, bool ZR = false, bool UA = false>
 __global__ __launch_bounds__(NW * 64, 1) void lds256w_pair_kernel(WideArgs h, WideArgs w, int nh) {
     __shared__ __attribute__((aligned(1024))) uint16_t lds[2][2][WSE];
     __shared__ float rv_s[LB];
     __shared__ float2 zs[ZR ? LB : 1];
-    if ((int)blockIdx.x < nh) wide_tile<kWideDH, TO, NW, ZR>(h, blockIdx.x, lds, rv_s, zs);
-    else wide_tile<kWideDW, float, NW, ZR>(w, (int)blockIdx.x - nh, lds, rv_s);
+    if ((int)blockIdx.x < nh) wide_tile<kWideDH, TO, NW, ZR, false, UA>(h, blockIdx.x, lds, rv_s, zs);
+    else wide_tile<kWideDW, float, NW, ZR, false, UA>(w, (int)blockIdx.x - nh, lds, rv_s);
 }
 
 // Split-K reduction for the rank-1 form over the rectangle [pm0, M) x [pn0, Nn) of the output, in split
@@ -1331,7 +1391,12 @@ __global__ __launch_bounds__(256) void splitk_rank1_kernel(const float* __restri
 // four 16-byte loads of W (and the matching q_hat) in flight per lane: upart[c][n]. Blocks
 // [nu, ...): partial column sums of H over rows in I, kHsRows rows by 512 columns per block (wave w adds rows
 // w, w + 4, ...; the four wave sums are added in wave order).
+// UA: W with rows at any 2-byte alignment and of any length from eight; the chunk across the end of a unit is
+// read from its last eight columns, with the columns that an earlier chunk holds masked out.
 constexpr int kHsRows = 128;
+typedef u32x4_t __attribute__((aligned(2))) u32x4_any_t;   // 16 bytes at any bf16 address
+typedef f32x4 __attribute__((aligned(4))) f32x4_any_t;
+template <bool UA>
 __global__ __launch_bounds__(256) void vjp_rank1_kernel(const uint16_t* __restrict__ W, int64_t ldw, int d, int V,
                                                         const float* __restrict__ q_hat, int nu, int uch, int ucw,
                                                         const uint16_t* __restrict__ H, int64_t ldh, int N,
@@ -1343,7 +1408,7 @@ __global__ __launch_bounds__(256) void vjp_rank1_kernel(const uint16_t* __restri
         for (int unit = blockIdx.x * 4 + wave; unit < d * uch; unit += nu * 4) {
             const int n = unit / uch, c = unit % uch;
             const uint16_t* wr = W + (int64_t)n * ldw;
-            const int j1 = min(V, (c + 1) * ucw);   // V and the chunk bounds are multiples of 8
+            const int j1 = min(V, (c + 1) * ucw);   // a multiple of 8 unless UA
             float acc[4] = {0.f, 0.f, 0.f, 0.f};
             for (int j = c * ucw + l * 8; j < j1; j += 4 * 512) {
                 uint4 w[4];
@@ -1353,14 +1418,32 @@ __global__ __launch_bounds__(256) void vjp_rank1_kernel(const uint16_t* __restri
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
                     const int jj = min(j + k * 512, j1 - 8);
-                    w[k] = *reinterpret_cast<const uint4*>(wr + jj);
-                    q[2 * k] = *reinterpret_cast<const float4*>(q_hat + jj);
-                    q[2 * k + 1] = *reinterpret_cast<const float4*>(q_hat + jj + 4);
+                    if constexpr (UA) {
+                        const u32x4_t x = *reinterpret_cast<const u32x4_any_t*>(wr + jj);
+                        w[k] = make_uint4(x[0], x[1], x[2], x[3]);
+                        const f32x4 q0 = *reinterpret_cast<const f32x4_any_t*>(q_hat + jj);
+                        const f32x4 q1 = *reinterpret_cast<const f32x4_any_t*>(q_hat + jj + 4);
+                        q[2 * k] = make_float4(q0[0], q0[1], q0[2], q0[3]);
+                        q[2 * k + 1] = make_float4(q1[0], q1[1], q1[2], q1[3]);
+                    } else {
+                        w[k] = *reinterpret_cast<const uint4*>(wr + jj);
+                        q[2 * k] = *reinterpret_cast<const float4*>(q_hat + jj);
+                        q[2 * k + 1] = *reinterpret_cast<const float4*>(q_hat + jj + 4);
+                    }
                 }
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
                     const uint32_t mk = lane_mask(j + k * 512 < j1);
                     w[k] = make_uint4(w[k].x & mk, w[k].y & mk, w[k].z & mk, w[k].w & mk);
+                    if constexpr (UA) {   // columns j + 512 k - j0 .. of the eight from j0 = j1 - 8 on
+                        const int drop = min(j + k * 512 - (j1 - 8), 8);
+                        if (drop > 0) {
+                            uint32_t* e = &w[k].x;
+#pragma unroll
+                            for (int i = 0; i < 4; ++i)
+                                e[i] &= (2 * i < drop ? 0u : 0xFFFFu) | (2 * i + 1 < drop ? 0u : 0xFFFF0000u);
+                        }
+                    }
                 }
 #pragma unroll
                 for (int k = 0; k < 4; ++k)
@@ -1466,7 +1549,24 @@ struct FusedArgs {
 // element offset of (row, col) in a 64 x 64 bf16 LDS tile whose 16-byte chunks are swizzled by row
 __device__ __forceinline__ int ftile_off(int row, int col) { return row * FB + ((((col >> 3) ^ (row & 7))) << 3) + (col & 7); }
 
-template <bool is_dw>
+// Elements i + sh of the eight bf16 of v at i (0 <= sh < 8), zeros past the last.
+__device__ __forceinline__ u32x4_t chunk_shr(u32x4_t v, int sh) {
+    uint64_t lo = v[0] | (uint64_t)v[1] << 32, hi = v[2] | (uint64_t)v[3] << 32;
+    if (sh >= 4) {
+        lo = hi;
+        hi = 0;
+    }
+    const int b = (sh & 3) * 16;
+    if (b != 0) {
+        lo = lo >> b | hi << (64 - b);
+        hi >>= b;
+    }
+    return u32x4_t{(uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32)};
+}
+
+// UA: R (or Z) and W at any 2-byte alignment and V of any size from eight: a chunk across the last column is read
+// from the row's last eight columns and shifted to its place on the way to LDS.
+template <bool is_dw, bool UA>
 __device__ __forceinline__ void fused_tile(const FusedArgs& a, int id, uint16_t (&sa)[2][FK * FB],
                                            uint16_t (&sb)[2][FK * FB], float (&red)[FB][33], float (&vec)[FB]) {
     const int t = threadIdx.x, l = t % kWave;
@@ -1489,25 +1589,28 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& a, int id, uint16_t 
     const uint16_t* pb = is_dw ? a.R : a.W;
     const int64_t lda = is_dw ? a.ldh : a.ldr, ldb = is_dw ? a.ldr : a.ldw;
     const int rows_a = is_dw ? a.N : a.N, rows_b = is_dw ? a.N : a.d;
-    const auto da = make_desc(pa, (int)(((int64_t)(rows_a - 1) * lda + (is_dw ? a.d : a.V)) * 2));
-    const auto db_ = make_desc(pb, (int)(((int64_t)(rows_b - 1) * ldb + a.V) * 2));
+    // UA: descriptors start at the 16-byte boundary at or before the operand
+    const int xa = UA ? (int)(reinterpret_cast<uintptr_t>(pa) & 15) : 0, xb = UA ? (int)(reinterpret_cast<uintptr_t>(pb) & 15) : 0;
+    const auto da = make_desc(pa - xa / 2, (int)(((int64_t)(rows_a - 1) * lda + (is_dw ? a.d : a.V)) * 2) + xa);
+    const auto db_ = make_desc(pb - xb / 2, (int)(((int64_t)(rows_b - 1) * ldb + a.V) * 2) + xb);
+    auto vcol = [&](int c) { return UA && c + 8 > a.V ? a.V - 8 : c; };   // where the chunk at column c < V is read
     auto off_a = [&](int k0, int e) {
         const int r = r0 + 32 * e;
         if constexpr (is_dw) {
             const int k = k0 + r, m = m0 + lc * 8;
-            return (k < a.N && m < a.d) ? (int)(((int64_t)k * lda + m) * 2) : kOob;
+            return (k < a.N && m < a.d) ? (int)(((int64_t)k * lda + m) * 2) + xa : kOob;
         }
         const int i = m0 + r, k = k0 + lc * 8;
-        return (i < a.N && k < a.V) ? (int)(((int64_t)i * lda + k) * 2) : kOob;
+        return (i < a.N && k < a.V) ? (int)(((int64_t)i * lda + vcol(k)) * 2) + xa : kOob;
     };
     auto off_b = [&](int k0, int e) {
         const int r = r0 + 32 * e;
         if constexpr (is_dw) {
             const int k = k0 + r, n = n0 + lc * 8;
-            return (k < a.N && n < a.V) ? (int)(((int64_t)k * ldb + n) * 2) : kOob;
+            return (k < a.N && n < a.V) ? (int)(((int64_t)k * ldb + vcol(n)) * 2) + xb : kOob;
         }
         const int j = n0 + r, k = k0 + lc * 8;
-        return (j < a.d && k < a.V) ? (int)(((int64_t)j * ldb + k) * 2) : kOob;
+        return (j < a.d && k < a.V) ? (int)(((int64_t)j * ldb + vcol(k)) * 2) + xb : kOob;
     };
     // one k tile in registers: the four 16-byte copies and what the rank-1 sums need with them
     struct Set {
@@ -1549,6 +1652,15 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& a, int id, uint16_t 
             }
         } else {
             const int k = k0 + lc * 8;
+            if constexpr (UA) {   // past V: any finite word, W is zero there
+                const int ks = min(k, a.V - 1), last = a.V - 1 - ks;
+                float q8[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) q8[i] = a.q_hat[ks + min(i, last)];
+                st.q[0] = make_float4(q8[0], q8[1], q8[2], q8[3]);
+                st.q[1] = make_float4(q8[4], q8[5], q8[6], q8[7]);
+                return;
+            }
             const int kc = k < a.V ? k : a.V - 8;
             st.q[0] = *reinterpret_cast<const float4*>(a.q_hat + kc);
             st.q[1] = *reinterpret_cast<const float4*>(a.q_hat + kc + 4);
@@ -1569,11 +1681,17 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& a, int id, uint16_t 
                     bool bad = false;
                     const bool valid = label_valid(st.lab[e], a.V, a.ig, &bad);
                     const int n = n0 + lc * 8;
-                    cb = z_chunk_to_r(cb, valid ? st.zl[e] * kLog2e : INFINITY, st.lab[e] - n, n < a.V);
+                    cb = z_chunk_to_r(cb, valid ? st.zl[e] * kLog2e : INFINITY, st.lab[e] - vcol(n), n < a.V);
                 } else {                 // R is operand A: row m0 + r, k chunk kt FK + 8 lc
                     const int k = st.kt * FK + lc * 8;
-                    ca = z_chunk_to_r(ca, zc_h[e], zy_h[e] - k, k < a.V);
+                    ca = z_chunk_to_r(ca, zc_h[e], zy_h[e] - vcol(k), k < a.V);
                 }
+            }
+            if constexpr (UA) {
+                const int c0 = is_dw ? n0 + lc * 8 : st.kt * FK + lc * 8;
+                const int sh = c0 < a.V ? c0 - vcol(c0) : 0;
+                cb = chunk_shr(cb, sh);
+                if constexpr (!is_dw) ca = chunk_shr(ca, sh);
             }
             *reinterpret_cast<u32x4_t*>(&sa[buf][o]) = ca;
             *reinterpret_cast<u32x4_t*>(&sb[buf][o]) = cb;
@@ -1594,10 +1712,15 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& a, int id, uint16_t 
 #pragma unroll
             for (int e = 0; e < 2; ++e) {
                 float acc = part[e];
+                u32x4_t wc = st.c[2 + e];
+                if constexpr (UA) {
+                    const int k = st.kt * FK + lc * 8;
+                    wc = chunk_shr(wc, k < a.V ? k - vcol(k) : 0);
+                }
 #pragma unroll
                 for (int p = 0; p < 4; ++p) {
-                    acc = fmaf(bf16_lo(st.c[2 + e][p]), q8[2 * p], acc);
-                    acc = fmaf(bf16_hi(st.c[2 + e][p]), q8[2 * p + 1], acc);
+                    acc = fmaf(bf16_lo(wc[p]), q8[2 * p], acc);
+                    acc = fmaf(bf16_hi(wc[p]), q8[2 * p + 1], acc);
                 }
                 part[e] = acc;
             }
@@ -1694,13 +1817,14 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& a, int id, uint16_t 
     }
 }
 
+template <bool UA>
 __global__ __launch_bounds__(256, 2) void vjp_fused_small_kernel(FusedArgs a) {
     __shared__ __attribute__((aligned(16))) uint16_t sa[2][FK * FB];
     __shared__ __attribute__((aligned(16))) uint16_t sb[2][FK * FB];
     __shared__ float red[FB][33];
     __shared__ float vec[FB];
-    if ((int)blockIdx.x < a.tw) fused_tile<true>(a, (int)blockIdx.x, sa, sb, red, vec);
-    else fused_tile<false>(a, (int)blockIdx.x - a.tw, sa, sb, red, vec);
+    if ((int)blockIdx.x < a.tw) fused_tile<true, UA>(a, (int)blockIdx.x, sa, sb, red, vec);
+    else fused_tile<false, UA>(a, (int)blockIdx.x - a.tw, sa, sb, red, vec);
 }
 
 constexpr int kCUs = 256;        // MI355X compute units
@@ -1780,6 +1904,9 @@ GemmPlan plan_wide(int64_t M, int64_t N, int64_t K, bool inner_is_m) {
     }
     return best;
 }
+
+// The fused launch of small products: each tile runs over the whole k range, so both k extents stay short.
+bool fused_extents(int64_t N, int64_t V) { return N <= 8192 && V <= 8192; }
 
 GemmPlan plan_gemm(bool mfma, bool big_ok, int64_t M, int64_t N, int64_t K, bool inner_is_m) {
     if (!mfma || !big_ok) return {kSimt, choose_splits(cdiv(M, SB) * cdiv(N, SB), M, N, K, SB, SK, 4)};
@@ -1920,15 +2047,28 @@ void plan_pair(Plan& p, int64_t N, int64_t d, int64_t V) {
     p.w.outer_dp = (int)ow;
 }
 
-Plan make_plan_uncached(int64_t N, int64_t d, int64_t V, bom_dtype dt) {
+// Whether the MFMA kernels take these extents: H's rows are read in whole 16-byte chunks, so d is a multiple
+// of eight; R's and W's rows (V long) are too unless ua, and need eight columns to read a chunk from. The
+// number of rows N is free.
+bool mfma_extents(int64_t d, int64_t V, bool ua) { return d % 8 == 0 && V >= 8 && (ua || V % 8 == 0); }
+
+Plan make_plan_uncached(int64_t N, int64_t d, int64_t V, bom_dtype dt, bool ua) {
     const bool mfma = dt == BOM_BF16;
     Plan p;
-    // the MFMA kernels load whole 16-byte chunks: extents along k and along contiguous rows must be
-    // multiples of 8 (H^T rows have N elements); other shapes use the SIMT kernels
-    const bool m8 = N % 8 == 0 && d % 8 == 0 && V % 8 == 0;
-    p.w = plan_gemm(mfma, m8, d, V, N, true);    // dW: M = d, N = V, K = rows; inner tiles along d
-    p.h = plan_gemm(mfma, m8, N, d, V, false);   // dH: M = rows, N = d, K = V
+    const bool ok = mfma_extents(d, V, ua);
+    p.w = plan_gemm(mfma, ok, d, V, N, true);    // dW: M = d, N = V, K = rows; inner tiles along d
+    p.h = plan_gemm(mfma, ok, N, d, V, false);   // dH: M = rows, N = d, K = V
     const PlanOverride& o = plan_override();
+    if (ua) {
+        // rows at any alignment have two kernels: the fused launch for small products, which takes both of them,
+        // and the 256-tile kernel for the rest
+        if (!(p.w.kind == kMfma128 && p.h.kind == kMfma128 && fused_extents(N, V))) {
+            if (p.w.kind == kMfma128) p.w = plan_wide(d, V, N, true);
+            if (p.h.kind == kMfma128) p.h = plan_wide(N, d, V, false);
+        }
+        if (p.w.kind == kRank1 && p.h.kind == kRank1) plan_pair(p, N, d, V);
+        return p;
+    }
     apply_override(p.w, o.kw, o.sw, d, V, N);
     apply_override(p.h, o.kh, o.sh, N, d, V);
     if (o.kw == 0 && o.kh == 0 && o.sw == 0 && o.sh == 0 && p.w.kind == kRank1 && p.h.kind == kRank1)
@@ -1937,24 +2077,23 @@ Plan make_plan_uncached(int64_t N, int64_t d, int64_t V, bom_dtype dt) {
 }
 
 // Plans are deterministic functions of the shape; the schedule simulation is kept per shape.
-Plan make_plan(int64_t N, int64_t d, int64_t V, bom_dtype dt) {
+Plan make_plan(int64_t N, int64_t d, int64_t V, bom_dtype dt, bool ua) {
     static std::mutex mu;
     static std::map<std::array<int64_t, 4>, Plan> cache;
-    const std::array<int64_t, 4> key{N, d, V, (int64_t)dt};
+    const std::array<int64_t, 4> key{N, d, V, (int64_t)dt + 16 * ua};
     {
         std::lock_guard<std::mutex> lk(mu);
         auto it = cache.find(key);
         if (it != cache.end()) return it->second;
     }
-    const Plan p = make_plan_uncached(N, d, V, dt);
+    const Plan p = make_plan_uncached(N, d, V, dt, ua);
     std::lock_guard<std::mutex> lk(mu);
     if (cache.size() < 256) cache.emplace(key, p);
     return p;
 }
 
-// Plan of the SIMT kernels, which run bf16 operands that the MFMA kernels cannot stage (a leading
-// dimension that is not a multiple of 8, or a base that is not 16-byte aligned): SIMT tiles with their own
-// k split over every tile.
+// Plan of the SIMT kernels, which run bf16 operands that the MFMA kernels cannot stage (H not aligned to 16
+// bytes, d not a multiple of 8, fewer than eight columns): SIMT tiles with their own k split over every tile.
 Plan simt_plan(int64_t N, int64_t d, int64_t V) {
     Plan p;
     p.w = plan_gemm(false, false, d, V, N, true);
@@ -1974,13 +2113,15 @@ size_t partial_bytes(const Plan& p, int64_t N, int64_t d, int64_t V) {
 }
 
 VjpWs vjp_ws(int64_t N, int64_t d, int64_t V, bom_dtype dt) {
-    const Plan p = make_plan(N, d, V, dt);
+    const Plan p = make_plan(N, d, V, dt, false);
+    // the same shape may come with rows at any alignment, and take the plan for those or the SIMT one
+    const Plan pu = dt == BOM_BF16 ? make_plan(N, d, V, dt, true) : p;
     VjpWs w;
     w.cq_off = 0;
     w.cqp_off = align256((size_t)V * 4);
     w.vmask_off = align256(w.cqp_off + (size_t)V * 4);
     w.scal_off = align256(w.vmask_off + (size_t)N * 4);
-    const bool r1 = p.w.kind == kRank1 || p.h.kind == kRank1;
+    const bool r1 = p.w.kind == kRank1 || p.h.kind == kRank1 || pu.w.kind == kRank1 || pu.h.kind == kRank1;
     w.zc_off = align256(w.scal_off + 16);
     w.hpart_off = align256(w.zc_off + (size_t)N * 4);
     w.hsum_off = align256(w.hpart_off + (r1 ? (size_t)cdiv(N, kHsRows) * d * 4 : 0));
@@ -1988,8 +2129,7 @@ VjpWs vjp_ws(int64_t N, int64_t d, int64_t V, bom_dtype dt) {
     w.upart_off = align256(w.u_off + (r1 ? (size_t)d * 4 : 0));
     w.part_off = align256(w.upart_off + (r1 ? (size_t)u_chunks(d, V) * d * 4 : 0));
     size_t need = partial_bytes(p, N, d, V);
-    // the same call may take the SIMT plan (misaligned operands)
-    if (dt == BOM_BF16) need = std::max(need, partial_bytes(simt_plan(N, d, V), N, d, V));
+    if (dt == BOM_BF16) need = std::max({need, partial_bytes(pu, N, d, V), partial_bytes(simt_plan(N, d, V), N, d, V)});
     w.total = align256(w.part_off + need);
     return w;
 }
@@ -1997,7 +2137,7 @@ VjpWs vjp_ws(int64_t N, int64_t d, int64_t V, bom_dtype dt) {
 template <typename TO>
 hipError_t run_gemm(bool is_dw, const GemmPlan& g, const void* A, int64_t lda, const void* B, int64_t ldb, bom_dtype dt,
                     int M, int Nn, int K, const Fold& f, TO* out, int64_t ldo, float beta, float* part, const float* rv,
-                    const float* cv, hipStream_t st) {
+                    const float* cv, bool ua, hipStream_t st) {
     const int splits = g.splits;
     if (g.kind == kRank1) {
         // rank-1 form: out = alpha A B + rv cv^T (+ beta out)
@@ -2016,7 +2156,11 @@ hipError_t run_gemm(bool is_dw, const GemmPlan& g, const void* A, int64_t lda, c
                 const WideArgs wa{a16, lda, b16, ldb, M, Nn, K, kp, tr, f.scal, rv, cv, out, ldo, beta, pp, nullptr,
                                   f.zc, f.labels};
                 const int nw = is_dw ? wave_cfg().dw : wave_cfg().dh;
-                if (f.zc != nullptr && is_dw)   // logits input: eight waves
+                if (ua && is_dw)   // rows at any alignment: eight waves
+                    hipLaunchKernelGGL((lds256w_kernel<true, float, 8, false, true>), gr, dim3(512), 0, st, wa);
+                else if (ua)
+                    hipLaunchKernelGGL((lds256w_kernel<false, TO, 8, false, true>), gr, dim3(512), 0, st, wa);
+                else if (f.zc != nullptr && is_dw)   // logits input: eight waves
                     hipLaunchKernelGGL((lds256w_kernel<true, float, 8, true>), gr, dim3(512), 0, st, wa);
                 else if (f.zc != nullptr)
                     hipLaunchKernelGGL((lds256w_kernel<false, TO, 8, true>), gr, dim3(512), 0, st, wa);
@@ -2141,7 +2285,6 @@ hipError_t launch_head_vjp(const HeadVjpArgs& a, hipStream_t st) {
 
 hipError_t launch_head_vjp_f32(const HeadVjpArgs& a, hipStream_t st) {
     const VjpWs L = vjp_ws(a.N, a.d, a.V, a.dt);
-    Plan p = make_plan(a.N, a.d, a.V, a.dt);
     char* base = static_cast<char*>(a.ws);
     float* cq = reinterpret_cast<float*>(base + L.cq_off);
     float* cqp = reinterpret_cast<float*>(base + L.cqp_off);
@@ -2155,13 +2298,19 @@ hipError_t launch_head_vjp_f32(const HeadVjpArgs& a, hipStream_t st) {
     float* zc = reinterpret_cast<float*>(base + L.zc_off);
     const bool zin = !a.is_residual;   // the R argument holds the logits Z
 
-    // MFMA kernels stage 16-byte rows: leading dimensions multiples of 8 and 16-byte bases;
-    // otherwise the SIMT kernels (same plan shape, SIMT tiles) run.
+    // MFMA kernels stage 16-byte chunks: of H at 16-byte aligned addresses, of R and W too or (ua) at any (with the
+    // 256-row offsets inside 31 bits, and R as stored in the large products); otherwise the SIMT kernels run,
+    // with their own k splits over every tile (the workspace covers their partials too).
     auto al = [](const void* ptr, int64_t ld) { return reinterpret_cast<uintptr_t>(ptr) % 16 == 0 && ld % 8 == 0; };
-    if (a.dt == BOM_BF16 && !(al(a.H, a.ldh) && al(a.W, a.ldw) && al(a.R, a.ldr))) {
-        // SIMT tiles with their own k splits over every tile (the workspace covers their partials too)
-        p = simt_plan(a.N, a.d, a.V);
-    }
+    const bool ua = a.dt == BOM_BF16 && !(a.V % 8 == 0 && al(a.W, a.ldw) && al(a.R, a.ldr));
+    Plan p = make_plan(a.N, a.d, a.V, a.dt, ua);
+    const bool h_ok = a.d % 8 == 0 && al(a.H, a.ldh);
+    const bool ld_ok = a.ldw < (1 << 22) && a.ldr < (1 << 22);
+    const bool fits31 = ((int64_t)(a.N - 1) * a.ldh + a.d) * 2 < (1LL << 31) &&
+                        ((int64_t)(a.N - 1) * a.ldr + a.V) * 2 < (1LL << 31) &&
+                        ((int64_t)(a.d - 1) * a.ldw + a.V) * 2 < (1LL << 31);
+    const bool small = p.w.kind == kMfma128 && p.h.kind == kMfma128;
+    if (a.dt == BOM_BF16 && (!h_ok || (ua && (!ld_ok || (small ? !fits31 : zin))))) p = simt_plan(a.N, a.d, a.V);
     if (L.part_off + partial_bytes(p, a.N, a.d, a.V) > L.total) return hipErrorInvalidValue;   // never taken
     if (!a.dH) p.h.kind = kSimt;   // no dH: no rank-1 vector for it
 
@@ -2181,12 +2330,8 @@ hipError_t launch_head_vjp_f32(const HeadVjpArgs& a, hipStream_t st) {
 
     // small products (both on the 128-tile kernel): one fused launch, nothing staged beforehand
     const PlanOverride& ov = plan_override();
-    const bool fits31 = ((int64_t)(a.N - 1) * a.ldh + a.d) * 2 < (1LL << 31) &&
-                        ((int64_t)(a.N - 1) * a.ldr + a.V) * 2 < (1LL << 31) &&
-                        ((int64_t)(a.d - 1) * a.ldw + a.V) * 2 < (1LL << 31);
-    // (each tile runs over the whole k range, so both k extents stay short)
-    if (a.dt == BOM_BF16 && p.w.kind == kMfma128 && (!a.dH || p.h.kind == kMfma128) && fits31 && a.N <= 8192 &&
-        a.V <= 8192 && ov.kw != 1 && ov.kh != 1) {
+    if (a.dt == BOM_BF16 && p.w.kind == kMfma128 && (!a.dH || p.h.kind == kMfma128) && fits31 &&
+        fused_extents(a.N, a.V) && (ua || (ov.kw != 1 && ov.kh != 1))) {
         FusedArgs fa;
         fa.H = static_cast<const uint16_t*>(a.H);
         fa.ldh = a.ldh;
@@ -2215,7 +2360,10 @@ hipError_t launch_head_vjp_f32(const HeadVjpArgs& a, hipStream_t st) {
         fa.th_n = (int)cdiv(a.d, FB);
         fa.row_lse = zin ? a.row_lse : nullptr;
         const int th = a.dH ? (int)cdiv(a.N, FB) * fa.th_n : 0;
-        hipLaunchKernelGGL(vjp_fused_small_kernel, dim3((unsigned)(fa.tw + th)), dim3(256), 0, st, fa);
+        if (ua)
+            hipLaunchKernelGGL(vjp_fused_small_kernel<true>, dim3((unsigned)(fa.tw + th)), dim3(256), 0, st, fa);
+        else
+            hipLaunchKernelGGL(vjp_fused_small_kernel<false>, dim3((unsigned)(fa.tw + th)), dim3(256), 0, st, fa);
         return hipGetLastError();
     }
 
@@ -2229,9 +2377,10 @@ hipError_t launch_head_vjp_f32(const HeadVjpArgs& a, hipStream_t st) {
     if (rw || rh) {
         const int nu = rh ? (int)cdiv(std::min<int64_t>((int64_t)a.d * uch, kUWaves), 4) : 0;
         const int ns = rw ? (int)cdiv(a.d, 512) * nrb : 0;
-        hipLaunchKernelGGL(vjp_rank1_kernel, dim3((unsigned)(nu + ns)), dim3(256), 0, st,
-                           static_cast<const uint16_t*>(a.W), a.ldw, a.d, a.V, a.q_hat, nu, uch, ucw,
-                           static_cast<const uint16_t*>(a.H), a.ldh, a.N, a.labels, a.ignore_index, upart, hpart);
+        auto r1 = ua ? vjp_rank1_kernel<true> : vjp_rank1_kernel<false>;
+        hipLaunchKernelGGL(r1, dim3((unsigned)(nu + ns)), dim3(256), 0, st, static_cast<const uint16_t*>(a.W), a.ldw,
+                           a.d, a.V, a.q_hat, nu, uch, ucw, static_cast<const uint16_t*>(a.H), a.ldh, a.N, a.labels,
+                           a.ignore_index, upart, hpart);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -2264,7 +2413,12 @@ hipError_t launch_head_vjp_f32(const HeadVjpArgs& a, hipStream_t st) {
         const int nw = (int)(cdiv(ow, 8) * 8 * inner);
         const dim3 grid((unsigned)(nh + nw));
         const bool w8 = wave_cfg().pair == 8;
-        if (zin) {   // logits input: eight waves
+        if (ua) {   // rows at any alignment: eight waves
+            if (a.dh_dt == BOM_BF16)
+                hipLaunchKernelGGL((lds256w_pair_kernel<uint16_t, 8, false, true>), grid, dim3(512), 0, st, wh, ww, nh);
+            else
+                hipLaunchKernelGGL((lds256w_pair_kernel<float, 8, false, true>), grid, dim3(512), 0, st, wh, ww, nh);
+        } else if (zin) {   // logits input: eight waves
             if (a.dh_dt == BOM_BF16)
                 hipLaunchKernelGGL((lds256w_pair_kernel<uint16_t, 8, true>), grid, dim3(512), 0, st, wh, ww, nh);
             else
@@ -2293,16 +2447,16 @@ hipError_t launch_head_vjp_f32(const HeadVjpArgs& a, hipStream_t st) {
 
     // dW = H^T G
     e = run_gemm<float>(true, p.w, a.H, a.ldh, a.R, a.ldr, a.dt, a.d, a.V, a.N, f, static_cast<float*>(a.dW), a.lddw,
-                        a.dW_beta, part, hist ? hsum : nullptr, cq,
-                        st);
+                        a.dW_beta, part, hist ? hsum : nullptr, cq, ua, st);
     if (e != hipSuccess) return e;
     // dH = G W^T (shares the split-K buffer: same stream, so it runs after the dW reduction)
     if (a.dH) {
         if (a.dh_dt == BOM_BF16)
             return run_gemm<uint16_t>(false, p.h, a.R, a.ldr, a.W, a.ldw, a.dt, a.N, a.d, a.V, f,
-                                      static_cast<uint16_t*>(a.dH), a.lddh, 0.f, part, hist ? vmask : nullptr, u, st);
+                                      static_cast<uint16_t*>(a.dH), a.lddh, 0.f, part, hist ? vmask : nullptr, u, ua,
+                                      st);
         return run_gemm<float>(false, p.h, a.R, a.ldr, a.W, a.ldw, a.dt, a.N, a.d, a.V, f, static_cast<float*>(a.dH),
-                               a.lddh, 0.f, part, hist ? vmask : nullptr, u, st);
+                               a.lddh, 0.f, part, hist ? vmask : nullptr, u, ua, st);
     }
     return hipSuccess;
 }
@@ -2365,15 +2519,18 @@ hipError_t launch_head_forward(const void* H, int64_t ldh, const void* W, int64_
     const uint16_t* W16 = static_cast<const uint16_t*>(W);
     const uint16_t* b16 = static_cast<const uint16_t*>(b);
     auto al = [](const void* ptr, int64_t ld) { return reinterpret_cast<uintptr_t>(ptr) % 16 == 0 && ld % 8 == 0; };
-    // 256-tile MFMA kernel: 16-byte chunks along H's rows (k = d) and W's rows (n = V)
-    if (d % 8 == 0 && V % 8 == 0 && al(H, ldh) && al(W, ldw) &&
+    // 256-tile MFMA kernel: 16-byte chunks along H's rows (k = d, aligned) and W's rows (n = V, at any alignment)
+    const bool ua = !(V % 8 == 0 && al(W, ldw));
+    if (mfma_extents(d, V, ua) && al(H, ldh) &&
         ((int64_t)(N - 1) * ldh + d) * 2 < (1LL << 31) && ((int64_t)(d - 1) * ldw + V) * 2 < (1LL << 31)) {
         const int MT = (int)cdiv(N, LB), NT = (int)cdiv(V, LB);
         const TileRange tr{MT, 0, NT, 1, 0, 0, 0, 0, xcd_blocked(MT)};
         const WideArgs wa{H16, ldh, W16, ldw, N, V, d, (int)(cdiv(d, WKT) * WKT), tr, nullptr, nullptr, nullptr, Z, ldz,
                           0.f, nullptr, b16};
         const dim3 grid((unsigned)(cdiv(NT, 8) * 8 * MT));
-        if (wave_cfg().fwd == 8)
+        if (ua)
+            hipLaunchKernelGGL((lds256w_fwd_kernel<uint16_t, 8, false, true>), grid, dim3(512), 0, st, wa);
+        else if (wave_cfg().fwd == 8)
             hipLaunchKernelGGL((lds256w_fwd_kernel<uint16_t, 8>), grid, dim3(512), 0, st, wa);
         else
             hipLaunchKernelGGL((lds256w_fwd_kernel<uint16_t, 4>), grid, dim3(256), 0, st, wa);

@@ -1,0 +1,90 @@
+"""Rows at any alignment: vocabularies that are not a multiple of eight, odd leading dimensions, odd bases. Each
+operand lies inside a buffer of NaNs, so a word read past a row's end that reaches a result shows."""
+import pytest
+import torch
+
+from paper_2609_36738_amd import bom
+from tests.gpu_util import dev, log
+
+pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not torch.cuda.is_available(), reason="needs an MI355X")]
+
+LAM = 0.5
+
+
+def _embed(t, pad=0, offset=0):
+    """t as a view with leading dimension V + pad and a base `offset` elements past an aligned one, NaNs around."""
+    n, v = t.shape
+    buf = torch.full((n * (v + pad) + offset + 64,), float("nan"), dtype=t.dtype, device=dev())
+    view = buf.as_strided((n, v), (v + pad, 1), offset)
+    view.copy_(t)
+    return view
+
+
+def _rand(g, shape, std, dtype):
+    return (torch.randn(shape, generator=g, device=dev()) * std).to(dtype)
+
+
+# name, N, d, V, row padding of R and W, base offset of R and W
+CASES = [
+    ("fused_v9", 37, 40, 9, 0, 0),
+    ("fused_v8_odd_ld", 64, 64, 8, 1, 0),
+    ("fused_one_row", 1, 72, 263, 0, 1),
+    ("fused_v65", 130, 200, 65, 0, 0),
+    ("fused_v333", 200, 64, 333, 0, 3),
+    ("fused_v8185", 70, 32, 8185, 0, 0),
+    ("wide_short_k", 5, 32, 9001, 0, 0),
+    ("wide_odd_base", 300, 264, 8200, 0, 1),
+    ("wide_odd_ld", 300, 264, 8192, 3, 0),
+    ("wide_n_tail_tile", 520, 776, 12289, 0, 0),   # the last column alone in its tile
+    ("wide_pair", 1031, 768, 32003, 0, 0),
+] + [(f"wide_k_tail{r}", 257, 520, 8192 + r, 0, r & 1) for r in range(1, 8)]
+
+
+@pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
+def test_head_vjp_any_alignment(case):
+    name, N, d, V, pad, off = case
+    log(f"[ragged vjp] {name} N={N} d={d} V={V} pad={pad} offset={off}")
+    g = torch.Generator(device=dev()).manual_seed(5)
+    H = _rand(g, (N, d), 1.0, torch.bfloat16)
+    W = _embed(_rand(g, (d, V), 0.02, torch.bfloat16), pad, off)
+    y = torch.randint(0, V, (N,), generator=g, device=dev(), dtype=torch.int32)
+    if N > 3:
+        y[1::7] = -100
+        y[2] = V          # out of range: not supervised
+    ok = (y >= 0) & (y < V)
+    R = _embed(_rand(g, (N, V), 0.1, torch.bfloat16) * ok[:, None], pad, off)
+    q = _rand(g, (V,), 0.05, torch.float32)
+    s = _rand(g, (V,), 0.05, torch.float32)
+    nv = ok.sum().to(torch.int32).reshape(1)
+    dW0 = _rand(g, (d, V), 0.01, torch.float32)
+    dW = torch.full((d, V + 1), 7.0, device=dev())   # an odd leading dimension; the extra column stays
+    dW[:, :V] = dW0
+    out = bom.bom_head_vjp(H, W, R, y, q, nv, s=s, lam=LAM, dW=dW[:, :V], dW_beta=0.5, want_db=True,
+                           dh_dtype=torch.float32)
+    G = (((1 - LAM) * R.double() + LAM * q.double()) * ok[:, None]) / nv
+    rW, rH = H.double().t() @ G + 0.5 * dW0.double(), G @ W.double().t()
+    eW = float((dW[:, :V] - rW).norm() / rW.norm())
+    eH = float((out["dH"] - rH).norm() / rH.norm())
+    log(f"    rel err dW={eW:.2e} dH={eH:.2e}")
+    # fp32 sums of exact bf16 products: the rounding of k terms grows like sqrt(k) 2^-24, below 1e-5 at k = 32003
+    assert eW <= 1e-5 and eH <= 1e-5
+    assert (dW[:, V] == 7.0).all()
+    ref = (1 - LAM) * s + LAM * q
+    assert float((out["db"] - ref).abs().max()) <= 1e-6
+
+
+@pytest.mark.parametrize("N,d,V,pad,off", [(33, 40, 9, 0, 0), (1, 64, 8, 1, 0), (300, 264, 8201, 0, 1),
+                                            (257, 520, 12289, 3, 0), (1031, 768, 32003, 0, 0)])
+def test_head_forward_any_alignment(N, d, V, pad, off):
+    log(f"[ragged forward] N={N} d={d} V={V} pad={pad} offset={off}")
+    g = torch.Generator(device=dev()).manual_seed(6)
+    H = _rand(g, (N, d), 1.0, torch.bfloat16)
+    W = _embed(_rand(g, (d, V), 0.02, torch.bfloat16), pad, off)
+    b = _rand(g, (V,), 0.1, torch.bfloat16)
+    Z = torch.full((N, V + 1), 7.0, dtype=torch.bfloat16, device=dev())
+    bom.bom_head_forward(H, W, b=b, Z=Z[:, :V])
+    ref = H.double() @ W.double() + b.double()
+    err = (Z[:, :V].double() - ref).abs()
+    # one rounding to bf16 (2^-9 of the value) and fp32 sums of d products of size 0.02
+    assert bool((err <= ref.abs() * 2.0 ** -8 + 1e-5).all())
+    assert (Z[:, V] == 7.0).all()
