@@ -136,11 +136,38 @@ __device__ __forceinline__ bool label_valid(int32_t y, int64_t V, int32_t ignore
     return true;
 }
 
+typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
+typedef u32x4_t __attribute__((aligned(2))) u32x4_any_t;   // 16 bytes at any bf16 address
+typedef f32x4 __attribute__((aligned(4))) f32x4_any_t;     // 16 bytes at any fp32 address
+
+// Elements i + sh of the eight bf16 of v at i (0 <= sh < 8), zeros past the last.
+__device__ __forceinline__ u32x4_t chunk_shr(u32x4_t v, int sh) {
+    uint64_t lo = v[0] | (uint64_t)v[1] << 32, hi = v[2] | (uint64_t)v[3] << 32;
+    if (sh >= 4) {
+        lo = hi;
+        hi = 0;
+    }
+    const int b = (sh & 3) * 16;
+    if (b != 0) {
+        lo = lo >> b | hi << (64 - b);
+        hi >>= b;
+    }
+    return u32x4_t{(uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32)};
+}
+// v with its elements from n on (n <= 0: all of them) replaced by bf16 -inf
+__device__ __forceinline__ u32x4_t pad_inf_from(u32x4_t v, int n) {
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+        const uint32_t keep = (2 * p < n ? 0xFFFFu : 0u) | (2 * p + 1 < n ? 0xFFFF0000u : 0u);
+        v[p] = (v[p] & keep) | (0xFF80FF80u & ~keep);
+    }
+    return v;
+}
+
 constexpr int kBufFlags = 0x00020000;   // raw buffer descriptor word 3: 32-bit data format
 constexpr int kOob = (int)0x80000000u;  // an offset past every range: the load returns zeros
 constexpr int kNonTemporal = 2;           // buffer access cache policy: nt (streamed data touched once)
 
-typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
 typedef int i32x4_t __attribute__((ext_vector_type(4)));   // buffer descriptor words for inline assembly
 
 // Raw buffer descriptor over [base, base + bytes): loads at offsets >= bytes return zeros and

@@ -922,11 +922,6 @@ __device__ __forceinline__ void wide_tile(const WideArgs& args, int id, uint16_t
     const int64_t lda = args.lda;
     const uint16_t* __restrict__ Xb = args.Xb;
     const int64_t ldb = args.ldb;
-    // UA: descriptors start at the 16-byte boundary at or before the operand, offsets carry the difference
-    const int da = UA ? (int)(reinterpret_cast<uintptr_t>(Xa) & 15) : 0;
-    const int db = UA ? (int)(reinterpret_cast<uintptr_t>(Xb) & 15) : 0;
-    Xa -= da / 2;
-    Xb -= db / 2;
     const int M = args.M, Nn = args.Nn, K = args.K, kps = args.kps;
     const int Km = UA && MODE == kWideDH ? K & ~7 : K;   // k of the main loop
     const TileRange& tr = args.tr;
@@ -990,16 +985,11 @@ __device__ __forceinline__ void wide_tile(const WideArgs& args, int id, uint16_t
     for (int q = 0; q < CPO; ++q) {
         geo(KA, lda, M - m0, q, &voff_a[q], &kc_a[q], &ok_a[q]);
         geo(KB, ldb, Nn - n0, q, &voff_b[q], &kc_b[q], &ok_b[q]);
-        if constexpr (UA) {
-            voff_a[q] += da;
-            if constexpr (KB) {
-                voff_b[q] += db;
-            } else {   // offsets from column 0, the chunk across the last column moved back, none past it
-                const int chunk = (wave * CPO + q) * 64 + l;
-                const int krow = chunk / 32, c0 = n0 + (((chunk % 32) ^ ((krow & 3) << 2)) << 3);
-                const int c = c0 + 8 <= Nn ? c0 : Nn - 8;
-                voff_b[q] = c0 < Nn ? (int)((int64_t)krow * ldb * 2) + c * 2 + db : kOob;
-            }
+        if constexpr (UA && !KB) {   // offsets from column 0, the chunk across the last column moved back, none past it
+            const int chunk = (wave * CPO + q) * 64 + l;
+            const int krow = chunk / 32, c0 = n0 + (((chunk % 32) ^ ((krow & 3) << 2)) << 3);
+            const int c = c0 + 8 <= Nn ? c0 : Nn - 8;
+            voff_b[q] = c0 < Nn ? (int)((int64_t)krow * ldb * 2) + c * 2 : kOob;
         }
     }
     // logits input: c of each row of the R operand and its label. dH: the tile's 256 rows are fixed, so
@@ -1018,8 +1008,8 @@ __device__ __forceinline__ void wide_tile(const WideArgs& args, int id, uint16_t
         if constexpr (ZB) zcol[q] = n0 + (((chunk % 32) ^ (((chunk / 32) & 3) << 2)) << 3);
     }
     // k-contiguous operands: one descriptor per workgroup over the tile's rows (exact extent)
-    const int bytes_ta = KA ? (int)(((int64_t)(min(LB, M - m0) - 1) * lda + K) * 2) + da : 0;
-    const int bytes_tb = KB ? (int)(((int64_t)(min(LB, Nn - n0) - 1) * ldb + K) * 2) + db : 0;
+    const int bytes_ta = KA ? (int)(((int64_t)(min(LB, M - m0) - 1) * lda + K) * 2) : 0;
+    const int bytes_tb = KB ? (int)(((int64_t)(min(LB, Nn - n0) - 1) * ldb + K) * 2) : 0;
     struct TileLoad {
         const uint16_t* ba;
         const uint16_t* bb;
@@ -1037,14 +1027,14 @@ __device__ __forceinline__ void wide_tile(const WideArgs& args, int id, uint16_t
             tl.bytes_a = bytes_ta;
         } else {
             tl.ba = Xa + (int64_t)kr * lda + m0;
-            tl.bytes_a = nv > 0 ? (int)(((int64_t)(nv1 - 1) * lda + (M - m0)) * 2) + da : 0;
+            tl.bytes_a = nv > 0 ? (int)(((int64_t)(nv1 - 1) * lda + (M - m0)) * 2) : 0;
         }
         if constexpr (KB) {
             tl.bb = Xb + (int64_t)n0 * ldb;
             tl.bytes_b = bytes_tb;
         } else if constexpr (UA) {
             tl.bb = Xb + (int64_t)kr * ldb;
-            tl.bytes_b = nv > 0 ? (int)(((int64_t)(nv1 - 1) * ldb + Nn) * 2) + db : 0;
+            tl.bytes_b = nv > 0 ? (int)(((int64_t)(nv1 - 1) * ldb + Nn) * 2) : 0;
         } else {
             tl.bb = Xb + (int64_t)kr * ldb + n0;
             tl.bytes_b = nv > 0 ? (int)(((int64_t)(nv1 - 1) * ldb + (Nn - n0)) * 2) : 0;
@@ -1394,8 +1384,6 @@ __global__ __launch_bounds__(256) void splitk_rank1_kernel(const float* __restri
 // UA: W with rows at any 2-byte alignment and of any length from eight; the chunk across the end of a unit is
 // read from its last eight columns, with the columns that an earlier chunk holds masked out.
 constexpr int kHsRows = 128;
-typedef u32x4_t __attribute__((aligned(2))) u32x4_any_t;   // 16 bytes at any bf16 address
-typedef f32x4 __attribute__((aligned(4))) f32x4_any_t;
 template <bool UA>
 __global__ __launch_bounds__(256) void vjp_rank1_kernel(const uint16_t* __restrict__ W, int64_t ldw, int d, int V,
                                                         const float* __restrict__ q_hat, int nu, int uch, int ucw,
@@ -1549,21 +1537,6 @@ struct FusedArgs {
 // element offset of (row, col) in a 64 x 64 bf16 LDS tile whose 16-byte chunks are swizzled by row
 __device__ __forceinline__ int ftile_off(int row, int col) { return row * FB + ((((col >> 3) ^ (row & 7))) << 3) + (col & 7); }
 
-// Elements i + sh of the eight bf16 of v at i (0 <= sh < 8), zeros past the last.
-__device__ __forceinline__ u32x4_t chunk_shr(u32x4_t v, int sh) {
-    uint64_t lo = v[0] | (uint64_t)v[1] << 32, hi = v[2] | (uint64_t)v[3] << 32;
-    if (sh >= 4) {
-        lo = hi;
-        hi = 0;
-    }
-    const int b = (sh & 3) * 16;
-    if (b != 0) {
-        lo = lo >> b | hi << (64 - b);
-        hi >>= b;
-    }
-    return u32x4_t{(uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32)};
-}
-
 // UA: R (or Z) and W at any 2-byte alignment and V of any size from eight: a chunk across the last column is read
 // from the row's last eight columns and shifted to its place on the way to LDS.
 template <bool is_dw, bool UA>
@@ -1589,28 +1562,26 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& a, int id, uint16_t 
     const uint16_t* pb = is_dw ? a.R : a.W;
     const int64_t lda = is_dw ? a.ldh : a.ldr, ldb = is_dw ? a.ldr : a.ldw;
     const int rows_a = is_dw ? a.N : a.N, rows_b = is_dw ? a.N : a.d;
-    // UA: descriptors start at the 16-byte boundary at or before the operand
-    const int xa = UA ? (int)(reinterpret_cast<uintptr_t>(pa) & 15) : 0, xb = UA ? (int)(reinterpret_cast<uintptr_t>(pb) & 15) : 0;
-    const auto da = make_desc(pa - xa / 2, (int)(((int64_t)(rows_a - 1) * lda + (is_dw ? a.d : a.V)) * 2) + xa);
-    const auto db_ = make_desc(pb - xb / 2, (int)(((int64_t)(rows_b - 1) * ldb + a.V) * 2) + xb);
+    const auto da = make_desc(pa, (int)(((int64_t)(rows_a - 1) * lda + (is_dw ? a.d : a.V)) * 2));
+    const auto db_ = make_desc(pb, (int)(((int64_t)(rows_b - 1) * ldb + a.V) * 2));
     auto vcol = [&](int c) { return UA && c + 8 > a.V ? a.V - 8 : c; };   // where the chunk at column c < V is read
     auto off_a = [&](int k0, int e) {
         const int r = r0 + 32 * e;
         if constexpr (is_dw) {
             const int k = k0 + r, m = m0 + lc * 8;
-            return (k < a.N && m < a.d) ? (int)(((int64_t)k * lda + m) * 2) + xa : kOob;
+            return (k < a.N && m < a.d) ? (int)(((int64_t)k * lda + m) * 2) : kOob;
         }
         const int i = m0 + r, k = k0 + lc * 8;
-        return (i < a.N && k < a.V) ? (int)(((int64_t)i * lda + vcol(k)) * 2) + xa : kOob;
+        return (i < a.N && k < a.V) ? (int)(((int64_t)i * lda + vcol(k)) * 2) : kOob;
     };
     auto off_b = [&](int k0, int e) {
         const int r = r0 + 32 * e;
         if constexpr (is_dw) {
             const int k = k0 + r, n = n0 + lc * 8;
-            return (k < a.N && n < a.V) ? (int)(((int64_t)k * ldb + vcol(n)) * 2) + xb : kOob;
+            return (k < a.N && n < a.V) ? (int)(((int64_t)k * ldb + vcol(n)) * 2) : kOob;
         }
         const int j = n0 + r, k = k0 + lc * 8;
-        return (j < a.d && k < a.V) ? (int)(((int64_t)j * ldb + vcol(k)) * 2) + xb : kOob;
+        return (j < a.d && k < a.V) ? (int)(((int64_t)j * ldb + vcol(k)) * 2) : kOob;
     };
     // one k tile in registers: the four 16-byte copies and what the rank-1 sums need with them
     struct Set {

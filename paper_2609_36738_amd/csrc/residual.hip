@@ -110,9 +110,19 @@ __device__ __forceinline__ int block_min(int v, int* sh) {
     return r;
 }
 
-template <int VEC>
+template <int VEC, bool UA = false>
 __device__ __forceinline__ void store_f32_chunk(float* row, int col, int V, const float* x) {
-    if (col < V) {
+    if (UA) {   // rows of any length: 4-byte aligned, the last chunk of a row element by element
+        if (col + VEC <= V) {
+#pragma unroll
+            for (int k = 0; k < VEC; k += 4)
+                *reinterpret_cast<f32x4_any_t*>(row + col + k) = f32x4{x[k], x[k + 1], x[k + 2], x[k + 3]};
+        } else {
+#pragma unroll
+            for (int k = 0; k < VEC; ++k)
+                if (col + k < V) row[col + k] = x[k];
+        }
+    } else if (col < V) {
         if (VEC % 4 == 0) {
 #pragma unroll
             for (int k = 0; k < VEC; k += 4) VecIO<float, 4>::store(row + col + k, x + k);
@@ -127,7 +137,8 @@ __device__ __forceinline__ void store_f32_chunk(float* row, int col, int V, cons
 // Single pass. Thread `tid` owns columns (c * THREADS + tid) * VEC + k, c < NCH, k < VEC.
 // PACKED (bf16 only, for wide rows): the row stays as raw bf16 pairs and exp is evaluated twice
 // (once for the sum, once for p); otherwise e = exp(z - m) is kept in fp32 registers.
-template <typename T, int THREADS, int VEC, int NCH, bool PACKED>
+// UA: bf16 rows at any alignment and of any length from eight.
+template <typename T, int THREADS, int VEC, int NCH, bool PACKED, bool UA>
 __global__ __launch_bounds__(THREADS) void residual_rows_kernel(
     const T* __restrict__ Z, int64_t ldz, int N, int V, const int32_t* __restrict__ labels, int32_t ignore_index,
     float* __restrict__ row_lse, int32_t* __restrict__ row_argmax, float* __restrict__ row_target,
@@ -173,8 +184,8 @@ __global__ __launch_bounds__(THREADS) void residual_rows_kernel(
                 } else {
                     xw[c * 4 + 0] = u.x; xw[c * 4 + 1] = u.y; xw[c * 4 + 2] = u.z; xw[c * 4 + 3] = u.w;
                 }
-            } else if (last) {
-                load_chunk<T, VEC>(zr, col, V, -INFINITY, &x[c * VEC]);
+            } else if (last || UA) {
+                load_row_chunk<T, VEC, UA>(zr, col, V, &x[c * VEC]);
             } else {
                 VecIO<T, VEC>::load(zr + col, &x[c * VEC]);
             }
@@ -250,14 +261,14 @@ __global__ __launch_bounds__(THREADS) void residual_rows_kernel(
                 }
 #pragma unroll
                 for (int k = 0; k < VEC; ++k) acc[c * VEC + k] += p[k];
-                if (rr) store_chunk<T, VEC>(rr, (c * THREADS + tid) * VEC, V, p);
+                if (rr) store_row_chunk<T, VEC, UA>(rr, (c * THREADS + tid) * VEC, V, p);
             }
         } else if (rr) {
             float zero[VEC];
 #pragma unroll
             for (int k = 0; k < VEC; ++k) zero[k] = 0.f;
 #pragma unroll
-            for (int c = 0; c < NCH; ++c) store_chunk<T, VEC>(rr, (c * THREADS + tid) * VEC, V, zero);
+            for (int c = 0; c < NCH; ++c) store_row_chunk<T, VEC, UA>(rr, (c * THREADS + tid) * VEC, V, zero);
         }
         if (tid == 0) {
             row_lse[i] = lse;
@@ -273,7 +284,7 @@ __global__ __launch_bounds__(THREADS) void residual_rows_kernel(
 
     float* prow = ws.part + (int64_t)blockIdx.x * V;
 #pragma unroll
-    for (int c = 0; c < NCH; ++c) store_f32_chunk<VEC>(prow, (c * THREADS + tid) * VEC, V, &acc[c * VEC]);
+    for (int c = 0; c < NCH; ++c) store_f32_chunk<VEC, UA>(prow, (c * THREADS + tid) * VEC, V, &acc[c * VEC]);
     if (tid == 0) {
         ws.wg_count[blockIdx.x] = cnt;
         ws.wg_loss[blockIdx.x] = ce;
@@ -293,7 +304,9 @@ __global__ __launch_bounds__(THREADS) void residual_rows_kernel(
 // where the thread's maximum first appeared. The second pass forms p = exp(z - lse), the
 // residual, the column sums and R. Per-row words shared across the workgroup are double buffered,
 // and the previous row's argmax and target logit are written after the next barrier.
-template <int THREADS, int NCH>
+// UA: rows at any alignment and of any length. Loads and stores are then unaligned 16-byte accesses; the V % 8
+// columns past the last whole chunk (the tail chunk) have a load and stores of their own in the thread that owns them.
+template <int THREADS, int NCH, bool UA>
 __global__ __launch_bounds__(THREADS) void residual_rows_lds_kernel(
     const uint16_t* __restrict__ Z, int64_t ldz, int N, int V, const int32_t* __restrict__ labels, int32_t ignore_index,
     float* __restrict__ row_lse, int32_t* __restrict__ row_argmax, float* __restrict__ row_target,
@@ -328,31 +341,46 @@ __global__ __launch_bounds__(THREADS) void residual_rows_lds_kernel(
     const int voff = tid * 16;
     // the first chunk index of this wave's lanes whose chunks may lie past the row's end
     const int wave_last = (tid | (kWave - 1));
-    auto row_desc = [&](int i) { return make_desc(Z + (int64_t)i * ldz, V * 2); };
+    const int Vw = UA ? V & ~(VEC - 1) : V;   // columns in whole chunks; UA: the tail chunk holds the others
+    auto row_desc = [&](int i) { return make_desc(Z + (int64_t)i * ldz, Vw * 2); };
     auto load_chunk = [&](const __amdgpu_buffer_rsrc_t& d, int c) {
         const u32x4_t w = __builtin_amdgcn_raw_buffer_load_b128(d, voff + c * THREADS * 16, 0, 0);
         return make_uint4(w[0], w[1], w[2], w[3]);
     };
+    // UA: the thread that owns the tail chunk (slot tail_slot) reads the row's last eight columns beside its whole
+    // chunks, parks them shifted to their place, and stores the tail's columns one by one
+    const int tail_slot = UA && Vw < V && (Vw / VEC) % THREADS == tid ? Vw / VEC : -1;
+    auto load_tail = [&](int i) {
+        const u32x4_t w = *reinterpret_cast<const u32x4_any_t*>(Z + (int64_t)i * ldz + (V - VEC));
+        return make_uint4(w[0], w[1], w[2], w[3]);
+    };
+    auto park_tail = [&](uint4 w) {
+        const u32x4_t x = pad_inf_from(chunk_shr(u32x4_t{w.x, w.y, w.z, w.w}, VEC - (V - Vw)), V - Vw);
+        slots[tail_slot] = make_uint4(x[0], x[1], x[2], x[3]);
+    };
     // park chunk c of a row (chunks past the row's end: bf16 -inf)
     auto park = [&](int c, uint4 w) {
-        if ((c * THREADS + wave_last) * VEC >= V) {   // uniform per wave
-            const bool ok = ((c * THREADS + tid) * VEC) < V;
+        if ((c * THREADS + wave_last) * VEC >= Vw) {   // uniform per wave
+            const bool ok = ((c * THREADS + tid) * VEC) < Vw;
             const uint32_t mk = lane_mask(ok), fb = 0xFF80FF80u & ~mk;
             w = make_uint4((w.x & mk) | fb, (w.y & mk) | fb, (w.z & mk) | fb, (w.w & mk) | fb);
         }
         slots[c * THREADS + tid] = w;
     };
-    uint4 nxt[NCH];
+    uint4 nxt[NCH], nxt_tail = make_uint4(0, 0, 0, 0);
     if (nr > 0) {
         const auto d0 = row_desc(row_of(0));
 #pragma unroll
         for (int c = 0; c < NCH; ++c) nxt[c] = load_chunk(d0, c);
+        if (tail_slot >= 0) nxt_tail = load_tail(row_of(0));
 #pragma unroll
         for (int c = 0; c < NCH; ++c) park(c, nxt[c]);
+        if (tail_slot >= 0) park_tail(nxt_tail);
         if (nr > 1) {
             const auto d1 = row_desc(row_of(1));
 #pragma unroll
             for (int c = 0; c < NCH; ++c) nxt[c] = load_chunk(d1, c);
+            if (tail_slot >= 0) nxt_tail = load_tail(row_of(1));
         }
     }
     if (tid < 2) sh_am[tid] = INT_MAX;   // first used after the first barrier
@@ -435,7 +463,7 @@ __global__ __launch_bounds__(THREADS) void residual_rows_lds_kernel(
         const bool valid = label_valid(y, V, ignore_index, &rbad);
         bad |= rbad;
         // R row stores go through a buffer descriptor (no R: an empty range, every store dropped)
-        const auto rdesc = make_desc(R ? R + (int64_t)i * ldr : nullptr, R ? V * 2 : 0);
+        const auto rdesc = make_desc(R ? R + (int64_t)i * ldr : nullptr, R ? Vw * 2 : 0);
         const bool has_next = j + 1 < nr, has_next2 = j + 2 < nr;
         const auto dn = row_desc(has_next2 ? row_of(j + 2) : i);
         // pass 2 (LDS): p = exp(z - lse), residual, column accumulation, R; the label's owner
@@ -472,15 +500,26 @@ __global__ __launch_bounds__(THREADS) void residual_rows_lds_kernel(
             w[3] = pack_bf16x2(p[6], p[7]);
             __builtin_amdgcn_raw_buffer_store_b128(w, rdesc, voff + c * THREADS * 16, 0, 0);
         }
+        if (tail_slot >= 0 && R != nullptr) {
+            float x[VEC];
+            unpack(slots[tail_slot], x);
+#pragma unroll
+            for (int k = 0; k < VEC - 1; ++k) {
+                const float p = exp2_fast(fmaf(x[k], kLog2e, -lse2)) - (y == Vw + k ? 1.f : 0.f);
+                if (Vw + k < V) R[(int64_t)i * ldr + Vw + k] = f32_to_bf16(valid ? p : 0.f);
+            }
+        }
         if (tid == 0) row_lse[i] = lse;
         // park the next row (its loads were issued before this row's stores, so waiting for them
         // does not wait for the stores) and load the one after into the freed registers
         if (has_next) {
 #pragma unroll
             for (int c = 0; c < NCH; ++c) park(c, nxt[c]);
+            if (tail_slot >= 0) park_tail(nxt_tail);
             if (has_next2) {
 #pragma unroll
                 for (int c = 0; c < NCH; ++c) nxt[c] = load_chunk(dn, c);
+                if (tail_slot >= 0) nxt_tail = load_tail(row_of(j + 2));
             }
         }
         prev_lse = lse;
@@ -490,7 +529,7 @@ __global__ __launch_bounds__(THREADS) void residual_rows_lds_kernel(
     if (tid == 0 && nr > 0) finish_row(row_of(nr - 1), (nr - 1) & 1, prev_lse, prev_valid);
     float* prow = ws.part + (int64_t)blockIdx.x * V;
 #pragma unroll
-    for (int c = 0; c < NCH; ++c) store_f32_chunk<VEC>(prow, (c * THREADS + tid) * VEC, V, &acc[c * VEC]);
+    for (int c = 0; c < NCH; ++c) store_f32_chunk<VEC, UA>(prow, (c * THREADS + tid) * VEC, V, &acc[c * VEC]);
     if (tid == 0) {
         ws.wg_count[blockIdx.x] = cnt;
         ws.wg_loss[blockIdx.x] = ce;
@@ -902,21 +941,22 @@ __global__ void zero_u64_kernel(unsigned long long* __restrict__ p, int64_t n) {
 
 // ---------------------------------------------------------------------------------------------
 // Two pass, stats: one wave per row, online (max, sum, argmax) per lane, then a butterfly merge.
-template <typename T, int VEC, int UNROLL>
+template <typename T, int VEC, int UNROLL, bool UA>
 __global__ __launch_bounds__(kStatsRowsPerWG * kWave) void residual_stats_kernel(
     const T* __restrict__ Z, int64_t ldz, int N, int V, const int32_t* __restrict__ labels, int32_t ignore_index,
     float* __restrict__ row_lse, int32_t* __restrict__ row_argmax, float* __restrict__ row_target, Partials ws) {
     constexpr int STEP = kWave * VEC * UNROLL;
+    const int Vw = UA ? V & ~(VEC - 1) : V;   // columns in whole chunks
     const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
     const int i = blockIdx.x * kStatsRowsPerWG + wave;
     float m = -INFINITY, l = 0.f;
     int idx = INT_MAX;
     if (i < N) {
         const T* zr = Z + (int64_t)i * ldz;
-        for (int base = 0; base < V; base += STEP) {
+        for (int base = 0; base < Vw; base += STEP) {
             float x[UNROLL * VEC];
 #pragma unroll
-            for (int u = 0; u < UNROLL; ++u) load_chunk<T, VEC>(zr, base + (u * kWave + lane) * VEC, V, -INFINITY, &x[u * VEC]);
+            for (int u = 0; u < UNROLL; ++u) load_whole_chunk<T, VEC, UA>(zr, base + (u * kWave + lane) * VEC, Vw, &x[u * VEC]);
             float cm = -INFINITY;
 #pragma unroll
             for (int k = 0; k < UNROLL * VEC; ++k) cm = fmaxf(cm, x[k]);
@@ -936,6 +976,15 @@ __global__ __launch_bounds__(kStatsRowsPerWG * kWave) void residual_stats_kernel
 #pragma unroll
                 for (int k = 0; k < UNROLL * VEC; ++k) l += exp2_fast(fmaf(x[k], kLog2e, -m2));
             }
+        }
+        if (UA && lane < V - Vw) {   // the columns past the last whole chunk, one per lane
+            const float x = load_scalar<T>(zr + Vw + lane);
+            if (x > m) {
+                l = (m == -INFINITY) ? 0.f : l * exp2_fast((m - x) * kLog2e);
+                m = x;
+                idx = Vw + lane;
+            }
+            if (m != -INFINITY) l += exp2_fast((x - m) * kLog2e);
         }
     }
 #pragma unroll
@@ -990,7 +1039,7 @@ __global__ __launch_bounds__(kStatsRowsPerWG * kWave) void residual_stats_kernel
 
 // Two pass, columns: workgroup (cb, rb) owns columns col0 + (c * THREADS + tid) * VEC + k and rows
 // [rb * row_block, ...); p = exp(z - lse) with the stats kernel's lse.
-template <typename T, int VEC>
+template <typename T, int VEC, bool UA>
 __global__ __launch_bounds__(kColsThreads) void residual_cols_kernel(
     const T* __restrict__ Z, int64_t ldz, int N, int V, const int32_t* __restrict__ labels, int32_t ignore_index,
     const float* __restrict__ row_lse, T* __restrict__ R, int64_t ldr, int row_block, float* __restrict__ part) {
@@ -1002,6 +1051,11 @@ __global__ __launch_bounds__(kColsThreads) void residual_cols_kernel(
     const int col0 = cb * SLAB;
     const int r0 = rb * row_block;
     const int r1 = min(N, r0 + row_block);
+    // UA: the chunks are the row's whole ones, at any alignment; the first threads of the last slab's workgroups
+    // take one each of the columns past them
+    const int Vw = UA ? V & ~(VEC - 1) : V;
+    const int tail = UA && cb == nslab - 1 && tid < V - Vw ? Vw + tid : -1;
+    float acc_tail = 0.f;
     float acc[VPT];
 #pragma unroll
     for (int k = 0; k < VPT; ++k) acc[k] = 0.f;
@@ -1016,7 +1070,8 @@ __global__ __launch_bounds__(kColsThreads) void residual_cols_kernel(
 #pragma unroll
                 for (int k = 0; k < VEC; ++k) zero[k] = 0.f;
 #pragma unroll
-                for (int c = 0; c < kColsCPT; ++c) store_chunk<T, VEC>(rr, col0 + (c * kColsThreads + tid) * VEC, V, zero);
+                for (int c = 0; c < kColsCPT; ++c) store_whole_chunk<T, VEC, UA>(rr, col0 + (c * kColsThreads + tid) * VEC, Vw, zero);
+                if (tail >= 0) store_scalar<T>(rr + tail, 0.f);
             }
             continue;
         }
@@ -1024,7 +1079,7 @@ __global__ __launch_bounds__(kColsThreads) void residual_cols_kernel(
         const float lse2 = row_lse[i] * kLog2e;
         float x[VPT];
 #pragma unroll
-        for (int c = 0; c < kColsCPT; ++c) load_chunk<T, VEC>(zr, col0 + (c * kColsThreads + tid) * VEC, V, -INFINITY, &x[c * VEC]);
+        for (int c = 0; c < kColsCPT; ++c) load_whole_chunk<T, VEC, UA>(zr, col0 + (c * kColsThreads + tid) * VEC, Vw, &x[c * VEC]);
 #pragma unroll
         for (int k = 0; k < VPT; ++k) x[k] = exp2_fast(fmaf(x[k], kLog2e, -lse2));
         const int yl = y - col0;
@@ -1036,14 +1091,20 @@ __global__ __launch_bounds__(kColsThreads) void residual_cols_kernel(
         }
 #pragma unroll
         for (int k = 0; k < VPT; ++k) acc[k] += x[k];
+        if (tail >= 0) {
+            const float p = exp2_fast(fmaf(load_scalar<T>(zr + tail), kLog2e, -lse2)) - (y == tail ? 1.0f : 0.f);
+            acc_tail += p;
+            if (rr) store_scalar<T>(rr + tail, p);
+        }
         if (rr) {
 #pragma unroll
-            for (int c = 0; c < kColsCPT; ++c) store_chunk<T, VEC>(rr, col0 + (c * kColsThreads + tid) * VEC, V, &x[c * VEC]);
+            for (int c = 0; c < kColsCPT; ++c) store_whole_chunk<T, VEC, UA>(rr, col0 + (c * kColsThreads + tid) * VEC, Vw, &x[c * VEC]);
         }
     }
     float* prow = part + (int64_t)rb * V;
 #pragma unroll
-    for (int c = 0; c < kColsCPT; ++c) store_f32_chunk<VEC>(prow, col0 + (c * kColsThreads + tid) * VEC, V, &acc[c * VEC]);
+    for (int c = 0; c < kColsCPT; ++c) store_f32_chunk<VEC, UA>(prow, col0 + (c * kColsThreads + tid) * VEC, Vw, &acc[c * VEC]);
+    if (tail >= 0) prow[tail] = acc_tail;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1123,7 +1184,7 @@ __global__ __launch_bounds__(kFinThreads) void residual_finish_kernel(int nparts
 }
 
 // ---------------------------------------------------------------------------------------------
-template <int THREADS, int NCH>
+template <int THREADS, int NCH, bool UA>
 hipError_t launch_rows_lds(const uint16_t* Z, int64_t ldz, int N, int V, const int32_t* labels, int32_t ignore_index,
                            float* row_lse, int32_t* row_argmax, float* row_target, uint16_t* R, int64_t ldr, Partials ws,
                            int* nwg_out, hipStream_t stream) {
@@ -1131,12 +1192,12 @@ hipError_t launch_rows_lds(const uint16_t* Z, int64_t ldz, int N, int V, const i
     const int rpw = (N + nwg - 1) / nwg;
     nwg = (N + rpw - 1) / rpw;
     *nwg_out = nwg;
-    hipLaunchKernelGGL((residual_rows_lds_kernel<THREADS, NCH>), dim3(nwg), dim3(THREADS), 0, stream, Z, ldz, N, V, labels,
+    hipLaunchKernelGGL((residual_rows_lds_kernel<THREADS, NCH, UA>), dim3(nwg), dim3(THREADS), 0, stream, Z, ldz, N, V, labels,
                        ignore_index, row_lse, row_argmax, row_target, R, ldr, rpw, ws);
     return hipGetLastError();
 }
 
-template <typename T, int THREADS, int VEC, int NCH>
+template <typename T, int THREADS, int VEC, int NCH, bool UA>
 hipError_t launch_rows(const T* Z, int64_t ldz, int N, int V, const int32_t* labels, int32_t ignore_index, float* row_lse,
                        int32_t* row_argmax, float* row_target, T* R, int64_t ldr, Partials ws, int* nwg_out,
                        hipStream_t stream) {
@@ -1146,7 +1207,7 @@ hipError_t launch_rows(const T* Z, int64_t ldz, int N, int V, const int32_t* lab
     *nwg_out = nwg;
     // wide bf16 rows at 512 threads keep raw pairs (registers: acc + packed row) instead of fp32 e
     constexpr bool kPacked = (VEC == 8) && (NCH > 8);
-    hipLaunchKernelGGL((residual_rows_kernel<T, THREADS, VEC, NCH, kPacked>), dim3(nwg), dim3(THREADS), 0, stream, Z,
+    hipLaunchKernelGGL((residual_rows_kernel<T, THREADS, VEC, NCH, kPacked, UA>), dim3(nwg), dim3(THREADS), 0, stream, Z,
                        ldz, N, V, labels, ignore_index, row_lse, row_argmax, row_target, R, ldr, rpw, ws);
     return hipGetLastError();
 }
@@ -1156,15 +1217,18 @@ constexpr int kNchSet[] = {1, 2, 3, 4, 6, 8, 10, 13};
 constexpr int kLdsNchSet[] = {2, 3, 4, 6, 8, 10, 12, 13, 14};
 constexpr int kLds1kNchSet[] = {2, 3, 4, 5, 6};
 
-template <typename T, int VEC>
+template <typename T, int VEC, bool UA>
 hipError_t dispatch_rows(int nch, int threads, const T* Z, int64_t ldz, int N, int V, const int32_t* labels,
                          int32_t ig, float* lse, int32_t* am, float* tg, T* R, int64_t ldr, Partials ws, int* nwg,
                          hipStream_t st) {
-#define BOM_ROWS(TH, NC) launch_rows<T, TH, VEC, NC>(Z, ldz, N, V, labels, ig, lse, am, tg, R, ldr, ws, nwg, st)
+#define BOM_ROWS(TH, NC) launch_rows<T, TH, VEC, NC, UA>(Z, ldz, N, V, labels, ig, lse, am, tg, R, ldr, ws, nwg, st)
     if (threads == 64) return BOM_ROWS(64, 1);
     if (threads == 128) return BOM_ROWS(128, 1);
     if (threads == 256) return BOM_ROWS(256, 1);
-    if (threads == 1024) {
+    if constexpr (UA) {   // rows of one chunk per thread, or parked in LDS (plan_single for 16-byte bf16 chunks)
+        if (threads == 512 && nch == 1) return BOM_ROWS(512, 1);
+        if (threads > 0) return hipErrorInvalidValue;
+    } else if (threads == 1024) {
         switch (nch) {
             case 1: return BOM_ROWS(1024, 1);
             case 2: return BOM_ROWS(1024, 2);
@@ -1175,7 +1239,7 @@ hipError_t dispatch_rows(int nch, int threads, const T* Z, int64_t ldz, int N, i
     }
     if constexpr (std::is_same<T, uint16_t>::value && VEC == 8) {
         if (threads == -512) {   // bf16 rows parked in LDS, next row prefetched
-#define BOM_LDS(NC) launch_rows_lds<512, NC>(Z, ldz, N, V, labels, ig, lse, am, tg, R, ldr, ws, nwg, st)
+#define BOM_LDS(NC) launch_rows_lds<512, NC, UA>(Z, ldz, N, V, labels, ig, lse, am, tg, R, ldr, ws, nwg, st)
             switch (nch) {
                 case 2: return BOM_LDS(2);
                 case 3: return BOM_LDS(3);
@@ -1191,7 +1255,7 @@ hipError_t dispatch_rows(int nch, int threads, const T* Z, int64_t ldz, int N, i
 #undef BOM_LDS
         }
         if (threads == -1024) {   // the same with 1024-thread workgroups (16 waves per CU)
-#define BOM_LDS(NC) launch_rows_lds<1024, NC>(Z, ldz, N, V, labels, ig, lse, am, tg, R, ldr, ws, nwg, st)
+#define BOM_LDS(NC) launch_rows_lds<1024, NC, UA>(Z, ldz, N, V, labels, ig, lse, am, tg, R, ldr, ws, nwg, st)
             switch (nch) {
                 case 2: return BOM_LDS(2);
                 case 3: return BOM_LDS(3);
@@ -1203,17 +1267,20 @@ hipError_t dispatch_rows(int nch, int threads, const T* Z, int64_t ldz, int N, i
 #undef BOM_LDS
         }
     }
-    switch (nch) {
-        case 1: return BOM_ROWS(512, 1);
-        case 2: return BOM_ROWS(512, 2);
-        case 3: return BOM_ROWS(512, 3);
-        case 4: return BOM_ROWS(512, 4);
-        case 6: return BOM_ROWS(512, 6);
-        case 8: return BOM_ROWS(512, 8);
-        case 10: return BOM_ROWS(512, 10);
-        case 13: return BOM_ROWS(512, 13);
-        default: return hipErrorInvalidValue;
+    if constexpr (!UA) {
+        switch (nch) {
+            case 1: return BOM_ROWS(512, 1);
+            case 2: return BOM_ROWS(512, 2);
+            case 3: return BOM_ROWS(512, 3);
+            case 4: return BOM_ROWS(512, 4);
+            case 6: return BOM_ROWS(512, 6);
+            case 8: return BOM_ROWS(512, 8);
+            case 10: return BOM_ROWS(512, 10);
+            case 13: return BOM_ROWS(512, 13);
+            default: return hipErrorInvalidValue;
+        }
     }
+    return hipErrorInvalidValue;
 #undef BOM_ROWS
 }
 
@@ -1338,7 +1405,9 @@ hipError_t launch_split(const uint16_t* Z, int64_t ldz, int N, int V, const int3
     return hipGetLastError();
 }
 
-template <typename T, int VEC>
+// UA: bf16 rows at any alignment and of any length from eight, in the same 16-byte chunks. Rows too wide for one
+// workgroup's LDS then take the two passes (the split rows' copies straight into LDS are aligned ones).
+template <typename T, int VEC, bool UA = false>
 hipError_t run_residual(const T* Z, int N, int V, int64_t ldz, const int32_t* labels, int32_t ig, float* s, float* lse,
                         int32_t* am, float* tg, T* R, int64_t ldr, float* loss, int32_t* n_valid, int32_t* flags,
                         Partials ws, hipStream_t st) {
@@ -1346,9 +1415,11 @@ hipError_t run_residual(const T* Z, int N, int V, int64_t ldz, const int32_t* la
     hipError_t e;
     int S = 0, W = 0;
     bool split = false;
-    if constexpr (std::is_same<T, uint16_t>::value && VEC == 8) split = plan_split(V, &S, &W, &nch);
-    if (plan_single(V, VEC, &threads, &nch)) {
-        e = dispatch_rows<T, VEC>(nch, threads, Z, ldz, N, V, labels, ig, lse, am, tg, R, ldr, ws, &nwg, st);
+    if constexpr (std::is_same<T, uint16_t>::value && VEC == 8 && !UA) split = plan_split(V, &S, &W, &nch);
+    // (a plan override may ask for several register chunks per thread, which UA rows do not have)
+    const bool single = plan_single(V, VEC, &threads, &nch) && !(UA && threads > 0 && (threads > 512 || nch > 1));
+    if (single) {
+        e = dispatch_rows<T, VEC, UA>(nch, threads, Z, ldz, N, V, labels, ig, lse, am, tg, R, ldr, ws, &nwg, st);
         nparts = nwg;
     } else if (split) {
         if constexpr (std::is_same<T, uint16_t>::value && VEC == 8)
@@ -1356,7 +1427,7 @@ hipError_t run_residual(const T* Z, int N, int V, int64_t ldz, const int32_t* la
     } else {
         nwg = (N + kStatsRowsPerWG - 1) / kStatsRowsPerWG;
         constexpr int UNROLL = VEC == 1 ? 8 : 4;
-        hipLaunchKernelGGL((residual_stats_kernel<T, VEC, UNROLL>), dim3(nwg), dim3(kStatsRowsPerWG * kWave), 0, st, Z,
+        hipLaunchKernelGGL((residual_stats_kernel<T, VEC, UNROLL, UA>), dim3(nwg), dim3(kStatsRowsPerWG * kWave), 0, st, Z,
                            ldz, N, V, labels, ig, lse, am, tg, ws);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
@@ -1364,7 +1435,7 @@ hipError_t run_residual(const T* Z, int N, int V, int64_t ldz, const int32_t* la
         const int rb = cols_row_block(N, V, VEC);
         nparts = (N + rb - 1) / rb;
         dim3 grid((unsigned)(((V + slab - 1) / slab) * nparts));
-        hipLaunchKernelGGL((residual_cols_kernel<T, VEC>), grid, dim3(kColsThreads), 0, st, Z, ldz, N, V, labels, ig,
+        hipLaunchKernelGGL((residual_cols_kernel<T, VEC, UA>), grid, dim3(kColsThreads), 0, st, Z, ldz, N, V, labels, ig,
                            lse, R, ldr, rb, ws.part);
         e = hipGetLastError();
     }
@@ -1492,6 +1563,9 @@ hipError_t launch_residual(const void* Z, bom_dtype dt, int N, int V, int64_t ld
     if (dt == BOM_BF16) {
         const uint16_t* z = static_cast<const uint16_t*>(Z);
         uint16_t* r = static_cast<uint16_t*>(R);
+        if (!vec_ok && V >= 8)
+            return run_residual<uint16_t, 8, true>(z, N, V, ldz, labels, ignore_index, s, row_lse, row_argmax, row_target,
+                                                   r, ldr, loss, n_valid, flags, ws, stream);
         return vec_ok ? run_residual<uint16_t, 8>(z, N, V, ldz, labels, ignore_index, s, row_lse, row_argmax, row_target,
                                                   r, ldr, loss, n_valid, flags, ws, stream)
                       : run_residual<uint16_t, 1>(z, N, V, ldz, labels, ignore_index, s, row_lse, row_argmax, row_target,
@@ -1553,7 +1627,7 @@ hipError_t launch_residual_from_stats(const uint16_t* Z, int64_t ldz, int N, int
     if (e != hipSuccess) return e;
     const int slab = kColsThreads * kColsCPT * 8;
     dim3 grid((unsigned)(((V + slab - 1) / slab) * L.nparts));
-    hipLaunchKernelGGL((residual_cols_kernel<uint16_t, 8>), grid, dim3(kColsThreads), 0, st, Z, ldz, N, V, labels,
+    hipLaunchKernelGGL((residual_cols_kernel<uint16_t, 8, false>), grid, dim3(kColsThreads), 0, st, Z, ldz, N, V, labels,
                        ignore_index, row_lse, R, ldr, L.rb, ws.part);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     hipLaunchKernelGGL(residual_finish_kernel, dim3((V + kWave - 1) / kWave), dim3(kFinThreads), 0, st, L.nparts, V, L.nwg,

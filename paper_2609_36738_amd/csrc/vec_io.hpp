@@ -84,4 +84,66 @@ __device__ __forceinline__ void store_chunk(T* row, int col, int V, const float*
     if (col < V) VecIO<T, VEC>::store(row + col, x);
 }
 
+// The same, for bf16 at any alignment if UA (V, the columns in whole chunks, is then a multiple of VEC and at least VEC).
+template <typename T, int VEC, bool UA>
+__device__ __forceinline__ void load_whole_chunk(const T* row, int col, int V, float* x) {
+    if constexpr (UA) {
+        const bool ok = col < V;
+        const u32x4_t w = *reinterpret_cast<const u32x4_any_t*>(row + (ok ? col : V - 8));
+        const uint32_t m = lane_mask(ok), fb = 0xFF80FF80u & ~m;
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            const uint32_t v = (w[p] & m) | fb;
+            x[2 * p] = bf16_lo(v);
+            x[2 * p + 1] = bf16_hi(v);
+        }
+    } else {
+        load_chunk<T, VEC>(row, col, V, -INFINITY, x);
+    }
+}
+template <typename T, int VEC, bool UA>
+__device__ __forceinline__ void store_whole_chunk(T* row, int col, int V, const float* x) {
+    if constexpr (UA) {
+        if (col < V)
+            *reinterpret_cast<u32x4_any_t*>(row + col) = u32x4_t{pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]),
+                                                                 pack_bf16x2(x[4], x[5]), pack_bf16x2(x[6], x[7])};
+    } else {
+        store_chunk<T, VEC>(row, col, V, x);
+    }
+}
+
+// The same for bf16 rows at any alignment and of any length V >= 8 (UA): the chunk across the row's end is read
+// from the row's last eight columns and shifted to its place, and its columns are stored one by one.
+template <typename T, int VEC, bool UA>
+__device__ __forceinline__ void load_row_chunk(const T* row, int col, int V, float* x) {
+    if constexpr (UA) {
+        const int at = min(col, V - 8);
+        u32x4_t w = *reinterpret_cast<const u32x4_any_t*>(row + at);
+        if (col != at) w = pad_inf_from(chunk_shr(w, min(col - at, 7)), V - col);
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            x[2 * p] = bf16_lo(w[p]);
+            x[2 * p + 1] = bf16_hi(w[p]);
+        }
+    } else {
+        load_chunk<T, VEC>(row, col, V, -INFINITY, x);
+    }
+}
+template <typename T, int VEC, bool UA>
+__device__ __forceinline__ void store_row_chunk(T* row, int col, int V, const float* x) {
+    if constexpr (UA) {
+        if (col + 8 <= V) {
+            const u32x4_t w = {pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]), pack_bf16x2(x[4], x[5]),
+                               pack_bf16x2(x[6], x[7])};
+            *reinterpret_cast<u32x4_any_t*>(row + col) = w;
+        } else if (col < V) {
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+                if (col + k < V) row[col + k] = f32_to_bf16(x[k]);
+        }
+    } else {
+        store_chunk<T, VEC>(row, col, V, x);
+    }
+}
+
 }  // namespace bom

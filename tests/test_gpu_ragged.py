@@ -88,3 +88,43 @@ def test_head_forward_any_alignment(N, d, V, pad, off):
     # one rounding to bf16 (2^-9 of the value) and fp32 sums of d products of size 0.02
     assert bool((err <= ref.abs() * 2.0 ** -8 + 1e-5).all())
     assert (Z[:, V] == 7.0).all()
+
+
+# One chunk per thread (64 to 512 threads), rows parked in LDS (1024 and 512 threads, the tail chunk in the first, a
+# middle and the last position), and rows past one workgroup's LDS (two passes).
+RES_CASES = [(37, 8, 1, 0), (300, 9, 0, 0), (5, 511, 0, 1), (260, 1001, 0, 0), (33, 4095, 2, 3), (40, 4096, 1, 0),
+             (700, 4097, 0, 0), (20, 8199, 0, 1), (300, 12345, 0, 0), (9, 32773, 1, 0), (600, 50257, 0, 0),
+             (3, 57343, 0, 1), (70, 57345, 0, 0), (21, 65541, 3, 0), (1, 128257, 0, 1)]
+
+
+@pytest.mark.parametrize("N,V,pad,off", RES_CASES)
+def test_residual_any_alignment(N, V, pad, off):
+    log(f"[ragged residual] N={N} V={V} pad={pad} offset={off}")
+    g = torch.Generator(device=dev()).manual_seed(7)
+    Z = _embed(_rand(g, (N, V), 2.0, torch.bfloat16), pad, off)
+    y = torch.randint(0, V, (N,), generator=g, device=dev(), dtype=torch.int32)
+    y[0] = V - 1                        # a label in the columns past the last whole chunk
+    if N > 4:
+        y[1::9] = -100
+        y[3] = V
+    ok = (y >= 0) & (y < V)
+    Rbuf = torch.full((N, V + pad), 7.0, dtype=torch.bfloat16, device=dev())
+    out = bom.bom_residual(Z, y, R=Rbuf[:, :V])
+    p = torch.softmax(Z.double(), 1)
+    p[torch.arange(N, device=dev())[ok], y[ok].long()] -= 1
+    p *= ok[:, None]
+    n = int(ok.sum())
+    lse = torch.logsumexp(Z.double(), 1)
+    assert out["n_valid"].item() == n and out["flags"].item() == (bom.BOM_FLAG_LABEL_RANGE if N > 4 else 0)
+    assert float((out["row_lse"] - lse).abs().max()) <= 4e-6          # fp32 of values up to about 14
+    zf = Z.float()
+    first = (zf == zf.max(1, keepdim=True).values).int().argmax(1)    # the lowest column holding the maximum
+    assert torch.equal(out["row_argmax"].long(), first)
+    tgt = torch.where(ok, zf.gather(1, y.clamp(0, V - 1).long()[:, None])[:, 0], torch.zeros(N, device=dev()))
+    assert torch.equal(out["row_target"], tgt)
+    # R: one rounding to bf16 of an fp32 value good to 1e-6
+    assert bool(((Rbuf[:, :V].double() - p).abs() <= p.abs() * 2.0 ** -8 + 1e-9).all())
+    assert (Rbuf[:, V:] == 7.0).all()
+    assert float((out["s"] - p.sum(0) / n).norm() / (p.sum(0) / n).norm()) <= 2e-6
+    again = bom.bom_residual(Z, y)
+    assert torch.equal(again["R"], Rbuf[:, :V]) and torch.equal(again["s"], out["s"])
