@@ -127,6 +127,13 @@ constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 __device__ __forceinline__ float exp2_fast(float x) { return __builtin_amdgcn_exp2f(x); }
 
+// Residual element from a logit: 2^(z log2 e - c) with c = lse log2 e, minus 1 at the label.
+__device__ __forceinline__ float r_from_z(float z, float c, bool at_label) {
+    float p = exp2_fast(fmaf(z, kLog2e, -c));
+    if (at_label) p -= 1.0f;
+    return p;
+}
+
 __device__ __forceinline__ bool label_valid(int32_t y, int64_t V, int32_t ignore_index, bool* bad) {
     if (y == ignore_index) return false;
     if (y < 0 || (int64_t)y >= V) {

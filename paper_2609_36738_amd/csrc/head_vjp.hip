@@ -13,8 +13,9 @@
 // 64 x 64 tiles of both products (vjp_fused_small_kernel), or 128 x 128 split-K tiles with a
 // fixed-order reduction. dW = H^T G has both operands k-outer in memory (transposing LDS reads or a
 // transpose while staging); dH = G W^T has both operands k-contiguous. The fused and the 256-tile
-// kernels also take R and W with rows at any alignment and of any length (UA). fp32 path (and bf16 with H unaligned):
-// a SIMT tiled GEMM, at 30-40 TFLOP/s; a 4088 x 1024 x 50,257 head VJP takes 0.93 ms with UA and took 22.5 ms there.
+// kernels also take R and W with rows at any alignment and of any length (UA): a 4088 x 1024 x 50,257 head VJP takes
+// 0.93 ms with it, against 22.5 ms on the SIMT tiled GEMM that is left for bf16 with H unaligned. fp32 path: one launch
+// for small heads here, the fp32 matrix kernels of head_f32.hip otherwise.
 #include <algorithm>
 #include <array>
 #include <map>
@@ -68,11 +69,6 @@ inline int u_chunks(int64_t d, int64_t V) {   // every chunk starts inside the r
 // copies pass through registers: r = exp2(z log2 e - c_i) with c_i = lse_i log2 e (c_i = +inf for rows
 // outside I, so their r is 0), minus 1 at column y_i, rounded once to the operand type -- the operations
 // bom_residual uses when it writes R, so R is the same whether it is stored or formed here.
-__device__ __forceinline__ float r_from_z(float z, float c, bool at_label) {
-    float p = exp2_fast(fmaf(z, kLog2e, -c));
-    if (at_label) p -= 1.0f;
-    return p;
-}
 // Eight bf16 logits of one row (columns j0 .. j0 + 7, lab_off = y_i - j0) to eight bf16 residuals; ok = false
 // gives zeros (a chunk outside the operand).
 __device__ __forceinline__ u32x4_t z_chunk_to_r(u32x4_t z, float c, int lab_off, bool ok) {
@@ -158,22 +154,19 @@ __device__ __forceinline__ void stf<float>(float* p, int64_t i, float x) { p[i] 
 template <>
 __device__ __forceinline__ void stf<uint16_t>(uint16_t* p, int64_t i, float x) { p[i] = f32_to_bf16(x); }
 
-// Element (row, col) of R: as stored, or formed from the logits (rounded to T like a stored R).
-template <typename T>
-__device__ __forceinline__ float r_elem(const T* RZ, int64_t ld, int row, int col, const Fold& f) {
+// Element (row, col) of R: as stored, or formed from the logits (rounded to bf16 like a stored R).
+__device__ __forceinline__ float r_elem(const uint16_t* RZ, int64_t ld, int row, int col, const Fold& f) {
     const float x = ldf(RZ, (int64_t)row * ld + col);
     if (f.zc == nullptr) return x;
-    const float p = r_from_z(x, f.zc[row], col == f.labels[row]);
-    if constexpr (std::is_same<T, uint16_t>::value) return bf16_to_f32(f32_to_bf16(p));
-    return p;
+    return bf16_to_f32(f32_to_bf16(r_from_z(x, f.zc[row], col == f.labels[row])));
 }
 
-// ---- SIMT fallback: 64 x 64 tiles, 16-deep k, 4 x 4 outputs per thread --------------------------
+// ---- SIMT fallback (bf16 with H unaligned): 64 x 64 tiles, 16-deep k, 4 x 4 outputs per thread --------------------------
 constexpr int SB = 64, SK = 16;
 
 // dW[m][n] = sum_k H[k][m] G[k][n];  M = d, Nn = V, K = N rows.
-template <typename T>
-__global__ __launch_bounds__(256) void simt_dW_kernel(const T* __restrict__ H, int64_t ldh, const T* __restrict__ R,
+__global__ __launch_bounds__(256) void simt_dW_kernel(const uint16_t* __restrict__ H, int64_t ldh,
+                                                      const uint16_t* __restrict__ R,
                                                       int64_t ldr, int M, int Nn, int K, int kps, Fold f,
                                                       float* __restrict__ out, int64_t ldo, float beta, int direct) {
     __shared__ float As[SK][SB + 4];
@@ -220,8 +213,9 @@ __global__ __launch_bounds__(256) void simt_dW_kernel(const T* __restrict__ H, i
 }
 
 // dH[i][n] = sum_j G[i][j] W[n][j];  M = N rows, Nn = d, K = V.
-template <typename T, typename TO>
-__global__ __launch_bounds__(256) void simt_dH_kernel(const T* __restrict__ R, int64_t ldr, const T* __restrict__ W,
+template <typename TO>
+__global__ __launch_bounds__(256) void simt_dH_kernel(const uint16_t* __restrict__ R, int64_t ldr,
+                                                      const uint16_t* __restrict__ W,
                                                       int64_t ldw, int M, int Nn, int K, int kps, Fold f,
                                                       TO* __restrict__ out, int64_t ldo, float* __restrict__ part,
                                                       int direct) {
@@ -2086,6 +2080,7 @@ size_t partial_bytes(const Plan& p, int64_t N, int64_t d, int64_t V) {
 VjpWs vjp_ws(int64_t N, int64_t d, int64_t V, bom_dtype dt) {
     const Plan p = make_plan(N, d, V, dt, false);
     // the same shape may come with rows at any alignment, and take the plan for those or the SIMT one
+    // (fp32 operands have products and partial sums of their own)
     const Plan pu = dt == BOM_BF16 ? make_plan(N, d, V, dt, true) : p;
     VjpWs w;
     w.cq_off = 0;
@@ -2099,7 +2094,7 @@ VjpWs vjp_ws(int64_t N, int64_t d, int64_t V, bom_dtype dt) {
     w.u_off = align256(w.hsum_off + (r1 ? (size_t)d * 4 : 0));
     w.upart_off = align256(w.u_off + (r1 ? (size_t)d * 4 : 0));
     w.part_off = align256(w.upart_off + (r1 ? (size_t)u_chunks(d, V) * d * 4 : 0));
-    size_t need = partial_bytes(p, N, d, V);
+    size_t need = dt == BOM_F32 ? vjp_f32_workspace_bytes(N, d, V, p.w.splits) : partial_bytes(p, N, d, V);
     if (dt == BOM_BF16) need = std::max({need, partial_bytes(pu, N, d, V), partial_bytes(simt_plan(N, d, V), N, d, V)});
     w.total = align256(w.part_off + need);
     return w;
@@ -2177,22 +2172,13 @@ hipError_t run_gemm(bool is_dw, const GemmPlan& g, const void* A, int64_t lda, c
             else
                 hipLaunchKernelGGL(mfma_dH_kernel<TO>, grid, dim3(256), 0, st, a16, lda, b16, ldb, M, Nn, K, kps, f, out,
                                    ldo, pz);
-        } else if (dt == BOM_BF16) {
-            if (is_dw)
-                hipLaunchKernelGGL(simt_dW_kernel<uint16_t>, grid, dim3(256), 0, st, a16, lda, b16, ldb, M, Nn, K, kps, f,
-                                   splits > 1 ? part : reinterpret_cast<float*>(out), ldo, beta, splits > 1 ? 0 : 1);
-            else
-                hipLaunchKernelGGL((simt_dH_kernel<uint16_t, TO>), grid, dim3(256), 0, st, a16, lda, b16, ldb, M, Nn, K,
-                                   kps, f, out, ldo, part, splits > 1 ? 0 : 1);
         } else {
-            const float* a32 = static_cast<const float*>(A);
-            const float* b32 = static_cast<const float*>(B);
             if (is_dw)
-                hipLaunchKernelGGL(simt_dW_kernel<float>, grid, dim3(256), 0, st, a32, lda, b32, ldb, M, Nn, K, kps, f,
+                hipLaunchKernelGGL(simt_dW_kernel, grid, dim3(256), 0, st, a16, lda, b16, ldb, M, Nn, K, kps, f,
                                    splits > 1 ? part : reinterpret_cast<float*>(out), ldo, beta, splits > 1 ? 0 : 1);
             else
-                hipLaunchKernelGGL((simt_dH_kernel<float, TO>), grid, dim3(256), 0, st, a32, lda, b32, ldb, M, Nn, K, kps,
-                                   f, out, ldo, part, splits > 1 ? 0 : 1);
+                hipLaunchKernelGGL(simt_dH_kernel<TO>, grid, dim3(256), 0, st, a16, lda, b16, ldb, M, Nn, K, kps, f, out,
+                                   ldo, part, splits > 1 ? 0 : 1);
         }
     }
     hipError_t e = hipGetLastError();
@@ -2282,7 +2268,7 @@ hipError_t launch_head_vjp_f32(const HeadVjpArgs& a, hipStream_t st) {
                         ((int64_t)(a.d - 1) * a.ldw + a.V) * 2 < (1LL << 31);
     const bool small = p.w.kind == kMfma128 && p.h.kind == kMfma128;
     if (a.dt == BOM_BF16 && (!h_ok || (ua && (!ld_ok || (small ? !fits31 : zin))))) p = simt_plan(a.N, a.d, a.V);
-    if (L.part_off + partial_bytes(p, a.N, a.d, a.V) > L.total) return hipErrorInvalidValue;   // never taken
+    if (a.dt == BOM_BF16 && L.part_off + partial_bytes(p, a.N, a.d, a.V) > L.total) return hipErrorInvalidValue;   // never taken
     if (!a.dH) p.h.kind = kSimt;   // no dH: no rank-1 vector for it
 
     // small fp32 heads (at most 64 tiles of 64 x 64 in both products, k ranges up to 8192): one launch
@@ -2297,6 +2283,7 @@ hipError_t launch_head_vjp_f32(const HeadVjpArgs& a, hipStream_t st) {
             hipLaunchKernelGGL(vjp_small_f32_kernel, dim3((unsigned)(tw + th)), dim3(256), 0, st, sa);
             return hipGetLastError();
         }
+        return launch_vjp_f32_products(a, p.w.splits, part, st);
     }
 
     // small products (both on the 128-tile kernel): one fused launch, nothing staged beforehand
@@ -2432,15 +2419,14 @@ hipError_t launch_head_vjp_f32(const HeadVjpArgs& a, hipStream_t st) {
     return hipSuccess;
 }
 
-// ---- head forward (support): Z = H W + b, fp32 SIMT ------------------------------------------------
+// ---- head forward (support): Z = H W + b -----------------------------------------------------------
 namespace {
-// SIMT forward (fp32, and bf16 shapes the MFMA tiles do not take): 64 x 64 tiles, 16-deep k, fp32
-// accumulation, Z rounded once to its type.
-template <typename T>
-__global__ __launch_bounds__(256) void head_forward_simt_kernel(const T* __restrict__ H, int64_t ldh,
-                                                                const T* __restrict__ W, int64_t ldw,
-                                                                const T* __restrict__ b, int N, int d, int V,
-                                                                T* __restrict__ Z, int64_t ldz) {
+// SIMT forward (bf16 shapes the MFMA tiles do not take): 64 x 64 tiles, 16-deep k, fp32 accumulation, Z
+// rounded once to bf16.
+__global__ __launch_bounds__(256) void head_forward_simt_kernel(const uint16_t* __restrict__ H, int64_t ldh,
+                                                                const uint16_t* __restrict__ W, int64_t ldw,
+                                                                const uint16_t* __restrict__ b, int N, int d, int V,
+                                                                uint16_t* __restrict__ Z, int64_t ldz) {
     __shared__ float As[SK][SB + 4];
     __shared__ float Bs[SK][SB + 4];
     const int t = threadIdx.x, tx = t % 16, ty = t / 16;
@@ -2450,9 +2436,9 @@ __global__ __launch_bounds__(256) void head_forward_simt_kernel(const T* __restr
         for (int e = 0; e < 4; ++e) {
             const int idx = e * 256 + t;
             const int rr = idx / SK, kk = idx % SK;
-            As[kk][rr] = (k0 + kk < d && m0 + rr < N) ? ldf<T>(H, (int64_t)(m0 + rr) * ldh + k0 + kk) : 0.f;
+            As[kk][rr] = (k0 + kk < d && m0 + rr < N) ? ldf<uint16_t>(H, (int64_t)(m0 + rr) * ldh + k0 + kk) : 0.f;
             const int kk2 = idx / SB, cc = idx % SB;
-            Bs[kk2][cc] = (k0 + kk2 < d && n0 + cc < V) ? ldf<T>(W, (int64_t)(k0 + kk2) * ldw + n0 + cc) : 0.f;
+            Bs[kk2][cc] = (k0 + kk2 < d && n0 + cc < V) ? ldf<uint16_t>(W, (int64_t)(k0 + kk2) * ldw + n0 + cc) : 0.f;
         }
         __syncthreads();
 #pragma unroll
@@ -2472,20 +2458,16 @@ __global__ __launch_bounds__(256) void head_forward_simt_kernel(const T* __restr
     for (int i = 0; i < 4; ++i)
         for (int j = 0; j < 4; ++j) {
             const int m = m0 + ty * 4 + i, n = n0 + tx * 4 + j;
-            if (m < N && n < V) stf<T>(Z, (int64_t)m * ldz + n, acc[i][j] + (b ? ldf<T>(b, n) : 0.f));
+            if (m < N && n < V) stf<uint16_t>(Z, (int64_t)m * ldz + n, acc[i][j] + (b ? ldf<uint16_t>(b, n) : 0.f));
         }
 }
 }  // namespace
 
 hipError_t launch_head_forward(const void* H, int64_t ldh, const void* W, int64_t ldw, const void* b, bom_dtype dt,
                                int N, int d, int V, void* Z, int64_t ldz, hipStream_t st) {
-    if (dt == BOM_F32) {
-        dim3 grid((V + SB - 1) / SB, (N + SB - 1) / SB);
-        hipLaunchKernelGGL(head_forward_simt_kernel<float>, grid, dim3(256), 0, st, static_cast<const float*>(H), ldh,
-                           static_cast<const float*>(W), ldw, static_cast<const float*>(b), N, d, V,
-                           static_cast<float*>(Z), ldz);
-        return hipGetLastError();
-    }
+    if (dt == BOM_F32)
+        return launch_forward_f32(static_cast<const float*>(H), ldh, static_cast<const float*>(W), ldw,
+                                  static_cast<const float*>(b), N, d, V, static_cast<float*>(Z), ldz, st);
     const uint16_t* H16 = static_cast<const uint16_t*>(H);
     const uint16_t* W16 = static_cast<const uint16_t*>(W);
     const uint16_t* b16 = static_cast<const uint16_t*>(b);
@@ -2508,7 +2490,7 @@ hipError_t launch_head_forward(const void* H, int64_t ldh, const void* W, int64_
         return hipGetLastError();
     }
     dim3 grid((V + SB - 1) / SB, (N + SB - 1) / SB);
-    hipLaunchKernelGGL(head_forward_simt_kernel<uint16_t>, grid, dim3(256), 0, st, H16, ldh, W16, ldw, b16, N, d, V,
+    hipLaunchKernelGGL(head_forward_simt_kernel, grid, dim3(256), 0, st, H16, ldh, W16, ldw, b16, N, d, V,
                        static_cast<uint16_t*>(Z), ldz);
     return hipGetLastError();
 }

@@ -46,6 +46,13 @@ struct HeadVjpArgs {
 size_t head_vjp_workspace_bytes(int64_t N, int64_t d, int64_t V, bom_dtype dt, bom_dtype dw_dt);
 hipError_t launch_head_vjp(const HeadVjpArgs& a, hipStream_t stream);
 
+// fp32 operands: both products (and db) on the fp32 matrix instructions. dW is the sum of `sums` partial sums of equal
+// k ranges, in order; `part` holds the sums of k ranges that go to units of their own.
+size_t vjp_f32_workspace_bytes(int64_t N, int64_t d, int64_t V, int sums);
+hipError_t launch_vjp_f32_products(const HeadVjpArgs& a, int sums, void* part, hipStream_t stream);
+hipError_t launch_forward_f32(const float* H, int64_t ldh, const float* W, int64_t ldw, const float* b, int N, int d,
+                              int V, float* Z, int64_t ldz, hipStream_t stream);
+
 // ---- head telemetry (diagnostic) --------------------------------------------------------------
 struct TeleArgs {
     const void* H; int64_t ldh; bom_dtype h_dt;

@@ -1,0 +1,66 @@
+"""The fp32 head products on the matrix cores: ragged tiles, split k ranges of either product, the logits route."""
+import pytest
+import torch
+
+from paper_2609_36738_amd import bom
+from tests.gpu_util import dev, log
+
+pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not torch.cuda.is_available(), reason="needs an MI355X")]
+
+LAM = 0.25
+
+
+def _rand(g, shape, std):
+    return torch.randn(shape, generator=g, device=dev()) * std
+
+
+# name, N, d, V: tiles of both edges, k shorter than one tile, dW's or dH's k range split, both unsplit
+CASES = [("ragged", 601, 301, 707), ("split_dh", 70, 300, 20011), ("split_dw", 8200, 66, 130), ("one_row", 1, 65, 9001),
+         ("two_columns", 9000, 130, 2), ("unsplit", 1500, 520, 1111)]
+
+
+@pytest.mark.parametrize("logits", [False, True], ids=["residual", "logits"])
+@pytest.mark.parametrize("name,N,d,V", CASES, ids=[c[0] for c in CASES])
+def test_head_vjp_f32(name, N, d, V, logits):
+    log(f"[f32 vjp] {name} N={N} d={d} V={V} logits={logits}")
+    g = torch.Generator(device=dev()).manual_seed(3)
+    H, W, Z = _rand(g, (N, d), 1.0), _rand(g, (d, V), 0.02), _rand(g, (N, V), 1.0)
+    y = torch.randint(0, V, (N,), generator=g, device=dev(), dtype=torch.int32)
+    if N > 3:
+        y[1::7] = -100
+        y[2] = V
+    ok = (y >= 0) & (y < V)
+    lse = torch.logsumexp(Z.double(), 1)
+    R = torch.softmax(Z.double(), 1)
+    R[torch.arange(N, device=dev())[ok], y[ok].long()] -= 1
+    R *= ok[:, None]
+    nv = ok.sum().to(torch.int32).reshape(1)
+    q, s = _rand(g, (V,), 0.05), _rand(g, (V,), 0.05)
+    dW = torch.full((d, V + 1), 7.0, device=dev())
+    dW0 = _rand(g, (d, V), 0.01)
+    dW[:, :V] = dW0
+    third = Z if logits else R.float()
+    for dt in (torch.float32, torch.bfloat16):
+        dW[:, :V] = dW0
+        out = bom.bom_head_vjp(H, W, third, y, q, nv, s=s, lam=LAM, dW=dW[:, :V], dW_beta=0.5, want_db=True,
+                               dh_dtype=dt, row_lse=lse.float() if logits else None)
+        G = ((1 - LAM) * R + LAM * q.double()) * ok[:, None] / nv
+        rW, rH = H.double().t() @ G + 0.5 * dW0.double(), G @ W.double().t()
+        eW = float((dW[:, :V] - rW).norm() / rW.norm())
+        eH = float((out["dH"].double() - rH).norm() / rH.norm())
+        log(f"    {dt} rel err dW={eW:.2e} dH={eH:.2e}")
+        # fp32 sums of up to 20011 terms: sqrt(k) 2^-24 stays below 1e-5; bf16 dH: one rounding, at most 2^-9
+        assert eW <= 1e-5 and eH <= (1e-5 if dt == torch.float32 else 2.0 ** -8)
+        assert (dW[:, V] == 7.0).all()
+    assert float((out["db"] - ((1 - LAM) * s + LAM * q)).abs().max()) <= 1e-6
+
+
+@pytest.mark.parametrize("N,d,V", [(1, 1, 2), (65, 33, 129), (600, 301, 1001)])
+def test_head_forward_f32(N, d, V):
+    log(f"[f32 forward] N={N} d={d} V={V}")
+    g = torch.Generator(device=dev()).manual_seed(4)
+    H, W, b = _rand(g, (N, d), 1.0), _rand(g, (d, V), 0.02), _rand(g, (V,), 0.1)
+    Z = torch.full((N, V + 3), 7.0, device=dev())
+    bom.bom_head_forward(H, W, b=b, Z=Z[:, :V])
+    ref = H.double() @ W.double() + b.double()
+    assert float((Z[:, :V] - ref).norm() / ref.norm()) <= 1e-6 and (Z[:, V:] == 7.0).all()
