@@ -164,13 +164,12 @@ bom_status bom_ema(float* q, const float* s, int64_t V, float beta1, int64_t t, 
  * N_t is read from the device word n_valid; when it is 0, G = 0.
  *
  * R_or_Z and is_residual: with is_residual = 1 the argument is R as bom_residual writes it (rows outside
- * I zero). With is_residual = 0 it is the logits Z, and the products form R themselves as their operand
- * copies pass through registers: R_ij = exp(z_ij - row_lse[i]) - [j == y_i] for rows in I, 0 for the
- * others, formed as bom_residual forms it for rows wider than one workgroup's registers (2^(z log2 e -
- * lse log2 e), minus 1 at the label) and rounded to dt once; it equals the stored R up to one rounding of
- * dt (bom_residual's narrow-row kernels scale exp(z - max) by 1/sum instead). bom_residual may then skip
- * writing R (R = NULL there): the step reads Z instead of writing and reading R, at the price of one
- * exponential per element of each operand copy.
+ * I zero). With is_residual = 0 it is the logits Z, and R is formed from them here: R_ij = exp(z_ij - row_lse[i]) -
+ * [j == y_i] for rows in I, 0 for the others, as bom_residual forms it for rows wider than one workgroup's registers
+ * (2^(z log2 e - lse log2 e), minus 1 at the label) and rounded to dt once; it equals the stored R up to one rounding of
+ * dt (bom_residual's narrow-row kernels scale exp(z - max) by 1/sum instead). Large bf16 products form it in the workspace,
+ * a panel of at most about 512 MB of columns at a time; the others as their operand copies pass through registers.
+ * bom_residual may then skip writing R (R = NULL there), and no [N, V] buffer of R is held.
  *
  *   H   device [N, ldh] of dt.   W device [d, ldw] of dt (the head as d x V).
  *   R_or_Z device [N, ldr] of dt.

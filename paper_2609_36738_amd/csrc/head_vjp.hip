@@ -45,7 +45,8 @@ struct Fold {
 };
 
 struct VjpWs {
-    size_t cq_off, cqp_off, vmask_off, scal_off, zc_off, hpart_off, hsum_off, u_off, upart_off, part_off, total;
+    size_t cq_off, cqp_off, vmask_off, scal_off, zc_off, hpart_off, hsum_off, u_off, upart_off, part_off;
+    size_t panel_off, hacc_off, total;   // logits input, large products: a panel of R, and dH's sums over panels
 };
 
 // Rank-1 vector u = W q_hat is summed over column chunks (one wave per row of W and chunk at a time, four
@@ -65,10 +66,11 @@ inline int u_chunks(int64_t d, int64_t V) {   // every chunk starts inside the r
 }
 
 // ---- residual rows from the logits ----------------------------------------------------------------
-// With the logits Z as input, the products take R = softmax(Z) - onehot(y) chunk by chunk as the operand
-// copies pass through registers: r = exp2(z log2 e - c_i) with c_i = lse_i log2 e (c_i = +inf for rows
-// outside I, so their r is 0), minus 1 at column y_i, rounded once to the operand type -- the operations
-// bom_residual uses when it writes R, so R is the same whether it is stored or formed here.
+// With the logits Z as input, R = softmax(Z) - onehot(y) is formed here: r = exp2(z log2 e - c_i) with
+// c_i = lse_i log2 e (c_i = +inf for rows outside I, so their r is 0), minus 1 at column y_i, rounded once to the
+// operand type -- the operations bom_residual uses when it writes R, so R is the same whether it is stored or formed
+// here. The small products form it chunk by chunk as their operand copies pass through registers; the large ones form it
+// once, a panel of columns at a time, in the workspace (z_panel_kernel), and read it as stored.
 // Eight bf16 logits of one row (columns j0 .. j0 + 7, lab_off = y_i - j0) to eight bf16 residuals; ok = false
 // gives zeros (a chunk outside the operand).
 __device__ __forceinline__ u32x4_t z_chunk_to_r(u32x4_t z, float c, int lab_off, bool ok) {
@@ -83,6 +85,54 @@ __device__ __forceinline__ u32x4_t z_chunk_to_r(u32x4_t z, float c, int lab_off,
 __device__ __forceinline__ float z_row_c(const float* row_lse, const int32_t* labels, int i, int V, int32_t ig) {
     bool bad = false;
     return label_valid(labels[i], V, ig, &bad) ? row_lse[i] * kLog2e : INFINITY;
+}
+
+// ---- panels of R from the logits ---------------------------------------------------------------
+// The 256-tile products read every element of R once per output tile of the other dimension (d / 256 times each), so an
+// R formed on its way to LDS cost one exponential per read on the VALU of kernels that are short of issue slots. A
+// panel costs one read of Z and one write and keeps the products at their speed: head VJP from the logits
+// 695 -> 518 us at N = 4096, d = 768, V = 32,000; N = 8192, d = 2048, V = 50,304 4.75 -> 3.12 ms; N = 16384, d = 4096,
+// V = 128,256 47.5 -> 30.7 ms. Panels hold about kPanelBytes (at least 4096 columns), small beside the logits (4.2 GB
+// at the last shape) and wide enough for several rounds of output tiles: there 256 MB measured 34.1 ms, 512 MB 30.7 and
+// 1 GB 29.3. dH adds its panels' products in fp32.
+constexpr size_t kPanelBytes = (size_t)512 << 20;
+constexpr int64_t kPanelTail = 64;   // fewer columns than this past the last whole panel go into it
+int64_t panel_cols(int64_t N, int64_t V) {
+    const int64_t fit = (int64_t)(kPanelBytes / 2 / (size_t)N);
+    if (V <= fit) return V;
+    const int64_t w = std::max<int64_t>(fit / 2048 * 2048, 4096);
+    return V <= w + kPanelTail ? V : w;
+}
+int64_t panel_count(int64_t V, int64_t w) { return std::max<int64_t>(1, (V - kPanelTail) / w + ((V - kPanelTail) % w > 0)); }
+int64_t panel_ld(int64_t N, int64_t V) {   // columns of the panel buffer's rows
+    const int64_t w = panel_cols(N, V);
+    return (w < V ? w + kPanelTail : (V + 7) / 8 * 8);
+}
+
+// Columns [c0, c0 + nc) of R to rows of ldo (a multiple of 8, at least nc rounded up): one row and 8192 columns per
+// workgroup, four 16-byte loads of Z (at any alignment) in flight per thread. Columns past V get zeros.
+__global__ __launch_bounds__(256) void z_panel_kernel(const uint16_t* __restrict__ Z, int64_t ldz, int V, int c0, int nc,
+                                                      const int32_t* __restrict__ labels, int32_t ig,
+                                                      const float* __restrict__ row_lse, uint16_t* __restrict__ out,
+                                                      int64_t ldo, int slabs) {
+    const int i = blockIdx.x / slabs, j0 = (blockIdx.x % slabs) * 8192 + threadIdx.x * 8;
+    const uint16_t* zr = Z + (int64_t)i * ldz;
+    const int y = labels[i];
+    bool bad = false;
+    const bool valid = label_valid(y, V, ig, &bad);
+    const float c = valid ? row_lse[i] * kLog2e : INFINITY;
+    u32x4_t w[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        w[q] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_any_t*>(zr + min(c0 + j0 + q * 2048, V - 8)));
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int j = j0 + q * 2048;
+        if (j >= nc) break;
+        const int col = c0 + j, moved = col - min(col, V - 8);
+        if (moved > 0) w[q] = pad_inf_from(chunk_shr(w[q], min(moved, 7)), V - col);
+        *reinterpret_cast<u32x4_t*>(out + (int64_t)i * ldo + j) = z_chunk_to_r(w[q], c, valid ? y - col : -1, true);
+    }
 }
 
 // ---- prep -------------------------------------------------------------------------------------
@@ -868,8 +918,8 @@ struct WideArgs {
     float beta;
     float* part;
     const uint16_t* bias;   // forward: bf16 bias [Nn] or null
-    const float* zc;        // logits input (ZR): c_i per row of R, and the labels
-    const int32_t* labels;
+    const float* add;       // dH: fp32 [M][Nn] added to the output, or null
+    const int32_t* labels;  // forward with row statistics
     // forward with row statistics: per (row, 256-column tile) records (max, sum of exp(z - max), first
     // argmax) of the rounded logits at stats + (row * stats_ld + tile) * 3, and the target logit of each
     // row whose label is valid (written by the tile that holds the label)
@@ -889,8 +939,6 @@ constexpr int kWideDH = 0, kWideDW = 1, kWideFWD = 2;
 // are the workgroup's LDS (two stages of both operands, and the rank-1 row vector of the tile).
 // NW waves share the 256 x 256 tile: four (one per SIMD) each own 128 x 128, or eight (two per SIMD,
 // so that one wave's copies and LDS reads overlap the other's MFMAs) each own 128 x 64.
-// ZR: the operand that is R (dH's A, dW's B) holds the logits Z, and each copy is turned into R in
-// registers before its LDS write (z_chunk_to_r).
 // UA: operands with the vocabulary along their rows (R, W) need not be aligned to 16 bytes nor have a multiple
 // of eight columns. Every chunk is then read with one 16-byte load at a 2-byte aligned address that lies
 // inside the row: the unaligned loads of a row pair run at half the rate of aligned ones (60 against 115 B/ns per
@@ -898,9 +946,8 @@ constexpr int kWideDH = 0, kWideDW = 1, kWideFWD = 2;
 // that would cross the end of the row is moved back to the row's last eight columns: along n (dW, forward) the
 // epilogue maps its tile columns to where they came from, along k (dH) the main loop stops at the last whole
 // chunk and the K % 8 columns left go through one MFMA step of their own before it.
-template <int MODE, typename TO, int NW, bool ZR = false, bool FS = false, bool UA = false>
-__device__ __forceinline__ void wide_tile(const WideArgs& args, int id, uint16_t (&lds)[2][2][WSE], float (&rv_s)[LB],
-                                          float2* zs = nullptr) {
+template <int MODE, typename TO, int NW, bool FS = false, bool UA = false>
+__device__ __forceinline__ void wide_tile(const WideArgs& args, int id, uint16_t (&lds)[2][2][WSE], float (&rv_s)[LB]) {
     static_assert(NW == 4 || NW == 8, "four or eight waves");
     constexpr int KT = WKT;
     constexpr int WCOLS = NW == 4 ? 128 : 64;   // columns of a wave's part of the tile
@@ -911,7 +958,7 @@ __device__ __forceinline__ void wide_tile(const WideArgs& args, int id, uint16_t
     constexpr bool RANK1 = MODE != kWideFWD;   // rank-1 epilogue (the head VJP products)
     constexpr bool KA = MODE != kWideDW;       // operand A k-contiguous
     constexpr bool KB = MODE == kWideDH;       // operand B k-contiguous
-    static_assert(!UA || (NW == 8 && !ZR && !FS), "unaligned rows: eight waves, R as stored");
+    static_assert(!UA || (NW == 8 && !FS), "unaligned rows: eight waves");
     const uint16_t* __restrict__ Xa = args.Xa;
     const int64_t lda = args.lda;
     const uint16_t* __restrict__ Xb = args.Xb;
@@ -986,21 +1033,6 @@ __device__ __forceinline__ void wide_tile(const WideArgs& args, int id, uint16_t
             voff_b[q] = c0 < Nn ? (int)((int64_t)krow * ldb * 2) + c * 2 : kOob;
         }
     }
-    // logits input: c of each row of the R operand and its label. dH: the tile's 256 rows are fixed, so
-    // (c, label) sit in LDS (zs) and each copy looks its row up at write time, the label as an offset
-    // from the chunk's k; dW: rows change with the k tile, so both are loaded into registers with each
-    // copy, the label as an offset from the chunk's first column
-    constexpr bool ZA = ZR && MODE == kWideDH, ZB = ZR && MODE == kWideDW;
-    float zrc[CPO];
-    int zry[CPO], zcol[CPO];
-#pragma unroll
-    for (int q = 0; q < CPO; ++q) {
-        zrc[q] = INFINITY;
-        zry[q] = -1;
-        zcol[q] = 0;
-        const int chunk = (wave * CPO + q) * 64 + l;
-        if constexpr (ZB) zcol[q] = n0 + (((chunk % 32) ^ (((chunk / 32) & 3) << 2)) << 3);
-    }
     // k-contiguous operands: one descriptor per workgroup over the tile's rows (exact extent)
     const int bytes_ta = KA ? (int)(((int64_t)(min(LB, M - m0) - 1) * lda + K) * 2) : 0;
     const int bytes_tb = KB ? (int)(((int64_t)(min(LB, Nn - n0) - 1) * ldb + K) * 2) : 0;
@@ -1042,31 +1074,12 @@ __device__ __forceinline__ void wide_tile(const WideArgs& args, int id, uint16_t
             return __builtin_amdgcn_raw_buffer_load_b128(make_desc(tl.ba, tl.bytes_a), vo, 0, 0);
         }
         const int r = q - CPO;
-        if constexpr (ZB) {   // the row of this copy: its c and its label's offset from the chunk's columns
-            const int k = tl.k0 + kc_b[r];
-            const bool kin = k < ke;
-            const int kcl = kin ? k : K - 1;
-            zrc[r] = kin ? args.zc[kcl] : INFINITY;
-            zry[r] = kin ? args.labels[kcl] - zcol[r] : -1;
-        }
         const int vo = !KB ? voff_b[r] : ((ok_b[r] && tl.k0 + kc_b[r] < ke) ? voff_b[r] + tl.k0 * 2 : kOob);
         return __builtin_amdgcn_raw_buffer_load_b128(make_desc(tl.bb, tl.bytes_b), vo, 0, 0);
     };
-    // k0w: the first k of the tile whose copy v holds
-    auto write_one = [&](int stage, int q, const u32x4_t& v, int k0w) {
+    auto write_one = [&](int stage, int q, const u32x4_t& v) {
         char* base = reinterpret_cast<char*>(&lds[stage][q / CPO][0]);
-        u32x4_t x = v;
-        if constexpr (ZA) {
-            if (q < CPO) {
-                const int j0 = k0w + kc_a[q];
-                const float2 zz = zs[((wave * CPO + q) * 64 + l) / 8];   // the copy's row: c and label
-                x = z_chunk_to_r(v, zz.x, __float_as_int(zz.y) - j0, ok_a[q] && j0 < ke);
-            }
-        }
-        if constexpr (ZB) {
-            if (q >= CPO) x = z_chunk_to_r(v, zrc[q - CPO], zry[q - CPO], true);
-        }
-        *reinterpret_cast<u32x4_t*>(base + (wave * CPO + q % CPO) * 1024 + l * 16) = x;
+        *reinterpret_cast<u32x4_t*>(base + (wave * CPO + q % CPO) * 1024 + l * 16) = v;
     };
 
     // fragments for MFMA step s (k = 16 s .. +15) of `cnt` 32-wide blocks from tile row/column `base`:
@@ -1121,7 +1134,7 @@ __device__ __forceinline__ void wide_tile(const WideArgs& args, int id, uint16_t
                 __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[m / NJ], b[m % NJ], acc[m / NJ][m % NJ], 0, 0, 0);
             if (q0 >= 0 && m < CPS) {
                 __builtin_amdgcn_sched_barrier(0);
-                write_one(ws, q0 + m, rg[q0 + m], tl.k0 - KT);
+                write_one(ws, q0 + m, rg[q0 + m]);
                 rg[q0 + m] = load_one(tl, q0 + m);
                 __builtin_amdgcn_sched_barrier(0);
             }
@@ -1141,13 +1154,6 @@ __device__ __forceinline__ void wide_tile(const WideArgs& args, int id, uint16_t
     };
     u32x4_t rg[2 * CPO];
     bf16x8_t a0[4], b0[NJ], a1[4], b1[NJ];
-    if constexpr (ZA) {   // logits rows of the tile: c and label, held in LDS (registers are taken in full)
-        for (int t = threadIdx.x; t < LB; t += NW * kWave) {
-            const int i = m0 + t;
-            zs[t] = i < M ? make_float2(args.zc[i], __int_as_float(args.labels[i])) : make_float2(INFINITY, __int_as_float(-1));
-        }
-        __syncthreads();
-    }
     if constexpr (UA && MODE == kWideDH) {
         if (Km < K && kz == 0) {   // the K % 8 columns past the last whole chunk: one MFMA step of their own
             static_assert(NW * kWave == 2 * LB, "one thread per operand row");
@@ -1175,7 +1181,7 @@ __device__ __forceinline__ void wide_tile(const WideArgs& args, int id, uint16_t
 #pragma unroll
         for (int q = 0; q < 2 * CPO; ++q) rg[q] = load_one(t0, q);
 #pragma unroll
-        for (int q = 0; q < 2 * CPO; ++q) write_one(0, q, rg[q], t0.k0);
+        for (int q = 0; q < 2 * CPO; ++q) write_one(0, q, rg[q]);
 #pragma unroll
         for (int q = 0; q < 2 * CPO; ++q) rg[q] = load_one(t1, q);
     }
@@ -1308,7 +1314,7 @@ __device__ __forceinline__ void wide_tile(const WideArgs& args, int id, uint16_t
                     float* p = reinterpret_cast<float*>(out) + (int64_t)m * ldo + n;
                     *p = beta != 0.f ? x + beta * *p : x;
                 } else {
-                    stf<TO>(out, (int64_t)m * ldo + n, x);
+                    stf<TO>(out, (int64_t)m * ldo + n, args.add ? x + args.add[(int64_t)m * Nn + n] : x);
                 }
             }
         });
@@ -1321,12 +1327,11 @@ __device__ __forceinline__ void wide_tile(const WideArgs& args, int id, uint16_t
     }
 }
 
-template <bool IS_DW, typename TO, int NW, bool ZR = false, bool UA = false>
+template <bool IS_DW, typename TO, int NW, bool UA = false>
 __global__ __launch_bounds__(NW * 64, 1) void lds256w_kernel(WideArgs a) {
     __shared__ __attribute__((aligned(1024))) uint16_t lds[2][2][WSE];
     __shared__ float rv_s[LB];
-    __shared__ float2 zs[ZR && !IS_DW ? LB : 1];
-    wide_tile<IS_DW ? kWideDW : kWideDH, TO, NW, ZR, false, UA>(a, blockIdx.x, lds, rv_s, zs);
+    wide_tile<IS_DW ? kWideDW : kWideDH, TO, NW, false, UA>(a, blockIdx.x, lds, rv_s);
 }
 
 // The head forward Z = H W (+ b) in bf16 on the same tiles (fp32 accumulation, one rounding of Z); FS:
@@ -1336,29 +1341,29 @@ template <typename TO, int NW, bool FS = false, bool UA = false>
 __global__ __launch_bounds__(NW * 64, 1) void lds256w_fwd_kernel(WideArgs a) {
     __shared__ __attribute__((aligned(1024))) uint16_t lds[2][2][WSE];
     __shared__ float rv_s[LB];
-    wide_tile<kWideFWD, TO, NW, false, FS, UA>(a, blockIdx.x, lds, rv_s);
+    wide_tile<kWideFWD, TO, NW, FS, UA>(a, blockIdx.x, lds, rv_s);
 }
 
 // Both products in one grid: blocks [0, nh) run dH's units (the long k ranges first), the rest dW's
 // tiles, so that the shorter dW tiles fill the compute units that dH's last round leaves idle instead of
 // a second launch starting after a partly empty round. nh is a multiple of 8, so each part keeps its
 // own XCD order.
-template <typename TO, int NW, bool ZR = false, bool UA = false>
+template <typename TO, int NW, bool UA = false>
 __global__ __launch_bounds__(NW * 64, 1) void lds256w_pair_kernel(WideArgs h, WideArgs w, int nh) {
     __shared__ __attribute__((aligned(1024))) uint16_t lds[2][2][WSE];
     __shared__ float rv_s[LB];
-    __shared__ float2 zs[ZR ? LB : 1];
-    if ((int)blockIdx.x < nh) wide_tile<kWideDH, TO, NW, ZR, false, UA>(h, blockIdx.x, lds, rv_s, zs);
-    else wide_tile<kWideDW, float, NW, ZR, false, UA>(w, (int)blockIdx.x - nh, lds, rv_s);
+    if ((int)blockIdx.x < nh) wide_tile<kWideDH, TO, NW, false, UA>(h, blockIdx.x, lds, rv_s);
+    else wide_tile<kWideDW, float, NW, false, UA>(w, (int)blockIdx.x - nh, lds, rv_s);
 }
 
 // Split-K reduction for the rank-1 form over the rectangle [pm0, M) x [pn0, Nn) of the output, in split
-// order: out = sum_z part[z] + rv[m] cv[n] (+ beta out); part[z] is that rectangle, row-major.
+// order: out = sum_z part[z] + rv[m] cv[n] (+ beta out or + add, fp32 [M][Nn], which may be out itself); part[z] is that
+// rectangle, row-major.
 template <typename TO>
 __global__ __launch_bounds__(256) void splitk_rank1_kernel(const float* __restrict__ part, int splits, int M, int Nn,
                                                            int pm0, int pn0, const float* __restrict__ rv,
-                                                           const float* __restrict__ cv, TO* __restrict__ out,
-                                                           int64_t ldo, float beta) {
+                                                           const float* __restrict__ cv, TO* out, int64_t ldo, float beta,
+                                                           const float* add) {
     const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const int64_t Nr = Nn - pn0;
     const int64_t MN = (int64_t)(M - pm0) * Nr;
@@ -1367,6 +1372,7 @@ __global__ __launch_bounds__(256) void splitk_rank1_kernel(const float* __restri
     float a = 0.f;
     for (int z = 0; z < splits; ++z) a += part[(int64_t)z * MN + idx];
     if (rv != nullptr) a = fmaf(rv[m], cv[n], a);
+    if (add != nullptr) a += add[m * Nn + n];
     if (beta != 0.f) a += beta * ldf<TO>(out, m * ldo + n);
     stf<TO>(out, m * ldo + n, a);
 }
@@ -2096,14 +2102,29 @@ VjpWs vjp_ws(int64_t N, int64_t d, int64_t V, bom_dtype dt) {
     w.part_off = align256(w.upart_off + (r1 ? (size_t)u_chunks(d, V) * d * 4 : 0));
     size_t need = dt == BOM_F32 ? vjp_f32_workspace_bytes(N, d, V, p.w.splits) : partial_bytes(p, N, d, V);
     if (dt == BOM_BF16) need = std::max({need, partial_bytes(pu, N, d, V), partial_bytes(simt_plan(N, d, V), N, d, V)});
-    w.total = align256(w.part_off + need);
+    w.panel_off = w.hacc_off = w.total = align256(w.part_off + need);
+    if (dt == BOM_BF16 && r1 && V >= 8) {   // panels of R for the logits input
+        const int64_t pc = panel_cols(N, V);
+        if (pc < V) {
+            const int64_t np = panel_count(V, pc);
+            for (int64_t nc : {pc, V - (np - 1) * pc}) {
+                Plan q;
+                q.w = plan_wide(d, nc, N, true);
+                q.h = plan_wide(N, d, nc, false);
+                need = std::max(need, partial_bytes(q, N, d, nc));
+            }
+        }
+        w.panel_off = align256(w.part_off + need);
+        w.hacc_off = align256(w.panel_off + (size_t)N * panel_ld(N, V) * 2);
+        w.total = align256(w.hacc_off + (pc < V ? (size_t)N * d * 4 : 0));
+    }
     return w;
 }
 
 template <typename TO>
 hipError_t run_gemm(bool is_dw, const GemmPlan& g, const void* A, int64_t lda, const void* B, int64_t ldb, bom_dtype dt,
                     int M, int Nn, int K, const Fold& f, TO* out, int64_t ldo, float beta, float* part, const float* rv,
-                    const float* cv, bool ua, hipStream_t st) {
+                    const float* cv, bool ua, hipStream_t st, const float* add = nullptr) {
     const int splits = g.splits;
     if (g.kind == kRank1) {
         // rank-1 form: out = alpha A B + rv cv^T (+ beta out)
@@ -2120,15 +2141,11 @@ hipError_t run_gemm(bool is_dw, const GemmPlan& g, const void* A, int64_t lda, c
             auto launch = [&](int ob, int oe, int nsplit, int kp, float* pp, const TileRange& tr) {
                 dim3 gr((unsigned)(cdiv((int64_t)(oe - ob) * nsplit, 8) * 8 * inner));
                 const WideArgs wa{a16, lda, b16, ldb, M, Nn, K, kp, tr, f.scal, rv, cv, out, ldo, beta, pp, nullptr,
-                                  f.zc, f.labels};
+                                  add};
                 const int nw = is_dw ? wave_cfg().dw : wave_cfg().dh;
                 if (ua && is_dw)   // rows at any alignment: eight waves
-                    hipLaunchKernelGGL((lds256w_kernel<true, float, 8, false, true>), gr, dim3(512), 0, st, wa);
-                else if (ua)
-                    hipLaunchKernelGGL((lds256w_kernel<false, TO, 8, false, true>), gr, dim3(512), 0, st, wa);
-                else if (f.zc != nullptr && is_dw)   // logits input: eight waves
                     hipLaunchKernelGGL((lds256w_kernel<true, float, 8, true>), gr, dim3(512), 0, st, wa);
-                else if (f.zc != nullptr)
+                else if (ua)
                     hipLaunchKernelGGL((lds256w_kernel<false, TO, 8, true>), gr, dim3(512), 0, st, wa);
                 else if (is_dw && nw == 8)
                     hipLaunchKernelGGL((lds256w_kernel<true, float, 8>), gr, dim3(512), 0, st, wa);
@@ -2153,7 +2170,7 @@ hipError_t run_gemm(bool is_dw, const GemmPlan& g, const void* A, int64_t lda, c
             if (e != hipSuccess || splits == 1) return e;
             const int64_t MN = (int64_t)(M - pm0) * ldp;
             hipLaunchKernelGGL(splitk_rank1_kernel<TO>, dim3((unsigned)cdiv(MN, 256)), dim3(256), 0, st, part, splits, M,
-                               Nn, pm0, pn0, rv, cv, out, ldo, beta);
+                               Nn, pm0, pn0, rv, cv, out, ldo, beta, add);
             return hipGetLastError();
         }
     }
@@ -2219,7 +2236,7 @@ __global__ __launch_bounds__(256) void round_dw_bf16_kernel(const float* __restr
 }
 }  // namespace
 
-hipError_t launch_head_vjp_f32(const HeadVjpArgs& a, hipStream_t st);
+hipError_t launch_head_vjp_f32(const HeadVjpArgs& a, hipStream_t st);   // dW and db in fp32
 
 hipError_t launch_head_vjp(const HeadVjpArgs& a, hipStream_t st) {
     if (a.dw_dt != BOM_BF16) return launch_head_vjp_f32(a, st);
@@ -2240,6 +2257,90 @@ hipError_t launch_head_vjp(const HeadVjpArgs& a, hipStream_t st) {
     return hipGetLastError();
 }
 
+namespace {
+// Rank-1 vectors (u for dH if rh, row-block partial sums of H over I for dW if rw; lambda = 0 has no history term, so
+// neither is needed then and the epilogues add nothing), then the prep kernel.
+hipError_t launch_prep(const HeadVjpArgs& a, const VjpWs& L, bool rw, bool rh, bool ua, hipStream_t st) {
+    char* base = static_cast<char*>(a.ws);
+    auto at = [&](size_t off) { return reinterpret_cast<float*>(base + off); };
+    float *hpart = at(L.hpart_off), *upart = at(L.upart_off);
+    const int nrb = (int)cdiv(a.N, kHsRows);
+    const int uch = u_chunks(a.d, a.V), ucw = u_chunk_cols(a.d, a.V);
+    if (rw || rh) {
+        const int nu = rh ? (int)cdiv(std::min<int64_t>((int64_t)a.d * uch, kUWaves), 4) : 0;
+        const int ns = rw ? (int)cdiv(a.d, 512) * nrb : 0;
+        auto r1 = ua ? vjp_rank1_kernel<true> : vjp_rank1_kernel<false>;
+        hipLaunchKernelGGL(r1, dim3((unsigned)(nu + ns)), dim3(256), 0, st, static_cast<const uint16_t*>(a.W), a.ldw,
+                           a.d, a.V, a.q_hat, nu, uch, ucw, static_cast<const uint16_t*>(a.H), a.ldh, a.N, a.labels,
+                           a.ignore_index, upart, hpart);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    int nprep = a.V > a.N ? a.V : a.N;
+    if (nprep < a.d) nprep = a.d;
+    hipLaunchKernelGGL(vjp_prep_kernel, dim3((nprep + 255) / 256), dim3(256), 0, st, a.q_hat, a.s, a.n_valid, a.lambda,
+                       a.V, a.N, a.labels, a.ignore_index, at(L.cq_off), at(L.cqp_off), at(L.vmask_off), at(L.scal_off),
+                       static_cast<float*>(a.db), rw ? hpart : nullptr, nrb, a.d, at(L.hsum_off),
+                       a.is_residual ? nullptr : a.row_lse, at(L.zc_off), rh ? upart : nullptr, uch, at(L.u_off));
+    return hipGetLastError();
+}
+
+// Large products from the logits: R panel by panel. One panel: the products as planned for a stored R. Several: per
+// panel dW's columns, and dH's sum over the panels so far (the last one adds the rank-1 term and rounds).
+hipError_t launch_from_logits(const HeadVjpArgs& a, const VjpWs& L, hipStream_t st) {
+    char* base = static_cast<char*>(a.ws);
+    auto at = [&](size_t off) { return reinterpret_cast<float*>(base + off); };
+    uint16_t* panel = reinterpret_cast<uint16_t*>(base + L.panel_off);
+    const int64_t ldp = panel_ld(a.N, a.V), pc = panel_cols(a.N, a.V);
+    auto form = [&](int64_t c0, int64_t nc) {
+        const int64_t slabs = cdiv(nc, 8192);
+        hipLaunchKernelGGL(z_panel_kernel, dim3((unsigned)(a.N * slabs)), dim3(256), 0, st,
+                           static_cast<const uint16_t*>(a.R), a.ldr, a.V, (int)c0, (int)nc, a.labels, a.ignore_index,
+                           a.row_lse, panel, ldp, (int)slabs);
+        return hipGetLastError();
+    };
+    hipError_t e;
+    if (pc == a.V) {
+        if ((e = form(0, a.V)) != hipSuccess) return e;
+        HeadVjpArgs b = a;
+        b.R = panel;
+        b.ldr = ldp;
+        b.is_residual = 1;
+        return launch_head_vjp_f32(b, st);
+    }
+    const bool ua = a.V % 8 != 0 || reinterpret_cast<uintptr_t>(a.W) % 16 != 0 || a.ldw % 8 != 0;
+    const bool hist = a.lambda != 0.f;
+    if ((e = launch_prep(a, L, hist, hist && a.dH != nullptr, ua, st)) != hipSuccess) return e;
+    const float *cq = at(L.cq_off), *u = at(L.u_off), *hsum = at(L.hsum_off), *vmask = at(L.vmask_off);
+    float *part = at(L.part_off), *hacc = at(L.hacc_off);
+    const Fold f{cq, vmask, at(L.scal_off), at(L.cqp_off), nullptr, a.labels};
+    const int64_t np = panel_count(a.V, pc);
+    for (int64_t i = 0; i < np; ++i) {
+        const int64_t c0 = i * pc, nc = i + 1 < np ? pc : a.V - c0;
+        if ((e = form(c0, nc)) != hipSuccess) return e;
+        e = run_gemm<float>(true, plan_wide(a.d, nc, a.N, true), a.H, a.ldh, panel, ldp, a.dt, a.d, (int)nc, a.N, f,
+                            static_cast<float*>(a.dW) + c0, a.lddw, a.dW_beta, part, hist ? hsum : nullptr, cq + c0, ua,
+                            st);
+        if (e != hipSuccess) return e;
+        if (!a.dH) continue;
+        const uint16_t* w = static_cast<const uint16_t*>(a.W) + c0;
+        const GemmPlan gh = plan_wide(a.N, a.d, nc, false);
+        const float* add = i > 0 ? hacc : nullptr;
+        if (i + 1 < np)
+            e = run_gemm<float>(false, gh, panel, ldp, w, a.ldw, a.dt, a.N, a.d, (int)nc, f, hacc, a.d, 0.f, part, nullptr, u,
+                                ua, st, add);
+        else if (a.dh_dt == BOM_BF16)
+            e = run_gemm<uint16_t>(false, gh, panel, ldp, w, a.ldw, a.dt, a.N, a.d, (int)nc, f,
+                                   static_cast<uint16_t*>(a.dH), a.lddh, 0.f, part, hist ? vmask : nullptr, u, ua, st, add);
+        else
+            e = run_gemm<float>(false, gh, panel, ldp, w, a.ldw, a.dt, a.N, a.d, (int)nc, f, static_cast<float*>(a.dH),
+                                a.lddh, 0.f, part, hist ? vmask : nullptr, u, ua, st, add);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+}  // namespace
+
 hipError_t launch_head_vjp_f32(const HeadVjpArgs& a, hipStream_t st) {
     const VjpWs L = vjp_ws(a.N, a.d, a.V, a.dt);
     char* base = static_cast<char*>(a.ws);
@@ -2256,18 +2357,19 @@ hipError_t launch_head_vjp_f32(const HeadVjpArgs& a, hipStream_t st) {
     const bool zin = !a.is_residual;   // the R argument holds the logits Z
 
     // MFMA kernels stage 16-byte chunks: of H at 16-byte aligned addresses, of R and W too or (ua) at any (with the
-    // 256-row offsets inside 31 bits, and R as stored in the large products); otherwise the SIMT kernels run,
+    // 256-row offsets inside 31 bits); otherwise the SIMT kernels run,
     // with their own k splits over every tile (the workspace covers their partials too).
     auto al = [](const void* ptr, int64_t ld) { return reinterpret_cast<uintptr_t>(ptr) % 16 == 0 && ld % 8 == 0; };
     const bool ua = a.dt == BOM_BF16 && !(a.V % 8 == 0 && al(a.W, a.ldw) && al(a.R, a.ldr));
     Plan p = make_plan(a.N, a.d, a.V, a.dt, ua);
     const bool h_ok = a.d % 8 == 0 && al(a.H, a.ldh);
-    const bool ld_ok = a.ldw < (1 << 22) && a.ldr < (1 << 22);
+    const bool ld_ok = a.ldw < (1 << 22) && (zin || a.ldr < (1 << 22));
     const bool fits31 = ((int64_t)(a.N - 1) * a.ldh + a.d) * 2 < (1LL << 31) &&
                         ((int64_t)(a.N - 1) * a.ldr + a.V) * 2 < (1LL << 31) &&
                         ((int64_t)(a.d - 1) * a.ldw + a.V) * 2 < (1LL << 31);
     const bool small = p.w.kind == kMfma128 && p.h.kind == kMfma128;
-    if (a.dt == BOM_BF16 && (!h_ok || (ua && (!ld_ok || (small ? !fits31 : zin))))) p = simt_plan(a.N, a.d, a.V);
+    if (a.dt == BOM_BF16 && (!h_ok || (ua && (!ld_ok || (small && !fits31))))) p = simt_plan(a.N, a.d, a.V);
+    if (zin && (p.w.kind == kRank1 || (a.dH && p.h.kind == kRank1))) return launch_from_logits(a, L, st);
     if (a.dt == BOM_BF16 && L.part_off + partial_bytes(p, a.N, a.d, a.V) > L.total) return hipErrorInvalidValue;   // never taken
     if (!a.dH) p.h.kind = kSimt;   // no dH: no rank-1 vector for it
 
@@ -2325,29 +2427,8 @@ hipError_t launch_head_vjp_f32(const HeadVjpArgs& a, hipStream_t st) {
         return hipGetLastError();
     }
 
-    // rank-1 vectors first: u for dH, row-block partial sums of H over I for dW (lambda = 0: no history
-    // term, so neither is needed and the epilogues add nothing)
-    hipError_t e;
     const bool hist = a.lambda != 0.f;
-    const bool rw = p.w.kind == kRank1 && hist, rh = p.h.kind == kRank1 && hist;
-    const int nrb = (int)cdiv(a.N, kHsRows);
-    const int uch = u_chunks(a.d, a.V), ucw = u_chunk_cols(a.d, a.V);
-    if (rw || rh) {
-        const int nu = rh ? (int)cdiv(std::min<int64_t>((int64_t)a.d * uch, kUWaves), 4) : 0;
-        const int ns = rw ? (int)cdiv(a.d, 512) * nrb : 0;
-        auto r1 = ua ? vjp_rank1_kernel<true> : vjp_rank1_kernel<false>;
-        hipLaunchKernelGGL(r1, dim3((unsigned)(nu + ns)), dim3(256), 0, st, static_cast<const uint16_t*>(a.W), a.ldw,
-                           a.d, a.V, a.q_hat, nu, uch, ucw, static_cast<const uint16_t*>(a.H), a.ldh, a.N, a.labels,
-                           a.ignore_index, upart, hpart);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    int nprep = a.V > a.N ? a.V : a.N;
-    if (nprep < a.d) nprep = a.d;
-    hipLaunchKernelGGL(vjp_prep_kernel, dim3((nprep + 255) / 256), dim3(256), 0, st, a.q_hat, a.s, a.n_valid, a.lambda,
-                       a.V, a.N, a.labels, a.ignore_index, cq, cqp, vmask, scal, static_cast<float*>(a.db),
-                       rw ? hpart : nullptr, nrb, a.d, hsum, zin ? a.row_lse : nullptr, zc, rh ? upart : nullptr, uch, u);
-    e = hipGetLastError();
+    hipError_t e = launch_prep(a, L, p.w.kind == kRank1 && hist, p.h.kind == kRank1 && hist, ua, st);
     if (e != hipSuccess) return e;
     const Fold f{cq, vmask, scal, cqp, zin ? zc : nullptr, a.labels};
 
@@ -2364,19 +2445,14 @@ hipError_t launch_head_vjp_f32(const HeadVjpArgs& a, hipStream_t st) {
         const TileRange trh{inner, 0, oh, sh, 0, 0, a.d, (int64_t)a.N * a.d};
         const TileRange trw{inner, 0, ow, 1, 0, 0, 0, 0};
         const WideArgs wh{R16, a.ldr, W16, a.ldw, a.N, a.d, a.V, kps_h, trh, f.scal, hist ? vmask : nullptr, u, a.dH, a.lddh, 0.f,
-                          sh > 1 ? part : nullptr, nullptr, f.zc, a.labels};
+                          sh > 1 ? part : nullptr, nullptr};
         const WideArgs ww{H16, a.ldh, R16, a.ldr, a.d, a.V, a.N, kps_w, trw, f.scal, hist ? hsum : nullptr, cq, a.dW, a.lddw,
-                          a.dW_beta, nullptr, nullptr, f.zc, a.labels};
+                          a.dW_beta, nullptr, nullptr};
         const int nh = (int)(cdiv((int64_t)oh * sh, 8) * 8 * inner);
         const int nw = (int)(cdiv(ow, 8) * 8 * inner);
         const dim3 grid((unsigned)(nh + nw));
         const bool w8 = wave_cfg().pair == 8;
         if (ua) {   // rows at any alignment: eight waves
-            if (a.dh_dt == BOM_BF16)
-                hipLaunchKernelGGL((lds256w_pair_kernel<uint16_t, 8, false, true>), grid, dim3(512), 0, st, wh, ww, nh);
-            else
-                hipLaunchKernelGGL((lds256w_pair_kernel<float, 8, false, true>), grid, dim3(512), 0, st, wh, ww, nh);
-        } else if (zin) {   // logits input: eight waves
             if (a.dh_dt == BOM_BF16)
                 hipLaunchKernelGGL((lds256w_pair_kernel<uint16_t, 8, true>), grid, dim3(512), 0, st, wh, ww, nh);
             else
@@ -2396,10 +2472,10 @@ hipError_t launch_head_vjp_f32(const HeadVjpArgs& a, hipStream_t st) {
         const int64_t MN = (int64_t)a.N * a.d;
         if (a.dh_dt == BOM_BF16)
             hipLaunchKernelGGL(splitk_rank1_kernel<uint16_t>, dim3((unsigned)cdiv(MN, 256)), dim3(256), 0, st, part, sh,
-                               a.N, a.d, 0, 0, hist ? vmask : nullptr, u, static_cast<uint16_t*>(a.dH), a.lddh, 0.f);
+                               a.N, a.d, 0, 0, hist ? vmask : nullptr, u, static_cast<uint16_t*>(a.dH), a.lddh, 0.f, (const float*)nullptr);
         else
             hipLaunchKernelGGL(splitk_rank1_kernel<float>, dim3((unsigned)cdiv(MN, 256)), dim3(256), 0, st, part, sh, a.N,
-                               a.d, 0, 0, hist ? vmask : nullptr, u, static_cast<float*>(a.dH), a.lddh, 0.f);
+                               a.d, 0, 0, hist ? vmask : nullptr, u, static_cast<float*>(a.dH), a.lddh, 0.f, (const float*)nullptr);
         return hipGetLastError();
     }
 

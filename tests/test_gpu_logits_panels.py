@@ -1,0 +1,52 @@
+"""Large bf16 head VJPs from the logits: R formed in one panel of columns or in several, aligned and ragged."""
+import math
+
+import pytest
+import torch
+
+from paper_2609_36738_amd import bom
+from tests.gpu_util import dev, log
+
+pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not torch.cuda.is_available(), reason="needs an MI355X")]
+
+
+# name, N, d, V, lambda, want dH, ignore_index (one of them a class)
+CASES = [("one_panel_ragged", 2056, 264, 6001, 0.5, True, -100),
+         ("two_panels", 20000, 64, 16392, 0.5, True, -100),
+         ("two_panels_ragged", 20000, 72, 16395, 0.25, True, 0),
+         ("two_panels_no_history", 20000, 72, 16395, 0.0, True, -100),
+         ("narrow_panels_no_dH", 70000, 32, 8257, 0.5, False, -100)]
+
+
+@pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
+def test_head_vjp_logits_panels(case):
+    name, N, d, V, lam, want_dH, ig = case
+    log(f"[logits panels] {name} N={N} d={d} V={V}")
+    g = torch.Generator(device=dev()).manual_seed(9)
+
+    def rand(shape, std, dtype=torch.bfloat16):
+        return (torch.randn(shape, generator=g, device=dev()) * std).to(dtype)
+
+    H, W, Z = rand((N, d), 1.0), rand((d, V), 0.02), rand((N, V), 1.0)
+    y = torch.randint(0, V, (N,), generator=g, device=dev(), dtype=torch.int32)
+    y[1::7] = ig
+    y[2] = V
+    y[3] = V - 1
+    q, s = rand((V,), 0.01, torch.float32), rand((V,), 0.01, torch.float32)
+    res = bom.bom_residual(Z, y, ignore_index=ig)
+    kw = dict(s=s, lam=lam, ignore_index=ig, want_db=True, want_dH=want_dH, dh_dtype=torch.float32)
+    dW0 = rand((d, V), 1e-3, torch.float32)
+    a = bom.bom_head_vjp(H, W, Z, y, q, res["n_valid"], row_lse=res["row_lse"], dW=dW0.clone(), dW_beta=0.5, **kw)
+    b = bom.bom_head_vjp(H, W, res["R"], y, q, res["n_valid"], dW=dW0.clone(), dW_beta=0.5, **kw)
+    ok = (y >= 0) & (y < V) & (y != ig)
+    R = res["R"].double()
+    G = ((1 - lam) * R + lam * q.double()) * ok[:, None] / int(ok.sum())
+    ref = dict(dW=H.double().t() @ G + 0.5 * dW0.double(), dH=G @ W.double().t())
+    for k in ("dW", "dH") if want_dH else ("dW",):
+        # the stored R and the R formed from Z differ by at most one rounding of bf16 in some elements
+        ez = float((a[k] - ref[k]).norm() / ref[k].norm())
+        er = float((b[k] - ref[k]).norm() / ref[k].norm())
+        log(f"    {k}: rel err {ez:.2e} (stored R {er:.2e})")
+        assert er <= 1e-5 and ez <= 2.0 ** -9
+    assert torch.equal(a["db"], b["db"])
+    assert math.isfinite(float(a["dW"].sum()))
