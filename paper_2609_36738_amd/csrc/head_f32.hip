@@ -1,14 +1,16 @@
 // fp32 head products on the matrix cores (v_mfma_f32_32x32x2_f32: exact fp32 products, fp32 sums):
 //   dW = H^T G (+ beta dW),  dH = G W^T  with G_ij = [i in I] (alpha R_ij + cq_j) formed as R is staged,
 //   Z = H W (+ b).
-// Both VJP products run in one grid of 64 x 64 output tiles, four waves of 32 x 32 each, k tiles of 32 through two LDS
-// buffers with the next tile's words in registers. What bounds it: staging beside the matrix instructions. At N = 4096,
+// Both VJP products run in one grid of 64 x 64 (or 32 x 32) output tiles, four waves each, k tiles of 32 through two LDS
+// buffers with the next two tiles' words in registers. What bounds it: staging beside the matrix instructions. At N = 4096,
 // d = 1024, V = 2000 it runs at 101 TFLOP/s; without the loads 110, without the LDS writes too 128, and the same
 // fragment reads and products alone reach 153 of the 157 peak. At small sizes it is the waits of few tiles for their
 // loads. Any size, leading dimension and alignment takes this path.
-// Head VJP of a 1000-class head (N = 1024, d = 768): 53 us; the SIMT tiles that it replaces took 428 us there (two LDS
-// words read per product, 7-15 TFLOP/s).
+// Head VJP of a 1000-class head (N = 1024, d = 768): 51 us; the SIMT tiles that it replaces took 428 us there (two LDS
+// words read per product, 7-15 TFLOP/s). Of small heads, in one launch: N = 256, d = 128, V = 10 23.1 -> 8.3 us in the trace;
+// N = 64, d = 64, V = 4000 419 -> 15 us.
 #include <algorithm>
+#include <type_traits>
 
 #include "common.hpp"
 #include "kernels.hpp"
@@ -16,13 +18,8 @@
 namespace bom {
 namespace {
 
-typedef __attribute__((ext_vector_type(16))) float f32x16_t;
-
-constexpr int TB = 64;          // output tile (128 x 128 with waves of 64 x 64 measured no faster: 331 against 332 us
-                                // for N = 4096, d = 1024, V = 2000, and it fills the chip later)
 constexpr int TK = 32;          // k tile
-constexpr int LDC = TK + 4;     // LDS pitch of a k-contiguous operand tile [64][32]
-constexpr int kStage = TB * LDC > TK * TB ? TB * LDC : TK * TB;
+constexpr int LDC = TK + 4;     // LDS pitch of a k-contiguous operand tile [TB][32]
 constexpr int kF32MaxSplits = 64;
 
 enum { kDH = 0, kDW = 1, kFWD = 2 };
@@ -44,9 +41,12 @@ struct F32Args {
     float* part_w; float* part_h;               // [splits][rows][columns] sums of a product that splits k
 };
 
+// TB x TB output tiles: 64, or 32 for products of few tiles (128, with waves of 64 x 64, measured no faster than 64:
+// 331 against 332 us for N = 4096, d = 1024, V = 2000, and it fills the chip later).
+template <int TB>
 struct Stage {
-    float a[2][kStage];
-    float b[2][kStage];
+    float a[2][TB * LDC];
+    float b[2][TB * LDC];
 };
 
 // A chunk of four (from a multiple of four) across the end n >= 4 of its direction is read from n - 4 on: what its place x
@@ -59,14 +59,20 @@ __device__ __forceinline__ int moved(int x, int n) {
     return c < n && r >= c ? r : -1;
 }
 
-// One 64 x 64 tile over k in [kb, ke), each wave 32 x 32. A step of the matrix instruction adds two k: lanes 0-31 hold the
-// first, lanes 32-63 the second. With a k-contiguous operand these are k and k + 4 of a block of eight, so that a lane's
-// four fragments are one 16-byte LDS read; dW takes k and k + 1, the order of k. A k-outer tile [32][64] has the columns
-// of the second one's rows rotated by 32, so that the two halves of a wave read all 64 banks.
+// One TB x TB tile over k in [kb, ke), each wave a quarter of it in one accumulator block: 32 x 32 with a step of the
+// matrix instruction adding two k, or 16 x 16 with a step adding four (a quarter of the time per k that one tile takes
+// alone). The G = 2 or 4 lane groups of a wave hold one k of a step each. With a k-contiguous operand these are k,
+// k + 4, ... of a block of 4 G, so that a lane's four fragments are one 16-byte LDS read; dW takes them in the order of k.
+// A k-outer tile [32][TB] has the columns of some rows rotated so that a wave's groups read all 64 banks.
 // Sums of `flush` products at a time are added to the tile's total. dH: 512, so that the rounding error grows like the
 // root of 512 and of K / 512 instead of the root of K. dW: see F32Plan.
-template <int MODE, typename TO, bool ZR = false>
-__device__ __forceinline__ void f32_tile(const F32Args& g, int tile, int z, Stage& sh) {
+template <int TB, int MODE, typename TO, bool ZR = false>
+__device__ __forceinline__ void f32_tile(const F32Args& g, int tile, int z, Stage<TB>& sh) {
+    static_assert(TB == 64 || (TB == 32 && MODE != kFWD), "tile sizes");
+    constexpr int WB = TB / 2, G = kWave / WB, BK = 4 * G;   // block edge of a wave, lane groups, k per four steps
+    constexpr int OCT = TB / 4, ORS = 256 / OCT;             // k-outer chunks per row, rows per pass of the workgroup
+    typedef __attribute__((ext_vector_type(WB == 32 ? 16 : 4))) float acc_t;
+    constexpr int NR = WB == 32 ? 16 : 4;
     constexpr bool KA = MODE != kDW;   // operand A k-contiguous (dH: G rows, forward: H rows); dW: H^T
     constexpr bool KB = MODE == kDH;   // operand B k-contiguous (W rows); else k-outer
     const int M = MODE == kDW ? g.d : g.N, Nn = MODE == kDH ? g.d : g.V, K = MODE == kDW ? g.N : MODE == kDH ? g.V : g.d;
@@ -89,30 +95,30 @@ __device__ __forceinline__ void f32_tile(const F32Args& g, int tile, int z, Stag
         cs = nt > 0 ? (double)g.lambda / (double)nt : 0.0;
     }
     // Each thread stages chunks of four elements along the contiguous direction: k-contiguous k = 4 (t % 8) .. + 3 of
-    // rows t / 8 + 32 e, k-outer columns 4 (t % 16) .. + 3 of rows k = t / 16 + 16 e. A chunk is one 16-byte load at any
+    // rows t / 8 + 32 e, k-outer columns 4 (t % OCT) .. + 3 of rows k = t / OCT + ORS e. A chunk is one 16-byte load at any
     // 4-byte address inside the operand: see moved() for a chunk across an end. Rows past an end are clamped; they reach
     // only outputs that are not stored.
-    const int ck = 4 * (t % 8), cr = t / 8, oc = 4 * (t % 16), ok = t / 16;
+    const int ck = 4 * (t % 8), cr = t / 8, oc = 4 * (t % OCT), ok = t / OCT;
     constexpr int CH = TB * TK / 1024;   // chunks per thread and operand
     // chunk e of an operand whose rows (columns) start at x0 and end at `rows`; a product with an extent below four
     // loads words one by one
     const bool fast = min(min(M, Nn), K) >= 4;
     auto slot = [&](int x, int n) { return fast ? moved(x, n) : x < n ? x : -1; };
     auto load4 = [&](const float* X, int64_t ld, bool kcontig, int x0, int rows, int k0, int e) -> f32x4 {
-        const int r = kcontig ? min(x0 + cr + 32 * e, rows - 1) : max(moved(k0 + ok + 16 * e, K), 0);
+        const int r = kcontig ? min(x0 + cr + 32 * e, rows - 1) : max(moved(k0 + ok + ORS * e, K), 0);
         const int c = kcontig ? min(k0 + ck, K - 4) : min(x0 + oc, rows - 4);
         return *reinterpret_cast<const f32x4_any_t*>(X + (int64_t)r * ld + c);
     };
     auto load1 = [&](const float* X, int64_t ld, bool kcontig, int x0, int rows, int k0, int e) {
-        const int r = kcontig ? min(x0 + cr + 32 * e, rows - 1) : min(k0 + ok + 16 * e, K - 1);
+        const int r = kcontig ? min(x0 + cr + 32 * e, rows - 1) : min(k0 + ok + ORS * e, K - 1);
         const int c = kcontig ? k0 + ck : x0 + oc, last = (kcontig ? K : rows) - 1;
         const float* p = X + (int64_t)r * ld;
         return f32x4{p[min(c, last)], p[min(c + 1, last)], p[min(c + 2, last)], p[min(c + 3, last)]};
     };
     // rows of G: label and lse. dH: this thread's rows, fixed over k; dW: lane i of every wave holds row k0 + i
-    float lse_h[CH], lse_k = 0.f;
-    int y_h[CH], y_k = 0;
-    f32x4 cq_w = {0.f, 0.f, 0.f, 0.f}, q_k = {0.f, 0.f, 0.f, 0.f};
+    float lse_h[CH];
+    int y_h[CH];
+    f32x4 cq_w = {0.f, 0.f, 0.f, 0.f};
     auto valid = [&](int y) {
         bool bad = false;
         return label_valid(y, g.V, g.ig, &bad);
@@ -129,12 +135,17 @@ __device__ __forceinline__ void f32_tile(const F32Args& g, int tile, int z, Stag
 #pragma unroll
         for (int i = 0; i < 4; ++i) cq_w[i] = (float)(cs * (double)g.q_hat[max(slot(n0 + oc + i, Nn), 0)]);
 
-    f32x4 xa[CH], xb[CH];
-    auto load = [&](int k0) {
+    struct Set {   // one k tile in registers
+        f32x4 xa[CH], xb[CH], q_k;
+        float lse_k;
+        int y_k;
+    };
+    auto load = [&](Set& x, int k0) {
+        f32x4 (&xa)[CH] = x.xa, (&xb)[CH] = x.xb, &q_k = x.q_k;
         if constexpr (MODE == kDW) {
             const int k = max(slot(k0 + l % TK, K), 0);
-            y_k = g.labels[k];
-            if (ZR) lse_k = g.row_lse[k];
+            x.y_k = g.labels[k];
+            if (ZR) x.lse_k = g.row_lse[k];
         }
         // one branch around all of the tile's loads, so that they are in flight together
         if (fast) {
@@ -165,67 +176,77 @@ __device__ __forceinline__ void f32_tile(const F32Args& g, int tile, int z, Stag
         return r;
     };
     // row k and column c of a k-outer tile
-    auto outer = [](int k, int c) { return k * TB + (c ^ ((MODE == kDW ? k & 1 : (k >> 2) & 1) << 5)); };
-    auto store = [&](int buf, int k0) {
+    auto outer = [](int k, int c) {
+        const int rot = MODE != kDW ? (k >> 2) & 1 : TB == 64 ? k & 1 : (k >> 1) & 1;
+        return k * TB + (c ^ (rot * WB));
+    };
+    auto store = [&](const Set& x, int buf, int k0) {
         f32x4 cq_k = {0.f, 0.f, 0.f, 0.f};
         if constexpr (MODE == kDH)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) cq_k[i] = (float)(cs * (double)q_k[i]);
+            for (int i = 0; i < 4; ++i) cq_k[i] = (float)(cs * (double)x.q_k[i]);
         const bool tail = k0 + TK > ke;   // places past the end of k: zeros in both operands
 #pragma unroll
         for (int e = 0; e < CH; ++e) {
-            f32x4 a = xa[e], b = xb[e];
+            f32x4 a = x.xa[e], b = x.xb[e];
             if constexpr (MODE == kDH) a = g_of(a, valid(y_h[e]), y_h[e], lse_h[e], cq_k, k0 + ck);
-            if constexpr (MODE == kDW) {   // this thread's row of G: ok + 16 e, held by that lane
-                const int y = __shfl(y_k, ok + 16 * e, kWave);
-                b = g_of(b, valid(y), y, ZR ? __shfl(lse_k, ok + 16 * e, kWave) : 0.f, cq_w, n0 + oc);
+            if constexpr (MODE == kDW) {   // this thread's row of G: ok + ORS e, held by that lane
+                const int y = __shfl(x.y_k, ok + ORS * e, kWave);
+                b = g_of(b, valid(y), y, ZR ? __shfl(x.lse_k, ok + ORS * e, kWave) : 0.f, cq_w, n0 + oc);
             }
             if (tail) {
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const int ka = KA ? k0 + ck + i : k0 + ok + 16 * e, kk = KB ? k0 + ck + i : k0 + ok + 16 * e;
+                    const int ka = KA ? k0 + ck + i : k0 + ok + ORS * e, kk = KB ? k0 + ck + i : k0 + ok + ORS * e;
                     if (slot(ka, K) < 0 || (ka >= ke && ke < K)) a[i] = 0.f;
                     if (slot(kk, K) < 0 || (kk >= ke && ke < K)) b[i] = 0.f;
                 }
             }
-            *reinterpret_cast<f32x4*>(&sh.a[buf][KA ? (cr + 32 * e) * LDC + ck : outer(ok + 16 * e, oc)]) = a;
-            *reinterpret_cast<f32x4*>(&sh.b[buf][KB ? (cr + 32 * e) * LDC + ck : outer(ok + 16 * e, oc)]) = b;
+            *reinterpret_cast<f32x4*>(&sh.a[buf][KA ? (cr + 32 * e) * LDC + ck : outer(ok + ORS * e, oc)]) = a;
+            *reinterpret_cast<f32x4*>(&sh.b[buf][KB ? (cr + 32 * e) * LDC + ck : outer(ok + ORS * e, oc)]) = b;
         }
     };
-    auto frag = [&](const float* s, bool kcontig, int base, int b8, float (&f)[4]) {
-        const int r = base + l % 32, h = l / 32;
+    auto frag = [&](const float* s, bool kcontig, int base, int blk, float (&f)[4]) {
+        const int r = base + l % WB, h = l / WB;
         if (kcontig) {
-            const f32x4 v = *reinterpret_cast<const f32x4*>(s + r * LDC + b8 * 8 + h * 4);
+            const f32x4 v = *reinterpret_cast<const f32x4*>(s + r * LDC + blk * BK + h * 4);
 #pragma unroll
             for (int i = 0; i < 4; ++i) f[i] = v[i];
         } else {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) f[i] = s[outer(b8 * 8 + (MODE == kDW ? 2 * i + h : 4 * h + i), r)];
+            for (int i = 0; i < 4; ++i) f[i] = s[outer(blk * BK + (MODE == kDW ? G * i + h : 4 * h + i), r)];
         }
     };
     const int flush = MODE == kDW ? g.flush_w : 512;
-    f32x16_t acc, total;
+    acc_t acc, total;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = total[r] = 0.f;
-    load(kb);
-    store(0, kb);
+    for (int r = 0; r < NR; ++r) acc[r] = total[r] = 0.f;
+    // two k tiles in registers: tile j + 1 goes to the other LDS buffer after tile j's products, and tile j + 3 is loaded
+    // into its registers
+    Set sets[2];
+    load(sets[0], kb);
+    if (kb + TK < ke) load(sets[1], kb + TK);
+    store(sets[0], 0, kb);
+    if (kb + 2 * TK < ke) load(sets[0], kb + 2 * TK);
     __syncthreads();
-    int buf = 0, since = 0;
-    for (int k0 = kb; k0 < ke; k0 += TK) {
+    int since = 0;
+    auto step = [&](int k0, int buf, Set& next) {
         const bool more = k0 + TK < ke;
-        if (more) load(k0 + TK);
 #pragma unroll
-        for (int b8 = 0; b8 < TK / 8; ++b8) {
+        for (int blk = 0; blk < TK / BK; ++blk) {
             float fa[4], fb[4];
-            frag(sh.a[buf], KA, wm * 32, b8, fa);
-            frag(sh.b[buf], KB, wn * 32, b8, fb);
+            frag(sh.a[buf], KA, wm * WB, blk, fa);
+            frag(sh.b[buf], KB, wn * WB, blk, fb);
 #pragma unroll
-            for (int q = 0; q < 4; ++q) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[q], fb[q], acc, 0, 0, 0);
-            if (b8 % 2 == 1) {
+            for (int q = 0; q < 4; ++q) {
+                if constexpr (WB == 32) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[q], fb[q], acc, 0, 0, 0);
+                else acc = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[q], fb[q], acc, 0, 0, 0);
+            }
+            if ((blk + 1) * BK % 16 == 0) {
                 since += 16;
-                if (since == flush || (b8 == TK / 8 - 1 && !more)) {
+                if (since == flush || (blk == TK / BK - 1 && !more)) {
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) {
+                    for (int r = 0; r < NR; ++r) {
                         total[r] += acc[r];
                         acc[r] = 0.f;
                     }
@@ -233,19 +254,25 @@ __device__ __forceinline__ void f32_tile(const F32Args& g, int tile, int z, Stag
                 }
             }
         }
-        if (more) store(buf ^ 1, k0 + TK);
+        if (more) {
+            store(next, buf ^ 1, k0 + TK);
+            if (k0 + 3 * TK < ke) load(next, k0 + 3 * TK);
+        }
         __syncthreads();
-        buf ^= 1;
+    };
+    for (int k0 = kb; k0 < ke; k0 += 2 * TK) {
+        step(k0, 0, sets[1]);
+        if (k0 + TK < ke) step(k0 + TK, 1, sets[0]);
     }
-    // accumulator element r of lane l: tile row wm*32 + (r/4)*8 + (l/32)*4 + r%4, column wn*32 + l%32
+    // accumulator element r of lane l: block row (r/4) 4G + (l/WB) 4 + r%4, block column l % WB
     const int splits = MODE == kDW ? g.splits_w : MODE == kDH ? g.splits_h : 1;
-    const int nt = n0 + wn * 32 + l % 32;
+    const int nt = n0 + wn * WB + l % WB;
     const int n = KB ? (nt < Nn ? nt : -1) : slot(nt, Nn);
     if (n >= 0) {
         const float bn = MODE == kFWD && g.bias != nullptr ? g.bias[n] : 0.f;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int mt = m0 + wm * 32 + (r / 4) * 8 + (l / 32) * 4 + r % 4;
+        for (int r = 0; r < NR; ++r) {
+            const int mt = m0 + wm * WB + (r / 4) * BK + (l / WB) * 4 + r % 4;
             const int m = KA ? (mt < M ? mt : -1) : slot(mt, M);
             if (m < 0) continue;
             if constexpr (MODE == kFWD) {
@@ -275,23 +302,23 @@ __device__ __forceinline__ void f32_tile(const F32Args& g, int tile, int z, Stag
 __device__ __forceinline__ int xcd_unit(int id, int n) { return (id % 8) * ((n + 7) / 8) + id / 8; }
 
 // Blocks [0, tiles_w * splits_w), padded: dW's units; the rest dH's. A unit is (split, tile), tiles varying fastest.
-template <typename TO, bool ZR>
+template <int TB, typename TO, bool ZR>
 __global__ __launch_bounds__(256) void vjp_f32_mfma_kernel(F32Args g) {
-    __shared__ __attribute__((aligned(16))) Stage sh;
+    __shared__ __attribute__((aligned(16))) Stage<TB> sh;
     const int uw = g.tiles_w * g.splits_w, bw = (uw + 7) / 8 * 8, uh = g.tiles_h * g.splits_h;
     if ((int)blockIdx.x < bw) {
         const int u = xcd_unit(blockIdx.x, uw);
-        if (u < uw) f32_tile<kDW, float, ZR>(g, u % g.tiles_w, u / g.tiles_w, sh);
+        if (u < uw) f32_tile<TB, kDW, float, ZR>(g, u % g.tiles_w, u / g.tiles_w, sh);
     } else {
         const int u = xcd_unit((int)blockIdx.x - bw, uh);
-        if (u < uh) f32_tile<kDH, TO, ZR>(g, u % g.tiles_h, u / g.tiles_h, sh);
+        if (u < uh) f32_tile<TB, kDH, TO, ZR>(g, u % g.tiles_h, u / g.tiles_h, sh);
     }
 }
 
 __global__ __launch_bounds__(256) void forward_f32_mfma_kernel(F32Args g) {
-    __shared__ __attribute__((aligned(16))) Stage sh;
+    __shared__ __attribute__((aligned(16))) Stage<64> sh;
     const int u = xcd_unit(blockIdx.x, g.tiles_w);
-    if (u < g.tiles_w) f32_tile<kFWD, float>(g, u, 0, sh);
+    if (u < g.tiles_w) f32_tile<64, kFWD, float>(g, u, 0, sh);
 }
 
 // Sums of the k splits in split order, both products' in one launch: dW = sum_z part_w[z] (+ beta dW), dH = sum_z
@@ -315,42 +342,46 @@ __global__ __launch_bounds__(256) void f32_splits_kernel(F32Args g, int64_t nw, 
 
 int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
-// k splits of both products: the length of dH's k ranges, a power of two, and dW's split or not, that give the least
-// modelled time: the units a CU gets times 20 ns per k of a tile (what the kernel reaches with four resident), at least 27 ns per k of the
-// longest unit (alone on its CU it waits for its loads), plus the partial sums' traffic and the reduction launch where
-// a product splits. Measured (N x d x V: unsplit, ranges of 512, of 256): 1024 x 768 x 1000 57, 51, 58 us;
-// 256 x 1024 x 1000 36, 27, 23 us; 3469 x 224 x 8307 322, 341, 397 us.
+// Tile size, the length of dH's k ranges (a power of two) and dW's split or not: those of the least modelled time. A CU
+// takes its units at 20 ns per k of a 64 x 64 tile and 7.5 ns of a 32 x 32 one (the rates with several resident); a unit
+// alone on its CU waits for its loads and its own steps, 30 and 15 ns per k; a unit's start and end take 0.6 us; splits add the partial sums' traffic and the
+// reduction launch. Measured (N x d x V, tiles of 64 and of 32): 4096 x 1024 x 2000 336 and 483 us, 256 x 1024 x 1000
+// 21.0 and 25.6, 1024 x 768 x 1000 50.7 and 50.5, 1024 x 128 x 10 36.5 and 20.3, 4096 x 64 x 10 23.9 and 15.9.
 // dW's sums keep one order whatever the plan: `sums` partial sums of equal k ranges, each in the order of k, added in that
 // order, either as that many units or as one unit that adds them itself. (The update divides by the gradient's own size
 // plus 1e-8 in its first steps, so there the last bits of a small sum reach theta.)
 struct F32Plan {
-    int splits_w = 1, kps_w, splits_h = 1, kps_h, flush_w;
+    int tb, splits_w = 1, kps_w, splits_h = 1, kps_h, flush_w;
 };
 F32Plan plan_f32(int64_t N, int64_t d, int64_t V, int sums) {
-    const int64_t tw = cdiv(d, TB) * cdiv(V, TB), th = cdiv(N, TB) * cdiv(d, TB);
     const int64_t per = cdiv(cdiv(N, sums), 16) * 16;
     F32Plan best;
     double best_t = 1e300;
-    for (int cut_w = 0; cut_w < (sums > 1 ? 2 : 1); ++cut_w) {
-        for (int64_t len = (int64_t)1 << 31; len >= 128; len /= 2) {
-            F32Plan p;
-            p.flush_w = (int)per;
-            p.splits_w = cut_w ? (int)cdiv(N, per) : 1;
-            p.kps_w = cut_w ? (int)per : (int)N;
-            p.splits_h = (int)std::min<int64_t>(kF32MaxSplits, cdiv(V, len));
-            p.kps_h = (int)std::min<int64_t>(cdiv(cdiv(V, p.splits_h), TK) * TK, 0x7fffffff / TK * TK);
-            p.splits_h = (int)cdiv(V, p.kps_h);
-            const double work = (double)tw * N + (double)th * V;   // tile k steps
-            const int64_t units = tw * p.splits_w + th * p.splits_h;
-            const double per_cu = units < 1024 ? (double)cdiv(units, 256) * work / units : work / 256;
-            const double longest = (double)std::max<int64_t>(p.kps_w, std::min<int64_t>(p.kps_h, V));
-            double t = std::max(per_cu * 20e-9, longest * 27e-9);
-            const double pw = p.splits_w > 1 ? (2.0 * p.splits_w + 1) * 4.0 * d * V : 0.0;
-            const double ph = p.splits_h > 1 ? (2.0 * p.splits_h + 1) * 4.0 * N * d : 0.0;
-            if (pw + ph > 0.0) t += (pw + ph) / 4e12 + 4e-6;
-            if (t < best_t * 0.98) {
-                best_t = t;
-                best = p;
+    for (int tb : {64, 32}) {
+        const int64_t tw = cdiv(d, tb) * cdiv(V, tb), th = cdiv(N, tb) * cdiv(d, tb);
+        for (int cut_w = 0; cut_w < (sums > 1 ? 2 : 1); ++cut_w) {
+            for (int64_t len = (int64_t)1 << 31; len >= 128; len /= 2) {
+                F32Plan p;
+                p.tb = tb;
+                p.flush_w = (int)per;
+                p.splits_w = cut_w ? (int)cdiv(N, per) : 1;
+                p.kps_w = cut_w ? (int)per : (int)N;
+                p.splits_h = (int)std::min<int64_t>(kF32MaxSplits, cdiv(V, len));
+                p.kps_h = (int)std::min<int64_t>(cdiv(cdiv(V, p.splits_h), TK) * TK, 0x7fffffff / TK * TK);
+                p.splits_h = (int)cdiv(V, p.kps_h);
+                const double work = (double)tw * N + (double)th * V;   // tile k steps
+                const int64_t units = tw * p.splits_w + th * p.splits_h;
+                const double per_cu = units < 1024 ? (double)cdiv(units, 256) * work / units : work / 256;
+                const double longest = (double)std::max<int64_t>(p.kps_w, std::min<int64_t>(p.kps_h, V));
+                double t = std::max(per_cu * (tb == 64 ? 20e-9 : 7.5e-9), longest * (tb == 64 ? 30e-9 : 15e-9));
+                const double pw = p.splits_w > 1 ? (2.0 * p.splits_w + 1) * 4.0 * d * V : 0.0;
+                const double ph = p.splits_h > 1 ? (2.0 * p.splits_h + 1) * 4.0 * N * d : 0.0;
+                t += 0.6e-6 * (double)cdiv(units, 256);
+                if (pw + ph > 0.0) t += (pw + ph) / 4e12 + 4e-6;
+                if (t < best_t * 0.98) {
+                    best_t = t;
+                    best = p;
+                }
             }
         }
     }
@@ -390,7 +421,7 @@ hipError_t launch_vjp_f32_products(const HeadVjpArgs& a, int sums, void* part, h
     g.db = static_cast<float*>(a.db);
     g.dH = a.dH;
     g.lddh = a.lddh;
-    const int64_t tw = cdiv(a.d, TB) * cdiv(a.V, TB), th = a.dH ? cdiv(a.N, TB) * cdiv(a.d, TB) : 0;
+    const int64_t tw = cdiv(a.d, p.tb) * cdiv(a.V, p.tb), th = a.dH ? cdiv(a.N, p.tb) * cdiv(a.d, p.tb) : 0;
     g.tiles_w = (int)tw;
     g.splits_w = p.splits_w;
     g.kps_w = p.kps_w;
@@ -404,8 +435,12 @@ hipError_t launch_vjp_f32_products(const HeadVjpArgs& a, int sums, void* part, h
     const int64_t units = cdiv(tw * p.splits_w, 8) * 8 + cdiv(th * p.splits_h, 8) * 8;
     if (units >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
     const bool h16 = a.dH != nullptr && a.dh_dt == BOM_BF16;
-    const auto kern = a.is_residual ? (h16 ? vjp_f32_mfma_kernel<uint16_t, false> : vjp_f32_mfma_kernel<float, false>)
-                                    : (h16 ? vjp_f32_mfma_kernel<uint16_t, true> : vjp_f32_mfma_kernel<float, true>);
+    auto pick = [&](auto tb) {
+        constexpr int TB = decltype(tb)::value;
+        return a.is_residual ? (h16 ? vjp_f32_mfma_kernel<TB, uint16_t, false> : vjp_f32_mfma_kernel<TB, float, false>)
+                             : (h16 ? vjp_f32_mfma_kernel<TB, uint16_t, true> : vjp_f32_mfma_kernel<TB, float, true>);
+    };
+    const auto kern = p.tb == 32 ? pick(std::integral_constant<int, 32>{}) : pick(std::integral_constant<int, 64>{});
     hipLaunchKernelGGL(kern, dim3((unsigned)units), dim3(256), 0, st, g);
     hipError_t e = hipGetLastError();
     const int64_t nw = p.splits_w > 1 ? (int64_t)a.d * a.V : 0, nh = a.dH && p.splits_h > 1 ? (int64_t)a.N * a.d : 0;
@@ -430,7 +465,7 @@ hipError_t launch_forward_f32(const float* H, int64_t ldh, const float* W, int64
     g.N = N;
     g.d = d;
     g.V = V;
-    const int64_t tiles = cdiv(N, TB) * cdiv(V, TB);
+    const int64_t tiles = cdiv(N, 64) * cdiv(V, 64);
     if (tiles >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
     g.tiles_w = (int)tiles;
     hipLaunchKernelGGL(forward_f32_mfma_kernel, dim3((unsigned)(cdiv(tiles, 8) * 8)), dim3(256), 0, st, g);

@@ -14,8 +14,7 @@
 // fixed-order reduction. dW = H^T G has both operands k-outer in memory (transposing LDS reads or a
 // transpose while staging); dH = G W^T has both operands k-contiguous. The fused and the 256-tile
 // kernels also take R and W with rows at any alignment and of any length (UA): a 4088 x 1024 x 50,257 head VJP takes
-// 0.93 ms with it, against 22.5 ms on the SIMT tiled GEMM that is left for bf16 with H unaligned. fp32 path: one launch
-// for small heads here, the fp32 matrix kernels of head_f32.hip otherwise.
+// 0.93 ms with it, against 22.5 ms on the SIMT tiled GEMM that is left for bf16 with H unaligned. fp32 path: head_f32.hip.
 #include <algorithm>
 #include <array>
 #include <map>
@@ -305,146 +304,6 @@ __global__ __launch_bounds__(256) void simt_dH_kernel(const uint16_t* __restrict
             if (direct) stf<TO>(out, (int64_t)m * ldo + n, acc[i][j]);
             else part[((int64_t)blockIdx.z * M + m) * Nn + n] = acc[i][j];
         }
-}
-
-// ---- fp32 small heads in one launch -------------------------------------------------------------------
-// Both products of a small fp32 head (the tiny classifier) in one grid, each workgroup one 64 x 64 SIMT tile
-// of dW (blocks [0, tw)) or of dH (the rest) over the whole k range in chunks of 64, with G folded in as its operand is
-// staged: G_ij = [i in I] (alpha R_ij + cq_j), alpha = (1 - lambda) / N_t, cq_j = lambda q_hat_j / N_t,
-// formed here from the device words (no prep kernel); R may come from the logits (row_lse given). Block 0
-// also writes db = (1 - lambda) s + lambda q_hat.
-struct SmallF32Args {
-    const float* H; int64_t ldh;
-    const float* W; int64_t ldw;
-    const float* R; int64_t ldr;
-    const float* row_lse;   // logits input: R formed from Z and lse; null: R is stored
-    const int32_t* labels; int32_t ig;
-    const float* q_hat; const float* s; const int32_t* n_valid; float lambda;
-    int N, d, V;
-    float* dW; int64_t lddw; float beta;
-    float* db;
-    void* dH; int64_t lddh; int dh_bf16;
-    int tw_n, tw, th_n;
-};
-
-__global__ __launch_bounds__(256) void vjp_small_f32_kernel(SmallF32Args a) {
-    constexpr int FK = 64;   // k chunk: every load of a chunk (16 per operand per thread) is in flight at once
-    __shared__ float As[FK][SB + 4];
-    __shared__ float Bs[FK][SB + 4];
-    const bool is_dw = (int)blockIdx.x < a.tw;
-    const int id = is_dw ? blockIdx.x : blockIdx.x - a.tw;
-    const int tn_count = is_dw ? a.tw_n : a.th_n;
-    const int m0 = (id / tn_count) * SB, n0 = (id % tn_count) * SB;
-    const int M = is_dw ? a.d : a.N, Nn = is_dw ? a.V : a.d, K = is_dw ? a.N : a.V;
-    const int t = threadIdx.x, tx = t % 16, ty = t / 16;
-    // a tile with at most 16 columns inside the output (the classifier's dW over 10 classes) maps its threads
-    // to 64 rows x 4 column groups, so no thread spends its products on columns past the output
-    const bool narrow = Nn - n0 <= 16;
-    const int nr = t / 4, nc = t % 4;
-    const int nt = *a.n_valid;
-    const float alpha = nt > 0 ? (float)((1.0 - (double)a.lambda) / (double)nt) : 0.f;
-    const double cs = nt > 0 ? (double)a.lambda / (double)nt : 0.0;
-    // G element of row i, column j from its loaded words (label y, R or Z value r, the row's lse, q_hat_j)
-    const bool zin = a.row_lse != nullptr;
-    auto g_from = [&](float r, int y, float lse, float q, int j) {
-        bool bad = false;
-        if (zin) r = r_from_z(r, lse * kLog2e, j == y);
-        return label_valid(y, a.V, a.ig, &bad) ? fmaf(alpha, r, (float)(cs * (double)q)) : 0.f;
-    };
-    // without the logits input the lse loads read q_hat[0] (a valid word whose value is not used), so that
-    // no load of the staging is conditional: all of a chunk's loads are then issued before the first wait
-    const float* lse_src = zin ? a.row_lse : a.q_hat;
-    const int lse_on = zin ? 1 : 0;
-    constexpr int EPT = FK * SB / 256;   // staged elements per thread and operand
-    float acc[4][4] = {};
-    // a chunk's words are loaded into registers one chunk ahead (issued right after the previous chunk was
-    // staged, so they are in flight during its products), from clamped in-range addresses; the product
-    // test is outside the unrolled loops, which keeps each chunk's loads together
-    float xa[EPT], xr[EPT], xl[EPT], xq[EPT];
-    int xy[EPT];
-    auto load_chunk = [&](int k0) {
-        if (is_dw) {   // A(m, k) = H[k][m], B(k, n) = G[k][n]
-#pragma unroll
-            for (int e = 0; e < EPT; ++e) {
-                const int idx = e * 256 + t, kk = idx / SB, cc = idx % SB;
-                const int kc = min(k0 + kk, K - 1), mc = min(m0 + cc, M - 1), nc = min(n0 + cc, Nn - 1);
-                xa[e] = a.H[(int64_t)kc * a.ldh + mc];
-                xr[e] = a.R[(int64_t)kc * a.ldr + nc];
-                xy[e] = a.labels[kc];
-                xl[e] = lse_src[kc * lse_on];
-                xq[e] = a.q_hat[nc];
-            }
-        } else {       // A(i, k) = G[i][k], B(k, n) = W[n][k]
-#pragma unroll
-            for (int e = 0; e < EPT; ++e) {
-                const int idx = e * 256 + t, rr = idx / FK, kk = idx % FK;
-                const int kc = min(k0 + kk, K - 1), ic = min(m0 + rr, M - 1), nc = min(n0 + rr, Nn - 1);
-                xa[e] = a.W[(int64_t)nc * a.ldw + kc];
-                xr[e] = a.R[(int64_t)ic * a.ldr + kc];
-                xy[e] = a.labels[ic];
-                xl[e] = lse_src[ic * lse_on];
-                xq[e] = a.q_hat[kc];
-            }
-        }
-    };
-    load_chunk(0);
-    for (int k0 = 0; k0 < K; k0 += FK) {
-        if (is_dw) {
-#pragma unroll
-            for (int e = 0; e < EPT; ++e) {
-                const int idx = e * 256 + t, kk = idx / SB, cc = idx % SB, k = k0 + kk;
-                As[kk][cc] = (k < K && m0 + cc < M) ? xa[e] : 0.f;
-                Bs[kk][cc] = (k < K && n0 + cc < Nn) ? g_from(xr[e], xy[e], xl[e], xq[e], n0 + cc) : 0.f;
-            }
-        } else {
-#pragma unroll
-            for (int e = 0; e < EPT; ++e) {
-                const int idx = e * 256 + t, rr = idx / FK, kk = idx % FK, k = k0 + kk;
-                As[kk][rr] = (k < K && m0 + rr < M) ? g_from(xr[e], xy[e], xl[e], xq[e], k) : 0.f;
-                Bs[kk][rr] = (k < K && n0 + rr < Nn) ? xa[e] : 0.f;
-            }
-        }
-        if (k0 + FK < K) load_chunk(k0 + FK);
-        __syncthreads();
-        const int kmax = min(FK, K - k0);   // the chunk's k range (a short last chunk skips its padding)
-        if (narrow) {   // at most 16 columns: thread (row nr, column group nc) owns 1 x 4 outputs
-#pragma unroll 8
-            for (int kk = 0; kk < kmax; ++kk) {
-                const float x = As[kk][nr];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[0][j] = fmaf(x, Bs[kk][nc * 4 + j], acc[0][j]);
-            }
-        } else {
-#pragma unroll 8
-            for (int kk = 0; kk < kmax; ++kk) {
-                float x[4], w[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) x[i] = As[kk][ty * 4 + i];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) w[j] = Bs[kk][tx * 4 + j];
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(x[i], w[j], acc[i][j]);
-            }
-        }
-        __syncthreads();
-    }
-    for (int i = 0; i < (narrow ? 1 : 4); ++i)
-        for (int j = 0; j < 4; ++j) {
-            const int m = narrow ? m0 + nr : m0 + ty * 4 + i, n = narrow ? n0 + nc * 4 + j : n0 + tx * 4 + j;
-            if (m >= M || n >= Nn) continue;
-            if (is_dw) {
-                float* p = a.dW + (int64_t)m * a.lddw + n;
-                *p = a.beta != 0.f ? acc[i][j] + a.beta * *p : acc[i][j];
-            } else if (a.dh_bf16) {
-                stf<uint16_t>(static_cast<uint16_t*>(a.dH), (int64_t)m * a.lddh + n, acc[i][j]);
-            } else {
-                stf<float>(static_cast<float*>(a.dH), (int64_t)m * a.lddh + n, acc[i][j]);
-            }
-        }
-    if (blockIdx.x == 0 && a.db != nullptr)
-        for (int j = t; j < a.V; j += 256) a.db[j] = nt > 0 ? (1.0f - a.lambda) * a.s[j] + a.lambda * a.q_hat[j] : 0.f;
 }
 
 // ---- MFMA bf16 path -----------------------------------------------------------------------------
@@ -2083,6 +1942,14 @@ size_t partial_bytes(const Plan& p, int64_t N, int64_t d, int64_t V) {
     return std::max(pw, ph);
 }
 
+// fp32 dW: the number of partial sums that it adds up. Small heads (at most 64 tiles of 64 x 64 in both products) take
+// one sum over their rows, others as many as fill the chip with such tiles.
+int f32_dw_sums(int64_t N, int64_t d, int64_t V) {
+    const int64_t tw = cdiv(d, SB) * cdiv(V, SB), th = cdiv(N, SB) * cdiv(d, SB);
+    if (tw + th <= 64 && N <= 8192 && V <= 8192) return 1;
+    return choose_splits(tw, d, V, N, SB, SK, 4);
+}
+
 VjpWs vjp_ws(int64_t N, int64_t d, int64_t V, bom_dtype dt) {
     const Plan p = make_plan(N, d, V, dt, false);
     // the same shape may come with rows at any alignment, and take the plan for those or the SIMT one
@@ -2100,7 +1967,7 @@ VjpWs vjp_ws(int64_t N, int64_t d, int64_t V, bom_dtype dt) {
     w.u_off = align256(w.hsum_off + (r1 ? (size_t)d * 4 : 0));
     w.upart_off = align256(w.u_off + (r1 ? (size_t)d * 4 : 0));
     w.part_off = align256(w.upart_off + (r1 ? (size_t)u_chunks(d, V) * d * 4 : 0));
-    size_t need = dt == BOM_F32 ? vjp_f32_workspace_bytes(N, d, V, p.w.splits) : partial_bytes(p, N, d, V);
+    size_t need = dt == BOM_F32 ? vjp_f32_workspace_bytes(N, d, V, f32_dw_sums(N, d, V)) : partial_bytes(p, N, d, V);
     if (dt == BOM_BF16) need = std::max({need, partial_bytes(pu, N, d, V), partial_bytes(simt_plan(N, d, V), N, d, V)});
     w.panel_off = w.hacc_off = w.total = align256(w.part_off + need);
     if (dt == BOM_BF16 && r1 && V >= 8) {   // panels of R for the logits input
@@ -2373,20 +2240,7 @@ hipError_t launch_head_vjp_f32(const HeadVjpArgs& a, hipStream_t st) {
     if (a.dt == BOM_BF16 && L.part_off + partial_bytes(p, a.N, a.d, a.V) > L.total) return hipErrorInvalidValue;   // never taken
     if (!a.dH) p.h.kind = kSimt;   // no dH: no rank-1 vector for it
 
-    // small fp32 heads (at most 64 tiles of 64 x 64 in both products, k ranges up to 8192): one launch
-    if (a.dt == BOM_F32) {
-        const int64_t tw = cdiv(a.d, SB) * cdiv(a.V, SB), th = a.dH ? cdiv(a.N, SB) * cdiv(a.d, SB) : 0;
-        if (tw + th <= 64 && a.N <= 8192 && a.V <= 8192) {
-            SmallF32Args sa{static_cast<const float*>(a.H), a.ldh, static_cast<const float*>(a.W), a.ldw,
-                            static_cast<const float*>(a.R), a.ldr, zin ? a.row_lse : nullptr, a.labels, a.ignore_index,
-                            a.q_hat, a.s, a.n_valid, a.lambda, a.N, a.d, a.V, static_cast<float*>(a.dW), a.lddw,
-                            a.dW_beta, static_cast<float*>(a.db), a.dH, a.lddh, a.dh_dt == BOM_BF16 ? 1 : 0,
-                            (int)cdiv(a.V, SB), (int)tw, (int)cdiv(a.d, SB)};
-            hipLaunchKernelGGL(vjp_small_f32_kernel, dim3((unsigned)(tw + th)), dim3(256), 0, st, sa);
-            return hipGetLastError();
-        }
-        return launch_vjp_f32_products(a, p.w.splits, part, st);
-    }
+    if (a.dt == BOM_F32) return launch_vjp_f32_products(a, f32_dw_sums(a.N, a.d, a.V), part, st);
 
     // small products (both on the 128-tile kernel): one fused launch, nothing staged beforehand
     const PlanOverride& ov = plan_override();
