@@ -128,10 +128,10 @@ constexpr float kLn2 = 0.6931471805599453f;
 __device__ __forceinline__ float exp2_fast(float x) { return __builtin_amdgcn_exp2f(x); }
 
 // Residual element from a logit: 2^(z log2 e - c) with c = lse log2 e, minus 1 at the label. Rows outside the batch's
-// supervised ones have c = +inf and are 0 (also at their label, which may be an ignore_index inside [0, V)).
+// supervised ones have c = +inf and are 0; the caller gives them no label (theirs may be an ignore_index inside [0, V)).
 __device__ __forceinline__ float r_from_z(float z, float c, bool at_label) {
     float p = exp2_fast(fmaf(z, kLog2e, -c));
-    if (at_label && c < INFINITY) p -= 1.0f;
+    if (at_label) p -= 1.0f;
     return p;
 }
 

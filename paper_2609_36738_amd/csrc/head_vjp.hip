@@ -21,6 +21,7 @@
 #include <mutex>
 #include <queue>
 #include <vector>
+#include <climits>
 #include <cstdio>
 #include <cstdlib>
 #include <type_traits>
@@ -207,7 +208,7 @@ __device__ __forceinline__ void stf<uint16_t>(uint16_t* p, int64_t i, float x) {
 __device__ __forceinline__ float r_elem(const uint16_t* RZ, int64_t ld, int row, int col, const Fold& f) {
     const float x = ldf(RZ, (int64_t)row * ld + col);
     if (f.zc == nullptr) return x;
-    return bf16_to_f32(f32_to_bf16(r_from_z(x, f.zc[row], col == f.labels[row])));
+    return bf16_to_f32(f32_to_bf16(r_from_z(x, f.zc[row], col == f.labels[row] && f.vmask[row] != 0.f)));
 }
 
 // ---- SIMT fallback (bf16 with H unaligned): 64 x 64 tiles, 16-deep k, 4 x 4 outputs per thread --------------------------
@@ -386,7 +387,7 @@ struct StageGt {
         if (f.zc != nullptr) {
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const u32x4_t y = z_chunk_to_r(u32x4_t{x[q].x, x[q].y, x[q].z, x[q].w}, zc[q], lo[q], true);
+                const u32x4_t y = z_chunk_to_r(u32x4_t{x[q].x, x[q].y, x[q].z, x[q].w}, zc[q], vm[q] != 0.f ? lo[q] : -1, true);
                 x[q] = make_uint4(y[0], y[1], y[2], y[3]);
             }
         }
@@ -449,7 +450,7 @@ struct StageK {
             const int c = e * 256 + t, lr = c / 8, lk = (c % 8) * 8;
             uint4 o = r[e];
             if (FOLD && f.zc != nullptr) {
-                const u32x4_t x = z_chunk_to_r(u32x4_t{o.x, o.y, o.z, o.w}, zc[e], lo[e], true);
+                const u32x4_t x = z_chunk_to_r(u32x4_t{o.x, o.y, o.z, o.w}, zc[e], vm[e] != 0.f ? lo[e] : -1, true);
                 o = make_uint4(x[0], x[1], x[2], x[3]);
             }
             if (FOLD) {
@@ -1460,7 +1461,8 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& a, int id, uint16_t 
             const int i = m0 + r0 + 32 * e;
             if (i < a.N) {
                 zc_h[e] = z_row_c(a.row_lse, a.labels, i, a.V, a.ig);
-                zy_h[e] = a.labels[i];
+                bool bad = false;
+                zy_h[e] = label_valid(a.labels[i], a.V, a.ig, &bad) ? a.labels[i] : INT_MIN;
             }
         }
     }
@@ -1511,10 +1513,10 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& a, int id, uint16_t 
                     bool bad = false;
                     const bool valid = label_valid(st.lab[e], a.V, a.ig, &bad);
                     const int n = n0 + lc * 8;
-                    cb = z_chunk_to_r(cb, valid ? st.zl[e] * kLog2e : INFINITY, st.lab[e] - vcol(n), n < a.V);
+                    cb = z_chunk_to_r(cb, valid ? st.zl[e] * kLog2e : INFINITY, valid ? st.lab[e] - vcol(n) : -1, n < a.V);
                 } else {                 // R is operand A: row m0 + r, k chunk kt FK + 8 lc
                     const int k = st.kt * FK + lc * 8;
-                    ca = z_chunk_to_r(ca, zc_h[e], zy_h[e] - vcol(k), k < a.V);
+                    ca = z_chunk_to_r(ca, zc_h[e], zy_h[e] == INT_MIN ? -1 : zy_h[e] - vcol(k), k < a.V);
                 }
             }
             if constexpr (UA) {
