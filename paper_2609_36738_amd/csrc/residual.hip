@@ -1184,6 +1184,132 @@ __global__ __launch_bounds__(kFinThreads) void residual_finish_kernel(int nparts
 }
 
 // ---------------------------------------------------------------------------------------------
+// Small batches of short rows (one chunk for each of 16 lanes) in one workgroup and one launch: 16 lanes take a row, 64 rows
+// at a time, and the residuals wait in LDS for the column sums. Row sums over 16 lanes and column sums in the finish
+// kernel's order give the outputs the bits of the rows and finish kernels (but for the rounding of a label's own
+// product, which the compiler contracts or not). What bounds it is latency: for a 256 x 10
+// batch those two launches took 3.2 and 3.8 us and a gap between them, this one takes 6.6 us. (One wave per row, as there,
+// took 18 us on the one CU.)
+constexpr int kSmallRows = 256;
+constexpr int kSmallElems = 16384;   // residuals in LDS
+
+template <typename T, int VEC, bool UA>
+__global__ __launch_bounds__(kFinThreads) void residual_small_kernel(
+    const T* __restrict__ Z, int64_t ldz, int N, int V, const int32_t* __restrict__ labels, int32_t ignore_index,
+    float* __restrict__ row_lse, int32_t* __restrict__ row_argmax, float* __restrict__ row_target, T* __restrict__ R,
+    int64_t ldr, float* __restrict__ s, float* __restrict__ loss, int32_t* __restrict__ n_valid,
+    int32_t* __restrict__ flags) {
+    constexpr int GROUPS = kFinThreads / 16, PASSES = kSmallRows / GROUPS;
+    __shared__ float sh_p[kSmallElems];
+    __shared__ float sh_s[kFinWaves][16 * VEC];
+    __shared__ double sh_ce[kSmallRows];
+    __shared__ double sh_l[kFinWaves];
+    __shared__ int sh_c[kFinWaves], sh_f[kFinWaves];
+    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+    const int grp = threadIdx.x / 16, gl = threadIdx.x % 16, col = gl * VEC;
+    // rows grp + 64 q, q < PASSES: all loaded together; rows past N repeat row N - 1 and are neither stored nor added
+    float x[PASSES][VEC];
+    int y[PASSES];
+#pragma unroll
+    for (int q = 0; q < PASSES; ++q) {
+        const int i = min(grp + GROUPS * q, N - 1);
+        load_row_chunk<T, VEC, UA>(Z + (int64_t)i * ldz, col, V, x[q]);
+        y[q] = labels[i];
+    }
+    int cnt = 0, bad = 0;
+#pragma unroll
+    for (int q = 0; q < PASSES; ++q) {
+        if (GROUPS * q >= N) break;   // uniform
+        const int i = grp + GROUPS * q;
+        float m = -INFINITY;
+#pragma unroll
+        for (int k = 0; k < VEC; ++k) m = fmaxf(m, x[q][k]);
+        m = row16_max(m);
+        int am = INT_MAX;
+#pragma unroll
+        for (int k = VEC - 1; k >= 0; --k) am = x[q][k] == m ? col + k : am;
+        am = min(am, __builtin_amdgcn_update_dpp(0, am, 0xB1, 0xF, 0xF, false));
+        am = min(am, __builtin_amdgcn_update_dpp(0, am, 0x4E, 0xF, 0xF, false));
+        am = min(am, __builtin_amdgcn_update_dpp(0, am, 0x141, 0xF, 0xF, false));
+        am = min(am, __builtin_amdgcn_update_dpp(0, am, 0x140, 0xF, 0xF, false));
+        bool rbad = false;
+        const bool valid = label_valid(y[q], V, ignore_index, &rbad);
+        const int slot = valid && y[q] / VEC == gl ? y[q] % VEC : -1;
+        float zt = 0.f, l = 0.f;
+        const float m2 = m * kLog2e;
+#pragma unroll
+        for (int k = 0; k < VEC; ++k) {
+            zt = k == slot ? x[q][k] : zt;
+            x[q][k] = exp2_fast(fmaf(x[q][k], kLog2e, -m2));
+            l += x[q][k];
+        }
+        l = row16_sum(l);
+        const float inv_l = 1.0f / l;
+        float p[VEC];
+#pragma unroll
+        for (int k = 0; k < VEC; ++k) {
+            p[k] = x[q][k] * inv_l;
+            asm("" : "+v"(p[k]));   // rounded before the label's 1 is taken off, as in the rows kernel
+            if (k == slot) p[k] -= 1.0f;
+            if (!valid) p[k] = 0.f;
+        }
+        if (i >= N) continue;
+        const float lse = m + logf(l);
+        if (R != nullptr) store_row_chunk<T, VEC, UA>(R + (int64_t)i * ldr, col, V, p);
+#pragma unroll
+        for (int k = 0; k < VEC; ++k)
+            if (col + k < V) sh_p[i * V + col + k] = p[k];
+        if (gl == 0) {
+            row_lse[i] = lse;
+            if (row_argmax) row_argmax[i] = am;
+            cnt += valid ? 1 : 0;
+            bad |= rbad ? BOM_FLAG_LABEL_RANGE : 0;
+        }
+        if (valid ? slot >= 0 : gl == 0) {   // the label's owner
+            if (row_target) row_target[i] = zt;
+            sh_ce[i] = valid ? (double)lse - (double)zt : 0.0;
+        }
+    }
+    cnt = wave_sum(cnt);
+    bad = wave_or(bad);
+    if (lane == 0) {
+        sh_c[wave] = cnt;
+        sh_f[wave] = bad;
+    }
+    __syncthreads();
+    // wave w adds rows w, w + 16, ...; the wave sums are added in wave order
+    for (int j = lane; j < V; j += kWave) {
+        float a = 0.f;
+        for (int i = wave; i < N; i += kFinWaves) a += sh_p[i * V + j];
+        sh_s[wave][j] = a;
+    }
+    const double e = wave_sum((int)threadIdx.x < N ? sh_ce[threadIdx.x] : 0.0);
+    if (lane == 0) sh_l[wave] = e;
+    __syncthreads();
+    int nt = 0;
+#pragma unroll
+    for (int w = 0; w < kFinWaves; ++w) nt += sh_c[w];
+    if ((int)threadIdx.x < V) {
+        const float inv_nt = nt > 0 ? (float)(1.0 / (double)nt) : 0.f;
+        float sum = 0.f;
+#pragma unroll
+        for (int w = 0; w < kFinWaves; ++w) sum += sh_s[w][threadIdx.x];
+        s[threadIdx.x] = sum * inv_nt;
+    }
+    if (threadIdx.x == 0) {
+        int f = 0;
+        double el = 0.0;
+        for (int w = 0; w < kFinWaves; ++w) {
+            f |= sh_f[w];
+            el += sh_l[w];
+        }
+        *n_valid = nt;
+        *flags = f | (nt == 0 ? BOM_FLAG_EMPTY : 0);
+        *loss = nt > 0 ? (float)(el / (double)nt) : 0.f;
+    }
+}
+
+// ---------------------------------------------------------------------------------------------
 template <int THREADS, int NCH, bool UA>
 hipError_t launch_rows_lds(const uint16_t* Z, int64_t ldz, int N, int V, const int32_t* labels, int32_t ignore_index,
                            float* row_lse, int32_t* row_argmax, float* row_target, uint16_t* R, int64_t ldr, Partials ws,
@@ -1418,6 +1544,11 @@ hipError_t run_residual(const T* Z, int N, int V, int64_t ldz, const int32_t* la
     if constexpr (std::is_same<T, uint16_t>::value && VEC == 8 && !UA) split = plan_split(V, &S, &W, &nch);
     // (a plan override may ask for several register chunks per thread, which UA rows do not have)
     const bool single = plan_single(V, VEC, &threads, &nch) && !(UA && threads > 0 && (threads > 512 || nch > 1));
+    if (single && threads == 64 && V <= 16 * VEC && N <= kSmallRows && N * V <= kSmallElems) {
+        hipLaunchKernelGGL((residual_small_kernel<T, VEC, UA>), dim3(1), dim3(kFinThreads), 0, st, Z, ldz, N, V, labels, ig,
+                           lse, am, tg, R, ldr, s, loss, n_valid, flags);
+        return hipGetLastError();
+    }
     if (single) {
         e = dispatch_rows<T, VEC, UA>(nch, threads, Z, ldz, N, V, labels, ig, lse, am, tg, R, ldr, ws, &nwg, st);
         nparts = nwg;

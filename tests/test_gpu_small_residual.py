@@ -1,0 +1,47 @@
+"""The one-workgroup residual of small batches of short rows, at the ends of its range and one step past them."""
+import pytest
+import torch
+
+from paper_2609_36738_amd import bom
+from tests.gpu_util import dev, log
+
+pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not torch.cuda.is_available(), reason="needs an MI355X")]
+
+
+@pytest.mark.parametrize("N", [1, 63, 65, 256, 257])
+@pytest.mark.parametrize("V,dtype", [(2, "f32"), (10, "f32"), (16, "f32"), (17, "f32"), (64, "f32"), (3, "bf16"),
+                                     (8, "bf16"), (63, "bf16"), (64, "bf16"), (127, "bf16"), (128, "bf16")])
+def test_small_residual(N, V, dtype):
+    log(f"[small residual] N={N} V={V} {dtype}")
+    g = torch.Generator(device=dev()).manual_seed(N + V)
+    Z = (torch.randn((N, V), generator=g, device=dev()) * 2).to(torch.float32 if dtype == "f32" else torch.bfloat16)
+    y = torch.randint(0, V, (N,), generator=g, device=dev(), dtype=torch.int32)
+    if N > 3:
+        y[1::5] = -100
+        y[2] = -7
+    ok = (y >= 0) & (y < V)
+    R = torch.full((N, V + 1), 7.0, dtype=Z.dtype, device=dev())
+    out = bom.bom_residual(Z, y, R=R[:, :V])
+    p = torch.softmax(Z.double(), 1)
+    p[torch.arange(N, device=dev())[ok], y[ok].long()] -= 1
+    p *= ok[:, None]
+    n = int(ok.sum())
+    lse = torch.logsumexp(Z.double(), 1)
+    zf = Z.float()
+    first = (zf == zf.max(1, keepdim=True).values).int().argmax(1)
+    tgt = torch.where(ok, zf.gather(1, y.clamp(0, V - 1).long()[:, None])[:, 0], torch.zeros(N, device=dev()))
+    assert out["n_valid"].item() == n and out["flags"].item() == (bom.BOM_FLAG_LABEL_RANGE if N > 3 else 0)
+    assert torch.equal(out["row_argmax"].long(), first) and torch.equal(out["row_target"], tgt)
+    assert float((out["row_lse"] - lse).abs().max()) <= 2e-6            # fp32 of values below 16
+    step = 2.0 ** -8 if dtype == "bf16" else 2.0 ** -21                 # one rounding; fp32: a few of exp and 1 / sum
+    assert bool(((R[:, :V].double() - p).abs() <= p.abs() * step + 2e-7).all()) and (R[:, V] == 7.0).all()
+    assert float((out["s"] - p.sum(0) / n).abs().max()) <= 3e-7         # means of values below 1
+    ce = float(((lse - tgt) * ok).sum() / n)
+    assert abs(float(out["loss"]) - ce) <= 1e-6 * max(1.0, ce)
+
+
+def test_small_residual_all_ignored():
+    Z = torch.randn((70, 9), device=dev())
+    out = bom.bom_residual(Z, torch.full((70,), -100, dtype=torch.int32, device=dev()))
+    assert out["flags"].item() == bom.BOM_FLAG_EMPTY and out["n_valid"].item() == 0 and out["loss"].item() == 0
+    assert (out["s"] == 0).all() and (out["R"] == 0).all() and (out["row_target"] == 0).all()
