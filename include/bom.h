@@ -329,7 +329,7 @@ bom_status bom_head_telemetry(const void* H, int64_t ldh, bom_dtype h_dt, const 
  * bom_head_forward -- support call (row a0 of the path; the forward is common work, not one of the
  * four steps): the linear head's logits Z = H W (+ b), fp32 accumulation, Z rounded once to dt.
  * dt = BOM_BF16 (the language-model and vision workloads' logits, as bf16 autocast computes them) runs
- * on the matrix cores (256 x 256 tiles) when d is a multiple of 8, V is at least 8 and H is 16-byte aligned with a
+ * on the matrix cores (256 x 256 tiles, 64 x 64 for small products) when d is a multiple of 8, V is at least 8 and H is 16-byte aligned with a
  * leading dimension that is a multiple of 8 (V, W and its leading dimension are free), and on a SIMT kernel otherwise; dt = BOM_F32
  * (the tiny classifier) runs on the SIMT kernel.
  *   H device [N, ldh], W device [d, ldw], b device [V] or NULL, Z device [N, ldz], all of dt.

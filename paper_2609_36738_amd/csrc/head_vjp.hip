@@ -677,7 +677,8 @@ struct TileRange {
     int inner_count, outer_begin, outer_end, splits;
     int pm0, pn0;
     int64_t ldp, pstride;
-    int blocked;   // 1: an XCD's 32 concurrent tiles are 4 outer x 8 inner (needs splits = 1, inner_count % 8 = 0)
+    int blocked;   // 1: an XCD's 32 concurrent tiles are 4 outer x 8 inner (needs splits = 1, inner_count % 8 = 0);
+                   // 2: tiles in order, inner ones fastest, whatever their XCD (needs splits = 1)
 };
 
 // Work unit of this workgroup. The pairs (outer tile, k split) are dealt to the 8 XCDs round-robin
@@ -691,6 +692,13 @@ struct TileRange {
 // inner tiles 8 at a time.
 __device__ __forceinline__ bool unit_of(const TileRange& r, bool inner_is_m, int id, int* tm, int* tn, int* z) {
     const int xcd = id % 8, rest = id / 8;
+    if (r.blocked == 2) {
+        const int inner = id % r.inner_count, outer = r.outer_begin + id / r.inner_count;
+        *z = 0;
+        *tm = inner_is_m ? inner : outer;
+        *tn = inner_is_m ? outer : inner;
+        return outer < r.outer_end;
+    }
     if (r.blocked) {
         constexpr int GO = 4, GI = 8;
         const int I = r.inner_count;
@@ -1392,6 +1400,8 @@ struct FusedArgs {
     float* db;
     int tw_n, tw, th_n;   // dW tiles along V, dW tile count, dH tiles along d
     const float* row_lse; // logits input: R is formed from Z (the R argument) and lse; null: R is stored
+    const uint16_t* bias; // forward: Z = H W (+ bias)
+    uint16_t* Z; int64_t ldz;
 };
 
 // element offset of (row, col) in a 64 x 64 bf16 LDS tile whose 16-byte chunks are swizzled by row
@@ -1399,15 +1409,16 @@ __device__ __forceinline__ int ftile_off(int row, int col) { return row * FB + (
 
 // UA: R (or Z) and W at any 2-byte alignment and V of any size from eight: a chunk across the last column is read
 // from the row's last eight columns and shifted to its place on the way to LDS.
-template <bool is_dw, bool UA>
+template <int MODE, bool UA>
 __device__ __forceinline__ void fused_tile(const FusedArgs& a, int id, uint16_t (&sa)[2][FK * FB],
                                            uint16_t (&sb)[2][FK * FB], float (&red)[FB][33], float (&vec)[FB]) {
     const int t = threadIdx.x, l = t % kWave;
     const int wave = __builtin_amdgcn_readfirstlane(t / kWave);
     const int wm = wave / 2, wn = wave % 2;
-    const int m0 = (id / (is_dw ? a.tw_n : a.th_n)) * FB, n0 = (id % (is_dw ? a.tw_n : a.th_n)) * FB;
-    const int M = is_dw ? a.d : a.N, Nn = is_dw ? a.V : a.d, K = is_dw ? a.N : a.V;
-    const int nt = *a.n_valid;
+    constexpr bool is_dw = MODE == kWideDW, fwd = MODE == kWideFWD;
+    const int m0 = (id / (MODE != kWideDH ? a.tw_n : a.th_n)) * FB, n0 = (id % (MODE != kWideDH ? a.tw_n : a.th_n)) * FB;
+    const int M = is_dw ? a.d : a.N, Nn = MODE != kWideDH ? a.V : a.d, K = is_dw ? a.N : fwd ? a.d : a.V;
+    const int nt = fwd ? 0 : *a.n_valid;
     const float alpha = nt > 0 ? (float)((1.0 - (double)a.lambda) / (double)nt) : 0.f;
     const double cscale = nt > 0 ? (double)a.lambda / (double)nt : 0.0;
     const int nk = ((K + FK - 1) / FK + FSETS - 1) / FSETS * FSETS;   // tiles past K hold zeros
@@ -1416,13 +1427,13 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& a, int id, uint16_t 
     // 16-byte chunk lc = t % 8 of that row
     const int lc = t % 8;
     const int r0 = t / 8;
-    // operand A: dW -> H rows k, columns m0 + 8 lc; dH -> R rows m0 + r, k chunk 8 lc
-    // operand B: dW -> R rows k, columns n0 + 8 lc; dH -> W rows n0 + r, k chunk 8 lc
-    const uint16_t* pa = is_dw ? a.H : a.R;
+    // operand A: dW -> H rows k, columns m0 + 8 lc; dH, forward -> rows m0 + r of R or H, k chunk 8 lc
+    // operand B: dW, forward -> rows k of R or W, columns n0 + 8 lc; dH -> W rows n0 + r, k chunk 8 lc
+    const uint16_t* pa = MODE != kWideDH ? a.H : a.R;
     const uint16_t* pb = is_dw ? a.R : a.W;
-    const int64_t lda = is_dw ? a.ldh : a.ldr, ldb = is_dw ? a.ldr : a.ldw;
-    const int rows_a = is_dw ? a.N : a.N, rows_b = is_dw ? a.N : a.d;
-    const auto da = make_desc(pa, (int)(((int64_t)(rows_a - 1) * lda + (is_dw ? a.d : a.V)) * 2));
+    const int64_t lda = MODE != kWideDH ? a.ldh : a.ldr, ldb = is_dw ? a.ldr : a.ldw;
+    const int rows_b = is_dw ? a.N : a.d;
+    const auto da = make_desc(pa, (int)(((int64_t)(a.N - 1) * lda + (MODE != kWideDH ? a.d : a.V)) * 2));
     const auto db_ = make_desc(pb, (int)(((int64_t)(rows_b - 1) * ldb + a.V) * 2));
     auto vcol = [&](int c) { return UA && c + 8 > a.V ? a.V - 8 : c; };   // where the chunk at column c < V is read
     auto off_a = [&](int k0, int e) {
@@ -1432,13 +1443,13 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& a, int id, uint16_t 
             return (k < a.N && m < a.d) ? (int)(((int64_t)k * lda + m) * 2) : kOob;
         }
         const int i = m0 + r, k = k0 + lc * 8;
-        return (i < a.N && k < a.V) ? (int)(((int64_t)i * lda + vcol(k)) * 2) : kOob;
+        return (i < a.N && k < K) ? (int)(((int64_t)i * lda + (fwd ? k : vcol(k))) * 2) : kOob;
     };
     auto off_b = [&](int k0, int e) {
         const int r = r0 + 32 * e;
-        if constexpr (is_dw) {
+        if constexpr (MODE != kWideDH) {
             const int k = k0 + r, n = n0 + lc * 8;
-            return (k < a.N && n < a.V) ? (int)(((int64_t)k * ldb + vcol(n)) * 2) : kOob;
+            return (k < K && n < a.V) ? (int)(((int64_t)k * ldb + vcol(n)) * 2) : kOob;
         }
         const int j = n0 + r, k = k0 + lc * 8;
         return (j < a.d && k < a.V) ? (int)(((int64_t)j * ldb + vcol(k)) * 2) : kOob;
@@ -1455,7 +1466,7 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& a, int id, uint16_t 
     // dH with logits input: c and label of this thread's two R rows (fixed over k)
     float zc_h[2] = {INFINITY, INFINITY};
     int zy_h[2] = {-1, -1};
-    if (!is_dw && zin) {
+    if (MODE == kWideDH && zin) {
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
             const int i = m0 + r0 + 32 * e;
@@ -1482,7 +1493,7 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& a, int id, uint16_t 
                 if (zin) st.zl[e] = a.row_lse[k < a.N ? k : a.N - 1];
                 if (k >= a.N) st.lab[e] = a.ig;
             }
-        } else {
+        } else if constexpr (!fwd) {
             const int k = k0 + lc * 8;
             if constexpr (UA) {   // past V: any finite word, W is zero there
                 const int ks = min(k, a.V - 1), last = a.V - 1 - ks;
@@ -1514,16 +1525,16 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& a, int id, uint16_t 
                     const bool valid = label_valid(st.lab[e], a.V, a.ig, &bad);
                     const int n = n0 + lc * 8;
                     cb = z_chunk_to_r(cb, valid ? st.zl[e] * kLog2e : INFINITY, valid ? st.lab[e] - vcol(n) : -1, n < a.V);
-                } else {                 // R is operand A: row m0 + r, k chunk kt FK + 8 lc
+                } else if constexpr (!fwd) {   // R is operand A: row m0 + r, k chunk kt FK + 8 lc
                     const int k = st.kt * FK + lc * 8;
                     ca = z_chunk_to_r(ca, zc_h[e], zy_h[e] == INT_MIN ? -1 : zy_h[e] - vcol(k), k < a.V);
                 }
             }
             if constexpr (UA) {
-                const int c0 = is_dw ? n0 + lc * 8 : st.kt * FK + lc * 8;
+                const int c0 = MODE != kWideDH ? n0 + lc * 8 : st.kt * FK + lc * 8;
                 const int sh = c0 < a.V ? c0 - vcol(c0) : 0;
                 cb = chunk_shr(cb, sh);
-                if constexpr (!is_dw) ca = chunk_shr(ca, sh);
+                if constexpr (MODE == kWideDH) ca = chunk_shr(ca, sh);
             }
             *reinterpret_cast<u32x4_t*>(&sa[buf][o]) = ca;
             *reinterpret_cast<u32x4_t*>(&sb[buf][o]) = cb;
@@ -1539,7 +1550,7 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& a, int id, uint16_t 
                     part[2 * p + 1] = fmaf(vm, bf16_hi(st.c[e][p]), part[2 * p + 1]);
                 }
             }
-        } else {
+        } else if constexpr (!fwd) {
             const float q8[8] = {st.q[0].x, st.q[0].y, st.q[0].z, st.q[0].w, st.q[1].x, st.q[1].y, st.q[1].z, st.q[1].w};
 #pragma unroll
             for (int e = 0; e < 2; ++e) {
@@ -1558,23 +1569,24 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& a, int id, uint16_t 
             }
         }
     };
-    // fragments of MFMA step s (k = 16 s .. 16 s + 15) of the tile in buffer buf
+    // fragments of MFMA step s (k = 16 s .. 16 s + 15) of the tile in buffer buf: transposing reads of a k-outer
+    // operand, 16-byte reads of a k-contiguous one
+    auto frag_tr = [&](const uint16_t* t, int s, int base) {
+        const int g = l / 16, sl = l % 16;
+        const int kr = 16 * s + (g / 2) * 8 + sl / 4, c = base + (g % 2) * 16 + (sl % 4) * 4;
+        const v4s_t x0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s_t*)&t[ftile_off(kr, c)]);
+        const v4s_t x1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s_t*)&t[ftile_off(kr + 4, c)]);
+        return __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(x0, x1, 0, 1, 2, 3, 4, 5, 6, 7));
+    };
+    auto frag_kc = [&](const uint16_t* t, int s, int base) {
+        const int r = base + l % 32, c = 2 * s + l / 32;
+        return *reinterpret_cast<const bf16x8_t*>(&t[r * FB + ((c ^ (r & 7)) << 3)]);
+    };
     auto read_frags = [&](int buf, int s, bf16x8_t& fa, bf16x8_t& fb) {
-        if constexpr (is_dw) {
-            const int g = l / 16, sl = l % 16;
-            const int kr = 16 * s + (g / 2) * 8 + sl / 4;
-            const int ca = wm * 32 + (g % 2) * 16 + (sl % 4) * 4, cb = wn * 32 + (g % 2) * 16 + (sl % 4) * 4;
-            const v4s_t a0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s_t*)&sa[buf][ftile_off(kr, ca)]);
-            const v4s_t a1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s_t*)&sa[buf][ftile_off(kr + 4, ca)]);
-            const v4s_t b0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s_t*)&sb[buf][ftile_off(kr, cb)]);
-            const v4s_t b1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s_t*)&sb[buf][ftile_off(kr + 4, cb)]);
-            fa = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(a0, a1, 0, 1, 2, 3, 4, 5, 6, 7));
-            fb = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(b0, b1, 0, 1, 2, 3, 4, 5, 6, 7));
-        } else {
-            const int ra = wm * 32 + l % 32, rb = wn * 32 + l % 32, c = 2 * s + l / 32;
-            fa = *reinterpret_cast<const bf16x8_t*>(&sa[buf][ra * FB + ((c ^ (ra & 7)) << 3)]);
-            fb = *reinterpret_cast<const bf16x8_t*>(&sb[buf][rb * FB + ((c ^ (rb & 7)) << 3)]);
-        }
+        if constexpr (is_dw) fa = frag_tr(sa[buf], s, wm * 32);
+        else fa = frag_kc(sa[buf], s, wm * 32);
+        if constexpr (MODE != kWideDH) fb = frag_tr(sb[buf], s, wn * 32);
+        else fb = frag_kc(sb[buf], s, wn * 32);
     };
 
     f32x16_t acc;
@@ -1605,6 +1617,17 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& a, int id, uint16_t 
         }
     }
 
+    if constexpr (fwd) {   // accumulator layout as below
+        const int n = n0 + wn * 32 + l % 32;
+        if (n >= Nn) return;
+        const float bn = a.bias ? bf16_to_f32(a.bias[n]) : 0.f;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int m = m0 + wm * 32 + (r / 4) * 8 + (l / 32) * 4 + r % 4;
+            if (m < M) stf<uint16_t>(a.Z, (int64_t)m * a.ldz + n, a.bias ? acc[r] + bn : acc[r]);
+        }
+        return;
+    }
     // rank-1 vectors of the tile: dW -> hsum over its 64 columns, dH -> u over its 64 rows of W
     if (is_dw) {
 #pragma unroll
@@ -1655,8 +1678,18 @@ __global__ __launch_bounds__(256, 2) void vjp_fused_small_kernel(FusedArgs a) {
     __shared__ __attribute__((aligned(16))) uint16_t sb[2][FK * FB];
     __shared__ float red[FB][33];
     __shared__ float vec[FB];
-    if ((int)blockIdx.x < a.tw) fused_tile<true, UA>(a, (int)blockIdx.x, sa, sb, red, vec);
-    else fused_tile<false, UA>(a, (int)blockIdx.x - a.tw, sa, sb, red, vec);
+    if ((int)blockIdx.x < a.tw) fused_tile<kWideDW, UA>(a, (int)blockIdx.x, sa, sb, red, vec);
+    else fused_tile<kWideDH, UA>(a, (int)blockIdx.x - a.tw, sa, sb, red, vec);
+}
+
+// The forward of small heads on the same 64 x 64 tiles.
+template <bool UA>
+__global__ __launch_bounds__(256, 2) void forward_small_kernel(FusedArgs a) {
+    __shared__ __attribute__((aligned(16))) uint16_t sa[2][FK * FB];
+    __shared__ __attribute__((aligned(16))) uint16_t sb[2][FK * FB];
+    __shared__ float red[FB][33];
+    __shared__ float vec[FB];
+    fused_tile<kWideFWD, UA>(a, (int)blockIdx.x, sa, sb, red, vec);
 }
 
 constexpr int kCUs = 256;        // MI355X compute units
@@ -2248,7 +2281,7 @@ hipError_t launch_head_vjp_f32(const HeadVjpArgs& a, hipStream_t st) {
     const PlanOverride& ov = plan_override();
     if (a.dt == BOM_BF16 && p.w.kind == kMfma128 && (!a.dH || p.h.kind == kMfma128) && fits31 &&
         fused_extents(a.N, a.V) && (ua || (ov.kw != 1 && ov.kh != 1))) {
-        FusedArgs fa;
+        FusedArgs fa{};
         fa.H = static_cast<const uint16_t*>(a.H);
         fa.ldh = a.ldh;
         fa.W = static_cast<const uint16_t*>(a.W);
@@ -2395,6 +2428,21 @@ __global__ __launch_bounds__(256) void head_forward_simt_kernel(const uint16_t* 
 }
 }  // namespace
 
+namespace {
+// Whether the 64 x 64 tiles of the small forward beat the 256 x 256 ones. Microseconds, from both kernels over N = 64 .. 16384,
+// V = 512 .. 32000, d = 64 .. 4096: a CU takes a 64-deep step of a small tile (two resident) in 0.34 (rows at any
+// alignment 0.48), a tile alone 0.3, in groups of four steps; a round of large tiles takes 8 beside its steps, of 1.25 with
+// few tiles to 1.85 with a full chip (times 1.2 at any alignment). At d = 768 (small, large): 512 x 1000 7.1 and 24.1 us,
+// 4096 x 1000 19.2 and 26.4, 8192 x 1000 34.3 and 32.1, 256 x 32000 38.5 and 26.5; 2048 x 2048 x 4096 66 and 84.
+bool forward_small(int64_t N, int64_t d, int64_t V, bool ua) {
+    const int64_t tiles = cdiv(N, FB) * cdiv(V, FB), T = cdiv(N, LB) * cdiv(V, LB), nk = cdiv(d, FK);
+    const double n4 = (double)(cdiv(nk, FSETS) * FSETS);
+    const double small = 3.0 + std::max((double)tiles * n4 / kCUs * (ua ? 0.48 : 0.34), n4 * 0.3);
+    const double large = (double)cdiv(T, kCUs) * (8.0 + (double)nk * (1.25 + 0.6 * std::min(1.0, (double)T / kCUs)));
+    return small < large * (ua ? 1.2 : 1.0);
+}
+}  // namespace
+
 hipError_t launch_head_forward(const void* H, int64_t ldh, const void* W, int64_t ldw, const void* b, bom_dtype dt,
                                int N, int d, int V, void* Z, int64_t ldz, hipStream_t st) {
     if (dt == BOM_F32)
@@ -2408,11 +2456,33 @@ hipError_t launch_head_forward(const void* H, int64_t ldh, const void* W, int64_
     const bool ua = !(V % 8 == 0 && al(W, ldw));
     if (mfma_extents(d, V, ua) && al(H, ldh) &&
         ((int64_t)(N - 1) * ldh + d) * 2 < (1LL << 31) && ((int64_t)(d - 1) * ldw + V) * 2 < (1LL << 31)) {
+        if (forward_small(N, d, V, ua) && ldw < (1 << 22)) {
+            FusedArgs fa{};
+            fa.H = H16;
+            fa.ldh = ldh;
+            fa.W = W16;
+            fa.ldw = ldw;
+            fa.N = N;
+            fa.d = d;
+            fa.V = V;
+            fa.bias = b16;
+            fa.Z = static_cast<uint16_t*>(Z);
+            fa.ldz = ldz;
+            fa.tw_n = (int)cdiv(V, FB);
+            const dim3 grid((unsigned)(cdiv(N, FB) * fa.tw_n));
+            if (ua)
+                hipLaunchKernelGGL(forward_small_kernel<true>, grid, dim3(256), 0, st, fa);
+            else
+                hipLaunchKernelGGL(forward_small_kernel<false>, grid, dim3(256), 0, st, fa);
+            return hipGetLastError();
+        }
         const int MT = (int)cdiv(N, LB), NT = (int)cdiv(V, LB);
-        const TileRange tr{MT, 0, NT, 1, 0, 0, 0, 0, xcd_blocked(MT)};
+        // few column tiles: dealt to the XCDs whole they would leave some idle, so the tiles go round one by one
+        const bool flat = cdiv(NT, 8) * MT > 32 * cdiv((int64_t)MT * NT, kCUs);
+        const TileRange tr{MT, 0, NT, 1, 0, 0, 0, 0, flat ? 2 : xcd_blocked(MT)};
         const WideArgs wa{H16, ldh, W16, ldw, N, V, d, (int)(cdiv(d, WKT) * WKT), tr, nullptr, nullptr, nullptr, Z, ldz,
                           0.f, nullptr, b16};
-        const dim3 grid((unsigned)(cdiv(NT, 8) * 8 * MT));
+        const dim3 grid((unsigned)(flat ? (int64_t)NT * MT : cdiv(NT, 8) * 8 * MT));
         if (ua)
             hipLaunchKernelGGL((lds256w_fwd_kernel<uint16_t, 8, false, true>), grid, dim3(512), 0, st, wa);
         else if (wave_cfg().fwd == 8)

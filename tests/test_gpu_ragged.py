@@ -73,8 +73,11 @@ def test_head_vjp_any_alignment(case):
     assert float((out["db"] - ref).abs().max()) <= 1e-6
 
 
-@pytest.mark.parametrize("N,d,V,pad,off", [(33, 40, 9, 0, 0), (1, 64, 8, 1, 0), (300, 264, 8201, 0, 1),
-                                            (257, 520, 12289, 3, 0), (1031, 768, 32003, 0, 0)])
+# 64 x 64 tiles (k in one to nine steps, both operands ragged), 256 x 256 tiles, and those dealt tile by tile (the last two:
+# fewer than eight column tiles under more than 32 row tiles)
+@pytest.mark.parametrize("N,d,V,pad,off", [(33, 40, 9, 0, 0), (1, 64, 8, 1, 0), (65, 520, 130, 0, 3), (200, 328, 1000, 0, 0),
+                                            (300, 264, 8201, 0, 1), (257, 520, 12289, 3, 0), (1031, 768, 32003, 0, 0),
+                                            (16384, 512, 1000, 0, 0), (9000, 520, 1027, 0, 0)])
 def test_head_forward_any_alignment(N, d, V, pad, off):
     log(f"[ragged forward] N={N} d={d} V={V} pad={pad} offset={off}")
     g = torch.Generator(device=dev()).manual_seed(6)
