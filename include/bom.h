@@ -342,12 +342,6 @@ bom_status bom_head_forward(const void* H, int64_t ldh, const void* W, int64_t l
  * bom_head_forward_residual -- the head forward and bom_residual in one call (appendix "First-order cost
  * accounting": the output-side work over N_out = N V coordinates is where BOM's bookkeeping sits).
  * Computes Z = H W (+ b) as bom_head_forward does and then every output of bom_residual on that Z.
- * For bf16 on the matrix cores (d and V multiples of 8, 16-byte aligned H, W, Z and R with leading
- * dimensions that are multiples of 8) the forward's epilogue also reduces each 256-column tile of every
- * row of the rounded logits (maximum, first column reaching it, sum of exp(z - max)) and records the
- * target logit, so the residual only merges those records per row and re-reads Z once for R and the
- * column sums: no row is split across workgroups and no row statistics pass is made over Z. Other shapes
- * and fp32 run the forward, then bom_residual.
  *
  *   H, ldh, W, ldw, b, dt, N, d, V, Z, ldz: as bom_head_forward (Z is written).
  *   labels, ignore_index, s, row_lse, row_argmax (nullable), row_target (required here), R (nullable), ldr,

@@ -401,8 +401,7 @@ bom_status bom_adamw_update(float* theta, float* m, float* v, float* v_col, cons
 
 size_t bom_head_forward_residual_workspace_bytes(int64_t N, int64_t V, bom_dtype dt) {
     if (N < 1 || V < 2 || N >= kMaxDim || V >= kMaxDim || !is_dtype(dt)) return 0;
-    const size_t a = bom::residual_from_stats_workspace_bytes(N, V), b = bom::residual_workspace_bytes(N, V, dt);
-    return a > b ? a : b;
+    return bom::residual_workspace_bytes(N, V, dt);
 }
 
 bom_status bom_head_forward_residual(const void* H, int64_t ldh, const void* W, int64_t ldw, const void* b, bom_dtype dt,
@@ -429,18 +428,10 @@ bom_status bom_head_forward_residual(const void* H, int64_t ldh, const void* W, 
         overlap(Z, zb, W, (size_t)((d - 1) * ldw + V) * esz))
         return fail(BOM_ERR_ALIAS, "bom_head_forward_residual: Z must not overlap H, W or R");
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const bool r_ok = R == nullptr || (reinterpret_cast<uintptr_t>(R) % 16 == 0 && ldr % 8 == 0);
-    if (dt == BOM_BF16 && r_ok && bom::head_forward_stats_supported(H, ldh, W, ldw, Z, ldz, (int)N, (int)d, (int)V)) {
-        hipError_t e = bom::launch_head_forward_stats(H, ldh, W, ldw, b, (int)N, (int)d, (int)V, Z, ldz, labels,
-                                                      ignore_index, static_cast<float*>(workspace), row_target, st);
-        if (e != hipSuccess) return hip_status(e, "bom_head_forward_residual (forward)");
-        return hip_status(bom::launch_residual_from_stats(static_cast<const uint16_t*>(Z), ldz, (int)N, (int)V, labels,
-                                                          ignore_index, s, row_lse, row_argmax, row_target,
-                                                          static_cast<uint16_t*>(R), ldr, loss, n_valid, flags,
-                                                          workspace, st),
-                          "bom_head_forward_residual (residual)");
-    }
-    // other shapes and fp32: the forward, then the residual on its logits
+    // The forward, then the residual on its logits. (Row statistics of each 256-column tile in the forward's epilogue and a
+    // residual from them, built and measured, lost at every shape: the epilogue's work while its CU issues no matrix
+    // instructions cost more than the residual, which reads Z once either way, could save: 482 against 377 us at
+    // N = 4096, d = 768, V = 32,000, 17.2 against 16.4 ms at N = 16384, d = 4096, V = 128,256.)
     hipError_t e = bom::launch_head_forward(H, ldh, W, ldw, b, dt, (int)N, (int)d, (int)V, Z, ldz, st);
     if (e != hipSuccess) return hip_status(e, "bom_head_forward_residual (forward)");
     return hip_status(bom::launch_residual(Z, dt, (int)N, (int)V, ldz, labels, ignore_index, s, row_lse, row_argmax,
