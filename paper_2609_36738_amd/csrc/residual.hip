@@ -3,8 +3,8 @@
 // token-level appendix for ignored targets).
 //
 // Three paths, all deterministic (fixed reduction orders, no floating-point atomics):
-//  * single pass (V up to ~53k bf16 / ~26k fp32): one persistent workgroup per CU keeps a whole
-//    row in registers or LDS, reduces max / argmax / sum across the workgroup, writes R, and
+//  * single pass (V up to ~53k bf16 / ~26k fp32): one wave per row for narrow rows, a workgroup for a small batch of them,
+//    otherwise one persistent workgroup per CU that keeps a whole row in registers or LDS, reduces max / argmax / sum across the workgroup, writes R, and
 //    accumulates its rows' residuals per column in registers; Z is read from HBM exactly once.
 //  * split rows (bf16 up to 524,288 columns): several workgroups share each row and exchange their
 //    per-part statistics; Z is still read once.
@@ -16,6 +16,7 @@
 #include <cmath>
 #include <cstdlib>
 #include <mutex>
+#include <algorithm>
 #include <type_traits>
 
 #include "common.hpp"
@@ -1184,6 +1185,201 @@ __global__ __launch_bounds__(kFinThreads) void residual_finish_kernel(int nparts
 }
 
 // ---------------------------------------------------------------------------------------------
+// Single pass, narrow rows: one wave per row, several waves per workgroup, no barrier in the row loop. Lane `lane` owns columns
+// (c * 64 + lane) * VEC + k, c < NCH, k < VEC; the next row's chunks are loaded before a row's reductions. The waves'
+// column sums are added in wave order at the end, into the workgroup's partial row. What bounds it: HBM, once every CU
+// holds several rows; before, the 64 to 512 threads of a workgroup took one row at a time, one workgroup per CU, and its
+// three barriers and reductions left the memory idle.
+template <typename T, int VEC>
+struct RawChunk {
+    typedef f32x4 type;
+};
+template <>
+struct RawChunk<uint16_t, 8> {
+    typedef u32x4_t type;
+};
+template <>
+struct RawChunk<float, 1> {
+    typedef float type;
+};
+template <>
+struct RawChunk<uint16_t, 1> {
+    typedef uint16_t type;
+};
+// waves per workgroup at most: the register file holds 16 waves of up to 128 registers, or eight of up to 256
+template <int VPT>
+constexpr int kWaveRowsMax = VPT > 32 ? 8 : 16;
+
+template <typename T, int VEC, int NCH, bool UA>
+__global__ __launch_bounds__(kWaveRowsMax<NCH * VEC> * kWave) void residual_wave_rows_kernel(
+    const T* __restrict__ Z, int64_t ldz, int N, int V, const int32_t* __restrict__ labels, int32_t ignore_index,
+    float* __restrict__ row_lse, int32_t* __restrict__ row_argmax, float* __restrict__ row_target, T* __restrict__ R,
+    int64_t ldr, Partials ws) {
+    typedef typename RawChunk<T, VEC>::type raw_t;
+    constexpr int VPT = NCH * VEC, MAXW = kWaveRowsMax<VPT>;
+    __shared__ float sh_s[kWave * VPT];
+    __shared__ double sh_ce[MAXW];
+    __shared__ int sh_c[MAXW], sh_f[MAXW];
+    const int lane = threadIdx.x % kWave, waves = blockDim.x / kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int stride = gridDim.x * waves;
+    float acc[VPT];
+#pragma unroll
+    for (int k = 0; k < VPT; ++k) acc[k] = 0.f;
+    int cnt = 0;
+    bool bad = false;
+    double ce = 0.0;
+    // the chunk of columns col .. of row i, from inside the row; unpacked with the columns past V as -inf
+    auto load = [&](int i, int c) {
+        const T* zr = Z + (int64_t)i * ldz;
+        const int col = (c * kWave + lane) * VEC;
+        if constexpr (UA) {
+            return (raw_t) * reinterpret_cast<const u32x4_any_t*>(zr + min(col, V - 8));
+        } else {
+            return *reinterpret_cast<const raw_t*>(zr + (col < V ? col : V - VEC));
+        }
+    };
+    auto unpack = [&](raw_t w, int c, float* x) {
+        const int col = (c * kWave + lane) * VEC;
+        const bool edge = (c + 1) * kWave * VEC > V;   // uniform
+        if constexpr (std::is_same<raw_t, u32x4_t>::value) {
+            if (edge) {
+                if constexpr (UA) {
+                    const int sh = col - min(col, V - 8);
+                    if (sh > 0) w = pad_inf_from(chunk_shr(w, min(sh, 7)), V - col);
+                } else {
+                    if (col >= V) w = u32x4_t{0xFF80FF80u, 0xFF80FF80u, 0xFF80FF80u, 0xFF80FF80u};
+                }
+            }
+#pragma unroll
+            for (int p = 0; p < 4; ++p) {
+                x[2 * p] = bf16_lo(w[p]);
+                x[2 * p + 1] = bf16_hi(w[p]);
+            }
+        } else {
+#pragma unroll
+            for (int k = 0; k < VEC; ++k) {
+                float v;
+                if constexpr (VEC > 1) v = w[k];
+                else if constexpr (std::is_same<T, uint16_t>::value) v = bf16_to_f32(w);
+                else v = w;
+                x[k] = edge && col >= V ? -INFINITY : v;
+            }
+        }
+    };
+    int i = blockIdx.x * waves + wave;
+    raw_t nxt[NCH];
+    int y_nxt = 0;
+    if (i < N) {
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) nxt[c] = load(i, c);
+        y_nxt = labels[i];
+    }
+    for (; i < N; i += stride) {
+        float x[VPT];
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) unpack(nxt[c], c, &x[c * VEC]);
+        const int y = __builtin_amdgcn_readfirstlane(y_nxt);
+        const int in = min(i + stride, N - 1);   // past the last row: a row that is there, not used
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) nxt[c] = load(in, c);
+        y_nxt = labels[in];
+        float m = -INFINITY;
+#pragma unroll
+        for (int k = 0; k < VPT; ++k) m = fmaxf(m, x[k]);
+        const float tm = m;
+        m = wave_max_dpp(m);
+        int ti = INT_MAX;
+        if (tm == m) {
+#pragma unroll
+            for (int c = NCH - 1; c >= 0; --c)
+#pragma unroll
+                for (int k = VEC - 1; k >= 0; --k)
+                    if (x[c * VEC + k] == m) ti = (c * kWave + lane) * VEC + k;
+        }
+        const int am = wave_min_dpp(ti);
+        bool rbad = false;
+        const bool valid = label_valid(y, V, ignore_index, &rbad);
+        bad |= rbad;
+        const int yv = y / VEC;
+        const int slot = valid && yv % kWave == lane ? (yv / kWave) * VEC + y % VEC : -1;
+        float zt = 0.f;
+        if (slot >= 0) {
+#pragma unroll
+            for (int k = 0; k < VPT; ++k)
+                if (k == slot) zt = x[k];
+        }
+        const float m2 = m * kLog2e;
+        float l = 0.f;
+#pragma unroll
+        for (int k = 0; k < VPT; ++k) {
+            x[k] = exp2_fast(fmaf(x[k], kLog2e, -m2));
+            l += x[k];
+        }
+        l = wave_sum_dpp(l);
+        const float lse = m + logf(l);
+        const float inv_l = valid ? 1.0f / l : 0.f;
+        T* rr = R ? R + (int64_t)i * ldr : nullptr;
+#pragma unroll
+        for (int k = 0; k < VPT; ++k) x[k] = valid ? x[k] * inv_l : 0.f;
+        if (slot >= 0) {
+#pragma unroll
+            for (int k = 0; k < VPT; ++k)
+                if (k == slot) x[k] -= 1.0f;
+        }
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) {
+#pragma unroll
+            for (int k = 0; k < VEC; ++k) acc[c * VEC + k] += x[c * VEC + k];
+            if (rr) store_row_chunk<T, VEC, UA>(rr, (c * kWave + lane) * VEC, V, &x[c * VEC]);
+        }
+        if (lane == 0) {
+            row_lse[i] = lse;
+            if (row_argmax) row_argmax[i] = am;
+            cnt += valid ? 1 : 0;
+        }
+        if (valid ? slot >= 0 : lane == 0) {   // the label's owner
+            if (row_target) row_target[i] = zt;
+            if (valid) ce += (double)lse - (double)zt;
+        }
+    }
+    // column sums of the waves, in wave order
+    for (int w = 0; w < waves; ++w) {
+        if (w == wave) {
+#pragma unroll
+            for (int c = 0; c < NCH; ++c)
+#pragma unroll
+                for (int k = 0; k < VEC; ++k) {
+                    float* p = &sh_s[(c * kWave + lane) * VEC + k];
+                    *p = w == 0 ? acc[c * VEC + k] : *p + acc[c * VEC + k];
+                }
+        }
+        __syncthreads();
+    }
+    float* prow = ws.part + (int64_t)blockIdx.x * V;
+    for (int j = threadIdx.x; j < V; j += blockDim.x) prow[j] = sh_s[j];
+    ce = wave_sum(ce);
+    if (lane == 0) {
+        sh_ce[wave] = ce;
+        sh_c[wave] = cnt;
+        sh_f[wave] = bad ? BOM_FLAG_LABEL_RANGE : 0;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int c = 0, f = 0;
+        double e = 0.0;
+        for (int w = 0; w < waves; ++w) {
+            c += sh_c[w];
+            f |= sh_f[w];
+            e += sh_ce[w];
+        }
+        ws.wg_count[blockIdx.x] = c;
+        ws.wg_loss[blockIdx.x] = e;
+        ws.wg_flags[blockIdx.x] = f;
+    }
+}
+
+// ---------------------------------------------------------------------------------------------
 // Small batches of short rows (one chunk for each of 16 lanes) in one workgroup and one launch: 16 lanes take a row, 64 rows
 // at a time, and the residuals wait in LDS for the column sums. Row sums over 16 lanes and column sums in the finish
 // kernel's order give the outputs the bits of the rows and finish kernels (but for the rounding of a label's own
@@ -1336,6 +1532,47 @@ hipError_t launch_rows(const T* Z, int64_t ldz, int N, int V, const int32_t* lab
     hipLaunchKernelGGL((residual_rows_kernel<T, THREADS, VEC, NCH, kPacked, UA>), dim3(nwg), dim3(THREADS), 0, stream, Z,
                        ldz, N, V, labels, ignore_index, row_lse, row_argmax, row_target, R, ldr, rpw, ws);
     return hipGetLastError();
+}
+
+// Chunks per lane of the one-wave-per-row kernel, or 0 where a row is too wide for it (more than 64 columns per lane), or
+// the rows too few: a wave takes its row's columns one after another, so with fewer than 32 rows per column of a lane
+// several waves per row finish sooner (300 x 4096 bf16 9.9 against 13.4 us, 64 x 1000 fp32 10.0 against 11.1; at 3000 x
+// 4095 they are level). Measured before and with it, bf16: 16384 x 1000 90 -> 22 us, 8192 x 128 39 -> 13, 8192 x 4096
+// 57 -> 35, 8192 x 1001 50 -> 18, 16384 x 10 78 -> 17; fp32: 4096 x 1000 26 -> 15, 8192 x 2000 51 -> 40.
+template <int VEC>
+int wave_rows_nch(int N, int V) {
+    const int need = (V + kWave * VEC - 1) / (kWave * VEC);
+    for (int c : {1, 2, 4, 8, 16})
+        if (c >= need) return c * VEC <= 64 && N >= 32 * c * VEC ? c : 0;
+    return 0;
+}
+
+template <typename T, int VEC, bool UA>
+hipError_t launch_wave_rows(int nch, const T* Z, int64_t ldz, int N, int V, const int32_t* labels, int32_t ig, float* lse,
+                            int32_t* am, float* tg, T* R, int64_t ldr, Partials ws, int* nwg, hipStream_t st) {
+    // one workgroup per CU; as many waves in it as there are rows for
+    auto go = [&](auto tag) {
+        constexpr int NCH = decltype(tag)::value;
+        if constexpr (NCH * VEC <= 64) {
+            constexpr int MAXW = kWaveRowsMax<NCH * VEC>;
+            int waves = 1;
+            while (waves < MAXW && (int64_t)waves * kSingleMaxWG < N) waves *= 2;
+            *nwg = (int)std::min<int64_t>(kSingleMaxWG, (N + waves - 1) / waves);
+            hipLaunchKernelGGL((residual_wave_rows_kernel<T, VEC, NCH, UA>), dim3(*nwg), dim3(waves * kWave), 0, st, Z, ldz,
+                               N, V, labels, ig, lse, am, tg, R, ldr, ws);
+            return hipGetLastError();
+        } else {
+            return hipErrorInvalidValue;
+        }
+    };
+    switch (nch) {
+        case 1: return go(std::integral_constant<int, 1>{});
+        case 2: return go(std::integral_constant<int, 2>{});
+        case 4: return go(std::integral_constant<int, 4>{});
+        case 8: return go(std::integral_constant<int, 8>{});
+        case 16: return go(std::integral_constant<int, 16>{});
+        default: return hipErrorInvalidValue;
+    }
 }
 
 // Allowed chunk counts for 512-thread single-pass workgroups (registers: 2 * NCH * VEC floats).
@@ -1549,7 +1786,11 @@ hipError_t run_residual(const T* Z, int N, int V, int64_t ldz, const int32_t* la
                            lse, am, tg, R, ldr, s, loss, n_valid, flags);
         return hipGetLastError();
     }
-    if (single) {
+    const int wave_nch = single && plan_override() == 0 ? wave_rows_nch<VEC>(N, V) : 0;
+    if (wave_nch > 0) {
+        e = launch_wave_rows<T, VEC, UA>(wave_nch, Z, ldz, N, V, labels, ig, lse, am, tg, R, ldr, ws, &nwg, st);
+        nparts = nwg;
+    } else if (single) {
         e = dispatch_rows<T, VEC, UA>(nch, threads, Z, ldz, N, V, labels, ig, lse, am, tg, R, ldr, ws, &nwg, st);
         nparts = nwg;
     } else if (split) {

@@ -95,7 +95,9 @@ def test_head_forward_any_alignment(N, d, V, pad, off):
 
 # One chunk per thread (64 to 512 threads), rows parked in LDS (1024 and 512 threads, the tail chunk in the first, a
 # middle and the last position), and rows past one workgroup's LDS (two passes).
-RES_CASES = [(37, 8, 1, 0), (300, 9, 0, 0), (5, 511, 0, 1), (260, 1001, 0, 0), (33, 4095, 2, 3), (40, 4096, 1, 0),
+# The first ones: one wave per row, with one to eight chunks per lane, aligned and ragged, rows in one and several turns.
+RES_CASES = [(9000, 8, 0, 0), (700, 511, 0, 0), (5000, 1000, 0, 0), (3000, 1025, 0, 1), (4200, 2049, 1, 0), (2100, 4096, 0, 0),
+             (37, 8, 1, 0), (300, 9, 0, 0), (5, 511, 0, 1), (260, 1001, 0, 0), (33, 4095, 2, 3), (40, 4096, 1, 0),
              (700, 4097, 0, 0), (20, 8199, 0, 1), (300, 12345, 0, 0), (9, 32773, 1, 0), (600, 50257, 0, 0),
              (3, 57343, 0, 1), (70, 57345, 0, 0), (21, 65541, 3, 0), (1, 128257, 0, 1)]
 

@@ -1,4 +1,4 @@
-"""The one-workgroup residual of small batches of short rows, at the ends of its range and one step past them."""
+"""The one-workgroup residual of small batches of short rows, at the ends of its range and past them (one wave per row)."""
 import pytest
 import torch
 
@@ -8,8 +8,8 @@ from tests.gpu_util import dev, log
 pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not torch.cuda.is_available(), reason="needs an MI355X")]
 
 
-@pytest.mark.parametrize("N", [1, 63, 65, 256, 257])
-@pytest.mark.parametrize("V,dtype", [(2, "f32"), (10, "f32"), (16, "f32"), (17, "f32"), (64, "f32"), (3, "bf16"),
+@pytest.mark.parametrize("N", [1, 63, 65, 256, 257, 5000])
+@pytest.mark.parametrize("V,dtype", [(1000, "f32"), (1023, "f32"), (2, "f32"), (10, "f32"), (16, "f32"), (17, "f32"), (64, "f32"), (3, "bf16"),
                                      (8, "bf16"), (63, "bf16"), (64, "bf16"), (127, "bf16"), (128, "bf16")])
 def test_small_residual(N, V, dtype):
     log(f"[small residual] N={N} V={V} {dtype}")
