@@ -140,12 +140,19 @@ __global__ __launch_bounds__(256) void z_panel_kernel(const uint16_t* __restrict
 // G = s_out (r_coef R + mask * cqp): for lambda < 1, s_out = alpha, r_coef = 1, cqp = lambda/(1-lambda) q_hat;
 // for lambda = 1, s_out = 1/N_t, r_coef = 0, cqp = q_hat. The large-tile kernels fold cqp with one
 // bf16 dot product per element and apply s_out to the fp32 accumulators.
+// db in fp32, or rounded to bf16
+__device__ __forceinline__ void store_db(void* db, int bf16, int j, float x) {
+    if (bf16) static_cast<uint16_t*>(db)[j] = f32_to_bf16(x);
+    else static_cast<float*>(db)[j] = x;
+}
+
 __global__ __launch_bounds__(256) void vjp_prep_kernel(const float* __restrict__ q_hat, const float* __restrict__ s,
                                                        const int32_t* __restrict__ n_valid, float lambda, int V, int N,
                                                        const int32_t* __restrict__ labels, int32_t ignore_index,
                                                        float* __restrict__ cq, float* __restrict__ cqp,
                                                        float* __restrict__ vmask, float* __restrict__ scal,
-                                                       float* __restrict__ db, const float* __restrict__ hpart, int nrb,
+                                                       void* __restrict__ db, int db_bf16,
+                                                       const float* __restrict__ hpart, int nrb,
                                                        int d, float* __restrict__ hsum, const float* __restrict__ row_lse,
                                                        float* __restrict__ zc, const float* __restrict__ upart, int uch,
                                                        float* __restrict__ u) {
@@ -173,7 +180,7 @@ __global__ __launch_bounds__(256) void vjp_prep_kernel(const float* __restrict__
     if (idx < V) {
         cq[idx] = nt > 0 ? (float)((double)lambda * (double)q_hat[idx] / (double)nt) : 0.f;
         cqp[idx] = hist_only ? q_hat[idx] : (float)((double)lambda / (1.0 - (double)lambda) * (double)q_hat[idx]);
-        if (db) db[idx] = nt > 0 ? (1.0f - lambda) * s[idx] + lambda * q_hat[idx] : 0.f;
+        if (db) store_db(db, db_bf16, idx, nt > 0 ? (1.0f - lambda) * s[idx] + lambda * q_hat[idx] : 0.f);
     }
     if (idx < N) {
         bool bad = false;
@@ -1096,8 +1103,7 @@ __device__ __forceinline__ void wide_tile(const WideArgs& args, int id, uint16_t
             if (m < M && n < Nn) {
                 const float x = fmaf(alpha, v, rv_s[r] * cvv[j]);
                 if constexpr (IS_DW) {
-                    float* p = reinterpret_cast<float*>(out) + (int64_t)m * ldo + n;
-                    *p = beta != 0.f ? x + beta * *p : x;
+                    stf<TO>(out, (int64_t)m * ldo + n, beta != 0.f ? x + beta * ldf<TO>(out, (int64_t)m * ldo + n) : x);
                 } else {
                     stf<TO>(out, (int64_t)m * ldo + n, args.add ? x + args.add[(int64_t)m * Nn + n] : x);
                 }
@@ -1131,12 +1137,12 @@ __global__ __launch_bounds__(NW * 64, 1) void lds256w_fwd_kernel(WideArgs a) {
 // tiles, so that the shorter dW tiles fill the compute units that dH's last round leaves idle instead of
 // a second launch starting after a partly empty round. nh is a multiple of 8, so each part keeps its
 // own XCD order.
-template <typename TO, int NW, bool UA = false>
+template <typename TO, typename TW, int NW, bool UA = false>
 __global__ __launch_bounds__(NW * 64, 1) void lds256w_pair_kernel(WideArgs h, WideArgs w, int nh) {
     __shared__ __attribute__((aligned(1024))) uint16_t lds[2][2][WSE];
     __shared__ float rv_s[LB];
     if ((int)blockIdx.x < nh) wide_tile<kWideDH, TO, NW, UA>(h, blockIdx.x, lds, rv_s);
-    else wide_tile<kWideDW, float, NW, UA>(w, (int)blockIdx.x - nh, lds, rv_s);
+    else wide_tile<kWideDW, TW, NW, UA>(w, (int)blockIdx.x - nh, lds, rv_s);
 }
 
 // Split-K reduction for the rank-1 form over the rectangle [pm0, M) x [pn0, Nn) of the output, in split
@@ -1310,9 +1316,9 @@ struct FusedArgs {
     const int32_t* labels; int32_t ig;
     const float* q_hat; const float* s; const int32_t* n_valid; float lambda;
     int N, d, V;
-    float* dW; int64_t lddw; float beta;
+    void* dW; int64_t lddw; float beta; int dw_bf16;   // dW and db in bf16
     void* dH; int64_t lddh; int dh_bf16;
-    float* db;
+    void* db;
     int tw_n, tw, th_n;   // dW tiles along V, dW tile count, dH tiles along d
     const float* row_lse; // logits input: R is formed from Z (the R argument) and lse; null: R is stored
     const uint16_t* bias; // forward: Z = H W (+ bias)
@@ -1570,9 +1576,15 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& a, int id, uint16_t 
         const int m = m0 + row;
         if (m >= M || n >= Nn) continue;
         if (is_dw) {
-            float x = fmaf(alpha, acc[r], vec[row] * cqn);
-            float* p = a.dW + (int64_t)m * a.lddw + n;
-            *p = a.beta != 0.f ? x + a.beta * *p : x;
+            const float x = fmaf(alpha, acc[r], vec[row] * cqn);
+            const int64_t at = (int64_t)m * a.lddw + n;
+            if (a.dw_bf16) {
+                uint16_t* p = static_cast<uint16_t*>(a.dW);
+                stf<uint16_t>(p, at, a.beta != 0.f ? x + a.beta * bf16_to_f32(p[at]) : x);
+            } else {
+                float* p = static_cast<float*>(a.dW);
+                p[at] = a.beta != 0.f ? x + a.beta * p[at] : x;
+            }
         } else {
             bool bad = false;
             const float vm = label_valid(a.labels[m], a.V, a.ig, &bad) ? 1.f : 0.f;
@@ -1583,7 +1595,7 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& a, int id, uint16_t 
     }
     if (is_dw && m0 == 0 && a.db != nullptr && t < FB && n0 + t < a.V) {
         const int j = n0 + t;
-        a.db[j] = nt > 0 ? (1.0f - a.lambda) * a.s[j] + a.lambda * a.q_hat[j] : 0.f;
+        store_db(a.db, a.dw_bf16, j, nt > 0 ? (1.0f - a.lambda) * a.s[j] + a.lambda * a.q_hat[j] : 0.f);
     }
 }
 
@@ -1961,11 +1973,11 @@ hipError_t run_gemm(bool is_dw, const GemmPlan& g, const void* A, int64_t lda, c
                                   add};
                 const int nw = is_dw ? wave_cfg().dw : wave_cfg().dh;
                 if (ua && is_dw)   // rows at any alignment: eight waves
-                    hipLaunchKernelGGL((lds256w_kernel<true, float, 8, true>), gr, dim3(512), 0, st, wa);
+                    hipLaunchKernelGGL((lds256w_kernel<true, TO, 8, true>), gr, dim3(512), 0, st, wa);
                 else if (ua)
                     hipLaunchKernelGGL((lds256w_kernel<false, TO, 8, true>), gr, dim3(512), 0, st, wa);
-                else if (is_dw && nw == 8)
-                    hipLaunchKernelGGL((lds256w_kernel<true, float, 8>), gr, dim3(512), 0, st, wa);
+                else if (is_dw && (nw == 8 || sizeof(TO) == 2))
+                    hipLaunchKernelGGL((lds256w_kernel<true, TO, 8>), gr, dim3(512), 0, st, wa);
                 else if (is_dw)
                     hipLaunchKernelGGL((lds256w_kernel<true, float, 4>), gr, dim3(256), 0, st, wa);
                 else if (nw == 8)
@@ -2053,10 +2065,44 @@ __global__ __launch_bounds__(256) void round_dw_bf16_kernel(const float* __restr
 }
 }  // namespace
 
-hipError_t launch_head_vjp_f32(const HeadVjpArgs& a, hipStream_t st);   // dW and db in fp32
+namespace {
+// How a call's operands are multiplied: the plan, and whether rows of R and W come at any alignment (ua).
+struct Route {
+    Plan p;
+    bool ua, fused;   // fused: both products in the one launch of small tiles
+};
+Route route_of(const HeadVjpArgs& a) {
+    Route r{make_plan(a.N, a.d, a.V, a.dt, false), false, false};
+    if (a.dt == BOM_F32) return r;
+    // MFMA kernels stage 16-byte chunks: of H at 16-byte aligned addresses, of R and W too or (ua) at any (with the
+    // 256-row offsets inside 31 bits); otherwise the SIMT kernels run, with their own k splits over every tile (the
+    // workspace covers their partials too).
+    auto al = [](const void* ptr, int64_t ld) { return reinterpret_cast<uintptr_t>(ptr) % 16 == 0 && ld % 8 == 0; };
+    r.ua = !(a.V % 8 == 0 && al(a.W, a.ldw) && al(a.R, a.ldr));
+    if (r.ua) r.p = make_plan(a.N, a.d, a.V, a.dt, true);
+    const bool h_ok = a.d % 8 == 0 && al(a.H, a.ldh);
+    const bool ld_ok = a.ldw < (1 << 22) && (!a.is_residual || a.ldr < (1 << 22));
+    const bool fits31 = ((int64_t)(a.N - 1) * a.ldh + a.d) * 2 < (1LL << 31) &&
+                        ((int64_t)(a.N - 1) * a.ldr + a.V) * 2 < (1LL << 31) &&
+                        ((int64_t)(a.d - 1) * a.ldw + a.V) * 2 < (1LL << 31);
+    const bool small = r.p.w.kind == kMfma128 && r.p.h.kind == kMfma128;
+    if (!h_ok || (r.ua && (!ld_ok || (small && !fits31)))) r.p = simt_plan(a.N, a.d, a.V);
+    if (!a.dH) r.p.h.kind = kSimt;   // no dH: no rank-1 vector for it
+    // small products (both on the 128-tile kernel): one fused launch, nothing staged beforehand
+    const PlanOverride& ov = plan_override();
+    r.fused = r.p.w.kind == kMfma128 && (!a.dH || r.p.h.kind == kMfma128) && fits31 && fused_extents(a.N, a.V) &&
+              (r.ua || (ov.kw != 1 && ov.kh != 1));
+    return r;
+}
+}  // namespace
+
+hipError_t launch_products(const HeadVjpArgs& a, const Route& r, hipStream_t st);   // dW and db in bf16: fused or rank-1 dW
 
 hipError_t launch_head_vjp(const HeadVjpArgs& a, hipStream_t st) {
-    if (a.dw_dt != BOM_BF16) return launch_head_vjp_f32(a, st);
+    const Route r = route_of(a);
+    // bf16 dW and db: the fused launch and the 256-tile kernel round their fp32 sums as they store them; the others form
+    // both in fp32 in the workspace and a pass rounds them (a dW of 768 x 32,000 cost 98 MB written and read back there)
+    if (a.dw_dt != BOM_BF16 || r.fused || r.p.w.kind == kRank1) return launch_products(a, r, st);
     HeadVjpArgs b = a;
     char* scratch = static_cast<char*>(a.ws) + vjp_ws(a.N, a.d, a.V, a.dt).total;
     b.dW = scratch;
@@ -2064,7 +2110,7 @@ hipError_t launch_head_vjp(const HeadVjpArgs& a, hipStream_t st) {
     b.lddw = a.V;
     b.dW_beta = 0.f;
     b.db = a.db ? scratch + align256((size_t)a.d * a.V * 4) : nullptr;
-    hipError_t e = launch_head_vjp_f32(b, st);
+    hipError_t e = launch_products(b, r, st);
     if (e != hipSuccess) return e;
     const int64_t n = (int64_t)a.d * a.V + (a.db ? a.V : 0);
     const unsigned grid = (unsigned)std::min<int64_t>(cdiv(n, 256), 8192);
@@ -2097,7 +2143,7 @@ hipError_t launch_prep(const HeadVjpArgs& a, const VjpWs& L, bool rw, bool rh, b
     if (nprep < a.d) nprep = a.d;
     hipLaunchKernelGGL(vjp_prep_kernel, dim3((nprep + 255) / 256), dim3(256), 0, st, a.q_hat, a.s, a.n_valid, a.lambda,
                        a.V, a.N, a.labels, a.ignore_index, at(L.cq_off), at(L.cqp_off), at(L.vmask_off), at(L.scal_off),
-                       static_cast<float*>(a.db), rw ? hpart : nullptr, nrb, a.d, at(L.hsum_off),
+                       a.db, a.dw_dt == BOM_BF16 ? 1 : 0, rw ? hpart : nullptr, nrb, a.d, at(L.hsum_off),
                        a.is_residual ? nullptr : a.row_lse, at(L.zc_off), rh ? upart : nullptr, uch, at(L.u_off));
     return hipGetLastError();
 }
@@ -2123,7 +2169,7 @@ hipError_t launch_from_logits(const HeadVjpArgs& a, const VjpWs& L, hipStream_t 
         b.R = panel;
         b.ldr = ldp;
         b.is_residual = 1;
-        return launch_head_vjp_f32(b, st);
+        return launch_head_vjp(b, st);
     }
     const bool ua = a.V % 8 != 0 || reinterpret_cast<uintptr_t>(a.W) % 16 != 0 || a.ldw % 8 != 0;
     const bool hist = a.lambda != 0.f;
@@ -2135,9 +2181,15 @@ hipError_t launch_from_logits(const HeadVjpArgs& a, const VjpWs& L, hipStream_t 
     for (int64_t i = 0; i < np; ++i) {
         const int64_t c0 = i * pc, nc = i + 1 < np ? pc : a.V - c0;
         if ((e = form(c0, nc)) != hipSuccess) return e;
-        e = run_gemm<float>(true, plan_wide(a.d, nc, a.N, true), a.H, a.ldh, panel, ldp, a.dt, a.d, (int)nc, a.N, f,
-                            static_cast<float*>(a.dW) + c0, a.lddw, a.dW_beta, part, hist ? hsum : nullptr, cq + c0, ua,
-                            st);
+        const GemmPlan gw = plan_wide(a.d, nc, a.N, true);
+        if (a.dw_dt == BOM_BF16)
+            e = run_gemm<uint16_t>(true, gw, a.H, a.ldh, panel, ldp, a.dt, a.d, (int)nc, a.N, f,
+                                   static_cast<uint16_t*>(a.dW) + c0, a.lddw, a.dW_beta, part, hist ? hsum : nullptr,
+                                   cq + c0, ua, st);
+        else
+            e = run_gemm<float>(true, gw, a.H, a.ldh, panel, ldp, a.dt, a.d, (int)nc, a.N, f,
+                                static_cast<float*>(a.dW) + c0, a.lddw, a.dW_beta, part, hist ? hsum : nullptr, cq + c0, ua,
+                                st);
         if (e != hipSuccess) return e;
         if (!a.dH) continue;
         const uint16_t* w = static_cast<const uint16_t*>(a.W) + c0;
@@ -2158,44 +2210,25 @@ hipError_t launch_from_logits(const HeadVjpArgs& a, const VjpWs& L, hipStream_t 
 }
 }  // namespace
 
-hipError_t launch_head_vjp_f32(const HeadVjpArgs& a, hipStream_t st) {
+hipError_t launch_products(const HeadVjpArgs& a, const Route& r, hipStream_t st) {
     const VjpWs L = vjp_ws(a.N, a.d, a.V, a.dt);
+    const Plan& p = r.p;
+    const bool ua = r.ua;
     char* base = static_cast<char*>(a.ws);
     float* cq = reinterpret_cast<float*>(base + L.cq_off);
     float* cqp = reinterpret_cast<float*>(base + L.cqp_off);
     float* vmask = reinterpret_cast<float*>(base + L.vmask_off);
     float* scal = reinterpret_cast<float*>(base + L.scal_off);
-    float* hpart = reinterpret_cast<float*>(base + L.hpart_off);
     float* hsum = reinterpret_cast<float*>(base + L.hsum_off);
     float* u = reinterpret_cast<float*>(base + L.u_off);
-    float* upart = reinterpret_cast<float*>(base + L.upart_off);
     float* part = reinterpret_cast<float*>(base + L.part_off);
     float* zc = reinterpret_cast<float*>(base + L.zc_off);
     const bool zin = !a.is_residual;   // the R argument holds the logits Z
-
-    // MFMA kernels stage 16-byte chunks: of H at 16-byte aligned addresses, of R and W too or (ua) at any (with the
-    // 256-row offsets inside 31 bits); otherwise the SIMT kernels run,
-    // with their own k splits over every tile (the workspace covers their partials too).
-    auto al = [](const void* ptr, int64_t ld) { return reinterpret_cast<uintptr_t>(ptr) % 16 == 0 && ld % 8 == 0; };
-    const bool ua = a.dt == BOM_BF16 && !(a.V % 8 == 0 && al(a.W, a.ldw) && al(a.R, a.ldr));
-    Plan p = make_plan(a.N, a.d, a.V, a.dt, ua);
-    const bool h_ok = a.d % 8 == 0 && al(a.H, a.ldh);
-    const bool ld_ok = a.ldw < (1 << 22) && (zin || a.ldr < (1 << 22));
-    const bool fits31 = ((int64_t)(a.N - 1) * a.ldh + a.d) * 2 < (1LL << 31) &&
-                        ((int64_t)(a.N - 1) * a.ldr + a.V) * 2 < (1LL << 31) &&
-                        ((int64_t)(a.d - 1) * a.ldw + a.V) * 2 < (1LL << 31);
-    const bool small = p.w.kind == kMfma128 && p.h.kind == kMfma128;
-    if (a.dt == BOM_BF16 && (!h_ok || (ua && (!ld_ok || (small && !fits31))))) p = simt_plan(a.N, a.d, a.V);
-    if (zin && (p.w.kind == kRank1 || (a.dH && p.h.kind == kRank1))) return launch_from_logits(a, L, st);
-    if (a.dt == BOM_BF16 && L.part_off + partial_bytes(p, a.N, a.d, a.V) > L.total) return hipErrorInvalidValue;   // never taken
-    if (!a.dH) p.h.kind = kSimt;   // no dH: no rank-1 vector for it
-
     if (a.dt == BOM_F32) return launch_vjp_f32_products(a, f32_dw_sums(a.N, a.d, a.V), part, st);
+    if (zin && (p.w.kind == kRank1 || (a.dH && p.h.kind == kRank1))) return launch_from_logits(a, L, st);
+    if (L.part_off + partial_bytes(p, a.N, a.d, a.V) > L.total) return hipErrorInvalidValue;   // never taken
 
-    // small products (both on the 128-tile kernel): one fused launch, nothing staged beforehand
-    const PlanOverride& ov = plan_override();
-    if (a.dt == BOM_BF16 && p.w.kind == kMfma128 && (!a.dH || p.h.kind == kMfma128) && fits31 &&
-        fused_extents(a.N, a.V) && (ua || (ov.kw != 1 && ov.kh != 1))) {
+    if (r.fused) {
         FusedArgs fa{};
         fa.H = static_cast<const uint16_t*>(a.H);
         fa.ldh = a.ldh;
@@ -2212,13 +2245,14 @@ hipError_t launch_head_vjp_f32(const HeadVjpArgs& a, hipStream_t st) {
         fa.N = a.N;
         fa.d = a.d;
         fa.V = a.V;
-        fa.dW = static_cast<float*>(a.dW);
+        fa.dW = a.dW;
+        fa.dw_bf16 = a.dw_dt == BOM_BF16;
         fa.lddw = a.lddw;
         fa.beta = a.dW_beta;
         fa.dH = a.dH;
         fa.lddh = a.lddh;
         fa.dh_bf16 = a.dh_dt == BOM_BF16;
-        fa.db = static_cast<float*>(a.db);
+        fa.db = a.db;
         fa.tw_n = (int)cdiv(a.V, FB);
         fa.tw = (int)cdiv(a.d, FB) * fa.tw_n;
         fa.th_n = (int)cdiv(a.d, FB);
@@ -2256,21 +2290,18 @@ hipError_t launch_head_vjp_f32(const HeadVjpArgs& a, hipStream_t st) {
         const int nw = (int)(cdiv(ow, 8) * 8 * inner);
         const dim3 grid((unsigned)(nh + nw));
         const bool w8 = wave_cfg().pair == 8;
-        if (ua) {   // rows at any alignment: eight waves
-            if (a.dh_dt == BOM_BF16)
-                hipLaunchKernelGGL((lds256w_pair_kernel<uint16_t, 8, true>), grid, dim3(512), 0, st, wh, ww, nh);
-            else
-                hipLaunchKernelGGL((lds256w_pair_kernel<float, 8, true>), grid, dim3(512), 0, st, wh, ww, nh);
-        } else if (a.dh_dt == BOM_BF16) {
-            if (w8)
-                hipLaunchKernelGGL((lds256w_pair_kernel<uint16_t, 8>), grid, dim3(512), 0, st, wh, ww, nh);
-            else
-                hipLaunchKernelGGL((lds256w_pair_kernel<uint16_t, 4>), grid, dim3(256), 0, st, wh, ww, nh);
+        const bool h16 = a.dh_dt == BOM_BF16;
+        if (a.dw_dt == BOM_BF16) {   // eight waves
+            const auto k = ua ? (h16 ? lds256w_pair_kernel<uint16_t, uint16_t, 8, true> : lds256w_pair_kernel<float, uint16_t, 8, true>)
+                              : (h16 ? lds256w_pair_kernel<uint16_t, uint16_t, 8> : lds256w_pair_kernel<float, uint16_t, 8>);
+            hipLaunchKernelGGL(k, grid, dim3(512), 0, st, wh, ww, nh);
+        } else if (ua || w8) {
+            const auto k = ua ? (h16 ? lds256w_pair_kernel<uint16_t, float, 8, true> : lds256w_pair_kernel<float, float, 8, true>)
+                              : (h16 ? lds256w_pair_kernel<uint16_t, float, 8> : lds256w_pair_kernel<float, float, 8>);
+            hipLaunchKernelGGL(k, grid, dim3(512), 0, st, wh, ww, nh);
         } else {
-            if (w8)
-                hipLaunchKernelGGL((lds256w_pair_kernel<float, 8>), grid, dim3(512), 0, st, wh, ww, nh);
-            else
-                hipLaunchKernelGGL((lds256w_pair_kernel<float, 4>), grid, dim3(256), 0, st, wh, ww, nh);
+            const auto k = h16 ? lds256w_pair_kernel<uint16_t, float, 4> : lds256w_pair_kernel<float, float, 4>;
+            hipLaunchKernelGGL(k, grid, dim3(256), 0, st, wh, ww, nh);
         }
         if ((e = hipGetLastError()) != hipSuccess || sh == 1) return e;
         const int64_t MN = (int64_t)a.N * a.d;
@@ -2284,8 +2315,12 @@ hipError_t launch_head_vjp_f32(const HeadVjpArgs& a, hipStream_t st) {
     }
 
     // dW = H^T G
-    e = run_gemm<float>(true, p.w, a.H, a.ldh, a.R, a.ldr, a.dt, a.d, a.V, a.N, f, static_cast<float*>(a.dW), a.lddw,
-                        a.dW_beta, part, hist ? hsum : nullptr, cq, ua, st);
+    if (a.dw_dt == BOM_BF16)
+        e = run_gemm<uint16_t>(true, p.w, a.H, a.ldh, a.R, a.ldr, a.dt, a.d, a.V, a.N, f, static_cast<uint16_t*>(a.dW),
+                               a.lddw, a.dW_beta, part, hist ? hsum : nullptr, cq, ua, st);
+    else
+        e = run_gemm<float>(true, p.w, a.H, a.ldh, a.R, a.ldr, a.dt, a.d, a.V, a.N, f, static_cast<float*>(a.dW), a.lddw,
+                            a.dW_beta, part, hist ? hsum : nullptr, cq, ua, st);
     if (e != hipSuccess) return e;
     // dH = G W^T (shares the split-K buffer: same stream, so it runs after the dW reduction)
     if (a.dH) {
