@@ -850,12 +850,12 @@ __device__ __forceinline__ void wide_tile(const WideArgs& args, int id, uint16_t
     const int kb = kz * kps, ke = min(Km, kb + kps);
     const int nk = (ke - kb + KT - 1) / KT;
     const int l = threadIdx.x % kWave;
-    // output column of tile column c, or one past every column where it has none
+    // column that tile column c holds, or one past every column where it holds none
     auto out_col = [&](int c) {
         const int n = n0 + c;
         if constexpr (UA && !KB) {
             const int cs = Nn & ~7;               // columns from cs on came from Nn - 8, Nn - 7, ...
-            if (n >= cs) return n < cs + 8 && n - 8 + (Nn - cs) >= cs ? n - 8 + (Nn - cs) : 0x7fffffff;
+            if (n >= cs) return n < cs + 8 && Nn > cs ? n - 8 + (Nn - cs) : 0x7fffffff;
         }
         return n;
     };
@@ -1075,45 +1075,98 @@ __device__ __forceinline__ void wide_tile(const WideArgs& args, int id, uint16_t
         __builtin_amdgcn_sched_barrier(0);
     }
     __syncthreads();
-    // accumulator element (i, j, r) of this lane: tile row and column, and the 32-column block j
-    auto for_each_acc = [&](auto&& fn) {
+    // The tile leaves through LDS, one wave's part of it at a time (16 KB, 32 KB with four waves; no barrier: a wave
+    // reads what it wrote): value(tile row, 32-column block j, accumulator) of every element as S, then 16-byte chunks
+    // of a row, emit(row m, column n, first column not also stored by a chunk before it, chunk), eight lanes or more
+    // side by side along each row. Lane halves hold rows four apart and write blocks j and j ^ 1 at once, so they use
+    // different banks. Element by element from the accumulators (128 stores per lane, each with its own address and
+    // checks) they took up to 9 us of a tile's time: forward 4096 x 1024 x 50304 484 -> 418 us, 8192 x 2048 x 50304
+    // 1529 -> 1447; both products there 2815 -> 2712, at 4088 x 1024 x 50257 950 -> 893.
+    auto emit_tile = [&](auto s0, auto&& value, auto&& emit) {
+        using S = decltype(s0);
+        constexpr int CH = 16 / sizeof(S);              // elements of a chunk
+        constexpr int IB = sizeof(S) == 2 ? 4 : 2;      // 32-row blocks per pass
+        constexpr int LPR = WCOLS / CH;                 // lanes per row
+        constexpr int RPI = kWave / LPR;                // rows per store instruction
+        static_assert(NW * IB * 32 * WCOLS * sizeof(S) <= sizeof(lds), "a part of the tile per wave");
+        char* mine = reinterpret_cast<char*>(&lds[0][0][0]) + wave * (IB * 32 * WCOLS * (int)sizeof(S));
+        const int n8 = n0 + wn * WCOLS + (l % LPR) * CH / 8 * 8;
+        const int at = UA && !KB ? min(n8, Nn - 8) : n8;   // where the eight columns from n8 came from
+        const int n = at + (l % LPR) * CH % 8;
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i0 = 0; i0 < 4; i0 += IB) {
 #pragma unroll
-            for (int j = 0; j < NJ; ++j)
+            for (int i = i0; i < i0 + IB; ++i)
 #pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    fn(wm * 128 + i * 32 + (r / 4) * 8 + (l / 32) * 4 + (r % 4), wn * WCOLS + j * 32 + l % 32, j,
-                       acc[i][j][r]);
+                for (int j = 0; j < NJ; ++j)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        const int row = (i - i0) * 32 + (r / 4) * 8 + (l / 32) * 4 + r % 4;
+                        S* q = reinterpret_cast<S*>(mine) + row * WCOLS + (j ^ (l / 32)) * 32 + l % 32;
+                        stf<S>(q, 0, value(wm * 128 + i * 32 + (r / 4) * 8 + (l / 32) * 4 + r % 4, j, acc[i][j][r]));
+                    }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int t = 0; t < IB * 32 / RPI; ++t) {
+                const int row = t * RPI + l / LPR, m = m0 + wm * 128 + i0 * 32 + row;
+                const int c = ((l % LPR) * CH) ^ (((row >> 2) & 1) * 32);
+                const u32x4_t v = *reinterpret_cast<const u32x4_t*>(reinterpret_cast<const S*>(mine) + row * WCOLS + c);
+                if (m < M && n8 < Nn) emit(m, n, n8, v);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+        }
+    };
+    // 16 bytes at any alignment of an element. The output streams out past the operands' panels in the L2 (forward,
+    // 4096 x 1024 x 50304: 441 us with plain stores, 418 non-temporal) except where chunks of dW straddle cache lines,
+    // which the L2 joins (4088 x 1024 x 50257, both products: 893 us plain, 913 non-temporal).
+    auto put = [&](auto* q, const u32x4_t& v) {
+        constexpr bool kStream = !UA || MODE == kWideFWD;
+        if constexpr (sizeof(*q) == 2) {
+            if constexpr (kStream) __builtin_nontemporal_store(v, reinterpret_cast<u32x4_any_t*>(q));
+            else *reinterpret_cast<u32x4_any_t*>(q) = v;
+        } else {
+            const f32x4 f = __builtin_bit_cast(f32x4, v);
+            if constexpr (kStream) __builtin_nontemporal_store(f, reinterpret_cast<f32x4_any_t*>(q));
+            else *reinterpret_cast<f32x4_any_t*>(q) = f;
+        }
     };
     if constexpr (MODE == kWideFWD) {
+        float bv[NJ];
         const uint16_t* __restrict__ bias = args.bias;
-        for_each_acc([&](int r, int c, int, float v) {
-            const int m = m0 + r, n = out_col(c);
-            if (m < M && n < Nn) stf<TO>(out, (int64_t)m * ldo + n, bias ? v + bf16_to_f32(bias[n]) : v);
-        });
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            const int n = out_col(wn * WCOLS + j * 32 + l % 32);
+            bv[j] = bias && n < Nn ? bf16_to_f32(bias[n]) : 0.f;
+        }
+        auto emit = [&](int m, int n, int, const u32x4_t& v) { put(out + (int64_t)m * ldo + n, v); };
+        if (bias) emit_tile(TO{}, [&](int, int j, float v) { return v + bv[j]; }, emit);
+        else emit_tile(TO{}, [&](int, int, float v) { return v; }, emit);
         return;
     }
     const float alpha = *alpha_p;
     if (part == nullptr) {
         if ((int)threadIdx.x < LB) rv_s[threadIdx.x] = rv_reg;
         __syncthreads();
-        for_each_acc([&](int r, int c, int j, float v) {
-            const int m = m0 + r, n = out_col(c);
-            if (m < M && n < Nn) {
-                const float x = fmaf(alpha, v, rv_s[r] * cvv[j]);
-                if constexpr (IS_DW) {
-                    stf<TO>(out, (int64_t)m * ldo + n, beta != 0.f ? x + beta * ldf<TO>(out, (int64_t)m * ldo + n) : x);
-                } else {
-                    stf<TO>(out, (int64_t)m * ldo + n, args.add ? x + args.add[(int64_t)m * Nn + n] : x);
+        auto value = [&](int r, int j, float v) { return fmaf(alpha, v, rv_s[r] * cvv[j]); };
+        if (IS_DW ? beta != 0.f : args.add != nullptr) {
+            emit_tile(0.f, value, [&](int m, int n, int first, const u32x4_t& v) {
+                TO* q = out + (int64_t)m * ldo + n;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const float x = __uint_as_float(v[k]);
+                    if constexpr (!IS_DW) stf<TO>(q, k, x + args.add[(int64_t)m * Nn + n + k]);
+                    else if (n + k >= first) stf<TO>(q, k, x + beta * ldf<TO>(q, k));
                 }
-            }
-        });
+            });
+        } else {
+            emit_tile(TO{}, value, [&](int m, int n, int, const u32x4_t& v) { put(out + (int64_t)m * ldo + n, v); });
+        }
     } else {
         float* pz = part + (int64_t)kz * tr.pstride;
-        for_each_acc([&](int r, int c, int, float v) {
-            const int m = m0 + r, n = out_col(c);
-            if (m < M && n < Nn) pz[(int64_t)(m - tr.pm0) * tr.ldp + (n - tr.pn0)] = alpha * v;
+        emit_tile(0.f, [&](int, int, float v) { return alpha * v; }, [&](int m, int n, int, const u32x4_t& v) {
+            put(pz + (int64_t)(m - tr.pm0) * tr.ldp + (n - tr.pn0), v);
         });
     }
 }

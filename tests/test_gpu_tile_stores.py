@@ -1,0 +1,40 @@
+"""Outputs of the 256 x 256 tiles at their edges: rows and columns left over, rows at any alignment, values beside the output."""
+import pytest
+import torch
+
+from paper_2609_36738_amd import bom
+from tests.gpu_util import dev, log
+
+pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not torch.cuda.is_available(), reason="needs an MI355X")]
+
+
+# last row tile of one row, of all but one and whole; last column tile of eight columns, of nine (the eighth and ninth
+# moved), of one and whole; the output's row pitch beyond its columns
+@pytest.mark.parametrize("N,d,V,pad", [(2049, 776, 8200, 0), (511, 264, 8201, 1), (512, 504, 8449, 3), (1535, 1032, 8192, 3),
+                                       (2049, 520, 16641, 1)])
+@pytest.mark.parametrize("out", [torch.float32, torch.bfloat16])
+def test_tile_edges(N, d, V, pad, out):
+    log(f"[tile stores] N={N} d={d} V={V} pad={pad} {out}")
+    g = torch.Generator(device=dev()).manual_seed(13)
+
+    def rand(shape, std, t=torch.bfloat16):
+        return (torch.randn(shape, generator=g, device=dev()) * std).to(t)
+
+    H, W = rand((N, d), 1.0), rand((d, V), 0.02)
+    y = torch.randint(0, V, (N,), generator=g, device=dev(), dtype=torch.int32)
+    R = rand((N, V), 0.1)
+    q = rand((V,), 0.05, torch.float32)
+    nv = torch.full((1,), N, dtype=torch.int32, device=dev())
+    dW = torch.full((d, V + pad + 1), 7.0, dtype=out, device=dev())
+    dH = torch.full((N, d + pad + 1), 7.0, dtype=out, device=dev())
+    bom.bom_head_vjp(H, W, R, y, q, nv, lam=0.5, dW=dW[:, :V], dH=dH[:, :d])
+    G = (0.5 * R.double() + 0.5 * q.double()) / N
+    for got, ref, k in ((dW[:, :V], H.double().t() @ G, N), (dH[:, :d], G @ W.double().t(), V)):
+        # fp32 sums of k exact products (error below sqrt(k) 2^-23 of the typical value), then one rounding to bf16
+        lim = ref.norm() / ref.numel() ** 0.5 * k ** 0.5 * 2.0 ** -20 + (ref.abs() * 2.0 ** -8 if out == torch.bfloat16 else 0.0)
+        assert bool(((got.double() - ref).abs() <= lim).all())
+    assert (dW[:, V:] == 7.0).all() and (dH[:, d:] == 7.0).all()
+    Z = torch.full((N, V + pad + 1), 7.0, dtype=torch.bfloat16, device=dev())
+    bom.bom_head_forward(H, W, Z=Z[:, :V])
+    ref = H.double() @ W.double()
+    assert bool(((Z[:, :V].double() - ref).abs() <= ref.abs() * 2.0 ** -8 + 1e-5).all()) and (Z[:, V:] == 7.0).all()
