@@ -794,6 +794,7 @@ struct WideArgs {
     float* part;
     const uint16_t* bias;   // forward: bf16 bias [Nn] or null
     const float* add;       // dH: fp32 [M][Nn] added to the output, or null
+    int units;              // streamed forward: ids of its units are below this
 };
 
 // Products of the 64-deep kernel: C = A B with
@@ -813,8 +814,15 @@ constexpr int kWideDH = 0, kWideDW = 1, kWideFWD = 2;
 // that would cross the end of the row is moved back to the row's last eight columns: along n (dW, forward) the
 // epilogue maps its tile columns to where they came from, along k (dH) the main loop stops at the last whole
 // chunk and the K % 8 columns left go through one MFMA step of their own before it.
-template <int MODE, typename TO, int NW, bool UA = false>
-__device__ __forceinline__ void wide_tile(const WideArgs& args, int id, uint16_t (&lds)[2][2][WSE], float (&rv_s)[LB]) {
+// STREAM (forward): the workgroup runs units id, id + gridDim.x, ... and its loads run on across the end of a tile, so
+// that the next tile's first two k tiles are on their way (the first already in LDS) while this one is stored. The
+// stores then leave through LDS of their own (`stage`, 4 KB per wave) and are buffer stores, with no branch around them:
+// a count of outstanding accesses that differs between paths would make the next tile's first loads wait for them.
+// Forward 4096 x 1024 x 50304: 417 us with one tile per workgroup, 396 streamed; 8192 x 2048 x 50304: 1464, 1450; with rows
+// of 50257 columns (4088 x 1024): 473, 453.
+template <int MODE, typename TO, int NW, bool UA = false, bool STREAM = false>
+__device__ __forceinline__ void wide_tile(const WideArgs& args, int id, uint16_t (&lds)[2][2][WSE], float* rv_s,
+                                          char* stage = nullptr) {
     static_assert(NW == 4 || NW == 8, "four or eight waves");
     constexpr int KT = WKT;
     constexpr int WCOLS = NW == 4 ? 128 : 64;   // columns of a wave's part of the tile
@@ -826,6 +834,7 @@ __device__ __forceinline__ void wide_tile(const WideArgs& args, int id, uint16_t
     constexpr bool KA = MODE != kWideDW;       // operand A k-contiguous
     constexpr bool KB = MODE == kWideDH;       // operand B k-contiguous
     static_assert(!UA || NW == 8, "unaligned rows: eight waves");
+    static_assert(!STREAM || (MODE == kWideFWD && NW == 8 && sizeof(TO) == 2), "streamed: the forward");
     const uint16_t* __restrict__ Xa = args.Xa;
     const int64_t lda = args.lda;
     const uint16_t* __restrict__ Xb = args.Xb;
@@ -841,12 +850,23 @@ __device__ __forceinline__ void wide_tile(const WideArgs& args, int id, uint16_t
     const float beta = args.beta;
     float* __restrict__ part = args.part;
     int tm, tn, kz;
-    if (!unit_of(tr, MODE != kWideDH, id, &tm, &tn, &kz)) return;
-    // uniform per workgroup: keep them scalar so that the buffer descriptors stay in SGPRs
-    tm = __builtin_amdgcn_readfirstlane(tm);
-    tn = __builtin_amdgcn_readfirstlane(tn);
-    kz = __builtin_amdgcn_readfirstlane(kz);
-    const int m0 = tm * LB, n0 = tn * LB;
+    // the first unit from *u on (every gridDim.x-th if streamed) that is a tile; its numbers are uniform per workgroup:
+    // keep them scalar so that the buffer descriptors stay in SGPRs
+    auto unit_from = [&](int* u) {
+        bool is = unit_of(tr, MODE != kWideDH, *u, &tm, &tn, &kz);
+        while (STREAM && !is) {
+            if ((*u += (int)gridDim.x) >= args.units) break;
+            is = unit_of(tr, MODE != kWideDH, *u, &tm, &tn, &kz);
+        }
+        tm = __builtin_amdgcn_readfirstlane(tm);
+        tn = __builtin_amdgcn_readfirstlane(tn);
+        kz = __builtin_amdgcn_readfirstlane(kz);
+        return is;
+    };
+    if (!unit_from(&id)) return;
+    int m0 = tm * LB, n0 = tn * LB;       // the tile computed
+    int lid = id, lm0 = m0, ln0 = n0;     // the tile loaded (streamed: up to two k tiles ahead)
+    bool lany = true;
     const int kb = kz * kps, ke = min(Km, kb + kps);
     const int nk = (ke - kb + KT - 1) / KT;
     const int l = threadIdx.x % kWave;
@@ -893,16 +913,20 @@ __device__ __forceinline__ void wide_tile(const WideArgs& args, int id, uint16_t
     for (int q = 0; q < CPO; ++q) {
         geo(KA, lda, M - m0, q, &voff_a[q], &kc_a[q], &ok_a[q]);
         geo(KB, ldb, Nn - n0, q, &voff_b[q], &kc_b[q], &ok_b[q]);
-        if constexpr (UA && !KB) {   // offsets from column 0, the chunk across the last column moved back, none past it
-            const int chunk = (wave * CPO + q) * 64 + l;
-            const int krow = chunk / 32, c0 = n0 + (((chunk % 32) ^ ((krow & 3) << 2)) << 3);
-            const int c = c0 + 8 <= Nn ? c0 : Nn - 8;
-            voff_b[q] = c0 < Nn ? (int)((int64_t)krow * ldb * 2) + c * 2 : kOob;
-        }
+        if constexpr (STREAM) ok_a[q] = true;   // rows past the last one lie past the descriptor's end (lda >= K)
     }
-    // k-contiguous operands: one descriptor per workgroup over the tile's rows (exact extent)
-    const int bytes_ta = KA ? (int)(((int64_t)(min(LB, M - m0) - 1) * lda + K) * 2) : 0;
-    const int bytes_tb = KB ? (int)(((int64_t)(min(LB, Nn - n0) - 1) * ldb + K) * 2) : 0;
+    auto set_columns = [&]() {   // UA: offsets from column 0, the chunk across the last column moved back, none past it
+        if constexpr (UA && !KB) {
+#pragma unroll
+            for (int q = 0; q < CPO; ++q) {
+                const int chunk = (wave * CPO + q) * 64 + l;
+                const int krow = chunk / 32, c0 = ln0 + (((chunk % 32) ^ ((krow & 3) << 2)) << 3);
+                const int c = c0 + 8 <= Nn ? c0 : Nn - 8;
+                voff_b[q] = c0 < Nn ? (int)((int64_t)krow * ldb * 2) + c * 2 : kOob;
+            }
+        }
+    };
+    set_columns();
     struct TileLoad {
         const uint16_t* ba;
         const uint16_t* bb;
@@ -915,24 +939,39 @@ __device__ __forceinline__ void wide_tile(const WideArgs& args, int id, uint16_t
         const int nv = min(KT, ke - tl.k0);
         const int nv1 = max(nv, 1);
         const int kr = min(tl.k0, K - 1);
-        if constexpr (KA) {
-            tl.ba = Xa + (int64_t)m0 * lda;
-            tl.bytes_a = bytes_ta;
+        if constexpr (KA) {   // k-contiguous operands: one descriptor over the tile's rows (exact extent)
+            tl.ba = Xa + (int64_t)lm0 * lda;
+            tl.bytes_a = (int)(((int64_t)(min(LB, M - lm0) - 1) * lda + K) * 2);
         } else {
             tl.ba = Xa + (int64_t)kr * lda + m0;
             tl.bytes_a = nv > 0 ? (int)(((int64_t)(nv1 - 1) * lda + (M - m0)) * 2) : 0;
         }
         if constexpr (KB) {
-            tl.bb = Xb + (int64_t)n0 * ldb;
-            tl.bytes_b = bytes_tb;
+            tl.bb = Xb + (int64_t)ln0 * ldb;
+            tl.bytes_b = (int)(((int64_t)(min(LB, Nn - ln0) - 1) * ldb + K) * 2);
         } else if constexpr (UA) {
             tl.bb = Xb + (int64_t)kr * ldb;
             tl.bytes_b = nv > 0 ? (int)(((int64_t)(nv1 - 1) * ldb + Nn) * 2) : 0;
         } else {
-            tl.bb = Xb + (int64_t)kr * ldb + n0;
-            tl.bytes_b = nv > 0 ? (int)(((int64_t)(nv1 - 1) * ldb + (Nn - n0)) * 2) : 0;
+            tl.bb = Xb + (int64_t)kr * ldb + ln0;
+            tl.bytes_b = nv > 0 ? (int)(((int64_t)(nv1 - 1) * ldb + (Nn - ln0)) * 2) : 0;
         }
+        if (!lany) tl.bytes_a = tl.bytes_b = 0;
         return tl;
+    };
+    int lkt = 0;   // streamed: k tile loaded last
+    auto next_load = [&](int kt) {   // the k tile after it (of the next unit past the last one), or this tile's k tile kt
+        if constexpr (!STREAM) return tile_load(kt);
+        if (++lkt == nk) {
+            lkt = 0;
+            lid += (int)gridDim.x;
+            if ((lany = lany && lid < args.units && unit_from(&lid))) {
+                lm0 = tm * LB;
+                ln0 = tn * LB;
+                set_columns();
+            }
+        }
+        return tile_load(lkt);
     };
     // copy op q < 2 CPO: q < CPO operand A, else operand B
     auto load_one = [&](const TileLoad& tl, int q) {
@@ -1044,19 +1083,20 @@ __device__ __forceinline__ void wide_tile(const WideArgs& args, int id, uint16_t
         }
     }
     {
-        const TileLoad t0 = tile_load(0), t1 = tile_load(1);
+        const TileLoad t0 = tile_load(0);
 #pragma unroll
         for (int q = 0; q < 2 * CPO; ++q) rg[q] = load_one(t0, q);
 #pragma unroll
         for (int q = 0; q < 2 * CPO; ++q) write_one(0, q, rg[q]);
+        const TileLoad t1 = next_load(1);
 #pragma unroll
         for (int q = 0; q < 2 * CPO; ++q) rg[q] = load_one(t1, q);
     }
     __syncthreads();
     read_frags(0, 0, a0, b0);
-    for (int kt = 0; kt < nk; ++kt) {
-        const int cur = kt & 1, nxt = cur ^ 1;
-        const TileLoad tl = tile_load(kt + 2);
+    auto k_tile = [&](int cur, int kt) {
+        const int nxt = cur ^ 1;
+        const TileLoad tl = next_load(kt + 2);
         read_frags(cur, 1, a1, b1);
         step(a0, b0, 0, nxt, tl, rg);
         __builtin_amdgcn_sched_barrier(0);
@@ -1073,7 +1113,63 @@ __device__ __forceinline__ void wide_tile(const WideArgs& args, int id, uint16_t
         step(a1, b1, -1, nxt, tl, rg);
         spread_reads();
         __builtin_amdgcn_sched_barrier(0);
+    };
+    if constexpr (STREAM) {
+        static_assert(NJ == 2, "eight waves");
+        const uint16_t* __restrict__ bias = args.bias;
+        char* mine = stage + wave * 4096;
+        float bv[NJ];
+        int cur = 0;
+        // the tile's first k tile, apart from the others: the accesses outstanding before it are the stores
+        auto first = [&]() {
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) {
+                const int n = out_col(wn * WCOLS + j * 32 + l % 32);
+                bv[j] = bias && n < Nn ? bf16_to_f32(bias[n]) : -0.f;   // x + -0 = x
+            }
+            k_tile(cur, 0);
+            cur ^= 1;
+        };
+        first();
+        for (;;) {
+            for (int kt = 1; kt < nk; ++kt) {
+                k_tile(cur, kt);
+                cur ^= 1;
+            }
+            const int n8 = n0 + wn * WCOLS + l % 8 * 8, at = UA ? min(n8, Nn - 8) : n8;
+            const auto desc = make_desc(out + (int64_t)m0 * ldo, (int)(((int64_t)(min(LB, M - m0) - 1) * ldo + Nn) * 2));
+            int vo = n8 < Nn ? (int)((wm * 128 + l / 8) * ldo + at) * 2 : kOob;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+#pragma unroll
+                for (int j = 0; j < NJ; ++j)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        const int row = (r / 4) * 8 + (l / 32) * 4 + r % 4;
+                        reinterpret_cast<TO*>(mine)[row * WCOLS + (j ^ (l / 32)) * 32 + l % 32] =
+                            f32_to_bf16(acc[i][j][r] + bv[j]);
+                        acc[i][j][r] = 0.f;
+                    }
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const int row = t * 8 + l / 8, c = (l % 8 * 8) ^ (((row >> 2) & 1) * 32);
+                    const u32x4_t v = *reinterpret_cast<const u32x4_t*>(reinterpret_cast<const TO*>(mine) + row * WCOLS + c);
+                    __builtin_amdgcn_raw_buffer_store_b128(v, desc, vo, 0, kNonTemporal);
+                    vo += (int)ldo * 16;
+                }
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+            }
+            id += (int)gridDim.x;
+            if (id >= args.units || !unit_from(&id)) return;
+            m0 = tm * LB;
+            n0 = tn * LB;
+            first();
+        }
     }
+    for (int kt = 0; kt < nk; ++kt) k_tile(kt & 1, kt);
     __syncthreads();
     // The tile leaves through LDS, one wave's part of it at a time (16 KB, 32 KB with four waves; no barrier: a wave
     // reads what it wrote): value(tile row, 32-column block j, accumulator) of every element as S, then 16-byte chunks
@@ -1179,6 +1275,12 @@ __global__ __launch_bounds__(NW * 64, 1) void lds256w_kernel(WideArgs a) {
 }
 
 // The head forward Z = H W (+ b) in bf16 on the same tiles (fp32 accumulation, one rounding of Z).
+template <bool UA>
+__global__ __launch_bounds__(512, 1) void lds256w_fwd_stream_kernel(WideArgs a) {
+    __shared__ __attribute__((aligned(1024))) uint16_t lds[2][2][WSE];
+    __shared__ __attribute__((aligned(1024))) char stage[8 * 4096];
+    wide_tile<kWideFWD, uint16_t, 8, UA, true>(a, blockIdx.x, lds, nullptr, stage);
+}
 template <typename TO, int NW, bool UA = false>
 __global__ __launch_bounds__(NW * 64, 1) void lds256w_fwd_kernel(WideArgs a) {
     __shared__ __attribute__((aligned(1024))) uint16_t lds[2][2][WSE];
@@ -2484,9 +2586,14 @@ hipError_t launch_head_forward(const void* H, int64_t ldh, const void* W, int64_
         const bool flat = cdiv(NT, 8) * MT > 32 * cdiv((int64_t)MT * NT, kCUs);
         const TileRange tr{MT, 0, NT, 1, 0, 0, 0, 0, flat ? 2 : xcd_blocked(MT)};
         const WideArgs wa{H16, ldh, W16, ldw, N, V, d, (int)(cdiv(d, WKT) * WKT), tr, nullptr, nullptr, nullptr, Z, ldz,
-                          0.f, nullptr, b16};
-        const dim3 grid((unsigned)(flat ? (int64_t)NT * MT : cdiv(NT, 8) * 8 * MT));
-        if (ua)
+                          0.f, nullptr, b16, nullptr, (int)(flat ? (int64_t)NT * MT : cdiv(NT, 8) * 8 * MT)};
+        const dim3 grid((unsigned)wa.units);
+        const dim3 sgrid((unsigned)std::min(wa.units, kCUs));
+        // streamed tiles; their stores' offsets reach over 256 rows of Z
+        if (wave_cfg().fwd == 8 && ldz < (1 << 21))
+            hipLaunchKernelGGL(ua ? lds256w_fwd_stream_kernel<true> : lds256w_fwd_stream_kernel<false>, sgrid, dim3(512), 0,
+                               st, wa);
+        else if (ua)
             hipLaunchKernelGGL((lds256w_fwd_kernel<uint16_t, 8, true>), grid, dim3(512), 0, st, wa);
         else if (wave_cfg().fwd == 8)
             hipLaunchKernelGGL((lds256w_fwd_kernel<uint16_t, 8>), grid, dim3(512), 0, st, wa);

@@ -38,3 +38,23 @@ def test_tile_edges(N, d, V, pad, out):
     bom.bom_head_forward(H, W, Z=Z[:, :V])
     ref = H.double() @ W.double()
     assert bool(((Z[:, :V].double() - ref).abs() <= ref.abs() * 2.0 ** -8 + 1e-5).all()) and (Z[:, V:] == 7.0).all()
+
+
+# forward tiles streamed one after another by a workgroup: one k tile and less, a part of a second, several, both orders of
+# the tiles and a row pitch of Z past the streamed stores' range (single tiles)
+@pytest.mark.parametrize("N,d,V,ldz", [(4099, 40, 20000, 0), (4099, 72, 20003, 0), (4400, 64, 16648, 3), (9000, 136, 2568, 0),
+                                       (2300, 200, 33288, 1), (257, 64, 20008, 1 << 21)])
+@pytest.mark.parametrize("bias", [False, True])
+def test_streamed_forward(N, d, V, ldz, bias):
+    log(f"[streamed forward] N={N} d={d} V={V} ldz={ldz} bias={bias}")
+    g = torch.Generator(device=dev()).manual_seed(14)
+
+    def rand(shape, std):
+        return (torch.randn(shape, generator=g, device=dev()) * std).to(torch.bfloat16)
+
+    H, W = rand((N, d), 1.0), rand((d, V), 0.02)
+    b = rand((V,), 0.1) if bias else None
+    Z = torch.full((N, ldz if ldz > V else V + ldz), 7.0, dtype=torch.bfloat16, device=dev())
+    bom.bom_head_forward(H, W, b=b, Z=Z[:, :V])
+    ref = H.double() @ W.double() + (b.double() if bias else 0.0)
+    assert bool(((Z[:, :V].double() - ref).abs() <= ref.abs() * 2.0 ** -8 + 1e-5).all()) and (Z[:, V:] == 7.0).all()
