@@ -18,6 +18,8 @@
 // (per-workgroup fp64 partial sums, one finishing workgroup). Factored layout: no extra pass over u;
 // the statistics kernel keeps the row sums rho_i of u'^2 unclipped, their total is ||u'||^2, and
 // the finish kernels fold c^2 into the updates of Rr and Cc before the parameter step uses c u'.
+#include <type_traits>
+
 #include "common.hpp"
 #include "kernels.hpp"
 
@@ -27,6 +29,24 @@ namespace {
 constexpr int kUpdThreads = 256;
 constexpr int kFacRowsPerWG = 64;   // rows of u per statistics workgroup (inside one block)
 constexpr int kFacUpdRows = 8;      // rows per update workgroup
+
+// A numerator that is read twice (the norm or the statistics, then the step) is read the second time from its end: the
+// first pass streams past the 256 MB memory-side cache except over the numerator's last kKeepBytes, which it leaves there.
+// Clipped dense step: 41M parameters 157 -> 149 us, 146M 571 -> 541, 596M 2341 -> 2299; factored: 124M 336 -> 329, 350M
+// 919 -> 913. The order alone gave nothing (non-temporal reads are not kept); 128 MB gave a third of
+// it, and plain loads throughout cost the factored step 45 us at 1.1G parameters. There the last 256 MB are too small a
+// part to pay (2886 to 2890 us before, 2881 to 2910 with them): the factored step keeps a numerator of up to 2 GB only.
+constexpr int64_t kKeepBytes = 256ll << 20;
+// first element, of n of `bytes` each (of u, or of u and h), that the first pass leaves in the cache
+__device__ __forceinline__ int64_t keep_from(int64_t n, int bytes) { return n - kKeepBytes / bytes; }
+__host__ __device__ __forceinline__ bool factored_keeps(int64_t P) { return P <= 8 * kKeepBytes / 4; }
+template <bool KEEP, typename V, typename T>
+__device__ __forceinline__ V ld_first(const T* p) {
+    if constexpr (KEEP) return *reinterpret_cast<const V*>(p);
+    else return __builtin_nontemporal_load(reinterpret_cast<const V*>(p));
+}
+// block of the second pass over data that a first pass has left in the cache
+__device__ __forceinline__ int64_t from_end(bool second) { return second ? (int64_t)gridDim.x - 1 - blockIdx.x : blockIdx.x; }
 
 __device__ __forceinline__ float decay_of(int64_t e, const SegTable& t) {
     float wd = t.wd_default;
@@ -64,7 +84,7 @@ __global__ __launch_bounds__(kUpdThreads) void update_dense_vec4_kernel(float* _
                                                                         const float* __restrict__ h, int64_t head,
                                                                         int64_t nvec, int64_t P, SegTable segs,
                                                                         UpdateScalars sc) {
-    const int64_t q = (int64_t)blockIdx.x * kUpdThreads + threadIdx.x;
+    const int64_t q = from_end(sc.clip != nullptr) * kUpdThreads + threadIdx.x;
     sc = clipped(sc);
     if (q >= nvec) {
         const int64_t r = q - nvec;
@@ -182,7 +202,7 @@ __global__ __launch_bounds__(kUpdThreads) void update_dense_bf16x8_kernel(uint16
                                                                           const uint16_t* __restrict__ h, int64_t head,
                                                                           int64_t nvec, int64_t P, SegTable segs,
                                                                           UpdateScalars sc) {
-    const int64_t q = (int64_t)blockIdx.x * kUpdThreads + threadIdx.x;
+    const int64_t q = from_end(sc.clip != nullptr) * kUpdThreads + threadIdx.x;
     sc = clipped(sc);
     if (q >= nvec) {
         const int64_t r = q - nvec;
@@ -390,7 +410,7 @@ __global__ __launch_bounds__(kUpdThreads) void factored_update_rows_kernel(float
                                                                           UpdateScalars sc) {
     constexpr int BC = NV * 256;
     constexpr int KV = NV / 4;   // 16-byte groups per thread
-    const int64_t i = blockIdx.x;
+    const int64_t i = from_end(factored_keeps(P));
     sc = clipped(sc);
     const int64_t b = i / block_rows;
     const float rs = rsum[b];
@@ -438,7 +458,7 @@ __global__ __launch_bounds__(kUpdThreads) void factored_adamw_rows_kernel(float*
                                                                           UpdateScalars sc) {
     constexpr int BC = NV * 256;
     constexpr int KV = NV / 4;
-    const int64_t i = blockIdx.x;
+    const int64_t i = from_end(factored_keeps(P));
     const int64_t b = i / block_rows;
     const float rs = rsum[b];
     const float a = rs > 0.f ? Rr[i] / rs * sc.inv_bc2 : 0.f;
@@ -473,7 +493,8 @@ __global__ __launch_bounds__(kUpdThreads) void factored_adamw_rows_kernel(float*
     }
 }
 
-template <bool SPLIT, int NV>
+// KEEP: factored_keeps(P)
+template <bool SPLIT, int NV, bool KEEP>
 __global__ __launch_bounds__(kUpdThreads) void factored_stats_rows_kernel(const float* __restrict__ u,
                                                                           const float* __restrict__ h, int64_t P,
                                                                           int64_t nrows, int64_t block_rows,
@@ -491,16 +512,16 @@ __global__ __launch_bounds__(kUpdThreads) void factored_stats_rows_kernel(const 
     f32x4 kap[NV];
 #pragma unroll
     for (int k = 0; k < NV; ++k) kap[k] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int64_t i = r0 + w; i < r1; i += kUpdThreads / kWave) {
+    auto row = [&](int64_t i, auto kept) {
         f32x4 a[NV];
 #pragma unroll
         for (int k = 0; k < NV; ++k) {
             const int64_t e = i * BC + (k * kWave + l) * 4;
             const bool ok = e < P;
             const int64_t ec = ok ? e : P - 4;
-            const f32x4 u4 = ld_stream(u + ec);
+            const f32x4 u4 = ld_first<decltype(kept)::value, f32x4>(u + ec);
             f32x4 h4 = {0.f, 0.f, 0.f, 0.f};
-            if (SPLIT) h4 = ld_stream(h + ec);
+            if (SPLIT) h4 = ld_first<decltype(kept)::value, f32x4>(h + ec);
             const float z = ok ? 1.f : 0.f;
 #pragma unroll
             for (int c = 0; c < 4; ++c) a[k][c] = z * numerator<SPLIT>(u4[c], h4[c], sc);
@@ -517,6 +538,14 @@ __global__ __launch_bounds__(kUpdThreads) void factored_stats_rows_kernel(const 
             if (rho_out) rho_out[i] = rho;   // clipping: Rr is updated once the factor is known
             else Rr[i] = sc.beta2 * Rr[i] + sc.one_minus_beta2 * rho;
         }
+    };
+    int64_t i = r0 + w;   // two loops: the two loads in one would become plain ones
+    if constexpr (KEEP) {
+        const int64_t keep = keep_from(P, SPLIT ? 8 : 4) / BC;   // rows from it on
+        for (; i < min(r1, keep); i += kUpdThreads / kWave) row(i, std::false_type{});
+        for (; i < r1; i += kUpdThreads / kWave) row(i, std::true_type{});
+    } else {
+        for (; i < r1; i += kUpdThreads / kWave) row(i, std::false_type{});
     }
     if (w > 0) {
 #pragma unroll
@@ -774,12 +803,13 @@ __global__ __launch_bounds__(kUpdThreads) void clip_partial_kernel(const float* 
         const int64_t nvec = n / 4;
         int64_t q = (int64_t)blockIdx.x * kUpdThreads + t;
         // kClipUnroll groups per thread in flight, then the remainder one group at a time
-        for (; q + (kClipUnroll - 1) * stride < nvec; q += kClipUnroll * stride) {
+        const int64_t keep = SQUARE ? keep_from(n, SPLIT ? 8 : 4) / 4 : 0;   // groups from about it on
+        auto groups = [&](auto kept) {
             f32x4 u4[kClipUnroll], h4[kClipUnroll];
 #pragma unroll
             for (int k = 0; k < kClipUnroll; ++k) {
-                u4[k] = ld_stream(u + (q + k * stride) * 4);
-                h4[k] = SPLIT ? ld_stream(h + (q + k * stride) * 4) : f32x4{0.f, 0.f, 0.f, 0.f};
+                u4[k] = ld_first<decltype(kept)::value, f32x4>(u + (q + k * stride) * 4);
+                h4[k] = SPLIT ? ld_first<decltype(kept)::value, f32x4>(h + (q + k * stride) * 4) : f32x4{0.f, 0.f, 0.f, 0.f};
             }
 #pragma unroll
             for (int k = 0; k < kClipUnroll; ++k)
@@ -788,11 +818,13 @@ __global__ __launch_bounds__(kUpdThreads) void clip_partial_kernel(const float* 
                     const double x = SQUARE ? (double)numerator<SPLIT>(u4[k][c], h4[k][c], sc) : (double)u4[k][c];
                     acc += SQUARE ? x * x : x;
                 }
-        }
+        };
+        for (; q + (kClipUnroll - 1) * stride < min(nvec, keep); q += kClipUnroll * stride) groups(std::false_type{});
+        for (; q + (kClipUnroll - 1) * stride < nvec; q += kClipUnroll * stride) groups(std::true_type{});
         for (; q < nvec; q += stride) {
-            const f32x4 u4 = ld_stream(u + q * 4);
+            const f32x4 u4 = ld_first<true, f32x4>(u + q * 4);
             f32x4 h4 = {0.f, 0.f, 0.f, 0.f};
-            if (SPLIT) h4 = ld_stream(h + q * 4);
+            if (SPLIT) h4 = ld_first<true, f32x4>(h + q * 4);
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
                 const double x = SQUARE ? (double)numerator<SPLIT>(u4[c], h4[c], sc) : (double)u4[c];
@@ -824,10 +856,11 @@ __global__ __launch_bounds__(kUpdThreads) void clip_partial_bf16_kernel(const ui
     int64_t done = 0;
     if (vec8) {
         const int64_t nvec = n / 8;
-        for (int64_t q = (int64_t)blockIdx.x * kUpdThreads + t; q < nvec; q += stride) {
-            const u32x4_t u8 = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(u + q * 8));
+        const int64_t keep = keep_from(n, SPLIT ? 4 : 2) / 8;   // groups from about it on
+        auto group = [&](int64_t q, auto kept) {
+            const u32x4_t u8 = ld_first<decltype(kept)::value, u32x4_t>(u + q * 8);
             u32x4_t h8 = {0u, 0u, 0u, 0u};
-            if (SPLIT) h8 = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(h + q * 8));
+            if (SPLIT) h8 = ld_first<decltype(kept)::value, u32x4_t>(h + q * 8);
 #pragma unroll
             for (int c = 0; c < 8; ++c) {
                 const float uc = c & 1 ? bf16_hi(u8[c / 2]) : bf16_lo(u8[c / 2]);
@@ -835,7 +868,10 @@ __global__ __launch_bounds__(kUpdThreads) void clip_partial_bf16_kernel(const ui
                 const double x = (double)numerator<SPLIT>(uc, hc, sc);
                 acc += x * x;
             }
-        }
+        };
+        int64_t q = (int64_t)blockIdx.x * kUpdThreads + t;
+        for (; q < min(nvec, keep); q += stride) group(q, std::false_type{});
+        for (; q < nvec; q += stride) group(q, std::true_type{});
         done = nvec * 8;
     }
     for (int64_t e = done + (int64_t)blockIdx.x * kUpdThreads + t; e < n; e += stride) {
@@ -960,7 +996,8 @@ hipError_t run_factored_rows(float* theta, float* Rr, float* Cc, const float* u,
     float* kpart = reinterpret_cast<float*>(static_cast<char*>(ws) + L.kpart_off);
     float* rsum = reinterpret_cast<float*>(static_cast<char*>(ws) + L.rsum_off);
     float* rho = clip ? reinterpret_cast<float*>(static_cast<char*>(ws) + L.rho_off) : nullptr;
-    hipLaunchKernelGGL((factored_stats_rows_kernel<SPLIT, NV>), dim3((unsigned)L.ngroups), dim3(kUpdThreads), 0, st, u, h,
+    const auto stats = factored_keeps(P) ? factored_stats_rows_kernel<SPLIT, NV, true> : factored_stats_rows_kernel<SPLIT, NV, false>;
+    hipLaunchKernelGGL(stats, dim3((unsigned)L.ngroups), dim3(kUpdThreads), 0, st, u, h,
                        P, L.nrows, br, (int)L.groups_per_block, Rr, kpart, rho, sc);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -1234,7 +1271,8 @@ hipError_t run_adamw_factored_rows(float* theta, float* m, float* Rr, float* Cc,
     float* kpart = reinterpret_cast<float*>(static_cast<char*>(ws) + L.kpart_off);
     float* rsum = reinterpret_cast<float*>(static_cast<char*>(ws) + L.rsum_off);
     // the second moment's statistics are those of the factored BOM update with numerator g
-    hipLaunchKernelGGL((factored_stats_rows_kernel<false, NV>), dim3((unsigned)L.ngroups), dim3(kUpdThreads), 0, st, g,
+    const auto stats = factored_keeps(P) ? factored_stats_rows_kernel<false, NV, true> : factored_stats_rows_kernel<false, NV, false>;
+    hipLaunchKernelGGL(stats, dim3((unsigned)L.ngroups), dim3(kUpdThreads), 0, st, g,
                        nullptr, P, L.nrows, br, (int)L.groups_per_block, Rr, kpart, nullptr, sc);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
