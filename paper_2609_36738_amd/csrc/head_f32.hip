@@ -344,8 +344,8 @@ int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // Tile size, the length of dH's k ranges (a power of two) and dW's split or not: those of the least modelled time. A CU
 // takes its units at 20 ns per k of a 64 x 64 tile and 7.5 ns of a 32 x 32 one (the rates with several resident); a unit
-// alone on its CU waits for its loads and its own steps, 30 and 15 ns per k; a unit's start and end take 0.6 us; splits add the partial sums' traffic and the
-// reduction launch. Measured (N x d x V, tiles of 64 and of 32): 4096 x 1024 x 2000 336 and 483 us, 256 x 1024 x 1000
+// alone on its CU waits for its loads and its own steps, 30 and 15 ns per k; a unit's start and end take 0.6 us; splits
+// add the partial sums' traffic and the reduction launch. Measured (N x d x V, tiles of 64 and of 32): 4096 x 1024 x 2000 336 and 483 us, 256 x 1024 x 1000
 // 21.0 and 25.6, 1024 x 768 x 1000 50.7 and 50.5, 1024 x 128 x 10 36.5 and 20.3, 4096 x 64 x 10 23.9 and 15.9.
 // dW's sums keep one order whatever the plan: `sums` partial sums of equal k ranges, each in the order of k, added in that
 // order, either as that many units or as one unit that adds them itself. (The update divides by the gradient's own size

@@ -14,7 +14,7 @@
 // fixed-order reduction. dW = H^T G has both operands k-outer in memory (transposing LDS reads or a
 // transpose while staging); dH = G W^T has both operands k-contiguous. The fused and the 256-tile
 // kernels also take R and W with rows at any alignment and of any length (UA): a 4088 x 1024 x 50,257 head VJP takes
-// 0.93 ms with it, against 22.5 ms on the SIMT tiled GEMM that is left for bf16 with H unaligned. fp32 path: head_f32.hip.
+// 0.87 ms with it, against 22.5 ms on the SIMT tiled GEMM that is left for bf16 with H unaligned. fp32 path: head_f32.hip.
 #include <algorithm>
 #include <array>
 #include <map>
@@ -767,8 +767,8 @@ __device__ __forceinline__ bf16x8_t ld_frag_tr(const char* p) {
 // k-outer operand (dW's two) has LDS rows of 256 values per k (512 B), chunk c of row k at
 // c ^ ((k & 3) << 2), and fragments read with the transposing ds_read_b64_tr_b16 (a 16-lane group reads a
 // 4 x 16 block and each lane receives 4 consecutive k of one column); every 16-lane read phase touches
-// 16 distinct 16-byte bank groups, so there are no bank conflicts. (dW with A given as H^T, k-contiguous, from a transpose of H measured no
-// faster: the transposing reads of one operand are not what bounds it.) Tile kt+1 is written from registers at the start of
+// 16 distinct 16-byte bank groups, so there are no bank conflicts. (dW with A given as H^T, k-contiguous, from a
+// transpose of H measured no faster: the transposing reads of one operand are not what bounds it.) Tile kt+1 is written from registers at the start of
 // iteration kt and tile kt+2 loaded behind it; the barrier sits before the last MFMA step of the tile.
 // Measured on the three language-model shapes, eight waves (two per SIMD) beat four by 5-9 % on every
 // product: with one wave per SIMD the copies, LDS writes and fragment reads add to the MFMA time almost
@@ -2536,14 +2536,15 @@ __global__ __launch_bounds__(256) void head_forward_simt_kernel(const uint16_t* 
 namespace {
 // Whether the 64 x 64 tiles of the small forward beat the 256 x 256 ones. Microseconds, from both kernels over N = 64 .. 16384,
 // V = 512 .. 32000, d = 64 .. 4096: a CU takes a 64-deep step of a small tile (two resident) in 0.34 (rows at any
-// alignment 0.48), a tile alone 0.3, in groups of four steps; a round of large tiles takes 8 beside its steps, of 1.25 with
-// few tiles to 1.85 with a full chip (times 1.2 at any alignment). At d = 768 (small, large): 512 x 1000 7.1 and 24.1 us,
-// 4096 x 1000 19.2 and 26.4, 8192 x 1000 34.3 and 32.1, 256 x 32000 38.5 and 26.5; 2048 x 2048 x 4096 66 and 84.
+// alignment 0.48), a tile alone 0.3, in groups of four steps; a round of large tiles takes 5 beside its steps, of 1.25 with
+// few tiles to 1.85 with a full chip (times 1.2 at any alignment). At d = 768 (small, large): 512 x 1000 7.1 and 20.4 us,
+// 4096 x 1000 18.8 and 21.8, 8192 x 1000 33.1 and 28.9, 256 x 32000 38.3 and 21.0; 1024 x 4096 x 2048 35 and 83,
+// 2048 x 2048 x 4096 64 and 45.
 bool forward_small(int64_t N, int64_t d, int64_t V, bool ua) {
     const int64_t tiles = cdiv(N, FB) * cdiv(V, FB), T = cdiv(N, LB) * cdiv(V, LB), nk = cdiv(d, FK);
     const double n4 = (double)(cdiv(nk, FSETS) * FSETS);
     const double small = 3.0 + std::max((double)tiles * n4 / kCUs * (ua ? 0.48 : 0.34), n4 * 0.3);
-    const double large = (double)cdiv(T, kCUs) * (8.0 + (double)nk * (1.25 + 0.6 * std::min(1.0, (double)T / kCUs)));
+    const double large = (double)cdiv(T, kCUs) * (5.0 + (double)nk * (1.25 + 0.6 * std::min(1.0, (double)T / kCUs)));
     return small < large * (ua ? 1.2 : 1.0);
 }
 }  // namespace

@@ -3,9 +3,10 @@
 // token-level appendix for ignored targets).
 //
 // Three paths, all deterministic (fixed reduction orders, no floating-point atomics):
-//  * single pass (V up to ~53k bf16 / ~26k fp32): one wave per row for narrow rows, a workgroup for a small batch of them,
-//    otherwise one persistent workgroup per CU that keeps a whole row in registers or LDS, reduces max / argmax / sum across the workgroup, writes R, and
-//    accumulates its rows' residuals per column in registers; Z is read from HBM exactly once.
+//  * single pass (V up to ~53k bf16 / ~26k fp32): one wave per row for narrow rows, a workgroup for a small batch
+//    of them, otherwise one persistent workgroup per CU that keeps a whole row in registers or LDS, reduces max /
+//    argmax / sum across the workgroup, writes R, and accumulates its rows' residuals per column in registers; Z is
+//    read from HBM exactly once.
 //  * split rows (bf16 up to 524,288 columns): several workgroups share each row and exchange their
 //    per-part statistics; Z is still read once.
 //  * two pass (other shapes): a stats kernel (one wave per row, online max / sum / argmax) writes the
