@@ -38,10 +38,10 @@ METRIC = "BOM steps/s & tokens/s per config; % of HBM BW / MFMA peak per kernel"
 # also measures every other workload and reports it under "per_config"
 HEADLINE_WORKLOAD = "lm_8b_v128256"
 KERNEL_SOURCES = {
-    "bom_residual": "residual.hip",
-    "bom_ema": "ema.hip",
-    "bom_head_vjp": "head_vjp.hip",
-    "bom_update": "update.hip",
+    "bom_residual": ("residual.hip",),
+    "bom_ema": ("ema.hip",),
+    "bom_head_vjp": ("head_vjp.hip", "head_f32.hip"),
+    "bom_update": ("update.hip",),
 }
 
 
@@ -50,8 +50,8 @@ def log(msg):
 
 
 def source_hash(stage: str) -> str:
-    path = os.path.join(ROOT, "paper_2609_36738_amd", "csrc", KERNEL_SOURCES[stage])
-    return hashlib.sha256(open(path, "rb").read()).hexdigest()[:16]
+    csrc = os.path.join(ROOT, "paper_2609_36738_amd", "csrc")
+    return hashlib.sha256(b"".join(open(os.path.join(csrc, f), "rb").read() for f in KERNEL_SOURCES[stage])).hexdigest()[:16]
 
 
 def bf16_dev(bits: np.ndarray, shape, dev):
