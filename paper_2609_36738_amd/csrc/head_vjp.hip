@@ -819,7 +819,7 @@ constexpr int kWideDH = 0, kWideDW = 1, kWideFWD = 2;
 // stores then leave through LDS of their own (`stage`, 4 KB per wave) and are buffer stores, with no branch around them:
 // a count of outstanding accesses that differs between paths would make the next tile's first loads wait for them.
 // Forward 4096 x 1024 x 50304: 417 us with one tile per workgroup, 396 streamed; 8192 x 2048 x 50304: 1464, 1450; with rows
-// of 50257 columns (4088 x 1024): 473, 453.
+// of 50257 columns (4088 x 1024): 473, 444.
 template <int MODE, typename TO, int NW, bool UA = false, bool STREAM = false>
 __device__ __forceinline__ void wide_tile(const WideArgs& args, int id, uint16_t (&lds)[2][2][WSE], float* rv_s,
                                           char* stage = nullptr) {
@@ -915,18 +915,22 @@ __device__ __forceinline__ void wide_tile(const WideArgs& args, int id, uint16_t
         geo(KB, ldb, Nn - n0, q, &voff_b[q], &kc_b[q], &ok_b[q]);
         if constexpr (STREAM) ok_a[q] = true;   // rows past the last one lie past the descriptor's end (lda >= K)
     }
-    auto set_columns = [&]() {   // UA: offsets from column 0, the chunk across the last column moved back, none past it
-        if constexpr (UA && !KB) {
-#pragma unroll
-            for (int q = 0; q < CPO; ++q) {
-                const int chunk = (wave * CPO + q) * 64 + l;
-                const int krow = chunk / 32, c0 = ln0 + (((chunk % 32) ^ ((krow & 3) << 2)) << 3);
-                const int c = c0 + 8 <= Nn ? c0 : Nn - 8;
-                voff_b[q] = c0 < Nn ? (int)((int64_t)krow * ldb * 2) + c * 2 : kOob;
-            }
-        }
+    // UA, n along the rows: offsets from column 0, the chunk across the last column moved back, none past it
+    auto column_chunk = [&](int q) {
+        const int chunk = (wave * CPO + q) * 64 + l;
+        const int krow = chunk / 32, c0 = ln0 + (((chunk % 32) ^ ((krow & 3) << 2)) << 3);
+        const int c = c0 + 8 <= Nn ? c0 : Nn - 8;
+        return c0 < Nn ? (int)((int64_t)krow * ldb * 2) + c * 2 : kOob;
     };
-    set_columns();
+    if constexpr (UA && !KB && !STREAM) {
+#pragma unroll
+        for (int q = 0; q < CPO; ++q) voff_b[q] = column_chunk(q);
+    }
+    // streamed: worked out at each load from what the copies share (an offset of one row, two columns), which leaves the
+    // accumulators their registers (4088 x 1024 x 50257: 450 us with stored offsets and 7 registers spilled, 444)
+    const int row_b = (int)((int64_t)(wave * CPO * 2 + l / 32) * ldb * 2);
+    const int col_b[2] = {((l % 32) ^ ((l / 32) << 2)) << 3, ((l % 32) ^ ((2 + l / 32) << 2)) << 3};
+    static_assert(CPO % 2 == 0, "copies alternate between two columns");
     struct TileLoad {
         const uint16_t* ba;
         const uint16_t* bb;
@@ -968,7 +972,6 @@ __device__ __forceinline__ void wide_tile(const WideArgs& args, int id, uint16_t
             if ((lany = lany && lid < args.units && unit_from(&lid))) {
                 lm0 = tm * LB;
                 ln0 = tn * LB;
-                set_columns();
             }
         }
         return tile_load(lkt);
@@ -980,6 +983,11 @@ __device__ __forceinline__ void wide_tile(const WideArgs& args, int id, uint16_t
             return __builtin_amdgcn_raw_buffer_load_b128(make_desc(tl.ba, tl.bytes_a), vo, 0, 0);
         }
         const int r = q - CPO;
+        if constexpr (STREAM && UA) {
+            const int c0 = ln0 + col_b[r % 2];
+            const int vo = c0 < Nn ? row_b + r * 4 * (int)ldb + min(c0, Nn - 8) * 2 : kOob;
+            return __builtin_amdgcn_raw_buffer_load_b128(make_desc(tl.bb, tl.bytes_b), vo, 0, 0);
+        }
         const int vo = !KB ? voff_b[r] : ((ok_b[r] && tl.k0 + kc_b[r] < ke) ? voff_b[r] + tl.k0 * 2 : kOob);
         return __builtin_amdgcn_raw_buffer_load_b128(make_desc(tl.bb, tl.bytes_b), vo, 0, 0);
     };
