@@ -1269,8 +1269,17 @@ __device__ __forceinline__ void wide_tile(const WideArgs& args, int id, uint16_t
         }
     } else {
         float* pz = part + (int64_t)kz * tr.pstride;
-        emit_tile(0.f, [&](int, int, float v) { return alpha * v; }, [&](int m, int n, int, const u32x4_t& v) {
-            put(pz + (int64_t)(m - tr.pm0) * tr.ldp + (n - tr.pn0), v);
+        // Of a chunk that was moved back only the columns that no chunk before it holds: the others may lie before the
+        // rectangle (its first column is the last tile's where that tile alone splits k, with fewer than eight columns).
+        emit_tile(0.f, [&](int, int, float v) { return alpha * v; }, [&](int m, int n, int first, const u32x4_t& v) {
+            float* row = pz + (int64_t)(m - tr.pm0) * tr.ldp;
+            if (!(UA && IS_DW) || n >= first) {
+                put(row + (n - tr.pn0), v);
+            } else {
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    if (n + k >= first) row[n + k - tr.pn0] = __uint_as_float(v[k]);
+            }
         });
     }
 }

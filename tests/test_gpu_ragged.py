@@ -73,6 +73,38 @@ def test_head_vjp_any_alignment(case):
     assert float((out["db"] - ref).abs().max()) <= 1e-6
 
 
+# dW's whole rounds run over the full k range and the column tile left over splits it: a last tile of one to nine columns,
+# whose chunk across the end of the row is read from columns of the tile before it. From R, and from the logits, where the
+# last of two panels has such a tile.
+@pytest.mark.parametrize("N,d,V,logits", [(2048, 1024, 16384 + r, False) for r in (1, 3, 7, 9)] +
+                         [(4099, 3848, 4097, False), (16300, 3848, 20481, True), (16300, 3848, 20487, True)])
+@pytest.mark.parametrize("beta", [0.0, 0.5])
+def test_split_tile_of_few_columns(N, d, V, logits, beta):
+    log(f"[ragged split tile] N={N} d={d} V={V} logits={logits} beta={beta}")
+    g = torch.Generator(device=dev()).manual_seed(8)
+    H, W = _rand(g, (N, d), 1.0, torch.bfloat16), _rand(g, (d, V), 0.02, torch.bfloat16)
+    y = torch.randint(0, V, (N,), generator=g, device=dev(), dtype=torch.int32)
+    y[1::7] = -100
+    y[::5] = V - 1                     # weight on the last column
+    ok = y >= 0
+    Z = _rand(g, (N, V), 1.0, torch.bfloat16)
+    res = bom.bom_residual(Z, y)
+    q = _rand(g, (V,), 1e-3, torch.float32)
+    dW0 = _rand(g, (d, V), 1e-3, torch.float32)
+    kw = dict(lam=LAM, dW_beta=beta, row_lse=res["row_lse"] if logits else None)
+    out = bom.bom_head_vjp(H, W, Z if logits else res["R"], y, q, res["n_valid"], dW=dW0.clone(), **kw)
+    c0 = V - 300                       # the last columns, the tile before them among them
+    G = (((1 - LAM) * res["R"][:, c0:].double() + LAM * q[c0:].double()) * ok[:, None]) / int(ok.sum())
+    ref = H.double().t() @ G + beta * dW0[:, c0:].double()
+    # per column: fp32 sums of N exact products; with the logits one more rounding of R to bf16 in some elements
+    err = (out["dW"][:, c0:] - ref).norm(dim=0) / ref.norm(dim=0)
+    log(f"    column error {float(err.max()):.2e}")
+    assert float(err.max()) <= (2.0 ** -8 if logits else 1e-5)
+    ws = out["workspace"].fill_(0xFF)  # NaN in every word: a partial sum that is not written shows
+    again = bom.bom_head_vjp(H, W, Z if logits else res["R"], y, q, res["n_valid"], dW=dW0.clone(), workspace=ws, **kw)
+    assert torch.equal(again["dW"], out["dW"])
+
+
 # 64 x 64 tiles (k in one to nine steps, both operands ragged), 256 x 256 tiles, and those dealt tile by tile (the last two:
 # fewer than eight column tiles under more than 32 row tiles)
 @pytest.mark.parametrize("N,d,V,pad,off", [(33, 40, 9, 0, 0), (1, 64, 8, 1, 0), (65, 520, 130, 0, 3), (200, 328, 1000, 0, 0),
