@@ -2259,7 +2259,7 @@ Route route_of(const HeadVjpArgs& a) {
                         ((int64_t)(a.d - 1) * a.ldw + a.V) * 2 < (1LL << 31);
     const bool small = r.p.w.kind == kMfma128 && r.p.h.kind == kMfma128;
     if (!h_ok || (r.ua && (!ld_ok || (small && !fits31)))) r.p = simt_plan(a.N, a.d, a.V);
-    if (!a.dH) r.p.h.kind = kSimt;   // no dH: no rank-1 vector for it
+    if (!a.dH) r.p.h = {kSimt, 1};   // no dH: no rank-1 vector and no partial sums for it
     // small products (both on the 128-tile kernel): one fused launch, nothing staged beforehand
     const PlanOverride& ov = plan_override();
     r.fused = r.p.w.kind == kMfma128 && (!a.dH || r.p.h.kind == kMfma128) && fits31 && fused_extents(a.N, a.V) &&

@@ -58,3 +58,22 @@ def test_streamed_forward(N, d, V, ldz, bias):
     bom.bom_head_forward(H, W, b=b, Z=Z[:, :V])
     ref = H.double() @ W.double() + (b.double() if bias else 0.0)
     assert bool(((Z[:, :V].double() - ref).abs() <= ref.abs() * 2.0 ** -8 + 1e-5).all()) and (Z[:, V:] == 7.0).all()
+
+
+# dW alone where the plan of dH has whole rounds and leftover rows that split k, aligned and ragged
+@pytest.mark.parametrize("N,d,V", [(4100, 3848, 4096), (4100, 3848, 4097)])
+def test_no_dH(N, d, V):
+    log(f"[no dH] N={N} d={d} V={V}")
+    g = torch.Generator(device=dev()).manual_seed(15)
+
+    def rand(shape, std, t=torch.bfloat16):
+        return (torch.randn(shape, generator=g, device=dev()) * std).to(t)
+
+    H, W, R = rand((N, d), 1.0), rand((d, V), 0.02), rand((N, V), 0.1)
+    y = torch.randint(0, V, (N,), generator=g, device=dev(), dtype=torch.int32)
+    q = rand((V,), 0.05, torch.float32)
+    nv = torch.full((1,), N, dtype=torch.int32, device=dev())
+    a = bom.bom_head_vjp(H, W, R, y, q, nv, lam=0.5, want_dH=False)
+    ref = H.double().t() @ ((0.5 * R.double() + 0.5 * q.double()) / N)
+    # fp32 sums of N exact products
+    assert a["dH"] is None and float((a["dW"] - ref).norm() / ref.norm()) <= 1e-5
