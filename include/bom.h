@@ -167,9 +167,12 @@ bom_status bom_ema(float* q, const float* s, int64_t V, float beta1, int64_t t, 
  * I zero). With is_residual = 0 it is the logits Z, and R is formed from them here: R_ij = exp(z_ij - row_lse[i]) -
  * [j == y_i] for rows in I, 0 for the others, as bom_residual forms it for rows wider than one workgroup's registers
  * (2^(z log2 e - lse log2 e), minus 1 at the label) and rounded to dt once; it equals the stored R up to one rounding of
- * dt (bom_residual's narrow-row kernels scale exp(z - max) by 1/sum instead). Large bf16 products form it in the workspace,
- * a panel of at most about 512 MB of columns at a time; the others as their operand copies pass through registers.
- * bom_residual may then skip writing R (R = NULL there), and no [N, V] buffer of R is held.
+ * dt (bom_residual's narrow-row kernels scale exp(z - max) by 1/sum instead). bom_residual may then skip writing R (R =
+ * NULL there). Large bf16 products form R a panel of columns at a time in a workspace of
+ * bom_head_vjp_logits_workspace_bytes: a panel is all of R where that is at most 512 MB (it then costs as much memory as
+ * R), else a multiple of 2048 columns of about 512 MB, 4096 columns at least. With the workspace of
+ * bom_head_vjp_workspace_bytes, which holds no panel, they form R as they copy it, which is slower (and slow where V is
+ * not a multiple of 8 or W or Z not aligned to 16 bytes). The other products need no panel.
  *
  *   H   device [N, ldh] of dt.   W device [d, ldw] of dt (the head as d x V).
  *   R_or_Z device [N, ldr] of dt.
@@ -182,11 +185,13 @@ bom_status bom_ema(float* q, const float* s, int64_t V, float beta1, int64_t t, 
  *   dw_dt BOM_F32, or BOM_BF16 for bf16 gradient storage (dW, db formed in fp32 in the workspace, then
  *       rounded to nearest-even bf16: dW = bf16(H^T G + dW_beta * dW)).
  *   dH  device [N, lddh] of dh_dt (BOM_BF16 or BOM_F32), or NULL.
- *   workspace: at least bom_head_vjp_workspace_bytes(N, d, V, dt, dw_dt) bytes (may be 0).
+ *   workspace: at least bom_head_vjp_workspace_bytes(N, d, V, dt, dw_dt) bytes (may be 0); with is_residual = 0 best
+ *       bom_head_vjp_logits_workspace_bytes of the same arguments, which is that size plus the panel's.
  * Errors: BOM_ERR_NULL (also: row_lse missing with is_residual = 0), BOM_ERR_SHAPE (also: is_residual
  *         not 0 or 1), BOM_ERR_DTYPE, BOM_ERR_HYPER (lambda not in [0,1]), BOM_ERR_WORKSPACE, BOM_ERR_HIP.
  * ---------------------------------------------------------------------------------------- */
 size_t bom_head_vjp_workspace_bytes(int64_t N, int64_t d, int64_t V, bom_dtype dt, bom_dtype dw_dt);
+size_t bom_head_vjp_logits_workspace_bytes(int64_t N, int64_t d, int64_t V, bom_dtype dt, bom_dtype dw_dt);
 bom_status bom_head_vjp(const void* H, int64_t ldh, const void* W, int64_t ldw,
                         const void* R_or_Z, int32_t is_residual, int64_t ldr,
                         bom_dtype dt, int64_t N, int64_t d, int64_t V,

@@ -91,6 +91,8 @@ def load(build_if_missing: bool = True):
         lib.bom_ema.argtypes = [vp, vp, i64, f32, i64, vp, vp]
         lib.bom_head_vjp_workspace_bytes.restype = sz
         lib.bom_head_vjp_workspace_bytes.argtypes = [i64, i64, i64, ctypes.c_int, ctypes.c_int]
+        lib.bom_head_vjp_logits_workspace_bytes.restype = sz
+        lib.bom_head_vjp_logits_workspace_bytes.argtypes = [i64, i64, i64, ctypes.c_int, ctypes.c_int]
         lib.bom_head_vjp.restype = ctypes.c_int
         lib.bom_head_vjp.argtypes = [vp, i64, vp, i64, vp, i32, i64, ctypes.c_int, i64, i64, i64, vp, i32, vp, vp, vp,
                                      vp, f32, vp, ctypes.c_int, i64, f32, vp, vp, ctypes.c_int, i64, vp, sz, vp]
@@ -158,8 +160,9 @@ def _residual_ws(N, V, dt):
 
 
 @functools.lru_cache(maxsize=256)
-def _head_vjp_ws(N, d, V, dt, dw_dt):
-    return load().bom_head_vjp_workspace_bytes(N, d, V, dt, dw_dt)
+def _head_vjp_ws(N, d, V, dt, dw_dt, logits):
+    size = load().bom_head_vjp_logits_workspace_bytes if logits else load().bom_head_vjp_workspace_bytes
+    return size(N, d, V, dt, dw_dt)
 
 
 @functools.lru_cache(maxsize=256)
@@ -249,6 +252,11 @@ def bom_head_vjp_workspace_bytes(N: int, d: int, V: int, dt: int, dw_dt: int = B
     return load().bom_head_vjp_workspace_bytes(N, d, V, dt, dw_dt)
 
 
+def bom_head_vjp_logits_workspace_bytes(N: int, d: int, V: int, dt: int, dw_dt: int = BOM_F32) -> int:
+    """The same with the panels of R that a call from the logits runs on."""
+    return load().bom_head_vjp_logits_workspace_bytes(N, d, V, dt, dw_dt)
+
+
 def bom_head_vjp(H, W, R, labels, q_hat, n_valid, *, s=None, lam=0.5, ignore_index=-100, dW=None, dW_beta=0.0,
                  want_db=False, db=None, want_dH=True, dH=None, dh_dtype=None, workspace=None, stream=None,
                  row_lse=None) -> dict:
@@ -276,7 +284,7 @@ def bom_head_vjp(H, W, R, labels, q_hat, n_valid, *, s=None, lam=0.5, ignore_ind
         dH = torch.empty((N, d), dtype=dh_dtype or H.dtype, device=dev)
     dh_dt = _dtype_code(dH) if dH is not None else BOM_F32
     lddh = _rowmajor(dH, "dH") if dH is not None else d
-    nb = _head_vjp_ws(N, d, V, dt, dw_dt)
+    nb = _head_vjp_ws(N, d, V, dt, dw_dt, row_lse is not None)
     workspace = _workspace(nb, dev, workspace)
     _check(lib.bom_head_vjp(_ptr(H), ldh, _ptr(W), ldw, _ptr(R), 0 if row_lse is not None else 1, ldr, dt, N, d, V,
                             _ptr(labels), ignore_index, _ptr(row_lse),

@@ -164,6 +164,12 @@ size_t bom_head_vjp_workspace_bytes(int64_t N, int64_t d, int64_t V, bom_dtype d
     return bom::head_vjp_workspace_bytes(N, d, V, dt, dw_dt);
 }
 
+size_t bom_head_vjp_logits_workspace_bytes(int64_t N, int64_t d, int64_t V, bom_dtype dt, bom_dtype dw_dt) {
+    if (N < 1 || d < 1 || V < 1 || N >= kMaxDim || d >= kMaxDim || V >= kMaxDim || !is_dtype(dt) || !is_dtype(dw_dt))
+        return 0;
+    return bom::head_vjp_logits_workspace_bytes(N, d, V, dt, dw_dt);
+}
+
 bom_status bom_head_vjp(const void* H, int64_t ldh, const void* W, int64_t ldw, const void* R, int32_t is_residual,
                         int64_t ldr, bom_dtype dt, int64_t N, int64_t d, int64_t V, const int32_t* labels,
                         int32_t ignore_index, const float* row_lse, const float* q_hat, const float* s,

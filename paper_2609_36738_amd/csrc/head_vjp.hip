@@ -45,8 +45,12 @@ struct Fold {
 };
 
 struct VjpWs {
-    size_t cq_off, cqp_off, vmask_off, scal_off, zc_off, hpart_off, hsum_off, u_off, upart_off, part_off;
-    size_t panel_off, hacc_off, total;   // logits input, large products: a panel of R, and dH's sums over panels
+    size_t cq_off, cqp_off, vmask_off, scal_off, zc_off, hpart_off, hsum_off, u_off, upart_off, part_off, total;
+};
+// Past it (and past the fp32 dW and db of a bf16 gradient), for logits of large products: a panel of R, dH's sums over
+// panels, and the panels' partial sums. Bytes from its start; total is 0 where the products take no panels.
+struct PanelWs {
+    size_t hacc_off, part_off, total;
 };
 
 // Rank-1 vector u = W q_hat is summed over column chunks (one wave per row of W and chunk at a time, four
@@ -70,7 +74,8 @@ inline int u_chunks(int64_t d, int64_t V) {   // every chunk starts inside the r
 // c_i = lse_i log2 e (c_i = +inf for rows outside I, so their r is 0), minus 1 at column y_i, rounded once to the
 // operand type -- the operations bom_residual uses when it writes R, so R is the same whether it is stored or formed
 // here. The small products form it chunk by chunk as their operand copies pass through registers; the large ones form it
-// once, a panel of columns at a time, in the workspace (z_panel_kernel), and read it as stored.
+// once, a panel of columns at a time, in the workspace (z_panel_kernel), and read it as stored, or in their copies too
+// where the workspace holds no panel.
 // Eight bf16 logits of one row (columns j0 .. j0 + 7, lab_off = y_i - j0) to eight bf16 residuals; ok = false
 // gives zeros (a chunk outside the operand).
 __device__ __forceinline__ u32x4_t z_chunk_to_r(u32x4_t z, float c, int lab_off, bool ok) {
@@ -795,6 +800,8 @@ struct WideArgs {
     const uint16_t* bias;   // forward: bf16 bias [Nn] or null
     const float* add;       // dH: fp32 [M][Nn] added to the output, or null
     int units;              // streamed forward: ids of its units are below this
+    const float* zc;        // ZR: c_i of each row of the logits, and the labels
+    const int32_t* labels;
 };
 
 // Products of the 64-deep kernel: C = A B with
@@ -820,9 +827,12 @@ constexpr int kWideDH = 0, kWideDW = 1, kWideFWD = 2;
 // a count of outstanding accesses that differs between paths would make the next tile's first loads wait for them.
 // Forward 4096 x 1024 x 50304: 417 us with one tile per workgroup, 396 streamed; 8192 x 2048 x 50304: 1464, 1450; with rows
 // of 50257 columns (4088 x 1024): 473, 444.
-template <int MODE, typename TO, int NW, bool UA = false, bool STREAM = false>
+// ZR: the operand that is R (dH's A, dW's B) holds the logits, and each copy is turned into R in registers on its way to
+// LDS, once per output tile of the other dimension: for a workspace without panels. At d <= 256 and several panels it is
+// also the faster way.
+template <int MODE, typename TO, int NW, bool UA = false, bool STREAM = false, bool ZR = false>
 __device__ __forceinline__ void wide_tile(const WideArgs& args, int id, uint16_t (&lds)[2][2][WSE], float* rv_s,
-                                          char* stage = nullptr) {
+                                          char* stage = nullptr, float2* zs = nullptr) {
     static_assert(NW == 4 || NW == 8, "four or eight waves");
     constexpr int KT = WKT;
     constexpr int WCOLS = NW == 4 ? 128 : 64;   // columns of a wave's part of the tile
@@ -835,6 +845,8 @@ __device__ __forceinline__ void wide_tile(const WideArgs& args, int id, uint16_t
     constexpr bool KB = MODE == kWideDH;       // operand B k-contiguous
     static_assert(!UA || NW == 8, "unaligned rows: eight waves");
     static_assert(!STREAM || (MODE == kWideFWD && NW == 8 && sizeof(TO) == 2), "streamed: the forward");
+    static_assert(!ZR || (MODE != kWideFWD && NW == 8 && !UA), "logits: the VJP's products on aligned rows");
+    constexpr bool ZA = ZR && MODE == kWideDH, ZB = ZR && MODE == kWideDW;
     const uint16_t* __restrict__ Xa = args.Xa;
     const int64_t lda = args.lda;
     const uint16_t* __restrict__ Xb = args.Xb;
@@ -915,6 +927,19 @@ __device__ __forceinline__ void wide_tile(const WideArgs& args, int id, uint16_t
         geo(KB, ldb, Nn - n0, q, &voff_b[q], &kc_b[q], &ok_b[q]);
         if constexpr (STREAM) ok_a[q] = true;   // rows past the last one lie past the descriptor's end (lda >= K)
     }
+    // ZR: c of each row of the R operand and its label. dH: the tile's 256 rows are fixed, so both sit in LDS (zs) and each
+    // copy looks its row up as it is written, the label as an offset from the chunk's k; dW: rows change with the k tile, so
+    // both are loaded with each copy, the label as an offset from the chunk's first column. Rows outside I (c = +inf) have
+    // no label (theirs may be an ignore_index inside [0, V)).
+    float zrc[ZB ? CPO : 1];
+    int zry[ZB ? CPO : 1], zcol[ZB ? CPO : 1];
+    if constexpr (ZB) {
+#pragma unroll
+        for (int q = 0; q < CPO; ++q) {
+            const int chunk = (wave * CPO + q) * 64 + l;
+            zcol[q] = n0 + (((chunk % 32) ^ (((chunk / 32) & 3) << 2)) << 3);
+        }
+    }
     // UA, n along the rows: offsets from column 0, the chunk across the last column moved back, none past it
     auto column_chunk = [&](int q) {
         const int chunk = (wave * CPO + q) * 64 + l;
@@ -988,8 +1013,28 @@ __device__ __forceinline__ void wide_tile(const WideArgs& args, int id, uint16_t
             const int vo = c0 < Nn ? row_b + r * 4 * (int)ldb + min(c0, Nn - 8) * 2 : kOob;
             return __builtin_amdgcn_raw_buffer_load_b128(make_desc(tl.bb, tl.bytes_b), vo, 0, 0);
         }
+        if constexpr (ZB) {   // rows at or past ke read zeros, which c = +inf keeps
+            const int k = tl.k0 + kc_b[r];
+            const bool kin = k < ke;
+            const int kcl = kin ? k : K - 1;
+            zrc[r] = kin ? args.zc[kcl] : INFINITY;
+            zry[r] = args.labels[kcl] - zcol[r];
+        }
         const int vo = !KB ? voff_b[r] : ((ok_b[r] && tl.k0 + kc_b[r] < ke) ? voff_b[r] + tl.k0 * 2 : kOob);
         return __builtin_amdgcn_raw_buffer_load_b128(make_desc(tl.bb, tl.bytes_b), vo, 0, 0);
+    };
+    // ZR: copy q, of the k tile that begins at k0, as R
+    auto as_r = [&](int q, const u32x4_t& v, int k0) {
+        if constexpr (ZA) {
+            if (q < CPO) {
+                const int j0 = k0 + kc_a[q];
+                const float2 zz = zs[((wave * CPO + q) * 64 + l) / 8];
+                return z_chunk_to_r(v, zz.x, __float_as_int(zz.y) - j0, ok_a[q] && j0 < ke);
+            }
+        }
+        if constexpr (ZB)
+            if (q >= CPO) return z_chunk_to_r(v, zrc[q - CPO], zrc[q - CPO] < INFINITY ? zry[q - CPO] : -1, true);
+        return v;
     };
     auto write_one = [&](int stage, int q, const u32x4_t& v) {
         char* base = reinterpret_cast<char*>(&lds[stage][q / CPO][0]);
@@ -1048,7 +1093,8 @@ __device__ __forceinline__ void wide_tile(const WideArgs& args, int id, uint16_t
                 __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[m / NJ], b[m % NJ], acc[m / NJ][m % NJ], 0, 0, 0);
             if (q0 >= 0 && m < CPS) {
                 __builtin_amdgcn_sched_barrier(0);
-                write_one(ws, q0 + m, rg[q0 + m]);
+                if constexpr (ZR) write_one(ws, q0 + m, as_r(q0 + m, rg[q0 + m], tl.k0 - KT));
+                else write_one(ws, q0 + m, rg[q0 + m]);
                 rg[q0 + m] = load_one(tl, q0 + m);
                 __builtin_amdgcn_sched_barrier(0);
             }
@@ -1068,6 +1114,14 @@ __device__ __forceinline__ void wide_tile(const WideArgs& args, int id, uint16_t
     };
     u32x4_t rg[2 * CPO];
     bf16x8_t a0[4], b0[NJ], a1[4], b1[NJ];
+    if constexpr (ZA) {   // (held in LDS: the registers are taken in full)
+        for (int t = threadIdx.x; t < LB; t += NW * kWave) {
+            const int i = m0 + t;
+            const float c = i < M ? args.zc[i] : INFINITY;
+            zs[t] = make_float2(c, __int_as_float(c < INFINITY ? args.labels[i] : -1));
+        }
+        __syncthreads();
+    }
     if constexpr (UA && MODE == kWideDH) {
         if (Km < K && kz == 0) {   // the K % 8 columns past the last whole chunk: one MFMA step of their own
             static_assert(NW * kWave == 2 * LB, "one thread per operand row");
@@ -1095,7 +1149,10 @@ __device__ __forceinline__ void wide_tile(const WideArgs& args, int id, uint16_t
 #pragma unroll
         for (int q = 0; q < 2 * CPO; ++q) rg[q] = load_one(t0, q);
 #pragma unroll
-        for (int q = 0; q < 2 * CPO; ++q) write_one(0, q, rg[q]);
+        for (int q = 0; q < 2 * CPO; ++q) {
+            if constexpr (ZR) write_one(0, q, as_r(q, rg[q], t0.k0));
+            else write_one(0, q, rg[q]);
+        }
         const TileLoad t1 = next_load(1);
 #pragma unroll
         for (int q = 0; q < 2 * CPO; ++q) rg[q] = load_one(t1, q);
@@ -1284,11 +1341,12 @@ __device__ __forceinline__ void wide_tile(const WideArgs& args, int id, uint16_t
     }
 }
 
-template <bool IS_DW, typename TO, int NW, bool UA = false>
+template <bool IS_DW, typename TO, int NW, bool UA = false, bool ZR = false>
 __global__ __launch_bounds__(NW * 64, 1) void lds256w_kernel(WideArgs a) {
     __shared__ __attribute__((aligned(1024))) uint16_t lds[2][2][WSE];
     __shared__ float rv_s[LB];
-    wide_tile<IS_DW ? kWideDW : kWideDH, TO, NW, UA>(a, blockIdx.x, lds, rv_s);
+    __shared__ float2 zs[ZR && !IS_DW ? LB : 1];
+    wide_tile<IS_DW ? kWideDW : kWideDH, TO, NW, UA, false, ZR>(a, blockIdx.x, lds, rv_s, nullptr, zs);
 }
 
 // The head forward Z = H W (+ b) in bf16 on the same tiles (fp32 accumulation, one rounding of Z).
@@ -1309,12 +1367,13 @@ __global__ __launch_bounds__(NW * 64, 1) void lds256w_fwd_kernel(WideArgs a) {
 // tiles, so that the shorter dW tiles fill the compute units that dH's last round leaves idle instead of
 // a second launch starting after a partly empty round. nh is a multiple of 8, so each part keeps its
 // own XCD order.
-template <typename TO, typename TW, int NW, bool UA = false>
+template <typename TO, typename TW, int NW, bool UA = false, bool ZR = false>
 __global__ __launch_bounds__(NW * 64, 1) void lds256w_pair_kernel(WideArgs h, WideArgs w, int nh) {
     __shared__ __attribute__((aligned(1024))) uint16_t lds[2][2][WSE];
     __shared__ float rv_s[LB];
-    if ((int)blockIdx.x < nh) wide_tile<kWideDH, TO, NW, UA>(h, blockIdx.x, lds, rv_s);
-    else wide_tile<kWideDW, TW, NW, UA>(w, (int)blockIdx.x - nh, lds, rv_s);
+    __shared__ float2 zs[ZR ? LB : 1];
+    if ((int)blockIdx.x < nh) wide_tile<kWideDH, TO, NW, UA, false, ZR>(h, blockIdx.x, lds, rv_s, nullptr, zs);
+    else wide_tile<kWideDW, TW, NW, UA, false, ZR>(w, (int)blockIdx.x - nh, lds, rv_s);
 }
 
 // Split-K reduction for the rank-1 form over the rectangle [pm0, M) x [pn0, Nn) of the output, in split
@@ -2103,22 +2162,32 @@ VjpWs vjp_ws(int64_t N, int64_t d, int64_t V, bom_dtype dt) {
     w.part_off = align256(w.upart_off + (r1 ? (size_t)u_chunks(d, V) * d * 4 : 0));
     size_t need = dt == BOM_F32 ? vjp_f32_workspace_bytes(N, d, V, f32_dw_sums(N, d, V)) : partial_bytes(p, N, d, V);
     if (dt == BOM_BF16) need = std::max({need, partial_bytes(pu, N, d, V), partial_bytes(simt_plan(N, d, V), N, d, V)});
-    w.panel_off = w.hacc_off = w.total = align256(w.part_off + need);
-    if (dt == BOM_BF16 && r1 && V >= 8) {   // panels of R for the logits input
-        const int64_t pc = panel_cols(N, V);
-        if (pc < V) {
-            const int64_t np = panel_count(V, pc);
-            for (int64_t nc : {pc, V - (np - 1) * pc}) {
-                Plan q;
-                q.w = plan_wide(d, nc, N, true);
-                q.h = plan_wide(N, d, nc, false);
-                need = std::max(need, partial_bytes(q, N, d, nc));
-            }
+    w.total = align256(w.part_off + need);
+    return w;
+}
+// fp32 dW and db of a bf16 gradient, for the products that round them in a pass of their own
+size_t dw_scratch_bytes(int64_t d, int64_t V, bom_dtype dw_dt) {
+    return dw_dt == BOM_BF16 ? align256((size_t)d * V * 4) + align256((size_t)V * 4) : 0;
+}
+PanelWs panel_ws(int64_t N, int64_t d, int64_t V, bom_dtype dt) {
+    PanelWs w{0, 0, 0};
+    if (dt != BOM_BF16 || V < 8) return w;
+    const Plan p = make_plan(N, d, V, dt, false), pu = make_plan(N, d, V, dt, true);
+    if (p.w.kind != kRank1 && p.h.kind != kRank1 && pu.w.kind != kRank1 && pu.h.kind != kRank1) return w;
+    const int64_t pc = panel_cols(N, V);
+    w.hacc_off = align256((size_t)N * panel_ld(N, V) * 2);
+    w.part_off = align256(w.hacc_off + (pc < V ? (size_t)N * d * 4 : 0));
+    size_t need = 0;
+    if (pc < V) {
+        const int64_t np = panel_count(V, pc);
+        for (int64_t nc : {pc, V - (np - 1) * pc}) {
+            Plan q;
+            q.w = plan_wide(d, nc, N, true);
+            q.h = plan_wide(N, d, nc, false);
+            need = std::max(need, partial_bytes(q, N, d, nc));
         }
-        w.panel_off = align256(w.part_off + need);
-        w.hacc_off = align256(w.panel_off + (size_t)N * panel_ld(N, V) * 2);
-        w.total = align256(w.hacc_off + (pc < V ? (size_t)N * d * 4 : 0));
     }
+    w.total = align256(w.part_off + need);
     return w;
 }
 
@@ -2142,12 +2211,16 @@ hipError_t run_gemm(bool is_dw, const GemmPlan& g, const void* A, int64_t lda, c
             auto launch = [&](int ob, int oe, int nsplit, int kp, float* pp, const TileRange& tr) {
                 dim3 gr((unsigned)(cdiv((int64_t)(oe - ob) * nsplit, 8) * 8 * inner));
                 const WideArgs wa{a16, lda, b16, ldb, M, Nn, K, kp, tr, f.scal, rv, cv, out, ldo, beta, pp, nullptr,
-                                  add};
+                                  add, 0, f.zc, f.labels};
                 const int nw = is_dw ? wave_cfg().dw : wave_cfg().dh;
                 if (ua && is_dw)   // rows at any alignment: eight waves
                     hipLaunchKernelGGL((lds256w_kernel<true, TO, 8, true>), gr, dim3(512), 0, st, wa);
                 else if (ua)
                     hipLaunchKernelGGL((lds256w_kernel<false, TO, 8, true>), gr, dim3(512), 0, st, wa);
+                else if (f.zc != nullptr && is_dw)   // logits: eight waves, dW in fp32
+                    hipLaunchKernelGGL((lds256w_kernel<true, float, 8, false, true>), gr, dim3(512), 0, st, wa);
+                else if (f.zc != nullptr)
+                    hipLaunchKernelGGL((lds256w_kernel<false, TO, 8, false, true>), gr, dim3(512), 0, st, wa);
                 else if (is_dw && (nw == 8 || sizeof(TO) == 2))
                     hipLaunchKernelGGL((lds256w_kernel<true, TO, 8>), gr, dim3(512), 0, st, wa);
                 else if (is_dw)
@@ -2209,12 +2282,13 @@ hipError_t run_gemm(bool is_dw, const GemmPlan& g, const void* A, int64_t lda, c
 
 }  // namespace
 
-// bf16 dW / db (bf16 gradient storage): the products are formed in fp32 in the workspace past the
-// products' own part, then rounded to nearest-even bf16 in one pass (dW = bf16(dW_fp32 + beta dW)).
+// bf16 dW and db: the fp32 scratch stays in the size although most routes round where they store (H may turn out not to
+// be aligned, which the size cannot know, and then the SIMT kernels' sums go through it).
 size_t head_vjp_workspace_bytes(int64_t N, int64_t d, int64_t V, bom_dtype dt, bom_dtype dw_dt) {
-    size_t n = vjp_ws(N, d, V, dt).total;
-    if (dw_dt == BOM_BF16) n += align256((size_t)d * V * 4) + align256((size_t)V * 4);
-    return n;
+    return vjp_ws(N, d, V, dt).total + dw_scratch_bytes(d, V, dw_dt);
+}
+size_t head_vjp_logits_workspace_bytes(int64_t N, int64_t d, int64_t V, bom_dtype dt, bom_dtype dw_dt) {
+    return head_vjp_workspace_bytes(N, d, V, dt, dw_dt) + panel_ws(N, d, V, dt).total;
 }
 
 namespace {
@@ -2242,9 +2316,10 @@ namespace {
 struct Route {
     Plan p;
     bool ua, fused;   // fused: both products in the one launch of small tiles
+    bool panels;      // logits of large products: R formed in panels (else in the products' copies)
 };
 Route route_of(const HeadVjpArgs& a) {
-    Route r{make_plan(a.N, a.d, a.V, a.dt, false), false, false};
+    Route r{make_plan(a.N, a.d, a.V, a.dt, false), false, false, false};
     if (a.dt == BOM_F32) return r;
     // MFMA kernels stage 16-byte chunks: of H at 16-byte aligned addresses, of R and W too or (ua) at any (with the
     // 256-row offsets inside 31 bits); otherwise the SIMT kernels run, with their own k splits over every tile (the
@@ -2259,6 +2334,11 @@ Route route_of(const HeadVjpArgs& a) {
                         ((int64_t)(a.d - 1) * a.ldw + a.V) * 2 < (1LL << 31);
     const bool small = r.p.w.kind == kMfma128 && r.p.h.kind == kMfma128;
     if (!h_ok || (r.ua && (!ld_ok || (small && !fits31)))) r.p = simt_plan(a.N, a.d, a.V);
+    if (!a.is_residual && (r.p.w.kind == kRank1 || (a.dH && r.p.h.kind == kRank1))) {
+        // a workspace without panels: the 256-tile products form R as they copy it, which takes aligned rows
+        r.panels = a.ws_bytes >= head_vjp_logits_workspace_bytes(a.N, a.d, a.V, a.dt, a.dw_dt);
+        if (!r.panels && r.ua) r.p = simt_plan(a.N, a.d, a.V);
+    }
     if (!a.dH) r.p.h = {kSimt, 1};   // no dH: no rank-1 vector and no partial sums for it
     // small products (both on the 128-tile kernel): one fused launch, nothing staged beforehand
     const PlanOverride& ov = plan_override();
@@ -2268,14 +2348,17 @@ Route route_of(const HeadVjpArgs& a) {
 }
 }  // namespace
 
-hipError_t launch_products(const HeadVjpArgs& a, const Route& r, hipStream_t st);   // dW and db in bf16: fused or rank-1 dW
+// dW and db in bf16: the fused launch, or dW on the 256-tile kernel with R stored or in panels
+hipError_t launch_products(const HeadVjpArgs& a, const Route& r, hipStream_t st);
 
 hipError_t launch_head_vjp(const HeadVjpArgs& a, hipStream_t st) {
     const Route r = route_of(a);
     // bf16 dW and db: the fused launch and the 256-tile kernel round their fp32 sums as they store them; the others form
     // both in fp32 in the workspace and a pass rounds them (a dW of 768 x 32,000 cost 98 MB written and read back there)
-    if (a.dw_dt != BOM_BF16 || r.fused || r.p.w.kind == kRank1) return launch_products(a, r, st);
+    const bool zcopy = !a.is_residual && !r.panels;
+    if (a.dw_dt != BOM_BF16 || r.fused || (r.p.w.kind == kRank1 && !zcopy)) return launch_products(a, r, st);
     HeadVjpArgs b = a;
+    b.scratch_bytes = dw_scratch_bytes(a.d, a.V, BOM_BF16);
     char* scratch = static_cast<char*>(a.ws) + vjp_ws(a.N, a.d, a.V, a.dt).total;
     b.dW = scratch;
     b.dw_dt = BOM_F32;
@@ -2325,7 +2408,9 @@ hipError_t launch_prep(const HeadVjpArgs& a, const VjpWs& L, bool rw, bool rh, b
 hipError_t launch_from_logits(const HeadVjpArgs& a, const VjpWs& L, hipStream_t st) {
     char* base = static_cast<char*>(a.ws);
     auto at = [&](size_t off) { return reinterpret_cast<float*>(base + off); };
-    uint16_t* panel = reinterpret_cast<uint16_t*>(base + L.panel_off);
+    const PanelWs PL = panel_ws(a.N, a.d, a.V, a.dt);
+    const size_t p0 = L.total + std::max(a.scratch_bytes, dw_scratch_bytes(a.d, a.V, a.dw_dt));
+    uint16_t* panel = reinterpret_cast<uint16_t*>(base + p0);
     const int64_t ldp = panel_ld(a.N, a.V), pc = panel_cols(a.N, a.V);
     auto form = [&](int64_t c0, int64_t nc) {
         const int64_t slabs = cdiv(nc, 8192);
@@ -2347,7 +2432,7 @@ hipError_t launch_from_logits(const HeadVjpArgs& a, const VjpWs& L, hipStream_t 
     const bool hist = a.lambda != 0.f;
     if ((e = launch_prep(a, L, hist, hist && a.dH != nullptr, ua, st)) != hipSuccess) return e;
     const float *cq = at(L.cq_off), *u = at(L.u_off), *hsum = at(L.hsum_off), *vmask = at(L.vmask_off);
-    float *part = at(L.part_off), *hacc = at(L.hacc_off);
+    float *part = at(p0 + PL.part_off), *hacc = at(p0 + PL.hacc_off);
     const Fold f{cq, vmask, at(L.scal_off), at(L.cqp_off), nullptr, a.labels};
     const int64_t np = panel_count(a.V, pc);
     for (int64_t i = 0; i < np; ++i) {
@@ -2397,7 +2482,7 @@ hipError_t launch_products(const HeadVjpArgs& a, const Route& r, hipStream_t st)
     float* zc = reinterpret_cast<float*>(base + L.zc_off);
     const bool zin = !a.is_residual;   // the R argument holds the logits Z
     if (a.dt == BOM_F32) return launch_vjp_f32_products(a, f32_dw_sums(a.N, a.d, a.V), part, st);
-    if (zin && (p.w.kind == kRank1 || (a.dH && p.h.kind == kRank1))) return launch_from_logits(a, L, st);
+    if (r.panels) return launch_from_logits(a, L, st);
     if (L.part_off + partial_bytes(p, a.N, a.d, a.V) > L.total) return hipErrorInvalidValue;   // never taken
 
     if (r.fused) {
@@ -2455,15 +2540,18 @@ hipError_t launch_products(const HeadVjpArgs& a, const Route& r, hipStream_t st)
         const TileRange trh{inner, 0, oh, sh, 0, 0, a.d, (int64_t)a.N * a.d};
         const TileRange trw{inner, 0, ow, 1, 0, 0, 0, 0};
         const WideArgs wh{R16, a.ldr, W16, a.ldw, a.N, a.d, a.V, kps_h, trh, f.scal, hist ? vmask : nullptr, u, a.dH, a.lddh, 0.f,
-                          sh > 1 ? part : nullptr, nullptr};
+                          sh > 1 ? part : nullptr, nullptr, nullptr, 0, f.zc, f.labels};
         const WideArgs ww{H16, a.ldh, R16, a.ldr, a.d, a.V, a.N, kps_w, trw, f.scal, hist ? hsum : nullptr, cq, a.dW, a.lddw,
-                          a.dW_beta, nullptr, nullptr};
+                          a.dW_beta, nullptr, nullptr, nullptr, 0, f.zc, f.labels};
         const int nh = (int)(cdiv((int64_t)oh * sh, 8) * 8 * inner);
         const int nw = (int)(cdiv(ow, 8) * 8 * inner);
         const dim3 grid((unsigned)(nh + nw));
         const bool w8 = wave_cfg().pair == 8;
         const bool h16 = a.dh_dt == BOM_BF16;
-        if (a.dw_dt == BOM_BF16) {   // eight waves
+        if (zin) {   // eight waves, dW in fp32
+            const auto k = h16 ? lds256w_pair_kernel<uint16_t, float, 8, false, true> : lds256w_pair_kernel<float, float, 8, false, true>;
+            hipLaunchKernelGGL(k, grid, dim3(512), 0, st, wh, ww, nh);
+        } else if (a.dw_dt == BOM_BF16) {   // eight waves
             const auto k = ua ? (h16 ? lds256w_pair_kernel<uint16_t, uint16_t, 8, true> : lds256w_pair_kernel<float, uint16_t, 8, true>)
                               : (h16 ? lds256w_pair_kernel<uint16_t, uint16_t, 8> : lds256w_pair_kernel<float, uint16_t, 8>);
             hipLaunchKernelGGL(k, grid, dim3(512), 0, st, wh, ww, nh);

@@ -42,8 +42,11 @@ struct HeadVjpArgs {
     void* db;
     void* dH; bom_dtype dh_dt; int64_t lddh;
     void* ws; size_t ws_bytes;
+    size_t scratch_bytes = 0;   // fp32 dW and db of the same call that lie past the workspace of the products
 };
+// The second: with the panels of R that large products from the logits run on when the workspace holds them.
 size_t head_vjp_workspace_bytes(int64_t N, int64_t d, int64_t V, bom_dtype dt, bom_dtype dw_dt);
+size_t head_vjp_logits_workspace_bytes(int64_t N, int64_t d, int64_t V, bom_dtype dt, bom_dtype dw_dt);
 hipError_t launch_head_vjp(const HeadVjpArgs& a, hipStream_t stream);
 
 // fp32 operands: both products (and db) on the fp32 matrix instructions. dW is the sum of `sums` partial sums of equal

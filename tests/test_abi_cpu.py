@@ -235,3 +235,17 @@ def _adamw(lib, P=1000, beta1=0.9, v_col=None, ws=None, wsb=0, m=ctypes.c_void_p
 ])
 def test_adamw_update_rejects(lib, kw, code):
     assert _adamw(lib, **kw) == code
+
+
+# The panels of the logits route (the whole of R up to 512 MB) are in its own size only: a call with a stored R needs none.
+@pytest.mark.parametrize("N,d,V,most", [(16384, 4096, 128256, 70e6), (8192, 2048, 50304, 60e6), (4096, 768, 32000, 52e6)])
+def test_head_vjp_workspace_without_panels(lib, N, d, V, most):
+    f, z = lib.bom_head_vjp_workspace_bytes, lib.bom_head_vjp_logits_workspace_bytes
+    for fn in (f, z):
+        fn.restype, fn.argtypes = ctypes.c_size_t, [ctypes.c_int64] * 3 + [ctypes.c_int] * 2
+    for dw in (bom.BOM_F32, bom.BOM_BF16):
+        stored = f(N, d, V, bom.BOM_BF16, dw)
+        assert 0 < stored <= most + (4 * d * V + 4 * V + 512 if dw == bom.BOM_BF16 else 0)
+        assert z(N, d, V, bom.BOM_BF16, dw) >= stored + min(2 * N * V, 2 * N * 4096)
+    assert z(256, 128, 10, bom.BOM_F32, bom.BOM_F32) == f(256, 128, 10, bom.BOM_F32, bom.BOM_F32)
+    assert z(0, 128, 10, bom.BOM_BF16, bom.BOM_F32) == 0
