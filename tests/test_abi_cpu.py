@@ -3,6 +3,7 @@ bad arguments on the host before any HIP call (fake non-null pointers are never 
 import ctypes
 import os
 import re
+import time
 
 import pytest
 import torch
@@ -249,3 +250,17 @@ def test_head_vjp_workspace_without_panels(lib, N, d, V, most):
         assert z(N, d, V, bom.BOM_BF16, dw) >= stored + min(2 * N * V, 2 * N * 4096)
     assert z(256, 128, 10, bom.BOM_F32, bom.BOM_F32) == f(256, 128, 10, bom.BOM_F32, bom.BOM_F32)
     assert z(0, 128, 10, bom.BOM_BF16, bom.BOM_F32) == 0
+
+
+# Plans are kept for a program whose shapes change: asking for the 400 sizes again takes a small part of the first time
+# (each lookup takes microseconds, each plan hundreds of them).
+def test_plans_are_kept_for_many_shapes(lib):
+    f = lib.bom_head_vjp_workspace_bytes
+    f.restype, f.argtypes = ctypes.c_size_t, [ctypes.c_int64] * 3 + [ctypes.c_int] * 2
+    shapes = [(1000 + 8 * i, 1024, 24000 + 8 * (i % 7)) for i in range(400)]
+    took = []
+    for _ in range(2):
+        t = time.perf_counter()
+        sizes = [f(*s, bom.BOM_BF16, bom.BOM_F32) for s in shapes]
+        took.append(time.perf_counter() - t)
+    assert min(sizes) > 0 and took[1] < took[0] / 8
