@@ -172,7 +172,8 @@ bom_status bom_ema(float* q, const float* s, int64_t V, float beta1, int64_t t, 
  * bom_head_vjp_logits_workspace_bytes: a panel is all of R where that is at most 512 MB (it then costs as much memory as
  * R), else a multiple of 2048 columns of about 512 MB, 4096 columns at least. With the workspace of
  * bom_head_vjp_workspace_bytes, which holds no panel, they form R as they copy it, which is slower (and slow where V is
- * not a multiple of 8 or W or Z not aligned to 16 bytes). The other products need no panel.
+ * not a multiple of 8 or W or Z not aligned to 16 bytes). The other products, and aligned ones of d <= 256 over many rows,
+ * take no panel.
  *
  *   H   device [N, ldh] of dt.   W device [d, ldw] of dt (the head as d x V).
  *   R_or_Z device [N, ldr] of dt.

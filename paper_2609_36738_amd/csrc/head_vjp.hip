@@ -75,7 +75,7 @@ inline int u_chunks(int64_t d, int64_t V) {   // every chunk starts inside the r
 // operand type -- the operations bom_residual uses when it writes R, so R is the same whether it is stored or formed
 // here. The small products form it chunk by chunk as their operand copies pass through registers; the large ones form it
 // once, a panel of columns at a time, in the workspace (z_panel_kernel), and read it as stored, or in their copies too
-// where the workspace holds no panel.
+// where the workspace holds no panel or d is small.
 // Eight bf16 logits of one row (columns j0 .. j0 + 7, lab_off = y_i - j0) to eight bf16 residuals; ok = false
 // gives zeros (a chunk outside the operand).
 __device__ __forceinline__ u32x4_t z_chunk_to_r(u32x4_t z, float c, int lab_off, bool ok) {
@@ -828,8 +828,8 @@ constexpr int kWideDH = 0, kWideDW = 1, kWideFWD = 2;
 // Forward 4096 x 1024 x 50304: 417 us with one tile per workgroup, 396 streamed; 8192 x 2048 x 50304: 1464, 1450; with rows
 // of 50257 columns (4088 x 1024): 473, 444.
 // ZR: the operand that is R (dH's A, dW's B) holds the logits, and each copy is turned into R in registers on its way to
-// LDS, once per output tile of the other dimension: for a workspace without panels. At d <= 256 and several panels it is
-// also the faster way.
+// LDS, once per output tile of the other dimension: for a workspace without panels, and with one tile along d often the
+// faster way (see route_of).
 template <int MODE, typename TO, int NW, bool UA = false, bool STREAM = false, bool ZR = false>
 __device__ __forceinline__ void wide_tile(const WideArgs& args, int id, uint16_t (&lds)[2][2][WSE], float* rv_s,
                                           char* stage = nullptr, float2* zs = nullptr) {
@@ -2346,8 +2346,13 @@ Route route_of(const HeadVjpArgs& a) {
     const bool small = r.p.w.kind == kMfma128 && r.p.h.kind == kMfma128;
     if (!h_ok || (r.ua && (!ld_ok || (small && !fits31)))) r.p = simt_plan(a.N, a.d, a.V);
     if (!a.is_residual && (r.p.w.kind == kRank1 || (a.dH && r.p.h.kind == kRank1))) {
-        // a workspace without panels: the 256-tile products form R as they copy it, which takes aligned rows
-        r.panels = a.ws_bytes >= head_vjp_logits_workspace_bytes(a.N, a.d, a.V, a.dt, a.dw_dt);
+        // Without panels the 256-tile products form R as they copy it, which takes aligned rows: where the workspace holds no
+        // panel, and where one tile covers d, so that each product forms an element once, and many rows keep the products
+        // busy. Panels and copies in us, N x d x V: 16384 x 256 x 128256 3973 and 2857, 8192 x 64 x 32000 454 and 358,
+        // 6144 x 256 x 16000 225 and 200, 6144 x 64 x 8000 107 and 95; but 5120 x 256 x 64000 661 and 1391, 8192 x 256 x
+        // 4000 223 and 269, 8192 x 512 x 32000 679 and 712.
+        const bool copies = !r.ua && a.d <= LB && a.N >= 6144 && a.V >= 8000;
+        r.panels = !copies && a.ws_bytes >= head_vjp_logits_workspace_bytes(a.N, a.d, a.V, a.dt, a.dw_dt);
         if (!r.panels && r.ua) r.p = simt_plan(a.N, a.d, a.V);
     }
     if (!a.dH) r.p.h = {kSimt, 1};   // no dH: no rank-1 vector and no partial sums for it

@@ -19,7 +19,10 @@ CASES = [("one_panel_ragged", 2056, 264, 6001, 0.5, True, -100),
          # the small products (one launch, and 128-tile kernels), an ignored label inside [0, V)
          ("fused_ignored_class", 200, 64, 264, 0.5, True, 3), ("fused_ignored_class_ragged", 200, 64, 333, 0.5, True, 3),
          ("tiles128_ignored_class", 64, 128, 8200, 0.5, True, 3),
-         ("narrow_panels_no_dH", 70000, 32, 8257, 0.5, False, -100)]
+         ("narrow_panels_no_dH", 70000, 32, 8257, 0.5, False, -100),
+         # one tile along d and many rows: no panel, above and below the line in N and in V
+         ("one_d_tile", 6200, 256, 8008, 0.5, True, 5), ("one_d_tile_few_rows", 6136, 256, 8008, 0.5, True, -100),
+         ("one_d_tile_few_columns", 6200, 256, 7992, 0.5, True, -100), ("one_d_tile_no_dH", 6149, 40, 8000, 0.25, False, -100)]
 
 
 @pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
@@ -63,7 +66,7 @@ def test_head_vjp_logits_panels(case):
 SMALL_WS = [("leftovers", 2048, 1024, 16392, 0.5, True, "f32"), ("rows_left", 4100, 3848, 4096, 0.5, True, "f32"),
             ("pair", 1032, 768, 32000, 0.25, True, "f32"), ("pair_bf16_dW", 1032, 768, 32000, 0.5, True, "bf16"),
             ("odd_rows", 2049, 520, 6008, 0.5, True, "f32"), ("no_history", 2056, 264, 6000, 0.0, True, "f32"),
-            ("no_dH", 4100, 3848, 4096, 0.5, False, "bf16"), ("several_panels", 20000, 72, 16392, 0.5, True, "f32"),
+            ("no_dH", 4100, 3848, 4096, 0.5, False, "bf16"), ("several_panels", 20000, 264, 16392, 0.5, True, "f32"),
             ("ragged", 520, 264, 6001, 0.5, True, "f32"), ("ragged_bf16_dW", 520, 264, 6001, 0.5, True, "bf16")]
 
 
