@@ -2679,9 +2679,11 @@ hipError_t launch_head_forward(const void* H, int64_t ldh, const void* W, int64_
     const uint16_t* W16 = static_cast<const uint16_t*>(W);
     const uint16_t* b16 = static_cast<const uint16_t*>(b);
     auto al = [](const void* ptr, int64_t ld) { return reinterpret_cast<uintptr_t>(ptr) % 16 == 0 && ld % 8 == 0; };
-    // 256-tile MFMA kernel: 16-byte chunks along H's rows (k = d, aligned) and W's rows (n = V, at any alignment)
+    // 256-tile MFMA kernel: 16-byte chunks along H's rows (k = d, aligned) and W's rows (n = V, at any alignment; then with
+    // the offsets of a whole k tile of W's rows, those past the last one too, inside 31 bits, so that none comes back
+    // into range: a row that is not there would meet H's zeros with W's infinities)
     const bool ua = !(V % 8 == 0 && al(W, ldw));
-    if (mfma_extents(d, V, ua) && al(H, ldh) &&
+    if (mfma_extents(d, V, ua) && al(H, ldh) && (!ua || ldw < (1 << 24)) &&
         ((int64_t)(N - 1) * ldh + d) * 2 < (1LL << 31) && ((int64_t)(d - 1) * ldw + V) * 2 < (1LL << 31)) {
         if (forward_small(N, d, V, ua) && ldw < (1 << 22)) {
             FusedArgs fa{};

@@ -125,6 +125,25 @@ def test_head_forward_any_alignment(N, d, V, pad, off):
     assert (Z[:, V] == 7.0).all()
 
 
+# Rows of W so far apart that 32 of them span 4 GB: none past the last one is read in place of a row that is there, whose
+# infinity would turn the sums to NaN
+def test_head_forward_rows_far_apart():
+    N, d, V, ld = 300, 8, 1001, 1 << 26
+    log(f"[ragged forward] rows {ld} apart")
+    g = torch.Generator(device=dev()).manual_seed(16)
+    H = _rand(g, (N, d), 1.0, torch.bfloat16).abs() + 0.5
+    W = torch.empty(((d - 1) * ld + V,), dtype=torch.bfloat16, device=dev()).as_strided((d, V), (ld, 1))
+    W.copy_(_rand(g, (d, V), 0.02, torch.bfloat16))
+    W[0, 3] = float("inf")
+    Z = bom.bom_head_forward(H, W)
+    assert (Z[:, 3] == float("inf")).all()
+    Z[:, 3] = 0
+    W[0, 3] = 0
+    ref = H.double() @ W.double()
+    ref[:, 3] = 0
+    assert bool(((Z.double() - ref).abs() <= ref.abs() * 2.0 ** -8 + 1e-5).all())
+
+
 # One chunk per thread (64 to 512 threads), rows parked in LDS (1024 and 512 threads, the tail chunk in the first, a
 # middle and the last position), and rows past one workgroup's LDS (two passes).
 # The first ones: one wave per row, with one to eight chunks per lane, aligned and ragged, rows in one and several turns.
