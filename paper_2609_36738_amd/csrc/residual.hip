@@ -136,6 +136,12 @@ __device__ __forceinline__ void store_f32_chunk(float* row, int col, int V, cons
 }
 
 // ---------------------------------------------------------------------------------------------
+// What a row's exponentials are taken relative to: its maximum, or a finite floor below that of any row with a column left
+// in. Masked columns (-inf, or the type's lowest value, whose product with log2 e overflows) then give 0 where a thread, a
+// wave or a part holds nothing else, and not inf - inf.
+constexpr float kExpFloor = -2.0e38f;
+__device__ __forceinline__ float exp_base(float m) { return __builtin_elementwise_maximum(m, kExpFloor); }
+
 // Single pass. Thread `tid` owns columns (c * THREADS + tid) * VEC + k, c < NCH, k < VEC.
 // PACKED (bf16 only, for wide rows): the row stays as raw bf16 pairs and exp is evaluated twice
 // (once for the sum, once for p); otherwise e = exp(z - m) is kept in fp32 registers.
@@ -404,7 +410,7 @@ __global__ __launch_bounds__(THREADS) void residual_rows_lds_kernel(
         const int b = j & 1;
         // pass 1 (LDS): online (max, sum) over this thread's chunks, in column order, with the
         // first chunk that reached the thread's maximum; the next chunk is read ahead
-        float m = -INFINITY, l = 0.f;
+        float m = -INFINITY, r = kExpFloor, l = 0.f;   // r = exp_base(m)
         int cmax = 0;
         uint4 u_next = slots[tid];
 #pragma unroll
@@ -417,21 +423,21 @@ __global__ __launch_bounds__(THREADS) void residual_rows_lds_kernel(
             auto mx = [](float a, float b2) { return __builtin_elementwise_maximum(a, b2); };
             const float cm = mx(mx(mx(x[0], x[1]), mx(x[2], x[3])), mx(mx(x[4], x[5]), mx(x[6], x[7])));
             const float mn = mx(m, cm);
-            // a padding-only chunk after real ones leaves (m, l) unchanged (mn == m, terms zero);
-            // chunk 0 of every thread lies inside the row, so mn is finite
-            const float mn2 = mn * kLog2e;
+            // a chunk of padding or masked columns alone leaves (m, l) unchanged (mn == m, terms zero)
+            const float rn = exp_base(mn), mn2 = rn * kLog2e;
             float e[VEC];
 #pragma unroll
             for (int k = 0; k < VEC; ++k) e[k] = exp2_fast(fmaf(x[k], kLog2e, -mn2));
             const float cl = ((e[0] + e[1]) + (e[2] + e[3])) + ((e[4] + e[5]) + (e[6] + e[7]));
-            l = (c == 0 ? cl : fmaf(l, exp2_fast((m - mn) * kLog2e), cl));
+            l = (c == 0 ? cl : fmaf(l, exp2_fast((r - rn) * kLog2e), cl));
             if (c > 0 && cm > m) cmax = c;
             m = mn;
+            r = rn;
         }
         const float m_thread = m;
         // wave: the maximum, then the lanes' sums rescaled to it (DPP lane permutes)
         const float mw = wave_max_dpp(m);
-        const float lw = wave_sum_dpp(l * exp2_fast((m - mw) * kLog2e));
+        const float lw = wave_sum_dpp(l * exp2_fast((r - exp_base(mw)) * kLog2e));
         if ((tid & (kWave - 1)) == 0) {
             sh_m[b][tid / kWave] = mw;
             sh_l[b][tid / kWave] = lw;
@@ -445,7 +451,7 @@ __global__ __launch_bounds__(THREADS) void residual_rows_lds_kernel(
             const int lane = tid & (kWave - 1);
             const float mg = lane < NW ? sh_m[b][lane] : -INFINITY;
             const float mm = lane_f32(row16_max(mg), 0);
-            const float lg = lane < NW ? sh_l[b][lane] * exp2_fast((mg - mm) * kLog2e) : 0.f;
+            const float lg = lane < NW ? sh_l[b][lane] * exp2_fast((exp_base(mg) - exp_base(mm)) * kLog2e) : 0.f;
             m = mm;
             l = lane_f32(row16_sum(lg), 0);
         }
@@ -459,7 +465,7 @@ __global__ __launch_bounds__(THREADS) void residual_rows_lds_kernel(
             for (int k = VEC - 2; k >= 0; --k) k0 = (x[k] == m) ? k : k0;
             atomicMin(&sh_am[b], (cmax * THREADS + tid) * VEC + k0);
         }
-        const float lse = m + logf(l);
+        const float lse = exp_base(m) + logf(l);
         const int y = labels[i];
         bool rbad = false;
         const bool valid = label_valid(y, V, ignore_index, &rbad);
@@ -703,7 +709,7 @@ __global__ __launch_bounds__(THREADS) void residual_split_kernel(
             unpack(pad(c, Vp, slots[b][c * THREADS + tid]), &e[c * VEC]);
             max_step(c, chunk_max(&e[c * VEC]), &m, &cmax);
         }
-        const float m2 = m * kLog2e;
+        const float m2 = exp_base(m) * kLog2e;
 #pragma unroll
         for (int c = 0; c < NCH; ++c) {
             const float cl = chunk_exp_sum(&e[c * VEC], m2);
@@ -726,7 +732,7 @@ __global__ __launch_bounds__(THREADS) void residual_split_kernel(
             unpack(chunk_at(c), x);
             max_step(c, chunk_max(x), &m, &cmax);
         }
-        const float m2 = m * kLog2e;
+        const float m2 = exp_base(m) * kLog2e;
 #pragma unroll 1
         for (int c = 0; c < NCH; ++c) {
             float x[VEC];
@@ -743,7 +749,7 @@ __global__ __launch_bounds__(THREADS) void residual_split_kernel(
     auto wave_stats = [&](float m, float l, float* shm, float* shl) {
 #pragma clang fp contract(off)
         const float mw = wave_max_dpp(m);
-        const float lw = wave_sum_dpp(l * exp2_fast((m - mw) * kLog2e));
+        const float lw = wave_sum_dpp(l * exp2_fast((exp_base(m) - exp_base(mw)) * kLog2e));
         if ((tid & (kWave - 1)) == 0) {
             shm[tid / kWave] = mw;
             shl[tid / kWave] = lw;
@@ -757,7 +763,7 @@ __global__ __launch_bounds__(THREADS) void residual_split_kernel(
         const int lane = tid & (kWave - 1);
         const float mg = lane < NW ? shm[lane] : -INFINITY;
         const float mm = lane_f32(row16_max(mg), 0);
-        const float lg = lane < NW ? shl[lane] * exp2_fast((mg - mm) * kLog2e) : 0.f;
+        const float lg = lane < NW ? shl[lane] * exp2_fast((exp_base(mg) - exp_base(mm)) * kLog2e) : 0.f;
         *mp = mm;
         *lp = lane_f32(row16_sum(lg), 0);
     };
@@ -868,15 +874,15 @@ __global__ __launch_bounds__(THREADS) void residual_split_kernel(
                     L = l2;
                     A = a2;
                 } else if (m2 > M) {
-                    L = fmaf(L, exp2_fast((M - m2) * kLog2e), l2);
+                    L = fmaf(L, exp2_fast((exp_base(M) - exp_base(m2)) * kLog2e), l2);
                     M = m2;
                     A = a2;
                 } else {
-                    L = fmaf(l2, exp2_fast((m2 - M) * kLog2e), L);
+                    L = fmaf(l2, exp2_fast((exp_base(m2) - exp_base(M)) * kLog2e), L);
                 }
             }
         }
-        const float lse = M + logf(L);
+        const float lse = exp_base(M) + logf(L);
         const int y = labels[i];
         bool rbad = false;
         const bool valid = label_valid(y, V, ignore_index, &rbad);
@@ -888,7 +894,7 @@ __global__ __launch_bounds__(THREADS) void residual_split_kernel(
         const int yv = yl / VEC;
         const int slot = (here && yv % THREADS == tid) ? (yv / THREADS) * VEC + (yl % VEC) : -1;
         // pass 2 (registers): p = exp(z - lse) = exp(z - m) exp(m - lse), one scale per thread
-        const float sc = exp2_fast(m_thread * kLog2e - lse * kLog2e);
+        const float sc = exp2_fast(exp_base(m_thread) * kLog2e - lse * kLog2e);
         if (slot >= 0) {
             const uint32_t w = reinterpret_cast<const uint32_t*>(&slots[b][(slot / VEC) * THREADS + tid])[(slot % VEC) >> 1];
             sh_zt[b] = (slot & 1) ? bf16_hi(w) : bf16_lo(w);
@@ -969,24 +975,22 @@ __global__ __launch_bounds__(kStatsRowsPerWG * kWave) void residual_stats_kernel
 #pragma unroll
                     for (int k = VEC - 1; k >= 0; --k)
                         if (x[u * VEC + k] == cm) ci = base + (u * kWave + lane) * VEC + k;
-                l = (m == -INFINITY) ? 0.f : l * exp2_fast((m - cm) * kLog2e);
+                l *= exp2_fast((exp_base(m) - exp_base(cm)) * kLog2e);
                 m = cm;
                 idx = ci;
             }
-            if (m != -INFINITY) {  // a lane that has only seen padding keeps l = 0
-                const float m2 = m * kLog2e;
+            const float m2 = exp_base(m) * kLog2e;   // a lane that has only seen padding keeps l = 0
 #pragma unroll
-                for (int k = 0; k < UNROLL * VEC; ++k) l += exp2_fast(fmaf(x[k], kLog2e, -m2));
-            }
+            for (int k = 0; k < UNROLL * VEC; ++k) l += exp2_fast(fmaf(x[k], kLog2e, -m2));
         }
         if (UA && lane < V - Vw) {   // the columns past the last whole chunk, one per lane
             const float x = load_scalar<T>(zr + Vw + lane);
             if (x > m) {
-                l = (m == -INFINITY) ? 0.f : l * exp2_fast((m - x) * kLog2e);
+                l *= exp2_fast((exp_base(m) - exp_base(x)) * kLog2e);
                 m = x;
                 idx = Vw + lane;
             }
-            if (m != -INFINITY) l += exp2_fast((x - m) * kLog2e);
+            l += exp2_fast((x - exp_base(m)) * kLog2e);
         }
     }
 #pragma unroll
@@ -995,9 +999,7 @@ __global__ __launch_bounds__(kStatsRowsPerWG * kWave) void residual_stats_kernel
         const float lo = __shfl_xor(l, o, kWave);
         const int io = __shfl_xor(idx, o, kWave);
         const float mn = fmaxf(m, mo);
-        const float a = (m == -INFINITY) ? 0.f : l * exp2_fast((m - mn) * kLog2e);
-        const float b = (mo == -INFINITY) ? 0.f : lo * exp2_fast((mo - mn) * kLog2e);
-        l = a + b;
+        l = l * exp2_fast((exp_base(m) - exp_base(mn)) * kLog2e) + lo * exp2_fast((exp_base(mo) - exp_base(mn)) * kLog2e);
         idx = (m > mo) ? idx : (mo > m ? io : min(idx, io));
         m = mn;
     }
@@ -1008,13 +1010,13 @@ __global__ __launch_bounds__(kStatsRowsPerWG * kWave) void residual_stats_kernel
         int c = 0, bd = 0;
         double e = 0.0;
         if (i < N) {
-            const float lse = m + logf(l);
+            const float lse = exp_base(m) + logf(l);
             const int y = labels[i];
             bool rbad = false;
             const bool valid = label_valid(y, V, ignore_index, &rbad);
             const float zt = valid ? load_scalar<T>(Z + (int64_t)i * ldz + y) : 0.f;
             row_lse[i] = lse;
-            if (row_argmax) row_argmax[i] = idx;
+            if (row_argmax) row_argmax[i] = m > -INFINITY ? idx : 0;
             if (row_target) row_target[i] = zt;
             c = valid ? 1 : 0;
             bd = rbad ? 1 : 0;
@@ -1726,7 +1728,7 @@ bool plan_split(int V, int* S, int* W, int* nch) {
     if (parts < 2 || parts > kSplitMaxParts) return false;
     const int per = (slots + parts - 1) / parts;
     if ((parts - 1) * per >= slots) return false;   // every part holds columns
-    // every thread holds columns of every part (a thread with padding only would turn its sum into NaN);
+    // every thread holds columns of every part;
     // the automatic plan always gives a part more than 2048 chunks, only the override can give fewer
     if (slots - (parts - 1) * per <= 1024) return false;
     *S = parts;
