@@ -1209,17 +1209,18 @@ template <>
 struct RawChunk<uint16_t, 1> {
     typedef uint16_t type;
 };
-// waves per workgroup at most: the register file holds 16 waves of up to 128 registers, or eight of up to 256
-template <int VPT>
-constexpr int kWaveRowsMax = VPT > 32 ? 8 : 16;
+// waves per workgroup at most: the register file holds 16 waves of up to 128 registers, or eight of up to 256 (fp32 rows of
+// 32 columns per lane spilled 25 registers into scratch in 128: 2560 x 1672 25 us, 17 with eight waves)
+template <typename T, int VPT>
+constexpr int kWaveRowsMax = VPT > 32 || (VPT == 32 && sizeof(T) == 4) ? 8 : 16;
 
 template <typename T, int VEC, int NCH, bool UA>
-__global__ __launch_bounds__(kWaveRowsMax<NCH * VEC> * kWave) void residual_wave_rows_kernel(
+__global__ __launch_bounds__((kWaveRowsMax<T, NCH * VEC>)*kWave) void residual_wave_rows_kernel(
     const T* __restrict__ Z, int64_t ldz, int N, int V, const int32_t* __restrict__ labels, int32_t ignore_index,
     float* __restrict__ row_lse, int32_t* __restrict__ row_argmax, float* __restrict__ row_target, T* __restrict__ R,
     int64_t ldr, Partials ws) {
     typedef typename RawChunk<T, VEC>::type raw_t;
-    constexpr int VPT = NCH * VEC, MAXW = kWaveRowsMax<VPT>;
+    constexpr int VPT = NCH * VEC, MAXW = kWaveRowsMax<T, VPT>;
     __shared__ float sh_s[kWave * VPT];
     __shared__ double sh_ce[MAXW];
     __shared__ int sh_c[MAXW], sh_f[MAXW];
@@ -1537,16 +1538,19 @@ hipError_t launch_rows(const T* Z, int64_t ldz, int N, int V, const int32_t* lab
     return hipGetLastError();
 }
 
-// Chunks per lane of the one-wave-per-row kernel, or 0 where a row is too wide for it (more than 64 columns per lane), or
-// the rows too few: a wave takes its row's columns one after another, so with fewer than 32 rows per column of a lane
-// several waves per row finish sooner (300 x 4096 bf16 9.9 against 13.4 us, 64 x 1000 fp32 10.0 against 11.1; at 3000 x
-// 4095 they are level). Measured before and with it, bf16: 16384 x 1000 90 -> 22 us, 8192 x 128 39 -> 13, 8192 x 4096
-// 57 -> 35, 8192 x 1001 50 -> 18, 16384 x 10 78 -> 17; fp32: 4096 x 1000 26 -> 15, 8192 x 2000 51 -> 40.
+// Chunks per lane of the one-wave-per-row kernel, or 0 where a row is too wide for it (more than 64 columns per lane, or 32
+// in fp32 chunks, which spill beyond), or the rows too few: a wave takes its row's columns one after another, so with fewer
+// than 32 rows per column of a lane several waves per row finish sooner (300 x 4096 bf16 9.9 against 13.4 us, 64 x 1000 fp32
+// 10.0 against 11.1), with 64 columns per lane fewer than 48 (2100 x 4096 bf16 20 against 22, 2100 x 2399 26 against 31; at
+// 3000 x 4096 they are level). Measured before and with it, bf16: 16384 x 1000 90 -> 22 us, 8192 x 128 39 -> 13, 8192 x 4096
+// 57 -> 35, 8192 x 1001 50 -> 18, 16384 x 10 78 -> 17; fp32: 4096 x 1000 26 -> 15, 8192 x 2000 51 -> 30, 2560 x 1672 20 -> 17.
+template <int VEC>
+constexpr int kWaveRowsCols = VEC == 4 ? 32 : 64;   // columns per lane at most
 template <int VEC>
 int wave_rows_nch(int N, int V) {
     const int need = (V + kWave * VEC - 1) / (kWave * VEC);
     for (int c : {1, 2, 4, 8, 16})
-        if (c >= need) return c * VEC <= 64 && N >= 32 * c * VEC ? c : 0;
+        if (c >= need) return c * VEC <= kWaveRowsCols<VEC> && N >= (c * VEC == 64 ? 48 : 32) * c * VEC ? c : 0;
     return 0;
 }
 
@@ -1556,11 +1560,10 @@ hipError_t launch_wave_rows(int nch, const T* Z, int64_t ldz, int N, int V, cons
     // one workgroup per CU; as many waves in it as there are rows for
     auto go = [&](auto tag) {
         constexpr int NCH = decltype(tag)::value;
-        if constexpr (NCH * VEC <= 64) {
-            constexpr int MAXW = kWaveRowsMax<NCH * VEC>;
-            int waves = 1;
-            while (waves < MAXW && (int64_t)waves * kSingleMaxWG < N) waves *= 2;
-            *nwg = (int)std::min<int64_t>(kSingleMaxWG, (N + waves - 1) / waves);
+        if constexpr (NCH * VEC <= kWaveRowsCols<VEC>) {
+            constexpr int MAXW = kWaveRowsMax<T, NCH * VEC>;
+            const int waves = (int)std::min<int64_t>(MAXW, ((int64_t)N + kSingleMaxWG - 1) / kSingleMaxWG);
+            *nwg = (int)std::min<int64_t>(kSingleMaxWG, ((int64_t)N + waves - 1) / waves);
             hipLaunchKernelGGL((residual_wave_rows_kernel<T, VEC, NCH, UA>), dim3(*nwg), dim3(waves * kWave), 0, st, Z, ldz,
                                N, V, labels, ig, lse, am, tg, R, ldr, ws);
             return hipGetLastError();

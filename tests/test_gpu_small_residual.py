@@ -45,3 +45,14 @@ def test_small_residual_all_ignored():
     out = bom.bom_residual(Z, torch.full((70,), -100, dtype=torch.int32, device=dev()))
     assert out["flags"].item() == bom.BOM_FLAG_EMPTY and out["n_valid"].item() == 0 and out["loss"].item() == 0
     assert (out["s"] == 0).all() and (out["R"] == 0).all() and (out["row_target"] == 0).all()
+
+
+# one wave per row with up to 32 fp32 columns per lane, any number of waves per workgroup; wider rows take the other kernels
+@pytest.mark.parametrize("N,V", [(1024, 1028), (1100, 2000), (2561, 2048), (2100, 1672), (9000, 2052)])
+def test_fp32_rows_per_wave(N, V):
+    test_small_residual(N, V, "f32")
+
+
+@pytest.mark.parametrize("N,V", [(3072, 2400), (3100, 4096), (3071, 2400), (3300, 3999), (700, 1000)])
+def test_bf16_rows_per_wave(N, V):
+    test_small_residual(N, V, "bf16")
