@@ -1226,7 +1226,7 @@ __global__ __launch_bounds__((kWaveRowsMax<T, NCH * VEC>)*kWave) void residual_w
     __shared__ int sh_c[MAXW], sh_f[MAXW];
     const int lane = threadIdx.x % kWave, waves = blockDim.x / kWave;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int stride = gridDim.x * waves;
+    const unsigned stride = gridDim.x * waves;   // (unsigned: a row's number plus a stride may pass 2^31)
     float acc[VPT];
 #pragma unroll
     for (int k = 0; k < VPT; ++k) acc[k] = 0.f;
@@ -1271,20 +1271,20 @@ __global__ __launch_bounds__((kWaveRowsMax<T, NCH * VEC>)*kWave) void residual_w
             }
         }
     };
-    int i = blockIdx.x * waves + wave;
+    unsigned i = blockIdx.x * waves + wave;
     raw_t nxt[NCH];
     int y_nxt = 0;
-    if (i < N) {
+    if (i < (unsigned)N) {
 #pragma unroll
         for (int c = 0; c < NCH; ++c) nxt[c] = load(i, c);
         y_nxt = labels[i];
     }
-    for (; i < N; i += stride) {
+    for (; i < (unsigned)N; i += stride) {
         float x[VPT];
 #pragma unroll
         for (int c = 0; c < NCH; ++c) unpack(nxt[c], c, &x[c * VEC]);
         const int y = __builtin_amdgcn_readfirstlane(y_nxt);
-        const int in = min(i + stride, N - 1);   // past the last row: a row that is there, not used
+        const int in = (int)min(i + stride, (unsigned)N - 1u);   // past the last row: a row that is there, not used
 #pragma unroll
         for (int c = 0; c < NCH; ++c) nxt[c] = load(in, c);
         y_nxt = labels[in];

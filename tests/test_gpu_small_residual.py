@@ -56,3 +56,20 @@ def test_fp32_rows_per_wave(N, V):
 @pytest.mark.parametrize("N,V", [(3072, 2400), (3100, 4096), (3071, 2400), (3300, 3999), (700, 1000)])
 def test_bf16_rows_per_wave(N, V):
     test_small_residual(N, V, "bf16")
+
+
+# Nearly 2^31 rows: a wave's next row number passes the largest int
+def test_rows_up_to_the_largest_int():
+    N, V = 2 ** 31 - 300, 2
+    if torch.cuda.mem_get_info()[0] < 80e9:
+        pytest.skip("needs 80 GB of free memory")
+    log(f"[small residual] N={N} V={V}")
+    Z = torch.zeros((N, V), dtype=torch.bfloat16, device=dev())
+    Z[N - 1, 1] = 3.0
+    out = bom.bom_residual(Z, torch.zeros(N, dtype=torch.int32, device=dev()), write_R=False)
+    assert out["n_valid"].item() == N and out["flags"].item() == 0
+    assert out["s"].tolist() == [-0.5, 0.5]                             # exact sums; the last row is below half a rounding
+    lse, am = out["row_lse"], out["row_argmax"]
+    assert abs(float(lse[N - 1]) - 3.0485874) < 1e-6 and int(am[N - 1]) == 1
+    assert float(lse[:N - 1].min()) == float(lse[:N - 1].max()) and abs(float(lse[0]) - 0.6931472) < 1e-7
+    assert int(am[:N - 1].max()) == 0
