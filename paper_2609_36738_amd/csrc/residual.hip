@@ -1513,8 +1513,8 @@ __global__ __launch_bounds__(kFinThreads) void residual_small_kernel(
 template <int THREADS, int NCH, bool UA>
 hipError_t launch_rows_lds(const uint16_t* Z, int64_t ldz, int N, int V, const int32_t* labels, int32_t ignore_index,
                            float* row_lse, int32_t* row_argmax, float* row_target, uint16_t* R, int64_t ldr, Partials ws,
-                           int* nwg_out, hipStream_t stream) {
-    int nwg = N < kSingleMaxWG ? N : kSingleMaxWG;
+                           int* nwg_out, hipStream_t stream, int max_wg) {
+    int nwg = N < max_wg ? N : max_wg;
     const int rpw = (N + nwg - 1) / nwg;
     nwg = (N + rpw - 1) / rpw;
     *nwg_out = nwg;
@@ -1589,7 +1589,7 @@ constexpr int kLds1kNchSet[] = {2, 3, 4, 5, 6};
 template <typename T, int VEC, bool UA>
 hipError_t dispatch_rows(int nch, int threads, const T* Z, int64_t ldz, int N, int V, const int32_t* labels,
                          int32_t ig, float* lse, int32_t* am, float* tg, T* R, int64_t ldr, Partials ws, int* nwg,
-                         hipStream_t st) {
+                         hipStream_t st, int max_wg) {   // (max_wg: workgroups of the rows parked in LDS)
 #define BOM_ROWS(TH, NC) launch_rows<T, TH, VEC, NC, UA>(Z, ldz, N, V, labels, ig, lse, am, tg, R, ldr, ws, nwg, st)
     if (threads == 64) return BOM_ROWS(64, 1);
     if (threads == 128) return BOM_ROWS(128, 1);
@@ -1608,7 +1608,7 @@ hipError_t dispatch_rows(int nch, int threads, const T* Z, int64_t ldz, int N, i
     }
     if constexpr (std::is_same<T, uint16_t>::value && VEC == 8) {
         if (threads == -512) {   // bf16 rows parked in LDS, next row prefetched
-#define BOM_LDS(NC) launch_rows_lds<512, NC, UA>(Z, ldz, N, V, labels, ig, lse, am, tg, R, ldr, ws, nwg, st)
+#define BOM_LDS(NC) launch_rows_lds<512, NC, UA>(Z, ldz, N, V, labels, ig, lse, am, tg, R, ldr, ws, nwg, st, max_wg)
             switch (nch) {
                 case 2: return BOM_LDS(2);
                 case 3: return BOM_LDS(3);
@@ -1624,7 +1624,7 @@ hipError_t dispatch_rows(int nch, int threads, const T* Z, int64_t ldz, int N, i
 #undef BOM_LDS
         }
         if (threads == -1024) {   // the same with 1024-thread workgroups (16 waves per CU)
-#define BOM_LDS(NC) launch_rows_lds<1024, NC, UA>(Z, ldz, N, V, labels, ig, lse, am, tg, R, ldr, ws, nwg, st)
+#define BOM_LDS(NC) launch_rows_lds<1024, NC, UA>(Z, ldz, N, V, labels, ig, lse, am, tg, R, ldr, ws, nwg, st, max_wg)
             switch (nch) {
                 case 2: return BOM_LDS(2);
                 case 3: return BOM_LDS(3);
@@ -1721,6 +1721,31 @@ bool plan_single(int V, int VEC, int* threads, int* nch) {
     return false;
 }
 
+// Ragged bf16 rows of up to 8192 columns (two chunks per thread of 512) or 12,288 (three): with 3500 rows or more three or two
+// workgroups per CU, so that one's loads and products fill the barriers of another (one took 2.0 or 2.85 us per row, whatever
+// it held: 16000 x 6001 131 us, 99 with three; 16000 x 9001 189 and 143 with two). Wider rows stay with one workgroup of 1024
+// threads (6000 x 14001 87 us, 91 with two of 512), fewer rows too (3000 x 6001 33 and 34).
+int ragged_wg_per_cu(int N, int V) { return N < 3500 || V > 12288 ? 1 : V > 8192 ? 2 : 3; }
+// as many of them as the workspace holds partial rows for (the column kernel's row blocks, at least 435 at 3500 rows)
+int ragged_max_wg(int N, int V, int per_cu) {
+    const int rb = cols_row_block(N, V, 8);
+    return std::min(per_cu * kSingleMaxWG, std::max((N + rb - 1) / rb, kSingleMaxWG));
+}
+
+// Whether ragged bf16 rows take the two passes, element by element, instead of being parked in LDS. The passes keep the chip
+// full with any number of columns, while parked rows cost the same up to 8192 columns (16,384 with 1024 threads): us for
+// passes and parked, without R: 16000 x 4099 76 and 90, 3000 x 4099 25 and 31, 3000 x 8201 35 and 42, but 16000 x 7001 102 and
+// 91; with R: 3000 x 4099 29 and 33, 12000 x 4500 74 and 74, 16000 x 6001 151 and 99. Modelled: 11 us and 0.82 (1.15 with R)
+// per million logits against the parked rows' start and time per 256 rows.
+bool ragged_two_pass(int N, int V, bool want_R) {
+    if (V <= 4096 || V > 16384 || N < 1536 || plan_override() != 0) return false;
+    const double passes = 11.0 + (want_R ? 1.15e-6 : 0.82e-6) * (double)N * V;
+    const int per_cu = ragged_wg_per_cu(N, V);
+    const double parked = per_cu == 1 ? 8.0 + (V <= 8192 ? 2.05 : 2.85) * ((N + 255) / 256)
+                                      : 15.0 + (per_cu == 3 ? 1.2 : 1.75) * N / 256.0;
+    return passes < parked;
+}
+
 // Split-row plan for bf16 rows of 16-byte chunks that no single workgroup holds: S parts (at most
 // kSplitMaxParts, so V up to 524,288) of at most kSplitMaxNch chunks per thread at 1024 threads; part
 // width W columns (a multiple of 8). Two LDS row buffers of four chunks fill 128 KB of the CU's LDS.
@@ -1797,7 +1822,16 @@ hipError_t run_residual(const T* Z, int N, int V, int64_t ldz, const int32_t* la
         e = launch_wave_rows<T, VEC, UA>(wave_nch, Z, ldz, N, V, labels, ig, lse, am, tg, R, ldr, ws, &nwg, st);
         nparts = nwg;
     } else if (single) {
-        e = dispatch_rows<T, VEC, UA>(nch, threads, Z, ldz, N, V, labels, ig, lse, am, tg, R, ldr, ws, &nwg, st);
+        int max_wg = kSingleMaxWG;
+        if (UA && threads < 0 && plan_override() == 0) {
+            const int per_cu = ragged_wg_per_cu(N, V);
+            if (per_cu > 1) {
+                threads = -512;
+                nch = std::max(2, ((V + 7) / 8 + 511) / 512);
+                max_wg = ragged_max_wg(N, V, per_cu);
+            }
+        }
+        e = dispatch_rows<T, VEC, UA>(nch, threads, Z, ldz, N, V, labels, ig, lse, am, tg, R, ldr, ws, &nwg, st, max_wg);
         nparts = nwg;
     } else if (split) {
         if constexpr (std::is_same<T, uint16_t>::value && VEC == 8)
@@ -1843,7 +1877,7 @@ hipError_t launch_residual(const void* Z, bom_dtype dt, int N, int V, int64_t ld
     if (dt == BOM_BF16) {
         const uint16_t* z = static_cast<const uint16_t*>(Z);
         uint16_t* r = static_cast<uint16_t*>(R);
-        if (!vec_ok && V >= 8)
+        if (!vec_ok && V >= 8 && !ragged_two_pass(N, V, R != nullptr))
             return run_residual<uint16_t, 8, true>(z, N, V, ldz, labels, ignore_index, s, row_lse, row_argmax, row_target,
                                                    r, ldr, loss, n_valid, flags, ws, stream);
         return vec_ok ? run_residual<uint16_t, 8>(z, N, V, ldz, labels, ignore_index, s, row_lse, row_argmax, row_target,

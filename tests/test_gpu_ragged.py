@@ -153,6 +153,11 @@ RES_CASES = [(9000, 8, 0, 0), (700, 511, 0, 0), (5000, 1000, 0, 0), (3000, 1025,
              (3, 57343, 0, 1), (70, 57345, 0, 0), (21, 65541, 3, 0), (1, 128257, 0, 1)]
 
 
+# Several workgroups per CU (two and three chunks per thread, from 3500 rows on), and the two passes element by element
+RES_CASES += [(3500, 8191, 0, 0), (3501, 8192, 1, 0), (3600, 12281, 0, 0), (3499, 8191, 0, 0), (9000, 6001, 0, 1), (3600, 12290, 0, 0),
+              (1536, 4097, 0, 0), (2100, 8201, 0, 0), (1536, 16000, 0, 1)]
+
+
 @pytest.mark.parametrize("N,V,pad,off", RES_CASES)
 def test_residual_any_alignment(N, V, pad, off):
     log(f"[ragged residual] N={N} V={V} pad={pad} offset={off}")
