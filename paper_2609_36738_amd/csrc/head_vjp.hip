@@ -825,12 +825,13 @@ constexpr int kWideDH = 0, kWideDW = 1, kWideFWD = 2;
 // that the next tile's first two k tiles are on their way (the first already in LDS) while this one is stored. The
 // stores then leave through LDS of their own (`stage`, 4 KB per wave) and are buffer stores, with no branch around them:
 // a count of outstanding accesses that differs between paths would make the next tile's first loads wait for them.
+// CACHED: the stores streamed go through the L2 (see launch_head_forward).
 // Forward 4096 x 1024 x 50304: 417 us with one tile per workgroup, 396 streamed; 8192 x 2048 x 50304: 1464, 1450; with rows
 // of 50257 columns (4088 x 1024): 473, 444.
 // ZR: the operand that is R (dH's A, dW's B) holds the logits, and each copy is turned into R in registers on its way to
 // LDS, once per output tile of the other dimension: for a workspace without panels, and with one tile along d often the
 // faster way (see route_of).
-template <int MODE, typename TO, int NW, bool UA = false, bool STREAM = false, bool ZR = false>
+template <int MODE, typename TO, int NW, bool UA = false, bool STREAM = false, bool ZR = false, bool CACHED = false>
 __device__ __forceinline__ void wide_tile(const WideArgs& args, int id, uint16_t (&lds)[2][2][WSE], float* rv_s,
                                           char* stage = nullptr, float2* zs = nullptr) {
     static_assert(NW == 4 || NW == 8, "four or eight waves");
@@ -1221,7 +1222,7 @@ __device__ __forceinline__ void wide_tile(const WideArgs& args, int id, uint16_t
                 for (int t = 0; t < 4; ++t) {
                     const int row = t * 8 + l / 8, c = (l % 8 * 8) ^ (((row >> 2) & 1) * 32);
                     const u32x4_t v = *reinterpret_cast<const u32x4_t*>(reinterpret_cast<const TO*>(mine) + row * WCOLS + c);
-                    __builtin_amdgcn_raw_buffer_store_b128(v, desc, vo, 0, kNonTemporal);
+                    __builtin_amdgcn_raw_buffer_store_b128(v, desc, vo, 0, CACHED ? 0 : kNonTemporal);
                     vo += (int)ldo * 16;
                 }
                 __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -1350,11 +1351,11 @@ __global__ __launch_bounds__(NW * 64, 1) void lds256w_kernel(WideArgs a) {
 }
 
 // The head forward Z = H W (+ b) in bf16 on the same tiles (fp32 accumulation, one rounding of Z).
-template <bool UA>
+template <bool UA, bool CACHED>
 __global__ __launch_bounds__(512, 1) void lds256w_fwd_stream_kernel(WideArgs a) {
     __shared__ __attribute__((aligned(1024))) uint16_t lds[2][2][WSE];
     __shared__ __attribute__((aligned(1024))) char stage[8 * 4096];
-    wide_tile<kWideFWD, uint16_t, 8, UA, true>(a, blockIdx.x, lds, nullptr, stage);
+    wide_tile<kWideFWD, uint16_t, 8, UA, true, false, CACHED>(a, blockIdx.x, lds, nullptr, stage);
 }
 template <typename TO, int NW, bool UA = false>
 __global__ __launch_bounds__(NW * 64, 1) void lds256w_fwd_kernel(WideArgs a) {
@@ -2712,11 +2713,20 @@ hipError_t launch_head_forward(const void* H, int64_t ldh, const void* W, int64_
         const WideArgs wa{H16, ldh, W16, ldw, N, V, d, (int)(cdiv(d, WKT) * WKT), tr, nullptr, nullptr, nullptr, Z, ldz,
                           0.f, nullptr, b16, nullptr, (int)(flat ? (int64_t)NT * MT : cdiv(NT, 8) * 8 * MT)};
         const dim3 grid((unsigned)wa.units);
+        // Z past the operands' panels in the L2 (kNonTemporal), unless its rows are not whole cache lines: a tile row's ends are
+        // then part of a line each, which the L2 joins. That counts where the stores are what is waited for: with few k tiles, and
+        // up to a Z that the 256 MB memory-side cache takes. us non-temporal and cached: 10939 x 32 x 26520 329 and 206,
+        // x 256 322 and 268, x 512 364 and 370; 4088 x 128 x 50257 263 and 161, x 1024 428 and 443; 4096 x 1024 x 32008 265
+        // and 254, x 2048 469 and 471; 1000 x 512 x 30008 48 and 37; whole lines: 4096 x 256 x 32000 85 and 86,
+        // 2048 x 256 x 128256 167 and 205.
+        const bool lines = ldz % 64 == 0 && reinterpret_cast<uintptr_t>(Z) % 128 == 0;
+        const bool cached = !lines && (d < 512 || (d < 2048 && (int64_t)N * V * 2 <= (int64_t)280 << 20));
         const dim3 sgrid((unsigned)std::min(wa.units, kCUs));
         // streamed tiles; their stores' offsets reach over 256 rows of Z
         if (wave_cfg().fwd == 8 && ldz < (1 << 21))
-            hipLaunchKernelGGL(ua ? lds256w_fwd_stream_kernel<true> : lds256w_fwd_stream_kernel<false>, sgrid, dim3(512), 0,
-                               st, wa);
+            hipLaunchKernelGGL(cached ? (ua ? lds256w_fwd_stream_kernel<true, true> : lds256w_fwd_stream_kernel<false, true>)
+                                      : (ua ? lds256w_fwd_stream_kernel<true, false> : lds256w_fwd_stream_kernel<false, false>),
+                               sgrid, dim3(512), 0, st, wa);
         else if (ua)
             hipLaunchKernelGGL((lds256w_fwd_kernel<uint16_t, 8, true>), grid, dim3(512), 0, st, wa);
         else if (wave_cfg().fwd == 8)

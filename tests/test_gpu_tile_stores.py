@@ -77,3 +77,10 @@ def test_no_dH(N, d, V):
     ref = H.double().t() @ ((0.5 * R.double() + 0.5 * q.double()) / N)
     # fp32 sums of N exact products
     assert a["dH"] is None and float((a["dW"] - ref).norm() / ref.norm()) <= 1e-5
+
+
+# rows of Z that are whole cache lines and not, and widths and sizes on both sides of where stores bypass the L2
+@pytest.mark.parametrize("N,d,V,ldz", [(3000, 32, 26520, 0), (3000, 504, 8200, 8201), (3000, 512, 8200, 0), (1000, 8, 30001, 0),
+                                       (2050, 64, 32000, 0), (2050, 64, 32000, 32064), (8200, 512, 17904, 0), (2050, 2048, 4104, 0)])
+def test_forward_stores(N, d, V, ldz):
+    test_streamed_forward(N, d, V, ldz, True)
