@@ -216,11 +216,12 @@ __device__ __forceinline__ void stf<float>(float* p, int64_t i, float x) { p[i] 
 template <>
 __device__ __forceinline__ void stf<uint16_t>(uint16_t* p, int64_t i, float x) { p[i] = f32_to_bf16(x); }
 
-// Element (row, col) of R: as stored, or formed from the logits (rounded to bf16 like a stored R).
+// Element (row, col) of R: as stored, or formed from the logits (rounded to bf16 like a stored R). A row outside I may come
+// with a 1 taken off at its label (an ignore_index inside [0, V)): the caller's mask of the row covers all of G.
 __device__ __forceinline__ float r_elem(const uint16_t* RZ, int64_t ld, int row, int col, const Fold& f) {
     const float x = ldf(RZ, (int64_t)row * ld + col);
     if (f.zc == nullptr) return x;
-    return bf16_to_f32(f32_to_bf16(r_from_z(x, f.zc[row], col == f.labels[row] && f.vmask[row] != 0.f)));
+    return bf16_to_f32(f32_to_bf16(r_from_z(x, f.zc[row], col == f.labels[row])));
 }
 
 // ---- SIMT fallback (bf16 with H unaligned): 64 x 64 tiles, 16-deep k, 4 x 4 outputs per thread --------------------------
@@ -243,7 +244,7 @@ __global__ __launch_bounds__(256) void simt_dW_kernel(const uint16_t* __restrict
             const int idx = e * 256 + t, kk = idx / SB, cc = idx % SB;
             const int k = k0 + kk;
             As[kk][cc] = (k < ke && m0 + cc < M) ? ldf(H, (int64_t)k * ldh + m0 + cc) : 0.f;
-            Bs[kk][cc] = (k < ke && n0 + cc < Nn) ? fmaf(alpha, r_elem(R, ldr, k, n0 + cc, f), f.vmask[k] * f.cq[n0 + cc]) : 0.f;
+            Bs[kk][cc] = (k < ke && n0 + cc < Nn) ? f.vmask[k] * fmaf(alpha, r_elem(R, ldr, k, n0 + cc, f), f.cq[n0 + cc]) : 0.f;
         }
         __syncthreads();
 #pragma unroll
@@ -292,7 +293,7 @@ __global__ __launch_bounds__(256) void simt_dH_kernel(const uint16_t* __restrict
         for (int e = 0; e < 4; ++e) {
             const int idx = e * 256 + t, rr = idx / SK, kk = idx % SK;
             const int k = k0 + kk;
-            As[kk][rr] = (k < ke && m0 + rr < M) ? fmaf(alpha, r_elem(R, ldr, m0 + rr, k, f), f.vmask[m0 + rr] * f.cq[k]) : 0.f;
+            As[kk][rr] = (k < ke && m0 + rr < M) ? f.vmask[m0 + rr] * fmaf(alpha, r_elem(R, ldr, m0 + rr, k, f), f.cq[k]) : 0.f;
             Bs[kk][rr] = (k < ke && n0 + rr < Nn) ? ldf(W, (int64_t)(n0 + rr) * ldw + k) : 0.f;
         }
         __syncthreads();
@@ -367,7 +368,7 @@ struct StageHt {
 };
 
 // B tile for dW: B(k, n) = G(k, n) from R[k][n]; same thread geometry as StageHt, the fold
-// G = fma(alpha, R, mask_k * cq_n) in fp32, rounded to bf16 pairs (k, k+1) -- the transpose.
+// G = mask_k fma(alpha, R, cq_n) in fp32, rounded to bf16 pairs (k, k+1) -- the transpose.
 struct StageGt {
     uint4 r[4];
     uint32_t mk[4];
@@ -399,7 +400,7 @@ struct StageGt {
         if (f.zc != nullptr) {
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const u32x4_t y = z_chunk_to_r(u32x4_t{x[q].x, x[q].y, x[q].z, x[q].w}, zc[q], vm[q] != 0.f ? lo[q] : -1, true);
+                const u32x4_t y = z_chunk_to_r(u32x4_t{x[q].x, x[q].y, x[q].z, x[q].w}, zc[q], lo[q], true);
                 x[q] = make_uint4(y[0], y[1], y[2], y[3]);
             }
         }
@@ -413,7 +414,7 @@ struct StageGt {
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const float rv = (c & 1) ? bf16_hi(w[q][c >> 1]) : bf16_lo(w[q][c >> 1]);
-                g[q] = fmaf(alpha, rv, vm[q] * cqn[c]);
+                g[q] = vm[q] * fmaf(alpha, rv, cqn[c]);
             }
             uint2 o;
             o.x = pack_bf16x2(g[0], g[1]) & ((mk[0] & 0x0000FFFFu) | (mk[1] & 0xFFFF0000u));
@@ -462,7 +463,7 @@ struct StageK {
             const int c = e * 256 + t, lr = c / 8, lk = (c % 8) * 8;
             uint4 o = r[e];
             if (FOLD && f.zc != nullptr) {
-                const u32x4_t x = z_chunk_to_r(u32x4_t{o.x, o.y, o.z, o.w}, zc[e], vm[e] != 0.f ? lo[e] : -1, true);
+                const u32x4_t x = z_chunk_to_r(u32x4_t{o.x, o.y, o.z, o.w}, zc[e], lo[e], true);
                 o = make_uint4(x[0], x[1], x[2], x[3]);
             }
             if (FOLD) {
@@ -471,8 +472,8 @@ struct StageK {
                 uint32_t g[4];
 #pragma unroll
                 for (int p = 0; p < 4; ++p)
-                    g[p] = pack_bf16x2(fmaf(alpha, bf16_lo(w[p]), vm[e] * q8[2 * p]),
-                                       fmaf(alpha, bf16_hi(w[p]), vm[e] * q8[2 * p + 1]));
+                    g[p] = pack_bf16x2(vm[e] * fmaf(alpha, bf16_lo(w[p]), q8[2 * p]),
+                                       vm[e] * fmaf(alpha, bf16_hi(w[p]), q8[2 * p + 1]));
                 o = make_uint4(g[0], g[1], g[2], g[3]);
             }
             *reinterpret_cast<uint4*>(&S[lr][lk]) = and_mask(o, mk[e]);
