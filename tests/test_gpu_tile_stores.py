@@ -84,3 +84,29 @@ def test_no_dH(N, d, V):
                                        (2050, 64, 32000, 0), (2050, 64, 32000, 32064), (8200, 512, 17904, 0), (2050, 2048, 4104, 0)])
 def test_forward_stores(N, d, V, ldz):
     test_streamed_forward(N, d, V, ldz, True)
+
+
+# dW alone over few rows: SIMT below a number of rows, the matrix kernels from it on, from R and from the logits
+@pytest.mark.parametrize("N", [1, 19, 20, 43, 44, 51, 52, 63, 64])
+@pytest.mark.parametrize("d,V", [(264, 1000), (72, 5001), (136, 9000)])
+@pytest.mark.parametrize("logits", [False, True])
+def test_no_dH_few_rows(N, d, V, logits):
+    log(f"[no dH] N={N} d={d} V={V} logits={logits}")
+    g = torch.Generator(device=dev()).manual_seed(17)
+
+    def rand(shape, std, t=torch.bfloat16):
+        return (torch.randn(shape, generator=g, device=dev()) * std).to(t)
+
+    H, W, Z = rand((N, d), 1.0), rand((d, V), 0.02), rand((N, V), 1.0)
+    y = torch.randint(0, V, (N,), generator=g, device=dev(), dtype=torch.int32)
+    y[1::5] = 3
+    res = bom.bom_residual(Z, y, ignore_index=3)
+    q, s = rand((V,), 0.05, torch.float32), rand((V,), 0.05, torch.float32)
+    a = bom.bom_head_vjp(H, W, Z if logits else res["R"], y, q, res["n_valid"], s=s, lam=0.5, ignore_index=3, want_dH=False,
+                         want_db=True, row_lse=res["row_lse"] if logits else None)
+    ok = y != 3
+    G = (0.5 * res["R"].double() + 0.5 * q.double()) * ok[:, None] / int(ok.sum())
+    ref = H.double().t() @ G
+    # fp32 sums of N exact products; on the 128-tile kernel G is rounded to bf16, from the logits R a second time in some places
+    assert float((a["dW"] - ref).norm() / ref.norm()) <= 2.0 ** -8
+    assert float((a["db"] - 0.5 * (s + q)).abs().max()) <= 1e-7
