@@ -2622,12 +2622,13 @@ hipError_t launch_products(const HeadVjpArgs& a, const Route& r, hipStream_t st)
 
 // ---- head forward (support): Z = H W + b -----------------------------------------------------------
 namespace {
-// SIMT forward (bf16 shapes the MFMA tiles do not take): 64 x 64 tiles, 16-deep k, fp32 accumulation, Z
-// rounded once to bf16.
-__global__ __launch_bounds__(256) void head_forward_simt_kernel(const uint16_t* __restrict__ H, int64_t ldh,
-                                                                const uint16_t* __restrict__ W, int64_t ldw,
-                                                                const uint16_t* __restrict__ b, int N, int d, int V,
-                                                                uint16_t* __restrict__ Z, int64_t ldz) {
+// SIMT forward (bf16 shapes the MFMA tiles do not take, fp32 heads of fewer than four features): 64 x 64 tiles, 16-deep k, fp32
+// accumulation, Z rounded once to its type.
+template <typename T>
+__global__ __launch_bounds__(256) void head_forward_simt_kernel(const T* __restrict__ H, int64_t ldh,
+                                                                const T* __restrict__ W, int64_t ldw,
+                                                                const T* __restrict__ b, int N, int d, int V,
+                                                                T* __restrict__ Z, int64_t ldz) {
     __shared__ float As[SK][SB + 4];
     __shared__ float Bs[SK][SB + 4];
     const int t = threadIdx.x, tx = t % 16, ty = t / 16;
@@ -2637,9 +2638,9 @@ __global__ __launch_bounds__(256) void head_forward_simt_kernel(const uint16_t* 
         for (int e = 0; e < 4; ++e) {
             const int idx = e * 256 + t;
             const int rr = idx / SK, kk = idx % SK;
-            As[kk][rr] = (k0 + kk < d && m0 + rr < N) ? ldf<uint16_t>(H, (int64_t)(m0 + rr) * ldh + k0 + kk) : 0.f;
+            As[kk][rr] = (k0 + kk < d && m0 + rr < N) ? ldf<T>(H, (int64_t)(m0 + rr) * ldh + k0 + kk) : 0.f;
             const int kk2 = idx / SB, cc = idx % SB;
-            Bs[kk2][cc] = (k0 + kk2 < d && n0 + cc < V) ? ldf<uint16_t>(W, (int64_t)(k0 + kk2) * ldw + n0 + cc) : 0.f;
+            Bs[kk2][cc] = (k0 + kk2 < d && n0 + cc < V) ? ldf<T>(W, (int64_t)(k0 + kk2) * ldw + n0 + cc) : 0.f;
         }
         __syncthreads();
 #pragma unroll
@@ -2659,7 +2660,7 @@ __global__ __launch_bounds__(256) void head_forward_simt_kernel(const uint16_t* 
     for (int i = 0; i < 4; ++i)
         for (int j = 0; j < 4; ++j) {
             const int m = m0 + ty * 4 + i, n = n0 + tx * 4 + j;
-            if (m < N && n < V) stf<uint16_t>(Z, (int64_t)m * ldz + n, acc[i][j] + (b ? ldf<uint16_t>(b, n) : 0.f));
+            if (m < N && n < V) stf<T>(Z, (int64_t)m * ldz + n, acc[i][j] + (b ? ldf<T>(b, n) : 0.f));
         }
 }
 }  // namespace
@@ -2682,6 +2683,14 @@ bool forward_small(int64_t N, int64_t d, int64_t V, bool ua) {
 
 hipError_t launch_head_forward(const void* H, int64_t ldh, const void* W, int64_t ldw, const void* b, bom_dtype dt,
                                int N, int d, int V, void* Z, int64_t ldz, hipStream_t st) {
+    // fp32 heads of fewer than four features read words one by one on the matrix kernel and are their write of Z: us on the
+    // SIMT and the matrix kernel at d = 1, 8000 x 27392 281 and 346, 1000 x 27392 40 and 49, 100 x 9000 8.2 and 7.4
+    if (dt == BOM_F32 && d < 4 && (int64_t)N * V >= 1 << 21 && N <= 65535 * SB) {
+        hipLaunchKernelGGL(head_forward_simt_kernel<float>, dim3((V + SB - 1) / SB, (N + SB - 1) / SB), dim3(256), 0, st,
+                           static_cast<const float*>(H), ldh, static_cast<const float*>(W), ldw, static_cast<const float*>(b), N,
+                           d, V, static_cast<float*>(Z), ldz);
+        return hipGetLastError();
+    }
     if (dt == BOM_F32)
         return launch_forward_f32(static_cast<const float*>(H), ldh, static_cast<const float*>(W), ldw,
                                   static_cast<const float*>(b), N, d, V, static_cast<float*>(Z), ldz, st);
@@ -2745,7 +2754,7 @@ hipError_t launch_head_forward(const void* H, int64_t ldh, const void* W, int64_
         return hipGetLastError();
     }
     dim3 grid((V + SB - 1) / SB, (N + SB - 1) / SB);
-    hipLaunchKernelGGL(head_forward_simt_kernel, grid, dim3(256), 0, st, H16, ldh, W16, ldw, b16, N, d, V,
+    hipLaunchKernelGGL(head_forward_simt_kernel<uint16_t>, grid, dim3(256), 0, st, H16, ldh, W16, ldw, b16, N, d, V,
                        static_cast<uint16_t*>(Z), ldz);
     return hipGetLastError();
 }

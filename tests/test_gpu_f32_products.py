@@ -64,3 +64,9 @@ def test_head_forward_f32(N, d, V):
     bom.bom_head_forward(H, W, b=b, Z=Z[:, :V])
     ref = H.double() @ W.double() + b.double()
     assert float((Z[:, :V] - ref).norm() / ref.norm()) <= 1e-6 and (Z[:, V:] == 7.0).all()
+
+
+# fewer than four features: a small Z and a large one (SIMT), and four
+@pytest.mark.parametrize("N,d,V", [(100, 1, 9000), (301, 1, 9001), (1000, 3, 9000), (65, 2, 40000), (301, 4, 9001)])
+def test_head_forward_f32_few_features(N, d, V):
+    test_head_forward_f32(N, d, V)
