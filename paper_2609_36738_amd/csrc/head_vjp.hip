@@ -114,6 +114,7 @@ int64_t panel_ld(int64_t N, int64_t V) {   // columns of the panel buffer's rows
     return (w < V ? w + kPanelTail : (V + 7) / 8 * 8);
 }
 
+constexpr int64_t kPanelBlocks = 1 << 23;   // workgroups per launch: a grid holds fewer than 2^32 threads
 // Columns [c0, c0 + nc) of R to rows of ldo (a multiple of 8, at least nc rounded up): one row and 8192 columns per
 // workgroup, four 16-byte loads of Z (at any alignment) in flight per thread. Columns past V get zeros.
 __global__ __launch_bounds__(256) void z_panel_kernel(const uint16_t* __restrict__ Z, int64_t ldz, int V, int c0, int nc,
@@ -2439,11 +2440,15 @@ hipError_t launch_from_logits(const HeadVjpArgs& a, const VjpWs& L, hipStream_t 
     uint16_t* panel = reinterpret_cast<uint16_t*>(base + p0);
     const int64_t ldp = panel_ld(a.N, a.V), pc = panel_cols(a.N, a.V);
     auto form = [&](int64_t c0, int64_t nc) {
-        const int64_t slabs = cdiv(nc, 8192);
-        hipLaunchKernelGGL(z_panel_kernel, dim3((unsigned)(a.N * slabs)), dim3(256), 0, st,
-                           static_cast<const uint16_t*>(a.R), a.ldr, a.V, (int)c0, (int)nc, a.labels, a.ignore_index,
-                           a.row_lse, panel, ldp, (int)slabs);
-        return hipGetLastError();
+        const int64_t slabs = cdiv(nc, 8192), step = std::max<int64_t>(1, kPanelBlocks / slabs);
+        for (int64_t i = 0; i < a.N; i += step) {
+            hipLaunchKernelGGL(z_panel_kernel, dim3((unsigned)(std::min<int64_t>(step, a.N - i) * slabs)), dim3(256), 0, st,
+                               static_cast<const uint16_t*>(a.R) + i * a.ldr, a.ldr, a.V, (int)c0, (int)nc, a.labels + i,
+                               a.ignore_index, a.row_lse + i, panel + i * ldp, ldp, (int)slabs);
+            const hipError_t e = hipGetLastError();
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
     };
     hipError_t e;
     if (pc == a.V) {

@@ -115,3 +115,31 @@ def test_logits_workspace_without_panel(case):
         # R (and dW in bf16) rounded to bf16: 2^-9 at most each
         assert max(e.values()) <= 2.0 ** -8
     assert torch.equal(out["panels"]["db"], out["copies"]["db"])
+
+
+# More rows than one grid of the panel kernel has workgroups for
+def test_panel_of_many_rows():
+    N, d, V = 2 ** 24 + 1000, 64, 256
+    if torch.cuda.mem_get_info()[0] < 100e9:
+        pytest.skip("needs 100 GB of free memory")
+    log(f"[logits panels] N={N} d={d} V={V}")
+    g = torch.Generator(device=dev()).manual_seed(18)
+    H = torch.empty((N, d), dtype=torch.bfloat16, device=dev()).normal_(generator=g)
+    W = (torch.randn((d, V), generator=g, device=dev()) * 0.02).to(torch.bfloat16)
+    Z = torch.empty((N, V), dtype=torch.bfloat16, device=dev()).normal_(generator=g)
+    y = torch.randint(0, V, (N,), generator=g, device=dev(), dtype=torch.int32)
+    q = torch.randn(V, generator=g, device=dev()) * 0.01
+    res = bom.bom_residual(Z, y, write_R=False)
+    out = bom.bom_head_vjp(H, W, Z, y, q, res["n_valid"], lam=0.5, row_lse=res["row_lse"], dh_dtype=torch.float32)
+    rW = torch.zeros((d, V), dtype=torch.float64, device=dev())
+    for i in range(0, N, 1 << 21):
+        j = min(N, i + (1 << 21))
+        G = torch.softmax(Z[i:j].double(), 1)
+        G[torch.arange(j - i, device=dev()), y[i:j].long()] -= 1
+        G = (0.5 * G + 0.5 * q.double()) / N
+        rW += H[i:j].double().t() @ G
+        rH = G @ W.double().t()
+        # R rounded to bf16
+        assert float((out["dH"][i:j] - rH).norm() / rH.norm()) <= 2.0 ** -8
+    # R rounded to bf16, and fp32 sums of 2^24 products
+    assert float((out["dW"] - rW).norm() / rW.norm()) <= 2.0 ** -8
