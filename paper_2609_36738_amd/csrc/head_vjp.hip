@@ -2348,6 +2348,13 @@ Route route_of(const HeadVjpArgs& a) {
                         ((int64_t)(a.d - 1) * a.ldw + a.V) * 2 < (1LL << 31);
     const bool small = r.p.w.kind == kMfma128 && r.p.h.kind == kMfma128;
     if (!h_ok || (r.ua && (!ld_ok || (small && !fits31)))) r.p = simt_plan(a.N, a.d, a.V);
+    // dW alone over few rows is its own write, which the SIMT kernel has less to do before (us on the SIMT and the matrix kernels,
+    // d = 2320, V = 27392, from R: 9 rows 98 and 119, 17 rows 112 and 119; from the logits: 9 rows 97 and 158, 41 rows 151 and
+    // 158; V = 5001, from R: 33 rows 39 and 45, 48 rows 42 and 45; from the logits 57 rows 51 and 56)
+    const int few = a.is_residual ? (r.ua ? 52 : 20) : (r.ua ? 64 : 44);
+    if (!a.dH && a.dw_dt == BOM_F32 && a.N < few) {
+        r.p = simt_plan(a.N, a.d, a.V);
+    }
     if (!a.is_residual && (r.p.w.kind == kRank1 || (a.dH && r.p.h.kind == kRank1))) {
         // Without panels the 256-tile products form R as they copy it, which takes aligned rows: where the workspace holds no
         // panel, and where one tile covers d, so that each product forms an element once, and many rows keep the products
@@ -2359,14 +2366,6 @@ Route route_of(const HeadVjpArgs& a) {
         if (!r.panels && r.ua) r.p = simt_plan(a.N, a.d, a.V);
     }
     if (!a.dH) r.p.h = {kSimt, 1};   // no dH: no rank-1 vector and no partial sums for it
-    // dW alone over few rows is its own write, which the SIMT kernel has less to do before (us on the SIMT and the matrix kernels,
-    // d = 2320, V = 27392, from R: 9 rows 98 and 119, 17 rows 112 and 119; from the logits: 9 rows 97 and 158, 41 rows 151 and
-    // 158; V = 5001, from R: 33 rows 39 and 45, 48 rows 42 and 45; from the logits 57 rows 51 and 56)
-    const int few = a.is_residual ? (r.ua ? 52 : 20) : (r.ua ? 64 : 44);
-    if (!a.dH && a.dw_dt == BOM_F32 && a.N < few) {
-        r.p = simt_plan(a.N, a.d, a.V);
-        r.p.h = {kSimt, 1};
-    }
     // small products (both on the 128-tile kernel): one fused launch, nothing staged beforehand
     const PlanOverride& ov = plan_override();
     r.fused = r.p.w.kind == kMfma128 && (!a.dH || r.p.h.kind == kMfma128) && fits31 && fused_extents(a.N, a.V) &&
