@@ -2352,9 +2352,7 @@ Route route_of(const HeadVjpArgs& a) {
     // d = 2320, V = 27392, from R: 9 rows 98 and 119, 17 rows 112 and 119; from the logits: 9 rows 97 and 158, 41 rows 151 and
     // 158; V = 5001, from R: 33 rows 39 and 45, 48 rows 42 and 45; from the logits 57 rows 51 and 56)
     const int few = a.is_residual ? (r.ua ? 52 : 20) : (r.ua ? 64 : 44);
-    if (!a.dH && a.dw_dt == BOM_F32 && a.N < few) {
-        r.p = simt_plan(a.N, a.d, a.V);
-    }
+    if (!a.dH && a.dw_dt == BOM_F32 && a.N < few) r.p = simt_plan(a.N, a.d, a.V);
     if (!a.is_residual && (r.p.w.kind == kRank1 || (a.dH && r.p.h.kind == kRank1))) {
         // Without panels the 256-tile products form R as they copy it, which takes aligned rows: where the workspace holds no
         // panel, and where one tile covers d, so that each product forms an element once, and many rows keep the products
@@ -2670,17 +2668,23 @@ __global__ __launch_bounds__(256) void head_forward_simt_kernel(const T* __restr
 }  // namespace
 
 namespace {
-// Whether the 64 x 64 tiles of the small forward beat the 256 x 256 ones. Microseconds, from both kernels over N = 64 .. 16384,
-// V = 512 .. 32000, d = 64 .. 4096: a CU takes a 64-deep step of a small tile (two resident) in 0.34 (rows at any
-// alignment 0.48), a tile alone 0.3, in groups of four steps; a round of large tiles takes 5 beside its steps, of 1.25 with
-// few tiles to 1.85 with a full chip (times 1.2 at any alignment). At d = 768 (small, large): 512 x 1000 7.1 and 20.4 us,
-// 4096 x 1000 18.8 and 21.8, 8192 x 1000 33.1 and 28.9, 256 x 32000 38.3 and 21.0; 1024 x 4096 x 2048 35 and 83,
-// 2048 x 2048 x 4096 64 and 45.
-bool forward_small(int64_t N, int64_t d, int64_t V, bool ua) {
+// Whether the 64 x 64 tiles of the small forward beat the 256 x 256 ones. Microseconds, from both kernels over N = 32 .. 16384,
+// V = 512 .. 128256, d = 64 .. 4096: a CU takes a 64-deep step of a small tile (two resident) in 0.34 (rows at any
+// alignment 0.48), a tile alone 0.3, in groups of four steps; a round of large tiles takes 5 beside its steps, of 1.1 or 1.25
+// with few tiles to 1.85 with a full chip (times 1.2 at any alignment). Small tiles read W once per 64 rows, in parts of
+// rows that are one cache line wide, or two where rows are not whole lines: 5 TB/s where W is past the caches. At
+// d = 768 (small, large): 512 x 1000 7.1 and 20.4 us, 4096 x 1000 18.8 and 21.8, 8192 x 1000 33.1 and 28.9, 256 x 32000 38.3 and
+// 21.0; 1024 x 4096 x 2048 35 and 83, 2048 x 2048 x 4096 64 and 45; 32 x 4096 x 67928 155 and 177, 86 x 4096 x 67928 290 and 186,
+// 86 x 888 x 67928 68 and 53, x 67968 43 and 52.
+bool forward_small(int64_t N, int64_t d, int64_t V, int64_t ldw, bool ua) {
     const int64_t tiles = cdiv(N, FB) * cdiv(V, FB), T = cdiv(N, LB) * cdiv(V, LB), nk = cdiv(d, FK);
     const double n4 = (double)(cdiv(nk, FSETS) * FSETS);
-    const double small = 3.0 + std::max((double)tiles * n4 / kCUs * (ua ? 0.48 : 0.34), n4 * 0.3);
-    const double large = (double)cdiv(T, kCUs) * (5.0 + (double)nk * (1.25 + 0.6 * std::min(1.0, (double)T / kCUs)));
+    double small = 3.0 + std::max((double)tiles * n4 / kCUs * (ua ? 0.48 : 0.34), n4 * 0.3);
+    const double w = 2.0 * (double)d * V;
+    if (w > 64e6) small = std::max(small, w * cdiv(N, FB) / 5e6 * (ldw % 64 == 0 ? 1.0 : 1.45));
+    const int64_t full = T / kCUs, rem = T % kCUs;
+    double large = (double)full * (5.0 + (double)nk * 1.85);
+    if (rem > 0) large += 5.0 + (double)nk * ((full > 0 ? 1.1 : 1.25) + 0.6 * (double)rem / kCUs);
     return small < large * (ua ? 1.2 : 1.0);
 }
 }  // namespace
@@ -2708,7 +2712,7 @@ hipError_t launch_head_forward(const void* H, int64_t ldh, const void* W, int64_
     const bool ua = !(V % 8 == 0 && al(W, ldw));
     if (mfma_extents(d, V, ua) && al(H, ldh) && (!ua || ldw < (1 << 24)) &&
         ((int64_t)(N - 1) * ldh + d) * 2 < (1LL << 31) && ((int64_t)(d - 1) * ldw + V) * 2 < (1LL << 31)) {
-        if (forward_small(N, d, V, ua) && ldw < (1 << 22)) {
+        if (forward_small(N, d, V, ldw, ua) && ldw < (1 << 22)) {
             FusedArgs fa{};
             fa.H = H16;
             fa.ldh = ldh;
