@@ -36,10 +36,18 @@ constexpr int kFacUpdRows = 8;      // rows per update workgroup
 // 919 -> 913. The order alone gave nothing (non-temporal reads are not kept); 128 MB gave a third of
 // it, and plain loads throughout cost the factored step 45 us at 1.1G parameters. There the last 256 MB are too small a
 // part to pay (2886 to 2890 us before, 2881 to 2910 with them): the factored step keeps a numerator of up to 2 GB only.
-constexpr int64_t kKeepBytes = 256ll << 20;
-// first element, of n of `bytes` each (of u, or of u and h), that the first pass leaves in the cache
-__device__ __forceinline__ int64_t keep_from(int64_t n, int bytes) { return n - kKeepBytes / bytes; }
-__host__ __device__ __forceinline__ bool factored_keeps(int64_t P) { return P <= 8 * kKeepBytes / 4; }
+// Where all that the step touches is no more than kCachedBytes it lies in that cache from the step before, or from whoever
+// wrote the numerator, and both passes stream in order (dense 4.9M 23.7 us, 26.0 with the last read first; 12.2M 48.8 and 50.3;
+// bf16 12.2M 27.7 and 30.5; factored 6.7M 60.3 and 65.1; at 22M dense 81 and 79).
+constexpr int64_t kKeepBytes = 256ll << 20, kCachedBytes = 200ll << 20;
+// whether the last part of a numerator of n elements is kept and read first, where the step touches `all` bytes of each
+__host__ __device__ __forceinline__ bool keeps(int64_t n, int all) { return n * all > kCachedBytes; }
+// first element, of `bytes` each (of u, or of u and h), that the first pass leaves in the cache
+__device__ __forceinline__ int64_t keep_from(int64_t n, int bytes, int all) { return keeps(n, all) ? n - kKeepBytes / bytes : n; }
+__host__ __device__ __forceinline__ bool factored_keeps(int64_t P) { return keeps(P, 8) && P <= 8 * kKeepBytes / 4; }
+// bytes of an element of the dense step: theta, v, u and h
+template <bool SPLIT, int E>
+constexpr int kDenseBytes = (SPLIT ? 4 : 3) * E;
 template <bool KEEP, typename V, typename T>
 __device__ __forceinline__ V ld_first(const T* p) {
     if constexpr (KEEP) return *reinterpret_cast<const V*>(p);
@@ -84,7 +92,7 @@ __global__ __launch_bounds__(kUpdThreads) void update_dense_vec4_kernel(float* _
                                                                         const float* __restrict__ h, int64_t head,
                                                                         int64_t nvec, int64_t P, SegTable segs,
                                                                         UpdateScalars sc) {
-    const int64_t q = from_end(sc.clip != nullptr) * kUpdThreads + threadIdx.x;
+    const int64_t q = from_end(sc.clip != nullptr && keeps(P, kDenseBytes<SPLIT, 4>)) * kUpdThreads + threadIdx.x;
     sc = clipped(sc);
     if (q >= nvec) {
         const int64_t r = q - nvec;
@@ -202,7 +210,7 @@ __global__ __launch_bounds__(kUpdThreads) void update_dense_bf16x8_kernel(uint16
                                                                           const uint16_t* __restrict__ h, int64_t head,
                                                                           int64_t nvec, int64_t P, SegTable segs,
                                                                           UpdateScalars sc) {
-    const int64_t q = from_end(sc.clip != nullptr) * kUpdThreads + threadIdx.x;
+    const int64_t q = from_end(sc.clip != nullptr && keeps(P, kDenseBytes<SPLIT, 2>)) * kUpdThreads + threadIdx.x;
     sc = clipped(sc);
     if (q >= nvec) {
         const int64_t r = q - nvec;
@@ -541,7 +549,7 @@ __global__ __launch_bounds__(kUpdThreads) void factored_stats_rows_kernel(const 
     };
     int64_t i = r0 + w;   // two loops: the two loads in one would become plain ones
     if constexpr (KEEP) {
-        const int64_t keep = keep_from(P, SPLIT ? 8 : 4) / BC;   // rows from it on
+        const int64_t keep = keep_from(P, SPLIT ? 8 : 4, 8) / BC;   // rows from it on
         for (; i < min(r1, keep); i += kUpdThreads / kWave) row(i, std::false_type{});
         for (; i < r1; i += kUpdThreads / kWave) row(i, std::true_type{});
     } else {
@@ -803,7 +811,7 @@ __global__ __launch_bounds__(kUpdThreads) void clip_partial_kernel(const float* 
         const int64_t nvec = n / 4;
         int64_t q = (int64_t)blockIdx.x * kUpdThreads + t;
         // kClipUnroll groups per thread in flight, then the remainder one group at a time
-        const int64_t keep = SQUARE ? keep_from(n, SPLIT ? 8 : 4) / 4 : 0;   // groups from about it on
+        const int64_t keep = SQUARE ? keep_from(n, SPLIT ? 8 : 4, kDenseBytes<SPLIT, 4>) / 4 : nvec;   // groups from about it on
         auto groups = [&](auto kept) {
             f32x4 u4[kClipUnroll], h4[kClipUnroll];
 #pragma unroll
@@ -821,16 +829,18 @@ __global__ __launch_bounds__(kUpdThreads) void clip_partial_kernel(const float* 
         };
         for (; q + (kClipUnroll - 1) * stride < min(nvec, keep); q += kClipUnroll * stride) groups(std::false_type{});
         for (; q + (kClipUnroll - 1) * stride < nvec; q += kClipUnroll * stride) groups(std::true_type{});
-        for (; q < nvec; q += stride) {
-            const f32x4 u4 = ld_first<true, f32x4>(u + q * 4);
+        auto group = [&](auto kept) {
+            const f32x4 u4 = ld_first<decltype(kept)::value, f32x4>(u + q * 4);
             f32x4 h4 = {0.f, 0.f, 0.f, 0.f};
-            if (SPLIT) h4 = ld_first<true, f32x4>(h + q * 4);
+            if (SPLIT) h4 = ld_first<decltype(kept)::value, f32x4>(h + q * 4);
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
                 const double x = SQUARE ? (double)numerator<SPLIT>(u4[c], h4[c], sc) : (double)u4[c];
                 acc += SQUARE ? x * x : x;
             }
-        }
+        };
+        for (; q < min(nvec, keep); q += stride) group(std::false_type{});
+        for (; q < nvec; q += stride) group(std::true_type{});
         done = nvec * 4;
     }
     for (int64_t e = done + (int64_t)blockIdx.x * kUpdThreads + t; e < n; e += stride) {
@@ -856,7 +866,7 @@ __global__ __launch_bounds__(kUpdThreads) void clip_partial_bf16_kernel(const ui
     int64_t done = 0;
     if (vec8) {
         const int64_t nvec = n / 8;
-        const int64_t keep = keep_from(n, SPLIT ? 4 : 2) / 8;   // groups from about it on
+        const int64_t keep = keep_from(n, SPLIT ? 4 : 2, kDenseBytes<SPLIT, 2>) / 8;   // groups from about it on
         auto group = [&](int64_t q, auto kept) {
             const u32x4_t u8 = ld_first<decltype(kept)::value, u32x4_t>(u + q * 8);
             u32x4_t h8 = {0u, 0u, 0u, 0u};

@@ -16,6 +16,13 @@ CASES = [("all_kept", KEEP - 3, "f32", "dense", False), ("some_streamed", KEEP +
          ("rows_kept", KEEP - 4, "f32", "factored", False), ("rows_streamed", KEEP + 4096 * 70 + 4, "f32", "factored", False),
          ("rows_split", KEEP // 2 + 4096 * 65 + 8, "f32", "factored", True)]
 
+# the step's buffers all cached (up to 200 MB) and just past it
+ALL = 200 << 20
+CASES += [("cached", ALL // 12, "f32", "dense", False), ("past_cached", ALL // 12 + 1, "f32", "dense", False),
+          ("cached_split", ALL // 16, "f32", "dense", True), ("past_cached_split", ALL // 16 + 4, "f32", "dense", True),
+          ("cached_bf16", ALL // 6, "bf16", "dense", False), ("past_cached_bf16", ALL // 6 + 8, "bf16", "dense", False),
+          ("rows_cached", ALL // 8, "f32", "factored", False), ("rows_past_cached", ALL // 8 + 4, "f32", "factored", False)]
+
 
 @pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
 def test_numerator_read_twice(case):
