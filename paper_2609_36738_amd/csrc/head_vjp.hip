@@ -1934,6 +1934,12 @@ GemmPlan plan_wide(int64_t M, int64_t N, int64_t K, bool inner_is_m) {
 // The fused launch of small products: each tile runs over the whole k range, so both k extents stay short.
 bool fused_extents(int64_t N, int64_t V) { return N <= 8192 && V <= 8192; }
 
+// Whether ragged small products take the fused launch, whose tiles run over all of V or N one step after another (3 us and
+// 0.015 per k, 0.0195 from the logits), or the 256-tile kernel, which splits k (22 us and 0.018 per row). N x d x V, us, fused
+// and 256 tiles: 24 x 144 x 1001 19 and 23, x 2001 33 and 24, x 7423 104 and 30; 1000 x 392 x 2001 41 and 55, 1000 x 64 x 4409
+// 71 and 46.
+bool fused_ragged(int64_t N, int64_t V) { return 3.0 + 0.015 * (double)std::max(N, V) < 22.0 + 0.018 * (double)N; }
+
 GemmPlan plan_gemm(bool mfma, bool big_ok, int64_t M, int64_t N, int64_t K, bool inner_is_m) {
     if (!mfma || !big_ok) return {kSimt, choose_splits(cdiv(M, SB) * cdiv(N, SB), M, N, K, SB, SK, 4)};
     // large products: 256-tile rank-1 kernel; small ones (a few dozen 256 tiles or a short k) are
@@ -2096,7 +2102,7 @@ Plan make_plan_uncached(int64_t N, int64_t d, int64_t V, bom_dtype dt, bool ua) 
     if (ua) {
         // rows at any alignment have two kernels: the fused launch for small products, which takes both of them,
         // and the 256-tile kernel for the rest
-        if (!(p.w.kind == kMfma128 && p.h.kind == kMfma128 && fused_extents(N, V))) {
+        if (!(p.w.kind == kMfma128 && p.h.kind == kMfma128 && fused_extents(N, V) && fused_ragged(N, V))) {
             if (p.w.kind == kMfma128) p.w = plan_wide(d, V, N, true);
             if (p.h.kind == kMfma128) p.h = plan_wide(N, d, V, false);
         }
