@@ -38,14 +38,13 @@ typedef __attribute__((ext_vector_type(16))) float f32x16_t;
 struct Fold {
     const float* cq;     // [V] lambda * q_hat / N_t
     const float* vmask;  // [N] 1 for rows in I, else 0
-    const float* scal;   // [0] alpha = (1 - lambda) / N_t; [1] s_out; [2], [3] bf16 pairs (r_coef, 0), (0, r_coef)
-    const float* cqp;    // [V] history term of the rescaled fold G = s_out * (r_coef * R + cqp)
+    const float* scal;   // [0] alpha = (1 - lambda) / N_t
     const float* zc;     // logits input: [N] lse_i log2 e for rows in I, +inf otherwise; null: R is stored
     const int32_t* labels;
 };
 
 struct VjpWs {
-    size_t cq_off, cqp_off, vmask_off, scal_off, zc_off, hpart_off, hsum_off, u_off, upart_off, part_off, total;
+    size_t cq_off, vmask_off, scal_off, zc_off, hpart_off, hsum_off, u_off, upart_off, part_off, total;
 };
 // Past it (and past the fp32 dW and db of a bf16 gradient), for logits of large products: a panel of R, dH's sums over
 // panels, and the panels' partial sums. Bytes from its start; total is 0 where the products take no panels.
@@ -142,11 +141,8 @@ __global__ __launch_bounds__(256) void z_panel_kernel(const uint16_t* __restrict
 }
 
 // ---- prep -------------------------------------------------------------------------------------
-// G = alpha R + mask * cq  (alpha = (1-lambda)/N_t, cq = lambda q_hat / N_t) is also written
-// G = s_out (r_coef R + mask * cqp): for lambda < 1, s_out = alpha, r_coef = 1, cqp = lambda/(1-lambda) q_hat;
-// for lambda = 1, s_out = 1/N_t, r_coef = 0, cqp = q_hat. The large-tile kernels fold cqp with one
-// bf16 dot product per element and apply s_out to the fp32 accumulators.
-// db in fp32, or rounded to bf16
+// The parts of G = mask * (alpha R + cq), alpha = (1-lambda)/N_t, cq = lambda q_hat / N_t, the rank-1 vectors from their partial
+// sums, and db (in fp32, or rounded to bf16).
 __device__ __forceinline__ void store_db(void* db, int bf16, int j, float x) {
     if (bf16) static_cast<uint16_t*>(db)[j] = f32_to_bf16(x);
     else static_cast<float*>(db)[j] = x;
@@ -155,8 +151,8 @@ __device__ __forceinline__ void store_db(void* db, int bf16, int j, float x) {
 __global__ __launch_bounds__(256) void vjp_prep_kernel(const float* __restrict__ q_hat, const float* __restrict__ s,
                                                        const int32_t* __restrict__ n_valid, float lambda, int V, int N,
                                                        const int32_t* __restrict__ labels, int32_t ignore_index,
-                                                       float* __restrict__ cq, float* __restrict__ cqp,
-                                                       float* __restrict__ vmask, float* __restrict__ scal,
+                                                       float* __restrict__ cq, float* __restrict__ vmask,
+                                                       float* __restrict__ scal,
                                                        void* __restrict__ db, int db_bf16,
                                                        const float* __restrict__ hpart, int nrb,
                                                        int d, float* __restrict__ hsum, const float* __restrict__ row_lse,
@@ -182,10 +178,8 @@ __global__ __launch_bounds__(256) void vjp_prep_kernel(const float* __restrict__
         for (int c = 0; c < uch; ++c) a += upart[(int64_t)c * d + idx];
         u[idx] = nt > 0 ? (float)((double)lambda / (double)nt) * a : 0.f;
     }
-    const bool hist_only = !(lambda < 1.0f);
     if (idx < V) {
         cq[idx] = nt > 0 ? (float)((double)lambda * (double)q_hat[idx] / (double)nt) : 0.f;
-        cqp[idx] = hist_only ? q_hat[idx] : (float)((double)lambda / (1.0 - (double)lambda) * (double)q_hat[idx]);
         if (db) store_db(db, db_bf16, idx, nt > 0 ? (1.0f - lambda) * s[idx] + lambda * q_hat[idx] : 0.f);
     }
     if (idx < N) {
@@ -194,13 +188,7 @@ __global__ __launch_bounds__(256) void vjp_prep_kernel(const float* __restrict__
         vmask[idx] = valid ? 1.f : 0.f;
         if (row_lse != nullptr) zc[idx] = valid ? row_lse[idx] * kLog2e : INFINITY;
     }
-    if (idx == 0) {
-        scal[0] = nt > 0 ? (float)((1.0 - (double)lambda) / (double)nt) : 0.f;
-        scal[1] = nt > 0 ? (hist_only ? (float)(1.0 / (double)nt) : scal[0]) : 0.f;
-        const uint32_t one = hist_only ? 0u : 0x3F80u;   // bf16 1.0 (or 0 when R drops out)
-        scal[2] = __uint_as_float(one);
-        scal[3] = __uint_as_float(one << 16);
-    }
+    if (idx == 0) scal[0] = nt > 0 ? (float)((1.0 - (double)lambda) / (double)nt) : 0.f;
 }
 
 template <typename T>
@@ -655,33 +643,6 @@ __global__ __launch_bounds__(256) void mfma_dH_kernel(const uint16_t* __restrict
 // c ^ ((r ^ (r >> 3)) & 7), free of bank conflicts on gfx950 for 16-byte fragment reads and for the
 // 1 KB-per-wave staging writes.
 __device__ __forceinline__ int swz(int row, int chunk) { return chunk ^ ((row ^ (row >> 3)) & 7); }
-
-template <typename F>
-__device__ __forceinline__ void for_each_acc256(const f32x16_t (&acc)[4][4], F&& fn) {
-    const int lane = threadIdx.x % kWave, w = threadIdx.x / kWave;
-    const int wm = w / 2, wn = w % 2;
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r)
-                fn(wm * 128 + i * 32 + (r / 4) * 8 + (lane / 32) * 4 + (r % 4), wn * 128 + j * 32 + lane % 32,
-                   acc[i][j][r]);
-}
-
-// Workgroup -> tile map: tiles along the short dimension ("inner", reused operand) that share a
-// long-dimension tile run on one XCD together (workgroups are dealt to the 8 XCDs round-robin).
-__device__ __forceinline__ bool tile_of(int inner_count, int outer_count, bool inner_is_m, int* tm, int* tn) {
-    const int id = blockIdx.x;
-    const int xcd = id % 8, rest = id / 8;
-    const int inner = rest % inner_count, og = rest / inner_count;
-    const int outer = og * 8 + xcd;
-    if (outer >= outer_count) return false;
-    *tm = inner_is_m ? inner : outer;
-    *tn = inner_is_m ? outer : inner;
-    return true;
-}
 
 // A launch over the outer tiles [outer_begin, outer_end), each split into `splits` k ranges (whole
 // rounds of the chip run with the full k range; the leftover tiles split k so that they fill the chip
@@ -2170,8 +2131,7 @@ VjpWs vjp_ws(int64_t N, int64_t d, int64_t V, bom_dtype dt) {
     const Plan pu = dt == BOM_BF16 ? make_plan(N, d, V, dt, true) : p;
     VjpWs w;
     w.cq_off = 0;
-    w.cqp_off = align256((size_t)V * 4);
-    w.vmask_off = align256(w.cqp_off + (size_t)V * 4);
+    w.vmask_off = align256((size_t)V * 4);
     w.scal_off = align256(w.vmask_off + (size_t)N * 4);
     const bool r1 = p.w.kind == kRank1 || p.h.kind == kRank1 || pu.w.kind == kRank1 || pu.h.kind == kRank1;
     w.zc_off = align256(w.scal_off + 16);
@@ -2427,7 +2387,7 @@ hipError_t launch_prep(const HeadVjpArgs& a, const VjpWs& L, bool rw, bool rh, b
     int nprep = a.V > a.N ? a.V : a.N;
     if (nprep < a.d) nprep = a.d;
     hipLaunchKernelGGL(vjp_prep_kernel, dim3((nprep + 255) / 256), dim3(256), 0, st, a.q_hat, a.s, a.n_valid, a.lambda,
-                       a.V, a.N, a.labels, a.ignore_index, at(L.cq_off), at(L.cqp_off), at(L.vmask_off), at(L.scal_off),
+                       a.V, a.N, a.labels, a.ignore_index, at(L.cq_off), at(L.vmask_off), at(L.scal_off),
                        a.db, a.dw_dt == BOM_BF16 ? 1 : 0, rw ? hpart : nullptr, nrb, a.d, at(L.hsum_off),
                        a.is_residual ? nullptr : a.row_lse, at(L.zc_off), rh ? upart : nullptr, uch, at(L.u_off));
     return hipGetLastError();
@@ -2467,7 +2427,7 @@ hipError_t launch_from_logits(const HeadVjpArgs& a, const VjpWs& L, hipStream_t 
     if ((e = launch_prep(a, L, hist, hist && a.dH != nullptr, ua, st)) != hipSuccess) return e;
     const float *cq = at(L.cq_off), *u = at(L.u_off), *hsum = at(L.hsum_off), *vmask = at(L.vmask_off);
     float *part = at(p0 + PL.part_off), *hacc = at(p0 + PL.hacc_off);
-    const Fold f{cq, vmask, at(L.scal_off), at(L.cqp_off), nullptr, a.labels};
+    const Fold f{cq, vmask, at(L.scal_off), nullptr, a.labels};
     const int64_t np = panel_count(a.V, pc);
     for (int64_t i = 0; i < np; ++i) {
         const int64_t c0 = i * pc, nc = i + 1 < np ? pc : a.V - c0;
@@ -2507,7 +2467,6 @@ hipError_t launch_products(const HeadVjpArgs& a, const Route& r, hipStream_t st)
     const bool ua = r.ua;
     char* base = static_cast<char*>(a.ws);
     float* cq = reinterpret_cast<float*>(base + L.cq_off);
-    float* cqp = reinterpret_cast<float*>(base + L.cqp_off);
     float* vmask = reinterpret_cast<float*>(base + L.vmask_off);
     float* scal = reinterpret_cast<float*>(base + L.scal_off);
     float* hsum = reinterpret_cast<float*>(base + L.hsum_off);
@@ -2559,7 +2518,7 @@ hipError_t launch_products(const HeadVjpArgs& a, const Route& r, hipStream_t st)
     const bool hist = a.lambda != 0.f;
     hipError_t e = launch_prep(a, L, p.w.kind == kRank1 && hist, p.h.kind == kRank1 && hist, ua, st);
     if (e != hipSuccess) return e;
-    const Fold f{cq, vmask, scal, cqp, zin ? zc : nullptr, a.labels};
+    const Fold f{cq, vmask, scal, zin ? zc : nullptr, a.labels};
 
     if (p.pair && a.dH && p.w.kind == kRank1 && p.h.kind == kRank1) {
         // one grid: dH's units (k split p.h.splits) first, then dW's tiles over the full k range
