@@ -183,11 +183,14 @@ bom_status bom_ema(float* q, const float* s, int64_t V, float beta1, int64_t t, 
  *   q_hat device fp32 [V].   s device fp32 [V] (only read when db != NULL).
  *   n_valid device int32 [1].
  *   dW  device [d, lddw] of dw_dt; lddw >= V.   db device [V] of dw_dt, or NULL.
- *   dw_dt BOM_F32, or BOM_BF16 for bf16 gradient storage (dW, db formed in fp32 in the workspace, then
- *       rounded to nearest-even bf16: dW = bf16(H^T G + dW_beta * dW)).
+ *   dw_dt BOM_F32, or BOM_BF16 for bf16 gradient storage: dW = bf16(H^T G + dW_beta * dW), rounded to nearest even once
+ *       from the fp32 sums, as most products store them, or in a pass over fp32 sums in the workspace (128-tile and SIMT
+ *       products, fp32 operands, and large products from the logits without a panel).
  *   dH  device [N, lddh] of dh_dt (BOM_BF16 or BOM_F32), or NULL.
  *   workspace: at least bom_head_vjp_workspace_bytes(N, d, V, dt, dw_dt) bytes (may be 0); with is_residual = 0 best
  *       bom_head_vjp_logits_workspace_bytes of the same arguments, which is that size plus the panel's.
+ * With infinities in H or W the large and the small bf16 products, which add the history as alpha H^T R + (sum of H over I)
+ * cq^T, may give NaN where the sum over G would be infinite.
  * Errors: BOM_ERR_NULL (also: row_lse missing with is_residual = 0), BOM_ERR_SHAPE (also: is_residual
  *         not 0 or 1), BOM_ERR_DTYPE, BOM_ERR_HYPER (lambda not in [0,1]), BOM_ERR_WORKSPACE, BOM_ERR_HIP.
  * ---------------------------------------------------------------------------------------- */
@@ -335,9 +338,10 @@ bom_status bom_head_telemetry(const void* H, int64_t ldh, bom_dtype h_dt, const 
  * bom_head_forward -- support call (row a0 of the path; the forward is common work, not one of the
  * four steps): the linear head's logits Z = H W (+ b), fp32 accumulation, Z rounded once to dt.
  * dt = BOM_BF16 (the language-model and vision workloads' logits, as bf16 autocast computes them) runs
- * on the matrix cores (256 x 256 tiles, 64 x 64 for small products) when d is a multiple of 8, V is at least 8 and H is 16-byte aligned with a
- * leading dimension that is a multiple of 8 (V, W and its leading dimension are free), and on a SIMT kernel otherwise; dt = BOM_F32
- * (the tiny classifier) runs on the SIMT kernel.
+ * on the matrix cores (256 x 256 tiles, 64 x 64 for small products) when d is a multiple of 8, V is at least 8 and H is
+ * 16-byte aligned with a leading dimension that is a multiple of 8 (V and W's alignment are free; rows of W that are not
+ * multiples of 16 bytes have to lie less than 2^24 columns apart), and on a SIMT kernel otherwise; dt = BOM_F32 runs on
+ * the fp32 matrix instructions (a large Z of fewer than four features on the SIMT kernel).
  *   H device [N, ldh], W device [d, ldw], b device [V] or NULL, Z device [N, ldz], all of dt.
  * Errors: BOM_ERR_NULL, BOM_ERR_SHAPE, BOM_ERR_DTYPE, BOM_ERR_HIP.
  * ---------------------------------------------------------------------------------------- */

@@ -436,8 +436,9 @@ bom_status bom_head_forward_residual(const void* H, int64_t ldh, const void* W, 
     hipStream_t st = static_cast<hipStream_t>(stream);
     // The forward, then the residual on its logits. (Row statistics of each 256-column tile in the forward's epilogue and a
     // residual from them, built and measured, lost at every shape: the epilogue's work while its CU issues no matrix
-    // instructions cost more than the residual, which reads Z once either way, could save: 482 against 377 us at
-    // N = 4096, d = 768, V = 32,000, 17.2 against 16.4 ms at N = 16384, d = 4096, V = 128,256.)
+    // instructions cost more than the residual, which reads Z once either way, could save: with the same tiles 476 against
+    // 374 us at N = 4096, d = 768, V = 32,000, 2154 against 1879 at 8192, 2048, 50,304, 17.4 against 16.1 ms at 16384, 4096,
+    // 128,256.)
     hipError_t e = bom::launch_head_forward(H, ldh, W, ldw, b, dt, (int)N, (int)d, (int)V, Z, ldz, st);
     if (e != hipSuccess) return hip_status(e, "bom_head_forward_residual (forward)");
     return hip_status(bom::launch_residual(Z, dt, (int)N, (int)V, ldz, labels, ignore_index, s, row_lse, row_argmax,

@@ -5,7 +5,7 @@
 // G is never stored. The large products (and the fused launch for small ones) use its rank-1 split
 //   dW = alpha H^T R + hsum cq^T,  dH = alpha R W^T + mask u^T,
 //   alpha = (1 - lambda) / N_t,  cq_j = lambda q_hat_j / N_t,  hsum = sum over rows in I of H,  u = W cq,
-// multiplying R as stored; the 128-tile split-K kernels instead form G = fma(alpha, R, mask_i * cq_j)
+// multiplying R as stored; the 128-tile split-K kernels instead form G = mask_i * fma(alpha, R, cq_j)
 // while staging R into LDS and round it to bf16 for the MFMA.
 //
 // bf16 path: v_mfma_f32_32x32x16_bf16. Large products: 256 x 256 output tiles, eight waves (two per
@@ -14,7 +14,8 @@
 // fixed-order reduction. dW = H^T G has both operands k-outer in memory (transposing LDS reads or a
 // transpose while staging); dH = G W^T has both operands k-contiguous. The fused and the 256-tile
 // kernels also take R and W with rows at any alignment and of any length (UA): a 4088 x 1024 x 50,257 head VJP takes
-// 0.87 ms with it, against 22.5 ms on the SIMT tiled GEMM that is left for bf16 with H unaligned. fp32 path: head_f32.hip.
+// 0.87 ms with it, against 22.5 ms on the SIMT tiled GEMM that is left for bf16 with H unaligned, dW alone over a few rows, and
+// large ragged products from the logits without a panel. fp32 path: head_f32.hip.
 #include <algorithm>
 #include <array>
 #include <map>
@@ -213,7 +214,7 @@ __device__ __forceinline__ float r_elem(const uint16_t* RZ, int64_t ld, int row,
     return bf16_to_f32(f32_to_bf16(r_from_z(x, f.zc[row], col == f.labels[row])));
 }
 
-// ---- SIMT fallback (bf16 with H unaligned): 64 x 64 tiles, 16-deep k, 4 x 4 outputs per thread --------------------------
+// ---- SIMT kernels (bf16; see route_of for what takes them): 64 x 64 tiles, 16-deep k, 4 x 4 outputs per thread -----------
 constexpr int SB = 64, SK = 16;
 
 // dW[m][n] = sum_k H[k][m] G[k][n];  M = d, Nn = V, K = N rows.
@@ -2097,7 +2098,7 @@ Plan make_plan(int64_t N, int64_t d, int64_t V, bom_dtype dt, bool ua) {
 }
 
 // Plan of the SIMT kernels, which run bf16 operands that the MFMA kernels cannot stage (H not aligned to 16
-// bytes, d not a multiple of 8, fewer than eight columns): SIMT tiles with their own k split over every tile.
+// bytes, d not a multiple of 8, fewer than eight columns) and what route_of gives them: SIMT tiles with their own k split over every tile.
 Plan simt_plan(int64_t N, int64_t d, int64_t V) {
     Plan p;
     p.w = plan_gemm(false, false, d, V, N, true);

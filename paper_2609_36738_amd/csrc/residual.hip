@@ -4,12 +4,12 @@
 //
 // Three paths, all deterministic (fixed reduction orders, no floating-point atomics):
 //  * single pass (V up to ~53k bf16 / ~26k fp32): one wave per row for narrow rows, a workgroup for a small batch
-//    of them, otherwise one persistent workgroup per CU that keeps a whole row in registers or LDS, reduces max /
-//    argmax / sum across the workgroup, writes R, and accumulates its rows' residuals per column in registers; Z is
+//    of them, otherwise one persistent workgroup per CU (two or three over many ragged bf16 rows of up to 12,288
+//    columns) that keeps a whole row in registers or LDS, reduces max / argmax / sum across the workgroup, writes R, and accumulates its rows' residuals per column in registers; Z is
 //    read from HBM exactly once.
 //  * split rows (bf16 up to 524,288 columns): several workgroups share each row and exchange their
 //    per-part statistics; Z is still read once.
-//  * two pass (other shapes): a stats kernel (one wave per row, online max / sum / argmax) writes the
+//  * two pass (other shapes, and ragged bf16 rows where it is faster): a stats kernel (one wave per row, online max / sum / argmax) writes the
 //    row statistics, then a column-slab kernel re-reads Z, writes R and accumulates per-column
 //    partials for blocks of rows.
 // A finish step sums the per-workgroup partials in a fixed order into s, loss, N_t and flags.
