@@ -345,8 +345,7 @@ def time_forward(prob, steps):
 
 def time_forward_residual(prob, steps):
     """The head forward followed by the residual, as two calls (bom_head_forward, bom_residual) and as the
-    fused call (bom_head_forward_residual: row statistics from the forward's epilogue, then one pass over Z
-    for R and s), each timed over `steps` calls into scratch Z and R; inputs H, W, labels of the workload."""
+    one call (bom_head_forward_residual), each timed over `steps` calls into scratch Z and R; inputs H, W, labels of the workload."""
     w = prob.w
     W = prob.W if prob.W is not None else prob.theta[: w.d * w.V].view(w.d, w.V)
     b = None if not w.has_bias else prob.theta[w.d * w.V: w.d * w.V + w.V]
@@ -706,8 +705,8 @@ def main():
                     help="also time the head forward Z = H W that produces the logits (common work, outside the "
                          "step) against the MFMA roofline")
     ap.add_argument("--fused-forward", action="store_true",
-                    help="also time the head forward plus the residual as two calls and as the fused call with the "
-                         "row statistics from the forward's epilogue (common work plus the residual, outside the step)")
+                    help="also time the head forward plus the residual as two calls and as one (common work plus the "
+                         "residual, outside the step)")
     ap.add_argument("--telemetry", action="store_true",
                     help="also time the head drift telemetry call (a diagnostic for telemetry steps, outside the "
                          "step) on the last step's residual, history and features")
