@@ -2071,6 +2071,13 @@ Plan make_plan_uncached(int64_t N, int64_t d, int64_t V, bom_dtype dt, bool ua) 
         if (p.w.kind == kRank1 && p.h.kind == kRank1) plan_pair(p, N, d, V);
         return p;
     }
+    // The 128-tile kernel rounds G to bf16, which loses R beside a larger history term (dW at 8200 x 32 x 4504: 1e-2 of its norm).
+    // A number of rows that is not a multiple of eight, which it once could not take, goes to the 256-tile kernel instead,
+    // which multiplies R as stored.
+    if (automatic && ok && N % 8 != 0 && !(p.w.kind == kMfma128 && p.h.kind == kMfma128 && fused_extents(N, V))) {
+        if (p.w.kind == kMfma128) p.w = plan_wide(d, V, N, true);
+        if (p.h.kind == kMfma128) p.h = plan_wide(N, d, V, false);
+    }
     apply_override(p.w, o.kw, o.sw, d, V, N);
     apply_override(p.h, o.kh, o.sh, N, d, V);
     if (automatic && p.w.kind == kRank1 && p.h.kind == kRank1) plan_pair(p, N, d, V);

@@ -189,3 +189,24 @@ def test_residual_any_alignment(N, V, pad, off):
     assert float((out["s"] - p.sum(0) / n).norm() / (p.sum(0) / n).norm()) <= 2e-6
     again = bom.bom_residual(Z, y)
     assert torch.equal(again["R"], Rbuf[:, :V]) and torch.equal(again["s"], out["s"])
+
+
+# A number of rows that is not a multiple of eight, past the fused launch and with few output tiles of either product: the
+# history term is much larger than R, and R is multiplied as stored all the same
+@pytest.mark.parametrize("N,d,V", [(8201, 32, 4504), (9001, 264, 64), (33, 264, 9000), (257, 64, 20000), (8193, 8, 16)])
+@pytest.mark.parametrize("want_dH", [True, False])
+def test_any_number_of_rows(N, d, V, want_dH):
+    log(f"[any rows] N={N} d={d} V={V} dH={want_dH}")
+    g = torch.Generator(device=dev()).manual_seed(19)
+    H, W = _rand(g, (N, d), 1.0, torch.bfloat16), _rand(g, (d, V), 0.05, torch.bfloat16)
+    y = torch.randint(0, V, (N,), generator=g, device=dev(), dtype=torch.int32)
+    y[1::7] = -100
+    ok = y >= 0
+    res = bom.bom_residual((H.float() @ W.float()).bfloat16(), y)
+    q = _rand(g, (V,), 0.05, torch.float32)
+    out = bom.bom_head_vjp(H, W, res["R"], y, q, res["n_valid"], lam=LAM, want_dH=want_dH, dh_dtype=torch.float32)
+    G = ((1 - LAM) * res["R"].double() + LAM * q.double()) * ok[:, None] / int(ok.sum())
+    rW, rH = H.double().t() @ G, G @ W.double().t()
+    # fp32 sums of exact products and the rank-1 term's fp32 vectors
+    assert float((out["dW"] - rW).norm() / rW.norm()) <= 1e-5
+    assert not want_dH or float((out["dH"] - rH).norm() / rH.norm()) <= 1e-5
