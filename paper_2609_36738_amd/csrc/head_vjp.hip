@@ -15,7 +15,7 @@
 // transpose while staging); dH = G W^T has both operands k-contiguous. The fused and the 256-tile
 // kernels also take R and W with rows at any alignment and of any length (UA): a 4088 x 1024 x 50,257 head VJP takes
 // 0.87 ms with it, against 22.5 ms on the SIMT tiled GEMM that is left for bf16 with H unaligned, dW alone over a few rows, and
-// large ragged products from the logits without a panel. fp32 path: head_f32.hip.
+// large ragged products from the logits without a panel. fp32 path: head_f32.hip; dW alone over a few rows here (SIMT).
 #include <algorithm>
 #include <array>
 #include <map>
@@ -206,35 +206,47 @@ __device__ __forceinline__ void stf<float>(float* p, int64_t i, float x) { p[i] 
 template <>
 __device__ __forceinline__ void stf<uint16_t>(uint16_t* p, int64_t i, float x) { p[i] = f32_to_bf16(x); }
 
-// Element (row, col) of R: as stored, or formed from the logits (rounded to bf16 like a stored R). A row outside I may come
+// Element (row, col) of R: as stored, or formed from the logits (bf16 ones rounded like a stored R). A row outside I may come
 // with a 1 taken off at its label (an ignore_index inside [0, V)): the caller's mask of the row covers all of G.
-__device__ __forceinline__ float r_elem(const uint16_t* RZ, int64_t ld, int row, int col, const Fold& f) {
+template <typename T>
+__device__ __forceinline__ float r_elem(const T* RZ, int64_t ld, int row, int col, const Fold& f) {
     const float x = ldf(RZ, (int64_t)row * ld + col);
     if (f.zc == nullptr) return x;
-    return bf16_to_f32(f32_to_bf16(r_from_z(x, f.zc[row], col == f.labels[row])));
+    const float p = r_from_z(x, f.zc[row], col == f.labels[row]);
+    if constexpr (sizeof(T) == 2) return bf16_to_f32(f32_to_bf16(p));
+    return p;
 }
 
-// ---- SIMT kernels (bf16; see route_of for what takes them): 64 x 64 tiles, 16-deep k, 4 x 4 outputs per thread -----------
+// ---- SIMT kernels (see route_of for what takes them): 64 x 64 tiles, 16-deep k, 4 x 4 outputs per thread -----------------
 constexpr int SB = 64, SK = 16;
 
+// Element (k, n) of dW's G. In fp32 a row outside I is 0 whatever it holds, as on the fp32 matrix kernel.
+template <typename T>
+__device__ __forceinline__ float dw_g(const Fold& f, float alpha, const T* R, int64_t ldr, int k, int n) {
+    const float x = fmaf(alpha, r_elem(R, ldr, k, n, f), f.cq[n]);
+    if constexpr (sizeof(T) == 4) return f.vmask[k] != 0.f ? x : 0.f;
+    return f.vmask[k] * x;
+}
+
 // dW[m][n] = sum_k H[k][m] G[k][n];  M = d, Nn = V, K = N rows.
-__global__ __launch_bounds__(256) void simt_dW_kernel(const uint16_t* __restrict__ H, int64_t ldh,
-                                                      const uint16_t* __restrict__ R,
+template <typename T>
+__global__ __launch_bounds__(256) void simt_dW_kernel(const T* __restrict__ H, int64_t ldh, const T* __restrict__ R,
                                                       int64_t ldr, int M, int Nn, int K, int kps, Fold f,
                                                       float* __restrict__ out, int64_t ldo, float beta, int direct) {
     __shared__ float As[SK][SB + 4];
     __shared__ float Bs[SK][SB + 4];
     const int t = threadIdx.x, tx = t % 16, ty = t / 16;
+    const int wave = __builtin_amdgcn_readfirstlane(t / SB);   // a wave stages one row of k: its label, lse and mask are scalars
     const int m0 = blockIdx.y * SB, n0 = blockIdx.x * SB;
     const int kb = blockIdx.z * kps, ke = min(K, kb + kps);
     const float alpha = f.scal[0];
     float acc[4][4] = {};
     for (int k0 = kb; k0 < ke; k0 += SK) {
         for (int e = 0; e < 4; ++e) {
-            const int idx = e * 256 + t, kk = idx / SB, cc = idx % SB;
+            const int kk = e * (256 / SB) + wave, cc = t % SB;
             const int k = k0 + kk;
             As[kk][cc] = (k < ke && m0 + cc < M) ? ldf(H, (int64_t)k * ldh + m0 + cc) : 0.f;
-            Bs[kk][cc] = (k < ke && n0 + cc < Nn) ? f.vmask[k] * fmaf(alpha, r_elem(R, ldr, k, n0 + cc, f), f.cq[n0 + cc]) : 0.f;
+            Bs[kk][cc] = (k < ke && n0 + cc < Nn) ? dw_g(f, alpha, R, ldr, k, n0 + cc) : 0.f;
         }
         __syncthreads();
 #pragma unroll
@@ -2253,7 +2265,7 @@ hipError_t run_gemm(bool is_dw, const GemmPlan& g, const void* A, int64_t lda, c
                                    ldo, pz);
         } else {
             if (is_dw)
-                hipLaunchKernelGGL(simt_dW_kernel, grid, dim3(256), 0, st, a16, lda, b16, ldb, M, Nn, K, kps, f,
+                hipLaunchKernelGGL(simt_dW_kernel<uint16_t>, grid, dim3(256), 0, st, a16, lda, b16, ldb, M, Nn, K, kps, f,
                                    splits > 1 ? part : reinterpret_cast<float*>(out), ldo, beta, splits > 1 ? 0 : 1);
             else
                 hipLaunchKernelGGL(simt_dH_kernel<TO>, grid, dim3(256), 0, st, a16, lda, b16, ldb, M, Nn, K, kps, f, out,
@@ -2305,10 +2317,34 @@ struct Route {
     Plan p;
     bool ua, fused;   // fused: both products in the one launch of small tiles
     bool panels;      // logits of large products: R formed in panels (else in the products' copies)
+    bool simt_f32;    // fp32 dW on the SIMT kernel (else on the fp32 matrix kernel)
 };
+
+// fp32 dW alone over few rows: the SIMT kernel, in one k range, up to the number of rows that this gives (0: none). Large
+// gradients are their own write there, and the matrix kernel's tiles of 64 or 32 with k tiles of 32 rows have too much to set up
+// for it; a whole k tile of 32 rows has no places to clear. us on the SIMT and the matrix kernels, from R (logits), d x V:
+// 4096 x 27392: 4 rows 156 and 229 (155 and 248), 32 rows 207 and 208 (212 and 224), 48 rows 251 and 281, 56 rows 286 and 280;
+// 768 x 50257: 28 rows 82 and 86, 32 rows 86 and 74, 44 rows 100 and 100; 1826 x 10800: 16 rows 37 and 47, 28 rows 43 and 48,
+// 48 rows 55 and 56 (61 and 60); 1024 x 4099: 16 rows 15 and 15, 18 rows 17 and 15; 768 x 5000: 14 rows 14 and 14; heads of one
+// or two tiles of features, 100 x 250000: 32 rows 64 and 79, 48 rows 78 and 84; 64 x 128256: 48 rows 29 and 32; 8 x 250000:
+// 16 rows 18 and 24, 32 rows 26 and 22; one tile of more than 32 features, 33 x 300000: 48 rows 45 and 68, 64 x 200000: 56 rows
+// 46 and 47, 64 rows 49 and 45, 64 x 450000: 64 rows 92 and 98.
+int f32_simt_rows(int64_t N, int64_t d, int64_t V) {
+    const double out = (double)d * (double)V;
+    if (d > (1 << 22) || V >= (1 << 30) || (out < 4e6 && V < 125000)) return 0;   // first two: the grid's extents
+    if (N == 32 && d > 128 && out < 1e8) return 0;
+    if (d > 32 && d <= 64 && V >= 200000) return V >= 300000 ? 64 : 60;
+    if (out >= 36e6 || (d > 32 && d < 128 && (out >= 8e6 || V >= 125000))) return 48;
+    return out >= 12e6 ? (d <= 128 ? 32 : 28) : 16;
+}
+
 Route route_of(const HeadVjpArgs& a) {
-    Route r{make_plan(a.N, a.d, a.V, a.dt, false), false, false, false};
-    if (a.dt == BOM_F32) return r;
+    Route r{make_plan(a.N, a.d, a.V, a.dt, false), false, false, false, false};
+    if (a.dt == BOM_F32) {
+        r.simt_f32 = !a.dH && a.N <= f32_simt_rows(a.N, a.d, a.V);
+        if (r.simt_f32) r.p.w = r.p.h = {kSimt, 1};
+        return r;
+    }
     // MFMA kernels stage 16-byte chunks: of H at 16-byte aligned addresses, of R and W too or (ua) at any (with the
     // 256-row offsets inside 31 bits); otherwise the SIMT kernels run, with their own k splits over every tile (the
     // workspace covers their partials too).
@@ -2326,7 +2362,7 @@ Route route_of(const HeadVjpArgs& a) {
     // d = 2320, V = 27392, from R: 9 rows 98 and 119, 17 rows 112 and 119; from the logits: 9 rows 97 and 158, 41 rows 151 and
     // 158; V = 5001, from R: 33 rows 39 and 45, 48 rows 42 and 45; from the logits 57 rows 51 and 56)
     const int few = a.is_residual ? (r.ua ? 52 : 20) : (r.ua ? 64 : 44);
-    if (!a.dH && a.dw_dt == BOM_F32 && a.N < few) r.p = simt_plan(a.N, a.d, a.V);
+    if (!a.dH && a.dw_dt == BOM_F32 && a.N < few && a.d <= (1 << 22)) r.p = simt_plan(a.N, a.d, a.V);
     if (!a.is_residual && (r.p.w.kind == kRank1 || (a.dH && r.p.h.kind == kRank1))) {
         // Without panels the 256-tile products form R as they copy it, which takes aligned rows: where the workspace holds no
         // panel, and where one tile covers d, so that each product forms an element once, and many rows keep the products
@@ -2482,7 +2518,7 @@ hipError_t launch_products(const HeadVjpArgs& a, const Route& r, hipStream_t st)
     float* part = reinterpret_cast<float*>(base + L.part_off);
     float* zc = reinterpret_cast<float*>(base + L.zc_off);
     const bool zin = !a.is_residual;   // the R argument holds the logits Z
-    if (a.dt == BOM_F32) return launch_vjp_f32_products(a, f32_dw_sums(a.N, a.d, a.V), part, st);
+    if (a.dt == BOM_F32 && !r.simt_f32) return launch_vjp_f32_products(a, f32_dw_sums(a.N, a.d, a.V), part, st);
     if (r.panels) return launch_from_logits(a, L, st);
     if (L.part_off + partial_bytes(p, a.N, a.d, a.V) > L.total) return hipErrorInvalidValue;   // never taken
 
@@ -2527,6 +2563,14 @@ hipError_t launch_products(const HeadVjpArgs& a, const Route& r, hipStream_t st)
     hipError_t e = launch_prep(a, L, p.w.kind == kRank1 && hist, p.h.kind == kRank1 && hist, ua, st);
     if (e != hipSuccess) return e;
     const Fold f{cq, vmask, scal, zin ? zc : nullptr, a.labels};
+
+    if (r.simt_f32) {
+        const dim3 grid((unsigned)cdiv(a.V, SB), (unsigned)cdiv(a.d, SB));
+        hipLaunchKernelGGL(simt_dW_kernel<float>, grid, dim3(256), 0, st, static_cast<const float*>(a.H), a.ldh,
+                           static_cast<const float*>(a.R), a.ldr, a.d, a.V, a.N, (int)(cdiv(a.N, SK) * SK), f,
+                           static_cast<float*>(a.dW), a.lddw, a.dW_beta, 1);
+        return hipGetLastError();
+    }
 
     if (p.pair && a.dH && p.w.kind == kRank1 && p.h.kind == kRank1) {
         // one grid: dH's units (k split p.h.splits) first, then dW's tiles over the full k range
